@@ -26,6 +26,7 @@ struct Ctx {
     std::vector<int> lvl_off;  // cells of level l are [lvl_off[l], lvl_off[l+1])
     int ncells = 0, nleaves = 0;
     int n_p2p = 0, n_blocks = 0;
+    int n_items = 0, n_partial = 0;      // P2P work items (parts of a block's list), float[6] partial results
     int64_t n_m2l = 0, p2p_pairs = 0;
     int img_B = 0, img_codes = 1;
     int nprob = 1;                       // independent problems in the tree (forest)
@@ -62,8 +63,10 @@ struct Ctx {
     DevBuf p2p_off, p2p_ent;             // CSR by target cell: int offsets, int4 (start, count, img, variant)
     DevBuf p2p_sh;                       // float4 per P2P entry: scaled offset between the two leaf centres
     DevBuf blocks;                       // int4 (tgt start, tgt count, list off, list count)
+    DevBuf bparts;                       // int2 per block (first partial result, parts)
+    DevBuf items, item_out;              // int4 per part (tgt start, tgt count, first entry, entries), first partial result
     DevBuf pairs64;                      // int64 reduction scratch
-    DevBuf gpart;                        // per-work-group partial pair counts of the P2P list
+    DevBuf gpart;                        // per-work-group partial pair and source counts of the P2P list
     int *hpin = nullptr;                 // pinned host ints written by k_read_ints (read_ints)
     // expansions
     DevBuf Mexp, Lexp;                   // float2 [ncells][3][NC(p)]
@@ -115,7 +118,7 @@ struct Ctx {
     // near field on a second stream, concurrent with the far field
     hipStream_t side = nullptr;          // non-blocking, default priority; created on first use
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-    DevBuf near;                         // float[6][n]: P2P u and dalpha in sorted order
+    DevBuf near;                         // float[6 n_partial]: P2P u and dalpha of every part, [6][targets] each
 
     // timing
     hipEvent_t ev[2 * PH_NUM + 4] = {};

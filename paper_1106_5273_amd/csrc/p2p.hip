@@ -3,7 +3,7 @@
 // sorted order, one buffer per part of the lists (below), and a finalize
 // kernel adds the parts and the far field and scatters to the caller's order.
 //
-// Work item: one wave64 per part (a quarter) of the P2P list of a block of
+// Work item: one wave64 per part (a piece of about equal work) of the P2P list of a block of
 // <= 64 targets of a leaf (one target per lane).  Source particles are the
 // same for every lane at a given step, so their records are read with scalar
 // loads and enter the vector ALU as scalar operands: no LDS staging and no
@@ -94,10 +94,13 @@ constexpr float q(int i) { return (float)(8.0 / (15.0 * SQRT_PI) * (double)VFMM_
 
 struct P2PArgs {
     const float4 *__restrict__ rec;  // float4[3n] (uniform cores) or float4[4n] (per-particle cores) records
+    const int4 *__restrict__ items;  // (target start, targets, first entry, entries) per wave
+    const int *__restrict__ item_out; // tree mode: first partial result of every item
     const int4 *__restrict__ blocks;
+    const int2 *__restrict__ bparts; // per block (first partial result, parts)
     const int4 *__restrict__ ent;
     const float4 *__restrict__ sh;   // per entry: (D', 0)
-    int nblocks;
+    int nitems, nblocks;
     const float *__restrict__ far_u;
     const float *__restrict__ far_da;
     int64_t n;
@@ -106,10 +109,8 @@ struct P2PArgs {
     float inv3V;
     int surface;
     float *ux, *uy, *uz, *dax, *day, *daz;
-    float *near;  // non-null: write u and dalpha in sorted order to near[6][n] instead of finishing
-    int parts;    // 2 or 4: each block's list is taken in that many parts by neighbouring
-                  // waves, part q writing to near + 6 n q (the finalize kernel adds the
-                  // parts); else 1
+    float *near;  // non-null: write u and dalpha of the item's targets to near + 6 item_out, [6][targets],
+                  // instead of finishing (the finalize kernel adds the parts of a block)
 };
 
 struct Acc9 {
@@ -424,12 +425,12 @@ __device__ __forceinline__ void p2p_block(const P2PConst &k, const P2PArgs &A, i
     d2 = fmaf(-3.0f, S[8], d2);
     float u0 = S[0] * k.inv_kappa, u1 = S[1] * k.inv_kappa, u2 = S[2] * k.inv_kappa;
     if (near) {
-        near[i] = u0;
-        near[A.n + i] = u1;
-        near[2 * A.n + i] = u2;
-        near[3 * A.n + i] = d0;
-        near[4 * A.n + i] = d1;
-        near[5 * A.n + i] = d2;
+        near[tl] = u0;
+        near[tc + tl] = u1;
+        near[2 * tc + tl] = u2;
+        near[3 * tc + tl] = d0;
+        near[4 * tc + tl] = d1;
+        near[5 * tc + tl] = d2;
         return;
     }
     if (A.far_u) {
@@ -457,25 +458,16 @@ __device__ __forceinline__ void p2p_block(const P2PConst &k, const P2PArgs &A, i
 
 template <int SCHEME, bool KAHAN, bool VAR>
 __global__ __launch_bounds__(256) void k_p2p(P2PConst k, P2PArgs A) {
-    const int item = xcd_logical(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
-    // the waves of a block's parts are neighbours (they share its target
+    // neighbouring waves take the parts of one block (they share its target
     // records and much of its source data in the caches)
-    const int np = A.parts == 4 ? 4 : (A.parts == 2 ? 2 : 1);
-    const int b = item / np;
-    if (b >= A.nblocks) return;
-    const int4 blk = A.blocks[b];
-    const int t0 = __builtin_amdgcn_readfirstlane(blk.x);
-    const int tc = __builtin_amdgcn_readfirstlane(blk.y);
-    int l0 = __builtin_amdgcn_readfirstlane(blk.z);
-    int lc = __builtin_amdgcn_readfirstlane(blk.w);
-    float *near = A.near;
-    if (np > 1) {  // part q: entries [q lc / np, (q + 1) lc / np)
-        const int q = item % np;
-        const int e0 = (q * lc) / np, e1 = ((q + 1) * lc) / np;
-        l0 += e0;
-        lc = e1 - e0;
-        near += 6 * A.n * q;
-    }
+    const int item = xcd_logical(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
+    if (item >= A.nitems) return;
+    const int4 it = A.items[item];
+    const int t0 = __builtin_amdgcn_readfirstlane(it.x);
+    const int tc = __builtin_amdgcn_readfirstlane(it.y);
+    const int l0 = __builtin_amdgcn_readfirstlane(it.z);
+    const int lc = __builtin_amdgcn_readfirstlane(it.w);
+    float *near = A.near ? A.near + 6 * (size_t)__builtin_amdgcn_readfirstlane(A.item_out[item]) : nullptr;
     if (tc <= 16)
         p2p_block<SCHEME, KAHAN, 4, VAR>(k, A, t0, tc, l0, lc, near);
     else if (tc <= 32)
@@ -727,12 +719,11 @@ void p2p_prepare(Ctx &c) { p2p_records(c); }
 
 template <int SCHEME, bool KAHAN>
 static void launch_p2p(const P2PConst &k, const P2PArgs &A, bool var, hipStream_t s) {
-    if (A.nblocks == 0) return;
-    const int64_t items = (int64_t)A.nblocks * (A.parts == 4 ? 4 : (A.parts == 2 ? 2 : 1));
+    if (A.nitems == 0) return;
     if (var)
-        k_p2p<SCHEME, KAHAN, true><<<xcd_grid(cdiv(items, 4)), 256, 0, s>>>(k, A);
+        k_p2p<SCHEME, KAHAN, true><<<xcd_grid(cdiv(A.nitems, 4)), 256, 0, s>>>(k, A);
     else
-        k_p2p<SCHEME, KAHAN, false><<<xcd_grid(cdiv(items, 4)), 256, 0, s>>>(k, A);
+        k_p2p<SCHEME, KAHAN, false><<<xcd_grid(cdiv(A.nitems, 4)), 256, 0, s>>>(k, A);
     VFMM_LAUNCH_CHECK();
 }
 
@@ -750,9 +741,13 @@ static void dispatch_p2p(const vfmm_params &prm, bool var, const P2PConst &k, co
 static P2PArgs tree_args(Ctx &c) {
     P2PArgs A{};
     A.rec = c.recp.as<float4>();
+    A.items = c.items.as<int4>();
+    A.item_out = c.item_out.as<int>();
     A.blocks = c.blocks.as<int4>();
+    A.bparts = c.bparts.as<int2>();
     A.ent = c.p2p_ent.as<int4>();
     A.sh = c.p2p_sh.as<float4>();
+    A.nitems = c.n_items;
     A.nblocks = c.n_blocks;
     A.n = c.n;
     A.perm = c.perm.as<int>();
@@ -762,41 +757,48 @@ static P2PArgs tree_args(Ctx &c) {
     return A;
 }
 
-// Parts of every block's list (see p2p_near).
-constexpr int P2P_PARTS = 4;
-// Near field alone, on stream s, into c.near (sorted order; part q of every
-// block's list in near[6 n q .. 6 n (q + 1))); the far field runs before,
-// after or beside it on the library stream and finalize_near_far adds the
-// parts and the far field.  Four parts per block quadruple the waves: at
-// 128^3 the 32,768 one-block waves would fill every SIMD exactly four times
-// over, and the uneven end of the last round costs a few percent; a
-// work-group then also covers one block instead of four, so fewer target
-// neighbourhoods are in flight on each XCD and more source records hit in L2.
+// Near field alone, on stream s, into c.near (the partial results of every
+// work item); the far field runs before, after or beside it on the library
+// stream and finalize_near_far adds a block's parts and the far field.  At
+// 128^3 a block's list is four parts: its 32,768 one-block waves would fill
+// every SIMD exactly four times over, and the uneven end of the last round
+// costs a few percent; a work-group then also covers one block instead of
+// four, so fewer target neighbourhoods are in flight on each XCD and more
+// source records hit in L2.
 void p2p_near(Ctx &c, hipStream_t s) {
     const P2PConst k = make_const(c.sigma_uniform, c.var_sigma);
-    c.near.ensure(sizeof(float) * 6 * P2P_PARTS * (size_t)c.n);
+    c.near.ensure(sizeof(float) * 6 * (size_t)std::max(c.n_partial, 1));
     P2PArgs A = tree_args(c);
     A.near = c.near.as<float>();
-    A.parts = P2P_PARTS;
     c.record(2 * PH_P2P, s);
     dispatch_p2p(c.prm, c.var_sigma, k, A, s);
     c.record(2 * PH_P2P + 1, s);
 }
 
 // out[perm[i]] = (sum of the near-field parts)[i] + far[i] (- the zero-mean
-// surface term for u)
+// surface term for u); one wave per block, a lane per target, parts added in
+// list order with four parts' loads in flight
 __global__ __launch_bounds__(256) void k_finalize(P2PArgs A, const float *__restrict__ near) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= A.n) return;
+    const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (b >= A.nblocks) return;
+    const int4 blk = A.blocks[b];
+    const int2 pt = A.bparts[b];
+    if (lane >= blk.y) return;
+    const int64_t i = blk.x + lane;
     const int64_t n = A.n;
-    // the four parts in a fixed pairwise order: (p0 + p1) + (p2 + p3), then the far field
-    float v[6];
+    const int tc = blk.y, np = pt.y;
+    const float *q = near + 6 * (size_t)pt.x + lane;
+    float v[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int p0 = 0; p0 < np; p0 += 4) {
+        float w[4][6];
 #pragma unroll
-    for (int c = 0; c < 6; ++c) {
-        const float *q = near + (int64_t)c * n + i;
-        float a = q[0] + q[6 * n];
-        a += q[12 * n] + q[18 * n];
-        v[c] = a;
+        for (int p = 0; p < 4; ++p)
+#pragma unroll
+            for (int c = 0; c < 6; ++c) w[p][c] = p0 + p < np ? q[(size_t)(6 * (p0 + p) + c) * tc] : 0.f;
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+#pragma unroll
+            for (int c = 0; c < 6; ++c) v[c] += w[p][c];
     }
     float u0 = v[0] + A.far_u[i], u1 = v[1] + A.far_u[n + i], u2 = v[2] + A.far_u[2 * n + i];
     float d0 = v[3] + A.far_da[i], d1 = v[4] + A.far_da[n + i], d2 = v[5] + A.far_da[2 * n + i];
@@ -821,7 +823,7 @@ void finalize_near_far(Ctx &c, float *ux, float *uy, float *uz, float *dax, floa
     A.far_da = c.far_da.as<float>();
     A.ux = ux; A.uy = uy; A.uz = uz; A.dax = dax; A.day = day; A.daz = daz;
     if (c.n == 0) return;
-    k_finalize<<<cdiv(c.n, 256), 256, 0, c.stream>>>(A, c.near.as<float>());
+    k_finalize<<<cdiv(c.n_blocks, 4), 256, 0, c.stream>>>(A, c.near.as<float>());
     VFMM_LAUNCH_CHECK();
 }
 
@@ -912,10 +914,10 @@ static void direct_f32_impl(const Ctx &c, Ctx *tc, hipStream_t s, int64_t n, con
     const P2PConst k = make_const(sig, var);
     P2PArgs A{};
     A.rec = b.recp;
-    A.blocks = b.blocks;
+    A.items = b.blocks;
     A.ent = b.ent;
     A.sh = b.sh;
-    A.nblocks = nb;
+    A.nitems = nb;
     A.far_u = nullptr;
     A.far_da = nullptr;
     A.n = n;

@@ -186,7 +186,7 @@ struct P2PEntryArgs {
 __global__ __launch_bounds__(TPB) void k_p2p_gather(P2PEntryArgs A, const int4 *raw, const uint32_t *order,
                                                     int64_t n, int4 *out, unsigned long long *part) {
     const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    unsigned long long np = 0;
+    unsigned long long np = 0, nsrc = 0;
     if (i < n) {
         const int4 e = raw[order[i]];
         const int t = e.x, s = e.y;
@@ -218,46 +218,129 @@ __global__ __launch_bounds__(TPB) void k_p2p_gather(P2PEntryArgs A, const int4 *
             A.sh[i] = make_float4((float)Dx, (float)Dy, (float)Dz, 0.f);
         }
         np = (unsigned long long)A.count[t] * (unsigned long long)sc;
+        nsrc = (unsigned long long)sc;
     }
-    // block reduction of the pair count
-    __shared__ unsigned long long sh[TPB];
-    sh[threadIdx.x] = np;
+    // pairs and sources of this work-group's entries, summed by k_sum_u64x2 (no contended atomics)
+    __shared__ unsigned long long red[2][TPB / 64];
+    unsigned long long ns = nsrc;
+    for (int o = 32; o > 0; o >>= 1) {
+        np += __shfl_xor(np, o, 64);
+        ns += __shfl_xor(ns, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[0][threadIdx.x >> 6] = np;
+        red[1][threadIdx.x >> 6] = ns;
+    }
     __syncthreads();
-    for (int o = TPB / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-        __syncthreads();
+    if (threadIdx.x < 2) {
+        unsigned long long t = 0;
+        for (int w = 0; w < TPB / 64; ++w) t += red[threadIdx.x][w];
+        part[2 * (size_t)blockIdx.x + threadIdx.x] = t;
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];  // summed by k_sum_u64 (no contended atomics)
 }
 
-// total of n unsigned 64-bit partial counts (one work-group)
-__global__ __launch_bounds__(TPB) void k_sum_u64(const unsigned long long *part, int n, unsigned long long *out) {
-    __shared__ unsigned long long sh[TPB];
-    unsigned long long v = 0;
-    for (int i = threadIdx.x; i < n; i += TPB) v += part[i];
-    sh[threadIdx.x] = v;
+// totals of n pairs of unsigned 64-bit partial counts (one work-group)
+__global__ __launch_bounds__(TPB) void k_sum_u64x2(const unsigned long long *part, int n, unsigned long long *out) {
+    __shared__ unsigned long long red[2][TPB / 64];
+    unsigned long long v0 = 0, v1 = 0;
+    for (int i = threadIdx.x; i < n; i += TPB) {
+        v0 += part[2 * (size_t)i];
+        v1 += part[2 * (size_t)i + 1];
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        v0 += __shfl_xor(v0, o, 64);
+        v1 += __shfl_xor(v1, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[0][threadIdx.x >> 6] = v0;
+        red[1][threadIdx.x >> 6] = v1;
+    }
     __syncthreads();
-    for (int o = TPB / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-        __syncthreads();
+    if (threadIdx.x < 2) {
+        unsigned long long t = 0;
+        for (int w = 0; w < TPB / 64; ++w) t += red[threadIdx.x][w];
+        out[threadIdx.x] = t;
     }
-    if (threadIdx.x == 0) out[0] = sh[0];
 }
 
-__global__ __launch_bounds__(TPB) void k_block_counts(const int *leaves, int nl, const int *count, int *nb) {
-    const int i = blockIdx.x * TPB + threadIdx.x;
-    if (i < nl) nb[i] = (count[leaves[i]] + 63) / 64;
+// ---------------------------------------------------------------------------
+// P2P work: every leaf's targets are cut into blocks of at most 64, and every
+// block's list into parts of about equal length, one wave each.  The length of
+// a part is chosen from the whole build's work: total wave steps / 57,344 (eight
+// rounds of the 7,168 waves that fill the chip), but at least 48 steps (shorter
+// parts cost more in their prologue and partial sums than they spread) and at
+// most 2,400 (the four parts of 37 leaves at 128^3).  A fixed four parts per
+// block left one list of 4,849 entries in a clustered tree of 100,003 particles
+// to four waves, which alone set the kernel's time.
+// ---------------------------------------------------------------------------
+struct LeafWork {
+    float src_per_entry;  // mean sources of a list entry
+    float part;           // wave steps per part
+};
+
+__device__ inline LeafWork leaf_work(const unsigned long long *tot, int64_t nent) {
+    const float pairs = (float)tot[0], srcs = (float)tot[1];
+    return LeafWork{fmaxf(1.f, srcs / (float)max((int64_t)1, nent)),
+                    fminf(2400.f, fmaxf(48.f, pairs * (1.f / (48.f * 57344.f))))};
 }
 
-__global__ __launch_bounds__(TPB) void k_block_fill(const int *leaves, int nl, const int *start, const int *count,
-                                                    const int *boff, const int *loff, int4 *blocks) {
+// parts of the list (lc entries) of a block of tc targets; the entry's fixed
+// cost counts as six steps, and small blocks take several sources per step
+__device__ inline int list_parts(const LeafWork &W, int tc, int lc) {
+    const float per = W.src_per_entry / (tc <= 16 ? 4.f : (tc <= 32 ? 2.f : 1.f)) + 6.f;
+    return max(1, min(lc, (int)((float)lc * per / W.part + 0.5f)));
+}
+
+// per leaf: its blocks, its parts and the float[6] outputs of its parts
+__global__ __launch_bounds__(TPB) void k_leaf_counts(const int *leaves, int nl, const int *count, const int *loff,
+                                                     const unsigned long long *tot, int64_t nent, int *out) {
     const int i = blockIdx.x * TPB + threadIdx.x;
     if (i >= nl) return;
+    const LeafWork W = leaf_work(tot, nent);
+    const int cell = leaves[i];
+    const int cnt = count[cell], lc = loff[cell + 1] - loff[cell];
+    int nb = 0, ni = 0, nu = 0;
+    for (int k = 0; k < cnt; k += 64, ++nb) {
+        const int tc = min(64, cnt - k), np = list_parts(W, tc, lc);
+        ni += np;
+        nu += np * tc;
+    }
+    out[i] = nb;
+    out[nl + i] = ni;
+    out[2 * nl + i] = nu;
+}
+
+// the three totals and the pair count, straight to pinned host memory
+__global__ void k_leaf_totals(const int *cnt, const int *off, int nl, const int *tot, int *out) {
+    for (int k = 0; k < 3; ++k) out[k] = off[(k + 1) * nl - 1] + cnt[(k + 1) * nl - 1] - off[k * nl];
+    out[3] = tot[0];
+    out[4] = tot[1];
+}
+
+// blocks (target start, targets, first entry, entries), their parts (first
+// output, parts), and one work item per part (target start, targets, first
+// entry, entries) with its first output
+__global__ __launch_bounds__(TPB) void k_leaf_items(const int *leaves, int nl, const int *start, const int *count,
+                                                    const int *loff, const unsigned long long *tot, int64_t nent,
+                                                    const int *off, int4 *blocks, int2 *bparts, int4 *items,
+                                                    int *item_out) {
+    const int i = blockIdx.x * TPB + threadIdx.x;
+    if (i >= nl) return;
+    const LeafWork W = leaf_work(tot, nent);
     const int cell = leaves[i];
     const int s = start[cell], cnt = count[cell];
-    const int l0 = loff[cell], l1 = loff[cell + 1];
-    int b = boff[i];
-    for (int k = 0; k < cnt; k += 64) blocks[b++] = make_int4(s + k, min(64, cnt - k), l0, l1 - l0);
+    const int l0 = loff[cell], lc = loff[cell + 1] - l0;
+    int b = off[i], it = off[nl + i] - off[nl], u = off[2 * nl + i] - off[2 * nl];
+    for (int k = 0; k < cnt; k += 64, ++b) {
+        const int tc = min(64, cnt - k), np = list_parts(W, tc, lc);
+        blocks[b] = make_int4(s + k, tc, l0, lc);
+        bparts[b] = make_int2(u, np);
+        for (int q = 0; q < np; ++q, ++it, u += tc) {
+            const int e0 = (int)((int64_t)q * lc / np), e1 = (int)((int64_t)(q + 1) * lc / np);
+            items[it] = make_int4(s + k, tc, l0 + e0, e1 - e0);
+            item_out[it] = u;
+        }
+    }
 }
 
 static int bits_for(int64_t v) {
@@ -379,7 +462,7 @@ void traverse_and_lists(Ctx &c) {
     const bool f32 = c.prm.precision != VFMM_PRECISION_FP64;
     if (f32) c.p2p_sh.ensure(sizeof(float4) * (size_t)std::max<int64_t>(n_p2p, 1));
     c.pairs64.ensure(64);
-    VFMM_HIP(hipMemsetAsync(c.pairs64.ptr, 0, 8, s));
+    VFMM_HIP(hipMemsetAsync(c.pairs64.ptr, 0, 16, s));
     if (n_p2p > 0) {
         P2PEntryArgs E{};
         E.start = c.c_start.as<int>();
@@ -398,31 +481,39 @@ void traverse_and_lists(Ctx &c) {
         E.nsrc = c.n_src_part >= 0 && c.n_src_part < c.n ? c.c_nsrc.as<int>() : nullptr;
         E.sh = f32 ? c.p2p_sh.as<float4>() : nullptr;
         const int ngb = (int)cdiv(n_p2p, TPB);
-        c.gpart.ensure(sizeof(unsigned long long) * (size_t)ngb);
+        c.gpart.ensure(2 * sizeof(unsigned long long) * (size_t)ngb);
         k_p2p_gather<<<ngb, TPB, 0, s>>>(E, c.p2p_raw.as<int4>(), c.lval.as<uint32_t>(), n_p2p, c.p2p_ent.as<int4>(),
                                          c.gpart.as<unsigned long long>());
         VFMM_LAUNCH_CHECK();
-        k_sum_u64<<<1, TPB, 0, s>>>(c.gpart.as<unsigned long long>(), ngb, c.pairs64.as<unsigned long long>());
+        k_sum_u64x2<<<1, TPB, 0, s>>>(c.gpart.as<unsigned long long>(), ngb, c.pairs64.as<unsigned long long>());
         VFMM_LAUNCH_CHECK();
     }
-    // ---- P2P work blocks (<= 64 targets each) ----
+    // ---- P2P work: blocks of <= 64 targets, their lists in parts ----
     const int nl = c.nleaves;
-    c.c_tmp.ensure(sizeof(int) * (2 * (size_t)nl + 2));
-    int *nb = c.c_tmp.as<int>();
-    int *boff = nb + nl + 1;
-    k_block_counts<<<cdiv(nl, TPB), TPB, 0, s>>>(c.leaves.as<int>(), nl, c.c_count.as<int>(), nb);
+    c.c_tmp.ensure(sizeof(int) * (6 * (size_t)nl + 2));
+    int *cnt = c.c_tmp.as<int>(), *off = cnt + 3 * (size_t)nl;
+    const unsigned long long *tot = c.pairs64.as<unsigned long long>();
+    k_leaf_counts<<<cdiv(nl, TPB), TPB, 0, s>>>(c.leaves.as<int>(), nl, c.c_count.as<int>(), c.p2p_off.as<int>(), tot,
+                                                n_p2p, cnt);
     VFMM_LAUNCH_CHECK();
-    scan_excl_i32(c, nb, boff, nl);
-    int h4[4];
-    read_ints(c, {boff + nl - 1, nb + nl - 1, c.pairs64.as<int>(), c.pairs64.as<int>() + 1}, h4);
-    h_tot[0] = h4[0];
-    h_tot[1] = h4[1];
-    const unsigned long long pairs = (unsigned long long)(uint32_t)h4[2] | ((unsigned long long)(uint32_t)h4[3] << 32);
-    c.n_blocks = h_tot[0] + h_tot[1];
-    c.p2p_pairs = (int64_t)pairs;
+    scan_excl_i32(c, cnt, off, 3 * (int64_t)nl);
+    k_leaf_totals<<<1, 1, 0, s>>>(cnt, off, nl, c.pairs64.as<int>(), pinned_ints(c));
+    VFMM_LAUNCH_CHECK();
+    int h5[5];
+    sync_ints(c, 5, h5);
+    c.n_blocks = h5[0];
+    c.n_items = h5[1];
+    c.n_partial = h5[2];
+    c.p2p_pairs = (int64_t)((unsigned long long)(uint32_t)h5[3] | ((unsigned long long)(uint32_t)h5[4] << 32));
+    if (c.n_blocks < 0 || c.n_items < 0 || c.n_partial < 0)
+        throw Error{VFMM_ENOMEM, "near-field work items exceed 2^31 entries"};
     c.blocks.ensure(sizeof(int4) * (size_t)std::max(c.n_blocks, 1));
-    k_block_fill<<<cdiv(nl, TPB), TPB, 0, s>>>(c.leaves.as<int>(), nl, c.c_start.as<int>(), c.c_count.as<int>(),
-                                                boff, c.p2p_off.as<int>(), c.blocks.as<int4>());
+    c.bparts.ensure(sizeof(int2) * (size_t)std::max(c.n_blocks, 1));
+    c.items.ensure(sizeof(int4) * (size_t)std::max(c.n_items, 1));
+    c.item_out.ensure(sizeof(int) * (size_t)std::max(c.n_items, 1));
+    k_leaf_items<<<cdiv(nl, TPB), TPB, 0, s>>>(c.leaves.as<int>(), nl, c.c_start.as<int>(), c.c_count.as<int>(),
+                                               c.p2p_off.as<int>(), tot, n_p2p, off, c.blocks.as<int4>(),
+                                               c.bparts.as<int2>(), c.items.as<int4>(), c.item_out.as<int>());
     VFMM_LAUNCH_CHECK();
 }
 
