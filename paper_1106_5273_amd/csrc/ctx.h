@@ -26,7 +26,9 @@ struct Ctx {
     std::vector<int> lvl_off;  // cells of level l are [lvl_off[l], lvl_off[l+1])
     int ncells = 0, nleaves = 0;
     int n_p2p = 0, n_blocks = 0;
-    int n_items = 0, n_partial = 0;      // P2P work items (parts of a block's list), float[6] partial results
+    int n_pblocks = 0;                   // near-field blocks (a leaf's targets, cut to fill waves)
+    int n_items = 0, n_items_w = 0;      // P2P work items (parts of a block's list); the first n_items_w take whole waves
+    int n_partial = 0;                   // float[6] partial results of the items
     int64_t n_m2l = 0, p2p_pairs = 0;
     int img_B = 0, img_codes = 1;
     int nprob = 1;                       // independent problems in the tree (forest)
@@ -63,7 +65,7 @@ struct Ctx {
     DevBuf p2p_off, p2p_ent;             // CSR by target cell: int offsets, int4 (start, count, img, variant)
     DevBuf p2p_sh;                       // float4 per P2P entry: scaled offset between the two leaf centres
     DevBuf blocks;                       // int4 (tgt start, tgt count, list off, list count)
-    DevBuf bparts;                       // int2 per block (first partial result, parts)
+    DevBuf pblocks;                      // int4 per near-field block (tgt start, tgt count, first partial result, parts)
     DevBuf items, item_out;              // int4 per part (tgt start, tgt count, first entry, entries), first partial result
     DevBuf pairs64;                      // int64 reduction scratch
     DevBuf gpart;                        // per-work-group partial pair and source counts of the P2P list
@@ -197,6 +199,10 @@ struct DirectBufs {
 void direct_f32(const Ctx &c, hipStream_t s, int64_t n, const Bounds &hb, const DirectBufs &b, const float *x,
                 const float *y, const float *z, const float *ax, const float *ay, const float *az,
                 const float *sigma, float *ux, float *uy, float *uz, float *dax, float *day, float *daz);
+// Lane groups of a near-field block of tc targets: more than 32 targets take the
+// wave alone; fewer are held by several groups of tc lanes each (at most 16),
+// which take different sources.
+__host__ __device__ inline int p2p_groups(int tc) { return tc > 32 ? 1 : tc < 4 ? 16 : 64 / tc; }
 // Scale of the float32 near field: lengths times kappa = log2(e)^(1/2) / (sqrt 2 sigma)
 // turn the Gaussian e^{-rho^2/(2 sigma^2)} into 2^{-rho'^2}; a = (2/sqrt pi) ln(2)^(1/2).
 inline double p2p_kappa(double sigma) { return std::sqrt(1.0 / std::log(2.0)) / (std::sqrt(2.0) * sigma); }

@@ -96,11 +96,11 @@ struct P2PArgs {
     const float4 *__restrict__ rec;  // float4[3n] (uniform cores) or float4[4n] (per-particle cores) records
     const int4 *__restrict__ items;  // (target start, targets, first entry, entries) per wave
     const int *__restrict__ item_out; // tree mode: first partial result of every item
-    const int4 *__restrict__ blocks;
-    const int2 *__restrict__ bparts; // per block (first partial result, parts)
+    const int4 *__restrict__ blocks;  // (target start, targets, first partial result, parts)
     const int4 *__restrict__ ent;
     const float4 *__restrict__ sh;   // per entry: (D', 0)
-    int nitems, nblocks;
+    int nitems, nitems_w;  // items; the first nitems_w take whole waves (k_p2p), the rest lane groups
+    int nblocks;
     const float *__restrict__ far_u;
     const float *__restrict__ far_da;
     int64_t n;
@@ -163,9 +163,9 @@ __device__ __forceinline__ void geo_trans(float4 sa, Geo &g) {
     if (V != 2) g.E = __builtin_amdgcn_exp2f(-g.r2s);
 }
 
-template <int V, int SCHEME, bool MASK, bool VAR>
+template <int V, int SCHEME, bool VAR>
 __device__ __forceinline__ void pair_rest(const P2PConst &k, const Tgt &t, const Geo &g, float4 sp, float4 sa,
-                                          float4 sb, bool ok, Acc9 &p) {
+                                          float4 sb, Acc9 &p) {
     const float dx = g.dx, dy = g.dy, dz = g.dz;
     const float rinv = g.rinv;
     const float rinv2 = rinv * rinv;
@@ -199,10 +199,6 @@ __device__ __forceinline__ void pair_rest(const P2PConst &k, const Tgt &t, const
         }
     }
     if (VAR) H *= sp.w;  // kappa_j^2
-    if (MASK) {  // a padding source contributes exactly zero
-        F = ok ? F : 0.f;
-        H = ok ? H : 0.f;
-    }
     if (SCHEME == VFMM_SCHEME_TRANSPOSE) {
         float d = fmaf(sa.x, t.w0, fmaf(sa.y, t.w1, sa.z * t.w2));
         d = fmaf(-t.ai0, sb.x, fmaf(-t.ai1, sb.y, fmaf(-t.ai2, sb.z, d)));
@@ -234,13 +230,12 @@ __device__ __forceinline__ void pair_rest(const P2PConst &k, const Tgt &t, const
     }
 }
 
-template <int V, int SCHEME, bool MASK, bool VAR>
-__device__ __forceinline__ void pair(const P2PConst &k, const Tgt &t, float4 sp, float4 sa, float4 sb, bool ok,
-                                     Acc9 &p) {
+template <int V, int SCHEME, bool VAR>
+__device__ __forceinline__ void pair(const P2PConst &k, const Tgt &t, float4 sp, float4 sa, float4 sb, Acc9 &p) {
     Geo g;
     geo_offsets<VAR>(t, sp, g);
     geo_trans<V, VAR>(sa, g);
-    pair_rest<V, SCHEME, MASK, VAR>(k, t, g, sp, sa, sb, ok, p);
+    pair_rest<V, SCHEME, VAR>(k, t, g, sp, sa, sb, p);
 }
 
 // One group of U sources against the lane's target: the offsets of all U
@@ -261,7 +256,7 @@ __device__ __forceinline__ void trip(const P2PConst &k, const Tgt &t, const floa
     for (int u = 0; u < U; ++u) geo_trans<V, VAR>(sa[u], g[u]);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < U; ++u) pair_rest<V, SCHEME, false, VAR>(k, t, g[u], sp[u], sa[u], sb[u], true, p);
+    for (int u = 0; u < U; ++u) pair_rest<V, SCHEME, VAR>(k, t, g[u], sp[u], sa[u], sb[u], p);
 }
 
 // All sources of one list entry, two per trip.  The scalar loads of the next
@@ -303,7 +298,7 @@ __device__ __forceinline__ void leaf_loop(const P2PConst &k, const float4 *__res
             trip<V, SCHEME, VAR, U>(k, t, sp, sa, sb, p);
         }
     }
-    if (j < cnt) pair<V, SCHEME, false, VAR>(k, t, src[RS * j], src[RS * j + 1], src[RS * j + 2], true, p);
+    if (j < cnt) pair<V, SCHEME, VAR>(k, t, src[RS * j], src[RS * j + 1], src[RS * j + 2], p);
 }
 
 __device__ __forceinline__ void kahan_add(float &s, float &c, float v) {
@@ -313,32 +308,9 @@ __device__ __forceinline__ void kahan_add(float &s, float &c, float v) {
     s = t;
 }
 
-// Blocks of few targets split the wave into SPLIT lane groups of 64/SPLIT
-// lanes that each hold every target of the block and take every SPLIT-th
-// source of the leaf (vector loads, one address per group); the groups' sums
-// are added at the end.  A group past the last source re-reads the last one
-// with its cutoff factors forced to zero, which contributes exactly zero.
-template <int V, int SCHEME, int SPLIT, bool VAR>
-__device__ __forceinline__ void leaf_loop_split(const P2PConst &k, const float4 *__restrict__ rec, int s0, int cnt,
-                                                int grp, const Tgt &t, Acc9 &p) {
-    constexpr int RS = VAR ? 4 : 3;
-    const float4 *src = rec + RS * (size_t)s0;
-    for (int j = 0; j < cnt; j += SPLIT) {
-        const bool ok = j + grp < cnt;
-        const int jj = ok ? j + grp : cnt - 1;
-        pair<V, SCHEME, true, VAR>(k, t, src[RS * jj], src[RS * jj + 1], src[RS * jj + 2], ok, p);
-    }
-}
-
-template <int SCHEME, bool KAHAN, int SPLIT, bool VAR>
-__device__ __forceinline__ void p2p_block(const P2PConst &k, const P2PArgs &A, int t0, int tc, int l0, int lc,
-                                          float *near) {
-    const int lane = threadIdx.x & 63;
-    constexpr int GL = 64 / SPLIT;  // lanes per group
-    const int tl = lane % GL, grp = lane / GL;
-    const bool valid = tl < tc;
-    const int i = t0 + (valid ? tl : 0);
-    Tgt t;
+// Target of a lane: its offset in its leaf and its strength.
+template <bool VAR>
+__device__ __forceinline__ float4 load_target(const P2PArgs &A, int i, Tgt &t) {
     float4 r0;
     if (VAR) {
         r0 = A.rec[4 * (size_t)i];
@@ -352,62 +324,45 @@ __device__ __forceinline__ void p2p_block(const P2PConst &k, const P2PArgs &A, i
         t.ai1 = A.rec[3 * (size_t)i + 1].w;
         t.ai2 = A.rec[3 * (size_t)i + 2].w;
     }
-    float S[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-    float Cc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-    for (int e = 0; e < lc; ++e) {
-        const int4 en = A.ent[l0 + e];
-        const float4 D = A.sh[l0 + e];
-        const int s0 = __builtin_amdgcn_readfirstlane(en.x);
-        const int sc = __builtin_amdgcn_readfirstlane(en.y);
-        const int var = __builtin_amdgcn_readfirstlane(en.w);
-        t.y0 = r0.x + D.x;
-        t.y1 = r0.y + D.y;
-        t.y2 = r0.z + D.z;
-        if (SCHEME == VFMM_SCHEME_TRANSPOSE) {
-            t.w0 = t.y1 * t.ai2 - t.y2 * t.ai1;
-            t.w1 = t.y2 * t.ai0 - t.y0 * t.ai2;
-            t.w2 = t.y0 * t.ai1 - t.y1 * t.ai0;
-        }
-        Acc9 p = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-        if (SPLIT == 1) {
-            if (var == 1)
-                leaf_loop<1, SCHEME, VAR>(k, A.rec, s0, sc, t, p);
-            else if (var == 0)
-                leaf_loop<0, SCHEME, VAR>(k, A.rec, s0, sc, t, p);
-            else
-                leaf_loop<2, SCHEME, VAR>(k, A.rec, s0, sc, t, p);
-        } else {
-            if (var == 1)
-                leaf_loop_split<1, SCHEME, SPLIT, VAR>(k, A.rec, s0, sc, grp, t, p);
-            else if (var == 0)
-                leaf_loop_split<0, SCHEME, SPLIT, VAR>(k, A.rec, s0, sc, grp, t, p);
-            else
-                leaf_loop_split<2, SCHEME, SPLIT, VAR>(k, A.rec, s0, sc, grp, t, p);
-        }
-        float u0 = p.u0, u1 = p.u1, u2 = p.u2;
-        if (SCHEME == VFMM_SCHEME_TRANSPOSE) {  // Ah x y_i - Bh
-            u0 = fmaf(p.a1, t.y2, fmaf(-p.a2, t.y1, -p.u0));
-            u1 = fmaf(p.a2, t.y0, fmaf(-p.a0, t.y2, -p.u1));
-            u2 = fmaf(p.a0, t.y1, fmaf(-p.a1, t.y0, -p.u2));
-        }
-        const float pv[9] = {u0, u1, u2, p.a0, p.a1, p.a2, p.t0, p.t1, p.t2};
-        if (KAHAN) {
-#pragma unroll
-            for (int q = 0; q < 9; ++q) kahan_add(S[q], Cc[q], pv[q]);
-        } else {
-#pragma unroll
-            for (int q = 0; q < 9; ++q) S[q] += pv[q];
-        }
+    return r0;
+}
+
+template <int SCHEME>
+__device__ __forceinline__ void set_offset(float4 r0, float4 D, Tgt &t) {
+    t.y0 = r0.x + D.x;
+    t.y1 = r0.y + D.y;
+    t.y2 = r0.z + D.z;
+    if (SCHEME == VFMM_SCHEME_TRANSPOSE) {
+        t.w0 = t.y1 * t.ai2 - t.y2 * t.ai1;
+        t.w1 = t.y2 * t.ai0 - t.y0 * t.ai2;
+        t.w2 = t.y0 * t.ai1 - t.y1 * t.ai0;
     }
-    if (SPLIT > 1) {
-#pragma unroll
-        for (int q = 0; q < 9; ++q) {
-            if (KAHAN) S[q] -= Cc[q];
-            S[q] += __shfl_xor(S[q], 32, 64);
-            if (SPLIT > 2) S[q] += __shfl_xor(S[q], 16, 64);
-        }
+}
+
+// adds one source leaf's sums to the running totals
+template <int SCHEME, bool KAHAN>
+__device__ __forceinline__ void add_leaf(const Tgt &t, const Acc9 &p, float *S, float *Cc) {
+    float u0 = p.u0, u1 = p.u1, u2 = p.u2;
+    if (SCHEME == VFMM_SCHEME_TRANSPOSE) {  // Ah x y_i - Bh
+        u0 = fmaf(p.a1, t.y2, fmaf(-p.a2, t.y1, -p.u0));
+        u1 = fmaf(p.a2, t.y0, fmaf(-p.a0, t.y2, -p.u1));
+        u2 = fmaf(p.a0, t.y1, fmaf(-p.a1, t.y0, -p.u2));
     }
-    if (!valid || grp != 0) return;
+    const float pv[9] = {u0, u1, u2, p.a0, p.a1, p.a2, p.t0, p.t1, p.t2};
+    if (KAHAN) {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) kahan_add(S[q], Cc[q], pv[q]);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) S[q] += pv[q];
+    }
+}
+
+// u and dalpha of target i (number tl of its block of tc) from the sums S:
+// a partial result when near is given, else the outputs
+template <int SCHEME>
+__device__ __forceinline__ void finish(const P2PConst &k, const P2PArgs &A, int i, int tl, int tc, const Tgt &t,
+                                       const float *S, float *near) {
     const float ai0 = t.ai0, ai1 = t.ai1, ai2 = t.ai2;
     // dalpha = alpha_i x A - 3 T (transpose) or A x alpha_i - 3 T (classical)
     float d0, d1, d2;
@@ -456,24 +411,207 @@ __device__ __forceinline__ void p2p_block(const P2PConst &k, const P2PArgs &A, i
     A.daz[o] = d2;
 }
 
+
+// A block of more than 32 targets: a lane per target, sources as scalar operands.
+template <int SCHEME, bool KAHAN, bool VAR>
+__device__ __forceinline__ void p2p_block(const P2PConst &k, const P2PArgs &A, int t0, int tc, int l0, int lc,
+                                          float *near) {
+    const int lane = threadIdx.x & 63;
+    const bool valid = lane < tc;
+    const int i = t0 + (valid ? lane : 0);
+    Tgt t;
+    const float4 r0 = load_target<VAR>(A, i, t);
+    float S[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    float Cc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    for (int e = 0; e < lc; ++e) {
+        const int4 en = A.ent[l0 + e];
+        const int s0 = __builtin_amdgcn_readfirstlane(en.x);
+        const int sc = __builtin_amdgcn_readfirstlane(en.y);
+        const int var = __builtin_amdgcn_readfirstlane(en.w);
+        set_offset<SCHEME>(r0, A.sh[l0 + e], t);
+        Acc9 p = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+        if (var == 1)
+            leaf_loop<1, SCHEME, VAR>(k, A.rec, s0, sc, t, p);
+        else if (var == 0)
+            leaf_loop<0, SCHEME, VAR>(k, A.rec, s0, sc, t, p);
+        else
+            leaf_loop<2, SCHEME, VAR>(k, A.rec, s0, sc, t, p);
+        add_leaf<SCHEME, KAHAN>(t, p, S, Cc);
+    }
+    if (valid) finish<SCHEME>(k, A, i, lane, tc, t, S, near);
+}
+
+// A block of at most 32 targets.  With a lane per target most of the wave would
+// idle, so ng = p2p_groups(tc) groups of tc lanes each hold every target and
+// take every ng-th source.  Scalar loads cannot give the groups different
+// sources, and vector loads of them pass the L1 separately for every lane, so
+// the wave stages 64 sources at a time in LDS, one per lane, and the groups
+// read them back as broadcasts.  The list is taken as one stream of sources,
+// 64 entries at a time: a prefix sum of the entries' source counts tells each
+// lane which source it stages (a binary search), so that the groups always
+// have equal work whatever the leaves' sizes, and a lane moves its source into
+// the target leaf's frame as it stages it (delta_j - D', and ah x of it), so
+// that there is no work per entry left in the pair loop.  Lanes past the end of
+// the stream stage zero strengths far away, which contribute exactly zero.
+// Bound by VALU issue like the scalar form (70 of about 85 instructions per
+// trip of two sources are pair arithmetic).  An 80^3 jittered lattice (15.6
+// particles per leaf, 2.88e9 pairs): 7.1 ms with groups of 16 or 32 lanes that
+// read every source from memory, 4.6 ms with groups that take whole entries
+// from LDS, 3.05 ms so; per-particle cores at 50^3 (27 to 64 per leaf): 1.8,
+// 1.6 and 1.1 ms.
+struct GroupLds {
+    float4 rec[3 * 64];  // staged records
+    float4 hd[64];       // D' of an entry; its first source less the sources before it
+    int incl[64];        // inclusive prefix sum of the source counts
+    int form[64];        // cutoff form
+};
+
+template <int V, int SCHEME, bool VAR>
+__device__ __forceinline__ void group_loop(const P2PConst &k, const float4 *stage, int ng, int trips, const Tgt &t,
+                                           Acc9 &p) {
+    for (int j = 0; j < trips; ++j) {
+        float4 sp[2], sa[2], sb[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            sp[u] = stage[0];
+            sa[u] = stage[1];
+            sb[u] = stage[2];
+            stage += 3 * ng;
+        }
+        trip<V, SCHEME, VAR, 2>(k, t, sp, sa, sb, p);
+    }
+}
+
+template <int SCHEME, bool KAHAN, bool VAR>
+__device__ __forceinline__ void p2p_group(const P2PConst &k, const P2PArgs &A, int t0, int tc, int l0, int lc,
+                                          float *near, GroupLds &L) {
+    constexpr int RS = VAR ? 4 : 3;
+    const int lane = threadIdx.x & 63;
+    const int ng = p2p_groups(tc);
+    const int chunk = ((64 / ng) & ~1) * ng;  // sources per pass: an even number per group
+    const int g0 = (int)(((float)lane + 0.5f) / (float)tc);
+    const int grp = min(g0, ng - 1);          // lanes past the last group repeat its reads
+    const int tl = lane - g0 * tc;
+    const int i = t0 + tl;
+    Tgt t;
+    const float4 r0 = load_target<VAR>(A, i, t);
+    set_offset<SCHEME>(r0, make_float4(0.f, 0.f, 0.f, 0.f), t);
+    float S[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    float Cc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    for (int b = 0; b < lc; b += 64) {
+        const bool has = b + lane < lc;
+        const int4 en = has ? A.ent[l0 + b + lane] : make_int4(0, 0, 0, 2);
+        const float4 D = has ? A.sh[l0 + b + lane] : make_float4(0.f, 0.f, 0.f, 0.f);
+        int x = en.y;  // inclusive prefix sum
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        const int total = __builtin_amdgcn_readlane(x, 63);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // LDS order within the wave
+        L.hd[lane] = make_float4(D.x, D.y, D.z, __int_as_float(en.x - (x - en.y)));
+        L.incl[lane] = x;
+        L.form[lane] = en.w;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        for (int f0 = 0; f0 < total; f0 += chunk) {
+            const int f = f0 + lane;
+            const bool ok = lane < chunk && f < total;
+            const int ff = ok ? f : total - 1;
+            int e = 0;  // the first entry whose inclusive sum exceeds ff
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1)
+                if (L.incl[e + o - 1] <= ff) e += o;
+            const float4 h = L.hd[e];
+            const int form = ok ? L.form[e] : 2;
+            const float4 *src = A.rec + RS * (size_t)(__float_as_int(h.w) + ff);
+            float4 sp = src[0], sa = src[1], sb = src[2];
+            // into the target leaf's frame
+            sp.x -= h.x;
+            sp.y -= h.y;
+            sp.z -= h.z;
+            sb.x = fmaf(sa.z, h.y, fmaf(-sa.y, h.z, sb.x));
+            sb.y = fmaf(sa.x, h.z, fmaf(-sa.z, h.x, sb.y));
+            sb.z = fmaf(sa.y, h.x, fmaf(-sa.x, h.y, sb.z));
+            if (!ok) {
+                sp = make_float4(1e4f, 0.f, 0.f, 1.f);
+                sa = sb = make_float4(0.f, 0.f, 0.f, 1.f);
+            }
+            // the form that every staged source allows
+            const int any0 = __any(form == 0), any1 = __any(form == 1);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the last pass has read its records
+            L.rec[3 * lane] = sp;
+            L.rec[3 * lane + 1] = sa;
+            L.rec[3 * lane + 2] = sb;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const int trips = (min(chunk, total - f0) + 2 * ng - 1) / (2 * ng);
+            const float4 *stage = L.rec + 3 * grp;
+            Acc9 p = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+            if (any0)
+                group_loop<0, SCHEME, VAR>(k, stage, ng, trips, t, p);
+            else if (any1)
+                group_loop<1, SCHEME, VAR>(k, stage, ng, trips, t, p);
+            else
+                group_loop<2, SCHEME, VAR>(k, stage, ng, trips, t, p);
+            const float pv[9] = {p.u0, p.u1, p.u2, p.a0, p.a1, p.a2, p.t0, p.t1, p.t2};
+#pragma unroll
+            for (int q = 0; q < 9; ++q) {
+                if (KAHAN)
+                    kahan_add(S[q], Cc[q], pv[q]);
+                else
+                    S[q] += pv[q];
+            }
+        }
+    }
+    // the groups' sums, added in group order
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        if (KAHAN) S[q] -= Cc[q];
+        float v = S[q];
+        for (int g = 1; g < ng; ++g) v += __shfl(S[q], (lane + g * tc) & 63, 64);
+        S[q] = v;
+    }
+    if (SCHEME == VFMM_SCHEME_TRANSPOSE) {  // Ah x y_i - Bh
+        const float b0 = S[0], b1 = S[1], b2 = S[2];
+        S[0] = fmaf(S[4], t.y2, fmaf(-S[5], t.y1, -b0));
+        S[1] = fmaf(S[5], t.y0, fmaf(-S[3], t.y2, -b1));
+        S[2] = fmaf(S[3], t.y1, fmaf(-S[4], t.y0, -b2));
+    }
+    if (lane < tc) finish<SCHEME>(k, A, i, tl, tc, t, S, near);
+}
+
+// One wave per item; neighbouring waves take the parts of one block (they share
+// its target records and much of its source data in the caches).  The two kinds
+// of blocks are two kernels: the group form needs 74 vector registers, which
+// would cost the scalar form (51) one of its seven waves per SIMD.
+__device__ __forceinline__ bool load_item(const P2PArgs &A, int item0, int nitems, int &t0, int &tc, int &l0, int &lc,
+                                          float *&near) {
+    const int j = xcd_logical(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
+    if (j >= nitems) return false;
+    const int item = item0 + j;
+    const int4 it = A.items[item];
+    t0 = __builtin_amdgcn_readfirstlane(it.x);
+    tc = __builtin_amdgcn_readfirstlane(it.y);
+    l0 = __builtin_amdgcn_readfirstlane(it.z);
+    lc = __builtin_amdgcn_readfirstlane(it.w);
+    near = A.near ? A.near + 6 * (size_t)__builtin_amdgcn_readfirstlane(A.item_out[item]) : nullptr;
+    return true;
+}
+
 template <int SCHEME, bool KAHAN, bool VAR>
 __global__ __launch_bounds__(256) void k_p2p(P2PConst k, P2PArgs A) {
-    // neighbouring waves take the parts of one block (they share its target
-    // records and much of its source data in the caches)
-    const int item = xcd_logical(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
-    if (item >= A.nitems) return;
-    const int4 it = A.items[item];
-    const int t0 = __builtin_amdgcn_readfirstlane(it.x);
-    const int tc = __builtin_amdgcn_readfirstlane(it.y);
-    const int l0 = __builtin_amdgcn_readfirstlane(it.z);
-    const int lc = __builtin_amdgcn_readfirstlane(it.w);
-    float *near = A.near ? A.near + 6 * (size_t)__builtin_amdgcn_readfirstlane(A.item_out[item]) : nullptr;
-    if (tc <= 16)
-        p2p_block<SCHEME, KAHAN, 4, VAR>(k, A, t0, tc, l0, lc, near);
-    else if (tc <= 32)
-        p2p_block<SCHEME, KAHAN, 2, VAR>(k, A, t0, tc, l0, lc, near);
-    else
-        p2p_block<SCHEME, KAHAN, 1, VAR>(k, A, t0, tc, l0, lc, near);
+    int t0, tc, l0, lc;
+    float *near;
+    if (load_item(A, 0, A.nitems_w, t0, tc, l0, lc, near)) p2p_block<SCHEME, KAHAN, VAR>(k, A, t0, tc, l0, lc, near);
+}
+
+template <int SCHEME, bool KAHAN, bool VAR>
+__global__ __launch_bounds__(256) void k_p2p_group(P2PConst k, P2PArgs A) {
+    __shared__ GroupLds lds[4];
+    int t0, tc, l0, lc;
+    float *near;
+    if (load_item(A, A.nitems_w, A.nitems - A.nitems_w, t0, tc, l0, lc, near))
+        p2p_group<SCHEME, KAHAN, VAR>(k, A, t0, tc, l0, lc, near, lds[threadIdx.x >> 6]);
 }
 
 // Records of the float32 near field (sorted order), one wave per leaf.
@@ -719,12 +857,22 @@ void p2p_prepare(Ctx &c) { p2p_records(c); }
 
 template <int SCHEME, bool KAHAN>
 static void launch_p2p(const P2PConst &k, const P2PArgs &A, bool var, hipStream_t s) {
-    if (A.nitems == 0) return;
-    if (var)
-        k_p2p<SCHEME, KAHAN, true><<<xcd_grid(cdiv(A.nitems, 4)), 256, 0, s>>>(k, A);
-    else
-        k_p2p<SCHEME, KAHAN, false><<<xcd_grid(cdiv(A.nitems, 4)), 256, 0, s>>>(k, A);
-    VFMM_LAUNCH_CHECK();
+    if (A.nitems_w > 0) {
+        const unsigned g = xcd_grid(cdiv(A.nitems_w, 4));
+        if (var)
+            k_p2p<SCHEME, KAHAN, true><<<g, 256, 0, s>>>(k, A);
+        else
+            k_p2p<SCHEME, KAHAN, false><<<g, 256, 0, s>>>(k, A);
+        VFMM_LAUNCH_CHECK();
+    }
+    if (A.nitems > A.nitems_w) {
+        const unsigned g = xcd_grid(cdiv(A.nitems - A.nitems_w, 4));
+        if (var)
+            k_p2p_group<SCHEME, KAHAN, true><<<g, 256, 0, s>>>(k, A);
+        else
+            k_p2p_group<SCHEME, KAHAN, false><<<g, 256, 0, s>>>(k, A);
+        VFMM_LAUNCH_CHECK();
+    }
 }
 
 static void dispatch_p2p(const vfmm_params &prm, bool var, const P2PConst &k, const P2PArgs &A, hipStream_t s) {
@@ -743,12 +891,12 @@ static P2PArgs tree_args(Ctx &c) {
     A.rec = c.recp.as<float4>();
     A.items = c.items.as<int4>();
     A.item_out = c.item_out.as<int>();
-    A.blocks = c.blocks.as<int4>();
-    A.bparts = c.bparts.as<int2>();
+    A.blocks = c.pblocks.as<int4>();
     A.ent = c.p2p_ent.as<int4>();
     A.sh = c.p2p_sh.as<float4>();
     A.nitems = c.n_items;
-    A.nblocks = c.n_blocks;
+    A.nitems_w = c.n_items_w;
+    A.nblocks = c.n_pblocks;
     A.n = c.n;
     A.perm = c.perm.as<int>();
     A.bounds = c.bres.as<Bounds>();
@@ -782,12 +930,11 @@ __global__ __launch_bounds__(256) void k_finalize(P2PArgs A, const float *__rest
     const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (b >= A.nblocks) return;
     const int4 blk = A.blocks[b];
-    const int2 pt = A.bparts[b];
     if (lane >= blk.y) return;
     const int64_t i = blk.x + lane;
     const int64_t n = A.n;
-    const int tc = blk.y, np = pt.y;
-    const float *q = near + 6 * (size_t)pt.x + lane;
+    const int tc = blk.y, np = blk.w;
+    const float *q = near + 6 * (size_t)blk.z + lane;
     float v[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int p0 = 0; p0 < np; p0 += 4) {
         float w[4][6];
@@ -823,7 +970,7 @@ void finalize_near_far(Ctx &c, float *ux, float *uy, float *uz, float *dax, floa
     A.far_da = c.far_da.as<float>();
     A.ux = ux; A.uy = uy; A.uz = uz; A.dax = dax; A.day = day; A.daz = daz;
     if (c.n == 0) return;
-    k_finalize<<<cdiv(c.n_blocks, 4), 256, 0, c.stream>>>(A, c.near.as<float>());
+    k_finalize<<<cdiv(c.n_pblocks, 4), 256, 0, c.stream>>>(A, c.near.as<float>());
     VFMM_LAUNCH_CHECK();
 }
 
@@ -917,7 +1064,7 @@ static void direct_f32_impl(const Ctx &c, Ctx *tc, hipStream_t s, int64_t n, con
     A.items = b.blocks;
     A.ent = b.ent;
     A.sh = b.sh;
-    A.nitems = nb;
+    A.nitems = A.nitems_w = nb;
     A.far_u = nullptr;
     A.far_da = nullptr;
     A.n = n;

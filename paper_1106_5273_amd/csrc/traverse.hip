@@ -266,7 +266,7 @@ __global__ __launch_bounds__(TPB) void k_sum_u64x2(const unsigned long long *par
 // ---------------------------------------------------------------------------
 // P2P work: every leaf's targets are cut into blocks of at most 64, and every
 // block's list into parts of about equal length, one wave each.  The length of
-// a part is chosen from the whole build's work: total wave steps / 57,344 (eight
+// a part is chosen from the whole build's work: total wave steps / 172,032 (24
 // rounds of the 7,168 waves that fill the chip), but at least 48 steps (shorter
 // parts cost more in their prologue and partial sums than they spread) and at
 // most 2,400 (the four parts of 37 leaves at 128^3).  A fixed four parts per
@@ -281,17 +281,59 @@ struct LeafWork {
 __device__ inline LeafWork leaf_work(const unsigned long long *tot, int64_t nent) {
     const float pairs = (float)tot[0], srcs = (float)tot[1];
     return LeafWork{fmaxf(1.f, srcs / (float)max((int64_t)1, nent)),
-                    fminf(2400.f, fmaxf(48.f, pairs * (1.f / (48.f * 57344.f))))};
+                    fminf(2400.f, fmaxf(48.f, pairs * (1.f / (48.f * 172032.f))))};
 }
 
-// parts of the list (lc entries) of a block of tc targets; the entry's fixed
-// cost counts as six steps, and small blocks take several sources per step
+// The remainder r = 1 .. 63 of a leaf's targets past its blocks of 64 is cut
+// into k blocks of nearly equal size.  A block of more than 32 targets leaves
+// the other lanes idle, one of g <= 32 fills the wave with several groups that
+// take different list entries (p2p_groups), so the wave rounds per list entry
+// are k / p2p_groups(ceil(r / k)); k grows where that saves at least a fifth
+// (33 .. 42 targets: two blocks, 2/3; 43 .. 48: three, 3/4).  Leaves of 27, 36
+// and 48 (per-particle cores, 50^3): near field 1.28 -> 1.10 ms.
+__device__ inline int remainder_blocks(int r) {
+    int best = 1;
+    float cost = 1.f / (float)p2p_groups(r);
+    for (int k = 2; k <= 3 && k <= r; ++k) {
+        const float ck = (float)k / (float)p2p_groups((r + k - 1) / k);
+        if (ck <= 0.8f * cost) {
+            best = k;
+            cost = ck;
+        }
+    }
+    return best;
+}
+
+// block b of a leaf of cnt targets: its first target and size (false past the last)
+__device__ inline bool leaf_block(int cnt, int b, int k, int &t0, int &tc) {
+    const int full = cnt / 64, r = cnt % 64;
+    if (b < full) {
+        t0 = 64 * b;
+        tc = 64;
+        return true;
+    }
+    if (r == 0 || b >= full + k) return false;
+    const int q = b - full;
+    const int lo = q * r / k, hi = (q + 1) * r / k;
+    t0 = 64 * full + lo;
+    tc = hi - lo;
+    return true;
+}
+
+// parts of the list (lc entries) of a block of tc targets: whole-wave blocks
+// take an entry's sources one per step with a fixed cost of about six steps
+// per entry, lane groups take a share of the list's sources; a part of theirs
+// holds at least 128 sources (the last pass of 64 is partly empty)
 __device__ inline int list_parts(const LeafWork &W, int tc, int lc) {
-    const float per = W.src_per_entry / (tc <= 16 ? 4.f : (tc <= 32 ? 2.f : 1.f)) + 6.f;
-    return max(1, min(lc, (int)((float)lc * per / W.part + 0.5f)));
+    if (tc > 32) return max(1, min(lc, (int)((float)lc * (W.src_per_entry + 6.f) / W.part + 0.5f)));
+    const float srcs = (float)lc * W.src_per_entry;
+    const int most = min(lc, (int)(srcs * (1.f / 128.f)));
+    return max(1, min(most, (int)(srcs / ((float)p2p_groups(tc) * W.part) + 0.5f)));
 }
 
-// per leaf: its blocks, its parts and the float[6] outputs of its parts
+// per leaf: its blocks of 64 (Gaussian sums, float64 form), its near-field
+// blocks, the parts of blocks that take whole waves and of those that take
+// lane groups, and the float[6] outputs of the parts
 __global__ __launch_bounds__(TPB) void k_leaf_counts(const int *leaves, int nl, const int *count, const int *loff,
                                                      const unsigned long long *tot, int64_t nent, int *out) {
     const int i = blockIdx.x * TPB + threadIdx.x;
@@ -299,47 +341,59 @@ __global__ __launch_bounds__(TPB) void k_leaf_counts(const int *leaves, int nl, 
     const LeafWork W = leaf_work(tot, nent);
     const int cell = leaves[i];
     const int cnt = count[cell], lc = loff[cell + 1] - loff[cell];
-    int nb = 0, ni = 0, nu = 0;
-    for (int k = 0; k < cnt; k += 64, ++nb) {
-        const int tc = min(64, cnt - k), np = list_parts(W, tc, lc);
-        ni += np;
+    const int k = remainder_blocks(max(1, cnt % 64));
+    int nb = 0, nw = 0, ng = 0, nu = 0, t0, tc;
+    for (; leaf_block(cnt, nb, k, t0, tc); ++nb) {
+        const int np = list_parts(W, tc, lc);
+        (tc > 32 ? nw : ng) += np;
         nu += np * tc;
     }
-    out[i] = nb;
-    out[nl + i] = ni;
-    out[2 * nl + i] = nu;
+    out[i] = (cnt + 63) / 64;
+    out[nl + i] = nb;
+    out[2 * nl + i] = nw;
+    out[3 * nl + i] = ng;
+    out[4 * nl + i] = nu;
 }
 
-// the three totals and the pair count, straight to pinned host memory
+// the five totals and the pair count, straight to pinned host memory
 __global__ void k_leaf_totals(const int *cnt, const int *off, int nl, const int *tot, int *out) {
-    for (int k = 0; k < 3; ++k) out[k] = off[(k + 1) * nl - 1] + cnt[(k + 1) * nl - 1] - off[k * nl];
-    out[3] = tot[0];
-    out[4] = tot[1];
+    for (int k = 0; k < 5; ++k) out[k] = off[(k + 1) * nl - 1] + cnt[(k + 1) * nl - 1] - off[k * nl];
+    out[5] = tot[0];
+    out[6] = tot[1];
 }
 
-// blocks (target start, targets, first entry, entries), their parts (first
-// output, parts), and one work item per part (target start, targets, first
-// entry, entries) with its first output
+// blocks of 64 (target start, targets, first entry, entries); near-field blocks
+// (target start, targets, first output, parts) and one work item per part
+// (target start, targets, first entry, entries) with its first output: items
+// [0, nw) take whole waves (more than 32 targets), the rest lane groups
 __global__ __launch_bounds__(TPB) void k_leaf_items(const int *leaves, int nl, const int *start, const int *count,
                                                     const int *loff, const unsigned long long *tot, int64_t nent,
-                                                    const int *off, int4 *blocks, int2 *bparts, int4 *items,
-                                                    int *item_out) {
-    const int i = blockIdx.x * TPB + threadIdx.x;
+                                                    const int *off, int nw, int4 *blocks, int4 *pblocks,
+                                                    int4 *items, int *item_out) {
+    // one wave per leaf: a leaf may have hundreds of parts
+    const int i = blockIdx.x * (TPB / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (i >= nl) return;
     const LeafWork W = leaf_work(tot, nent);
     const int cell = leaves[i];
     const int s = start[cell], cnt = count[cell];
     const int l0 = loff[cell], lc = loff[cell + 1] - l0;
-    int b = off[i], it = off[nl + i] - off[nl], u = off[2 * nl + i] - off[2 * nl];
-    for (int k = 0; k < cnt; k += 64, ++b) {
-        const int tc = min(64, cnt - k), np = list_parts(W, tc, lc);
-        blocks[b] = make_int4(s + k, tc, l0, lc);
-        bparts[b] = make_int2(u, np);
-        for (int q = 0; q < np; ++q, ++it, u += tc) {
-            const int e0 = (int)((int64_t)q * lc / np), e1 = (int)((int64_t)(q + 1) * lc / np);
-            items[it] = make_int4(s + k, tc, l0 + e0, e1 - e0);
-            item_out[it] = u;
+    for (int k = 64 * lane, b = off[i] + lane; k < cnt; k += 64 * 64, b += 64)
+        blocks[b] = make_int4(s + k, min(64, cnt - k), l0, lc);
+    const int k = remainder_blocks(max(1, cnt % 64));
+    const int pb = off[nl + i] - off[nl];
+    int iw = off[2 * nl + i] - off[2 * nl], ig = nw + off[3 * nl + i] - off[3 * nl];
+    int u = off[4 * nl + i] - off[4 * nl], t0, tc;
+    for (int q = 0; leaf_block(cnt, q, k, t0, tc); ++q) {
+        const int np = list_parts(W, tc, lc);
+        if (lane == 0) pblocks[pb + q] = make_int4(s + t0, tc, u, np);
+        int &it = tc > 32 ? iw : ig;
+        for (int p = lane; p < np; p += 64) {
+            const int e0 = (int)((int64_t)p * lc / np), e1 = (int)((int64_t)(p + 1) * lc / np);
+            items[it + p] = make_int4(s + t0, tc, l0 + e0, e1 - e0);
+            item_out[it + p] = u + p * tc;
         }
+        it += np;
+        u += np * tc;
     }
 }
 
@@ -490,30 +544,32 @@ void traverse_and_lists(Ctx &c) {
     }
     // ---- P2P work: blocks of <= 64 targets, their lists in parts ----
     const int nl = c.nleaves;
-    c.c_tmp.ensure(sizeof(int) * (6 * (size_t)nl + 2));
-    int *cnt = c.c_tmp.as<int>(), *off = cnt + 3 * (size_t)nl;
+    c.c_tmp.ensure(sizeof(int) * (10 * (size_t)nl + 2));
+    int *cnt = c.c_tmp.as<int>(), *off = cnt + 5 * (size_t)nl;
     const unsigned long long *tot = c.pairs64.as<unsigned long long>();
     k_leaf_counts<<<cdiv(nl, TPB), TPB, 0, s>>>(c.leaves.as<int>(), nl, c.c_count.as<int>(), c.p2p_off.as<int>(), tot,
                                                 n_p2p, cnt);
     VFMM_LAUNCH_CHECK();
-    scan_excl_i32(c, cnt, off, 3 * (int64_t)nl);
+    scan_excl_i32(c, cnt, off, 5 * (int64_t)nl);
     k_leaf_totals<<<1, 1, 0, s>>>(cnt, off, nl, c.pairs64.as<int>(), pinned_ints(c));
     VFMM_LAUNCH_CHECK();
-    int h5[5];
-    sync_ints(c, 5, h5);
-    c.n_blocks = h5[0];
-    c.n_items = h5[1];
-    c.n_partial = h5[2];
-    c.p2p_pairs = (int64_t)((unsigned long long)(uint32_t)h5[3] | ((unsigned long long)(uint32_t)h5[4] << 32));
-    if (c.n_blocks < 0 || c.n_items < 0 || c.n_partial < 0)
+    int h7[7];
+    sync_ints(c, 7, h7);
+    c.n_blocks = h7[0];
+    c.n_pblocks = h7[1];
+    c.n_items_w = h7[2];
+    c.n_items = h7[2] + h7[3];
+    c.n_partial = h7[4];
+    c.p2p_pairs = (int64_t)((unsigned long long)(uint32_t)h7[5] | ((unsigned long long)(uint32_t)h7[6] << 32));
+    if (c.n_pblocks < 0 || c.n_items < 0 || c.n_partial < 0)
         throw Error{VFMM_ENOMEM, "near-field work items exceed 2^31 entries"};
     c.blocks.ensure(sizeof(int4) * (size_t)std::max(c.n_blocks, 1));
-    c.bparts.ensure(sizeof(int2) * (size_t)std::max(c.n_blocks, 1));
+    c.pblocks.ensure(sizeof(int4) * (size_t)std::max(c.n_pblocks, 1));
     c.items.ensure(sizeof(int4) * (size_t)std::max(c.n_items, 1));
     c.item_out.ensure(sizeof(int) * (size_t)std::max(c.n_items, 1));
-    k_leaf_items<<<cdiv(nl, TPB), TPB, 0, s>>>(c.leaves.as<int>(), nl, c.c_start.as<int>(), c.c_count.as<int>(),
-                                               c.p2p_off.as<int>(), tot, n_p2p, off, c.blocks.as<int4>(),
-                                               c.bparts.as<int2>(), c.items.as<int4>(), c.item_out.as<int>());
+    k_leaf_items<<<cdiv(nl, TPB / 64), TPB, 0, s>>>(c.leaves.as<int>(), nl, c.c_start.as<int>(), c.c_count.as<int>(),
+                                               c.p2p_off.as<int>(), tot, n_p2p, off, c.n_items_w, c.blocks.as<int4>(),
+                                               c.pblocks.as<int4>(), c.items.as<int4>(), c.item_out.as<int>());
     VFMM_LAUNCH_CHECK();
 }
 
