@@ -296,7 +296,7 @@ vfmm_status vfmm_energy_spectrum(vfmm_ctx *ctx, int32_t n, const float *ux, cons
  * results bit for bit; the context's tree and lists are left as they were.
  * Inputs and outputs as in fmm_evaluate (device float32[n], caller order).
  * It allocates nothing: its scratch space is one device array of about
- * 6.7 MB compiled into the library, which every GPU that the library runs on
+ * 4.5 MB compiled into the library, which every GPU that the library runs on
  * holds until the process ends, and it is limited to n <= VFMM_STATIC_MAX_N.
  * Every call on one GPU uses that GPU's one array: calls that overlap on one
  * GPU (from several contexts, streams or threads) race and give wrong

@@ -151,9 +151,9 @@ static void do_build(Ctx &c, int64_t n, const float *x, const float *y, const fl
         c.built = true;
         return;
     }
-    compute_bounds(c, n, x, y, z, sigma, nullptr, nullptr, nullptr, false);
-    static_assert(sizeof(Bounds) % sizeof(int) == 0 && sizeof(Bounds) <= 256, "Bounds read through read_words");
-    read_words(c, c.bres.ptr, sizeof(Bounds), &c.hb);
+    static_assert(sizeof(Bounds) <= 256, "Bounds fit the pinned host memory");
+    compute_bounds(c, n, x, y, z, sigma, nullptr, nullptr, nullptr, false, true);
+    sync_bounds(c, &c.hb);
     c.build_fp = c.hb.fp;
     c.build_ptr[0] = x;
     c.build_ptr[1] = y;
@@ -466,16 +466,20 @@ vfmm_status vfmm_create(const vfmm_params *params, void *hip_stream, vfmm_ctx **
         vfmm::set_params(h->c, *params);
         h->c.stream = (hipStream_t)hip_stream;
         VFMM_HIP(hipGetDevice(&h->c.device));
-        // the device address of fmm_direct_static's scratch array on this device
+        // the pinned memory and, on this device, the address of the scratch array of
+        // fmm_direct_static, which allocates nothing itself
+        vfmm::pinned_ints(h->c);
         vfmm::resolve_static_scratch(h->c.device);
         *out = h;
         return VFMM_OK;
     } catch (const Error &e) {
         vfmm::g_create_error = e.msg;
+        if (h) h->c.release_all();
         delete h;
         return e.st;
     } catch (const std::exception &e) {
         vfmm::g_create_error = e.what();
+        if (h) h->c.release_all();
         delete h;
         return VFMM_ENOMEM;
     }
@@ -706,10 +710,9 @@ vfmm_status fmm_evaluate(vfmm_ctx *ctx, int64_t n, const float *x, const float *
         }
         if (n > 0 && (x != c.build_ptr[0] || y != c.build_ptr[1] || z != c.build_ptr[2] || sigma != c.build_ptr[3])) {
             // other arrays than the build's: their contents must be the build's positions and cores
-            vfmm::compute_bounds(c, n, x, y, z, sigma, ax, ay, az, true);
+            vfmm::compute_bounds(c, n, x, y, z, sigma, ax, ay, az, true, true);
             vfmm::Bounds b;
-            VFMM_HIP(hipMemcpyAsync(&b, c.bres.ptr, sizeof(b), hipMemcpyDeviceToHost, c.stream));
-            VFMM_HIP(hipStreamSynchronize(c.stream));
+            vfmm::sync_bounds(c, &b);
             if (b.stale) throw Error{VFMM_ESTATE, "fmm_evaluate: positions or cores differ from those of the last build"};
         }
         c.err.clear();

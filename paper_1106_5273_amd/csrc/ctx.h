@@ -145,12 +145,15 @@ struct Ctx {
 // bytes of the partial-sum buffer of the bounds pass (any n)
 size_t bounds_scratch_bytes();
 // the bounds pass into caller-given buffers: part (bounds_scratch_bytes()) and res;
-// check_fp compares the positions' fingerprint with fp_ref (Bounds::stale)
+// check_fp compares the positions' fingerprint with fp_ref (Bounds::stale);
+// host (may be null): pinned host memory that receives the result too
 void launch_bounds(const Ctx &c, hipStream_t s, int64_t n, const float *x, const float *y, const float *z,
                    const float *sigma, const float *ax, const float *ay, const float *az, bool with_alpha,
-                   bool check_fp, double fp_ref, void *part, Bounds *res);
+                   bool check_fp, double fp_ref, void *part, Bounds *res, Bounds *host);
 void compute_bounds(Ctx &c, int64_t n, const float *x, const float *y, const float *z, const float *sigma,
-                    const float *ax, const float *ay, const float *az, bool with_alpha);
+                    const float *ax, const float *ay, const float *az, bool with_alpha, bool to_host = false);
+// synchronises the stream and hands over the bounds that a pass with to_host wrote
+void sync_bounds(Ctx &c, Bounds *dst);
 void build_tree(Ctx &c, int64_t n, const float *x, const float *y, const float *z, const float *sigma);
 void gather_strengths(Ctx &c, const float *ax, const float *ay, const float *az, const float *sigma);
 void gather_records64(Ctx &c, const float *ax, const float *ay, const float *az);
@@ -168,8 +171,6 @@ void read_ints(Ctx &c, std::initializer_list<const int *> src, int *dst);
 // synchronisation that hands their first n values to the host.
 int *pinned_ints(Ctx &c);
 void sync_ints(Ctx &c, int n, int *dst);
-// The same for a small device struct (at most 256 bytes, whole 4-byte words).
-void read_words(Ctx &c, const void *src, size_t bytes, void *dst);
 // traverse.hip
 void traverse_and_lists(Ctx &c);
 // far.hip
@@ -184,20 +185,11 @@ void p2p_and_finalize(Ctx &c, float *ux, float *uy, float *uz, float *dax, float
 void direct_all_pairs(Ctx &c, const float *x, const float *y, const float *z, const float *ax,
                       const float *ay, const float *az, const float *sigma, float *ux, float *uy,
                       float *uz, float *dax, float *day, float *daz);
-// Device buffers of the float32 all-pairs evaluation of n particles.
-struct DirectBufs {
-    float4 *rec;     // float4[2n]  (x, y, z, sigma), alpha/(4 pi)
-    int *perm;       // int[n]
-    int4 *blocks;    // int4[ceil(n/64)]
-    int4 *ent;       // int4[ceil(n/64)]
-    float4 *sh;      // float4[ceil(n/64)]
-    float4 *recp;    // float4[3n] (uniform cores) or float4[4n] (per-particle cores)
-    Bounds *bounds;  // bounds of the n particles (already computed)
-};
 // float32 (and mixed) all-pairs near field of n free-space particles into the
-// outputs (caller order); hb: the bounds' host copy (cores, extent).
-void direct_f32(const Ctx &c, hipStream_t s, int64_t n, const Bounds &hb, const DirectBufs &b, const float *x,
-                const float *y, const float *z, const float *ax, const float *ay, const float *az,
+// outputs (caller order); hb: the bounds' host copy (cores, extent), bounds the
+// device's; recp: float4[3n] (uniform cores) or float4[4n] (per-particle cores).
+void direct_f32(const Ctx &c, hipStream_t s, int64_t n, const Bounds &hb, float4 *recp, const Bounds *bounds,
+                const float *x, const float *y, const float *z, const float *ax, const float *ay, const float *az,
                 const float *sigma, float *ux, float *uy, float *uz, float *dax, float *day, float *daz);
 // Lane groups of a near-field block of tc targets: more than 32 targets take the
 // wave alone; fewer are held by several groups of tc lanes each (at most 16),

@@ -15,16 +15,10 @@ namespace vfmm {
 // 256-byte boundary.
 constexpr size_t al256(size_t b) { return (b + 255) / 256 * 256; }
 constexpr int64_t SMAX = VFMM_STATIC_MAX_N;
-constexpr int64_t SBLK = (SMAX + 63) / 64;
 constexpr size_t S_PART = 0;                                        // bounds partial sums
 constexpr size_t S_PART_BYTES = 262144;
 constexpr size_t S_BOUNDS = S_PART + S_PART_BYTES;                  // Bounds
-constexpr size_t S_REC = S_BOUNDS + al256(sizeof(Bounds));          // float4[2n]
-constexpr size_t S_PERM = S_REC + al256(sizeof(float4) * 2 * SMAX); // int[n]
-constexpr size_t S_BLK = S_PERM + al256(sizeof(int) * SMAX);        // int4[nb]
-constexpr size_t S_ENT = S_BLK + al256(sizeof(int4) * SBLK);        // int4[nb]
-constexpr size_t S_SH = S_ENT + al256(sizeof(int4) * SBLK);         // float4[nb]
-constexpr size_t S_RECP = S_SH + al256(sizeof(float4) * SBLK);      // float4[4n]
+constexpr size_t S_RECP = S_BOUNDS + al256(sizeof(Bounds));         // float4[4n]
 constexpr size_t S_BYTES = S_RECP + al256(sizeof(float4) * 4 * SMAX);
 
 static __device__ __align__(256) unsigned char scratch[S_BYTES];
@@ -105,10 +99,10 @@ vfmm_status fmm_direct_static(vfmm_ctx *ctx, int64_t n, const float *x, const fl
         }
         unsigned char *base = vfmm::static_scratch(c.device);
         vfmm::Bounds *bres = reinterpret_cast<vfmm::Bounds *>(base + vfmm::S_BOUNDS);
-        vfmm::launch_bounds(c, c.stream, n, x, y, z, sigma, ax, ay, az, true, false, 0.0, base + vfmm::S_PART, bres);
+        vfmm::launch_bounds(c, c.stream, n, x, y, z, sigma, ax, ay, az, true, false, 0.0, base + vfmm::S_PART, bres,
+                            reinterpret_cast<vfmm::Bounds *>(c.hpin));
         vfmm::Bounds hb;
-        VFMM_HIP(hipMemcpyAsync(&hb, bres, sizeof(hb), hipMemcpyDeviceToHost, c.stream));
-        VFMM_HIP(hipStreamSynchronize(c.stream));
+        vfmm::sync_bounds(c, &hb);
         // the checks fmm_build applies in direct mode
         if (hb.nonfinite) throw Error{VFMM_EDOMAIN, "non-finite position or non-positive core"};
         if (c.prm.box_len > 0.0 && hb.outside)
@@ -117,11 +111,8 @@ vfmm_status fmm_direct_static(vfmm_ctx *ctx, int64_t n, const float *x, const fl
         for (int d = 0; d < 3; ++d) ext = std::max(ext, hb.hi[d] - hb.lo[d]);
         if (ext * vfmm::p2p_kappa(hb.sig_min) >= 16777216.0)
             throw Error{VFMM_EINVAL, "cores too small for the domain: extent / sigma must stay below about 2e7"};
-        vfmm::DirectBufs b{reinterpret_cast<float4 *>(base + vfmm::S_REC), reinterpret_cast<int *>(base + vfmm::S_PERM),
-                           reinterpret_cast<int4 *>(base + vfmm::S_BLK), reinterpret_cast<int4 *>(base + vfmm::S_ENT),
-                           reinterpret_cast<float4 *>(base + vfmm::S_SH), reinterpret_cast<float4 *>(base + vfmm::S_RECP),
-                           bres};
-        vfmm::direct_f32(c, c.stream, n, hb, b, x, y, z, ax, ay, az, sigma, ux, uy, uz, dax, day, daz);
+        vfmm::direct_f32(c, c.stream, n, hb, reinterpret_cast<float4 *>(base + vfmm::S_RECP), bres, x, y, z, ax, ay, az,
+                         sigma, ux, uy, uz, dax, day, daz);
         c.err.clear();
         return VFMM_OK;
     } catch (const Error &e) {

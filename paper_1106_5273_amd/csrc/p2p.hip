@@ -109,8 +109,8 @@ struct P2PArgs {
     float inv3V;
     int surface;
     float *ux, *uy, *uz, *dax, *day, *daz;
-    float *near;  // non-null: write u and dalpha of the item's targets to near + 6 item_out, [6][targets],
-                  // instead of finishing (the finalize kernel adds the parts of a block)
+    float *near;  // tree mode: u and dalpha of an item's targets go to near + 6 item_out, [6][targets]
+                  // (the finalize kernel adds the parts of a block)
 };
 
 struct Acc9 {
@@ -358,8 +358,30 @@ __device__ __forceinline__ void add_leaf(const Tgt &t, const Acc9 &p, float *S, 
     }
 }
 
-// u and dalpha of target i (number tl of its block of tc) from the sums S:
-// a partial result when near is given, else the outputs
+// u's Ah x y_i - Bh once the sums are complete (every source in the target leaf's frame)
+template <int SCHEME>
+__device__ __forceinline__ void cross_sums(const Tgt &t, float *S) {
+    if (SCHEME != VFMM_SCHEME_TRANSPOSE) return;
+    const float b0 = S[0], b1 = S[1], b2 = S[2];
+    S[0] = fmaf(S[4], t.y2, fmaf(-S[5], t.y1, -b0));
+    S[1] = fmaf(S[5], t.y0, fmaf(-S[3], t.y2, -b1));
+    S[2] = fmaf(S[3], t.y1, fmaf(-S[4], t.y0, -b2));
+}
+
+template <bool KAHAN>
+__device__ __forceinline__ void add_sums(const Acc9 &p, float *S, float *Cc) {
+    const float pv[9] = {p.u0, p.u1, p.u2, p.a0, p.a1, p.a2, p.t0, p.t1, p.t2};
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        if (KAHAN)
+            kahan_add(S[q], Cc[q], pv[q]);
+        else
+            S[q] += pv[q];
+    }
+}
+
+// u and dalpha of target i (number tl of its block of tc) from the sums S: a
+// partial result when near is given, else (direct mode) the outputs
 template <int SCHEME>
 __device__ __forceinline__ void finish(const P2PConst &k, const P2PArgs &A, int i, int tl, int tc, const Tgt &t,
                                        const float *S, float *near) {
@@ -388,29 +410,14 @@ __device__ __forceinline__ void finish(const P2PConst &k, const P2PArgs &A, int 
         near[5 * tc + tl] = d2;
         return;
     }
-    if (A.far_u) {
-        u0 += A.far_u[i];
-        u1 += A.far_u[A.n + i];
-        u2 += A.far_u[2 * A.n + i];
-        d0 += A.far_da[i];
-        d1 += A.far_da[A.n + i];
-        d2 += A.far_da[2 * A.n + i];
-    }
-    if (A.surface) {
-        u0 -= (float)(A.bounds->sum_xa[0]) * A.inv3V;
-        u1 -= (float)(A.bounds->sum_xa[1]) * A.inv3V;
-        u2 -= (float)(A.bounds->sum_xa[2]) * A.inv3V;
-    }
     if (A.bounds->stale) u0 = u1 = u2 = d0 = d1 = d2 = __builtin_nanf("");  // positions differ from the build's
-    const int o = A.perm[i];
-    A.ux[o] = u0;
-    A.uy[o] = u1;
-    A.uz[o] = u2;
-    A.dax[o] = d0;
-    A.day[o] = d1;
-    A.daz[o] = d2;
+    A.ux[i] = u0;
+    A.uy[i] = u1;
+    A.uz[i] = u2;
+    A.dax[i] = d0;
+    A.day[i] = d1;
+    A.daz[i] = d2;
 }
-
 
 // A block of more than 32 targets: a lane per target, sources as scalar operands.
 template <int SCHEME, bool KAHAN, bool VAR>
@@ -553,14 +560,7 @@ __device__ __forceinline__ void p2p_group(const P2PConst &k, const P2PArgs &A, i
                 group_loop<1, SCHEME, VAR>(k, stage, ng, trips, t, p);
             else
                 group_loop<2, SCHEME, VAR>(k, stage, ng, trips, t, p);
-            const float pv[9] = {p.u0, p.u1, p.u2, p.a0, p.a1, p.a2, p.t0, p.t1, p.t2};
-#pragma unroll
-            for (int q = 0; q < 9; ++q) {
-                if (KAHAN)
-                    kahan_add(S[q], Cc[q], pv[q]);
-                else
-                    S[q] += pv[q];
-            }
+            add_sums<KAHAN>(p, S, Cc);
         }
     }
     // the groups' sums, added in group order
@@ -571,12 +571,7 @@ __device__ __forceinline__ void p2p_group(const P2PConst &k, const P2PArgs &A, i
         for (int g = 1; g < ng; ++g) v += __shfl(S[q], (lane + g * tc) & 63, 64);
         S[q] = v;
     }
-    if (SCHEME == VFMM_SCHEME_TRANSPOSE) {  // Ah x y_i - Bh
-        const float b0 = S[0], b1 = S[1], b2 = S[2];
-        S[0] = fmaf(S[4], t.y2, fmaf(-S[5], t.y1, -b0));
-        S[1] = fmaf(S[5], t.y0, fmaf(-S[3], t.y2, -b1));
-        S[2] = fmaf(S[3], t.y1, fmaf(-S[4], t.y0, -b2));
-    }
+    cross_sums<SCHEME>(t, S);
     if (lane < tc) finish<SCHEME>(k, A, i, tl, tc, t, S, near);
 }
 
@@ -594,7 +589,7 @@ __device__ __forceinline__ bool load_item(const P2PArgs &A, int item0, int nitem
     tc = __builtin_amdgcn_readfirstlane(it.y);
     l0 = __builtin_amdgcn_readfirstlane(it.z);
     lc = __builtin_amdgcn_readfirstlane(it.w);
-    near = A.near ? A.near + 6 * (size_t)__builtin_amdgcn_readfirstlane(A.item_out[item]) : nullptr;
+    near = A.near + 6 * (size_t)__builtin_amdgcn_readfirstlane(A.item_out[item]);
     return true;
 }
 
@@ -621,51 +616,44 @@ __global__ __launch_bounds__(256) void k_p2p_group(P2PConst k, P2PArgs A) {
 // Per-source cores (kappa_j of each particle's own core):
 //   rec[4i] = (x_i - c_leaf, kappa_i^2), rec[4i+1] = (ah_i, 1/kappa_i),
 //   rec[4i+2] = (ah_i x delta_i, kappa_i^3), rec[4i+3] = (alpha_i, 0),  ah = kappa_i^3 alpha/(4 pi).
-// Computed in float64 and rounded once.  A null cell list means one common
-// origin for every particle (direct mode).
+// Computed in float64 and rounded once.
+template <bool VAR>
+__device__ __forceinline__ void put_record(float4 *__restrict__ out, int64_t i, double d0, double d1, double d2,
+                                           double kap, double a0, double a1, double a2, float al0, float al1,
+                                           float al2) {
+    const double s3 = kap * kap * kap;  // a: alpha / (4 pi)
+    const double h0 = s3 * a0, h1 = s3 * a1, h2 = s3 * a2;
+    const double b0 = h1 * d2 - h2 * d1, b1 = h2 * d0 - h0 * d2, b2 = h0 * d1 - h1 * d0;
+    if (VAR) {
+        out[4 * i] = make_float4((float)d0, (float)d1, (float)d2, (float)(kap * kap));
+        out[4 * i + 1] = make_float4((float)h0, (float)h1, (float)h2, (float)(1.0 / kap));
+        out[4 * i + 2] = make_float4((float)b0, (float)b1, (float)b2, (float)s3);
+        out[4 * i + 3] = make_float4(al0, al1, al2, 0.f);
+    } else {
+        out[3 * i] = make_float4((float)d0, (float)d1, (float)d2, al0);
+        out[3 * i + 1] = make_float4((float)h0, (float)h1, (float)h2, al1);
+        out[3 * i + 2] = make_float4((float)b0, (float)b1, (float)b2, al2);
+    }
+}
+
 template <bool VAR>
 __global__ __launch_bounds__(256) void k_p2p_records(const int *__restrict__ leaves, int nleaves,
                                                      const int *__restrict__ start, const int *__restrict__ count,
-                                                     const float4 *__restrict__ geo, int64_t n, double ox, double oy,
-                                                     double oz, double kappa, double sa,
+                                                     const float4 *__restrict__ geo, double kappa,
                                                      const float4 *__restrict__ rec_in, float4 *__restrict__ out) {
-    int64_t i0, i1;
-    double cx = ox, cy = oy, cz = oz;
     const int w = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (leaves) {
-        if (w >= nleaves) return;
-        const int cell = leaves[w];
-        i0 = start[cell];
-        i1 = i0 + count[cell];
-        const float4 g = geo[cell];
-        cx = g.x;
-        cy = g.y;
-        cz = g.z;
-    } else {
-        i0 = (int64_t)w * 64;
-        i1 = min<int64_t>(i0 + 64, n);
-        if (i0 >= n) return;
-    }
+    if (w >= nleaves) return;
+    const int cell = leaves[w];
+    const int64_t i0 = start[cell], i1 = i0 + count[cell];
+    const float4 g = geo[cell];
     const double fp = 12.566370614359172954;  // 4 pi: rec_in holds alpha/(4 pi)
     for (int64_t i = i0 + (threadIdx.x & 63); i < i1; i += 64) {
         const float4 p = rec_in[2 * i], a = rec_in[2 * i + 1];
         // VAR: kappa argument = sqrt(log2 e)/sqrt(2), divided by each core
         const double kap = VAR ? kappa / (double)p.w : kappa;
         const double sc = VAR ? 1.0 : kappa;
-        const double d0 = sc * ((double)p.x - cx), d1 = sc * ((double)p.y - cy), d2 = sc * ((double)p.z - cz);
-        const double s3 = VAR ? kap * kap * kap : sa;
-        const double h0 = s3 * a.x, h1 = s3 * a.y, h2 = s3 * a.z;
-        const double b0 = h1 * d2 - h2 * d1, b1 = h2 * d0 - h0 * d2, b2 = h0 * d1 - h1 * d0;
-        if (VAR) {
-            out[4 * i] = make_float4((float)d0, (float)d1, (float)d2, (float)(kap * kap));
-            out[4 * i + 1] = make_float4((float)h0, (float)h1, (float)h2, (float)(1.0 / kap));
-            out[4 * i + 2] = make_float4((float)b0, (float)b1, (float)b2, (float)(kap * kap * kap));
-            out[4 * i + 3] = make_float4((float)(fp * a.x), (float)(fp * a.y), (float)(fp * a.z), 0.f);
-        } else {
-            out[3 * i] = make_float4((float)d0, (float)d1, (float)d2, (float)(fp * a.x));
-            out[3 * i + 1] = make_float4((float)h0, (float)h1, (float)h2, (float)(fp * a.y));
-            out[3 * i + 2] = make_float4((float)b0, (float)b1, (float)b2, (float)(fp * a.z));
-        }
+        put_record<VAR>(out, i, sc * ((double)p.x - g.x), sc * ((double)p.y - g.y), sc * ((double)p.z - g.z), kap,
+                        a.x, a.y, a.z, (float)(fp * a.x), (float)(fp * a.y), (float)(fp * a.z));
     }
 }
 
@@ -826,31 +814,24 @@ static P2PConst make_const(double sigma, bool var) {
     return k;
 }
 
-// Launches the float32 near-field records from the sorted records rec into
-// recp (tree: one wave per leaf, offsets from the leaf centre; direct: waves of
-// 64 particles, offsets from one common origin).
-static void launch_records(hipStream_t s, bool var, float sigma_uniform, const int *lv, int nl, const int *start,
-                           const int *count, const float4 *geo, int64_t n, const double *origin,
-                           const float4 *rec, float4 *recp) {
-    // uniform: kappa of the shared core and ah = kappa^3 alpha/(4 pi); per source: the
-    // numerator of kappa_j (the kernel scales each strength by its own kappa_j^3)
-    const double kap = var ? p2p_kappa(1.0) : p2p_kappa(sigma_uniform);
-    const double sa = kap * kap * kap;
-    const double o0 = origin ? origin[0] : 0.0, o1 = origin ? origin[1] : 0.0, o2 = origin ? origin[2] : 0.0;
-    const unsigned grid = lv ? cdiv(nl, 4) : cdiv(cdiv(n, 64), 4);
-    if (var)
-        k_p2p_records<true><<<grid, 256, 0, s>>>(lv, nl, start, count, geo, n, o0, o1, o2, kap, sa, rec, recp);
-    else
-        k_p2p_records<false><<<grid, 256, 0, s>>>(lv, nl, start, count, geo, n, o0, o1, o2, kap, sa, rec, recp);
-    VFMM_LAUNCH_CHECK();
-}
+// Scale of the records: kappa of the shared core, or the numerator of kappa_j.
+static double record_kappa(bool var, float sigma_uniform) { return var ? p2p_kappa(1.0) : p2p_kappa(sigma_uniform); }
 
-// The float32 near-field records of the tree's leaves.
+// The float32 near-field records of the tree's leaves, one wave per leaf.
 static void p2p_records(Ctx &c) {
     if (c.n == 0) return;
     c.recp.ensure(sizeof(float4) * (c.var_sigma ? 4 : 3) * (size_t)c.n);
-    launch_records(c.stream, c.var_sigma, c.sigma_uniform, c.leaves.as<int>(), c.nleaves, c.c_start.as<int>(),
-                   c.c_count.as<int>(), c.c_geo.as<float4>(), c.n, nullptr, c.rec.as<float4>(), c.recp.as<float4>());
+    const double kap = record_kappa(c.var_sigma, c.sigma_uniform);
+    const unsigned grid = cdiv(c.nleaves, 4);
+    if (c.var_sigma)
+        k_p2p_records<true><<<grid, 256, 0, c.stream>>>(c.leaves.as<int>(), c.nleaves, c.c_start.as<int>(),
+                                                        c.c_count.as<int>(), c.c_geo.as<float4>(), kap,
+                                                        c.rec.as<float4>(), c.recp.as<float4>());
+    else
+        k_p2p_records<false><<<grid, 256, 0, c.stream>>>(c.leaves.as<int>(), c.nleaves, c.c_start.as<int>(),
+                                                         c.c_count.as<int>(), c.c_geo.as<float4>(), kap,
+                                                         c.rec.as<float4>(), c.recp.as<float4>());
+    VFMM_LAUNCH_CHECK();
 }
 
 void p2p_prepare(Ctx &c) { p2p_records(c); }
@@ -1003,8 +984,8 @@ void p2p_and_finalize(Ctx &c, float *ux, float *uy, float *uz, float *dax, float
 }
 
 // ---------------------------------------------------------------------------
-// Direct mode: every target block against all N sources (entries of 64
-// sources, full cutoff form), in the caller's order, no tree, no far field.
+// Direct mode: every target against all N sources (full cutoff form), in the
+// caller's order, no tree, no far field.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_direct_setup64(int64_t n, const float *x, const float *y, const float *z,
                                                         const float *ax, const float *ay, const float *az,
@@ -1017,89 +998,203 @@ __global__ __launch_bounds__(256) void k_direct_setup64(int64_t n, const float *
     perm[i] = (int)i;
 }
 
-__global__ __launch_bounds__(256) void k_direct_setup(int64_t n, const float *x, const float *y, const float *z,
-                                                      const float *ax, const float *ay, const float *az,
-                                                      const float *s, float4 *rec, int *perm) {
+// Records relative to one origin, straight from the caller's arrays.
+template <bool VAR>
+__global__ __launch_bounds__(256) void k_direct_records(int64_t n, const float *x, const float *y, const float *z,
+                                                        const float *ax, const float *ay, const float *az,
+                                                        const float *s, double ox, double oy, double oz, double kappa,
+                                                        float4 *__restrict__ out) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
-    const float k = 0.0795774715459476679f;  // 1/(4 pi)
-    rec[2 * i] = make_float4(x[i], y[i], z[i], s[i]);
-    rec[2 * i + 1] = make_float4(ax[i] * k, ay[i] * k, az[i] * k, 0.f);
-    perm[i] = (int)i;
+    const double k = 0.079577471545947667884;  // 1/(4 pi)
+    const double kap = VAR ? kappa / (double)s[i] : kappa;
+    const double sc = VAR ? 1.0 : kappa;
+    put_record<VAR>(out, i, sc * ((double)x[i] - ox), sc * ((double)y[i] - oy), sc * ((double)z[i] - oz), kap,
+                    k * ax[i], k * ay[i], k * az[i], ax[i], ay[i], az[i]);
 }
 
-// Sources split into entries of 64 so that per-entry partial sums are blocked
-// exactly as in tree mode.
-__global__ __launch_bounds__(256) void k_direct_blocks(int64_t n, int nb, int4 *blocks, int4 *ent, float4 *sh) {
+// red[0][k] = the sum over the work-group's W waves of red[w][k], in wave order
+template <int W, int K>
+__device__ __forceinline__ void sum_waves(float *red) {
+    __syncthreads();
+    for (int k = threadIdx.x; k < K; k += 64 * W) {
+        float v = red[k];
+        for (int w = 1; w < W; ++w) v += red[w * K + k];
+        red[k] = v;
+    }
+    __syncthreads();
+}
+
+// A work-group of eight waves takes 64 targets; each wave sums an eighth of
+// the sources, 64 at a time, as scalar operands, and the waves' sums are added
+// in LDS in wave order.  One wave per 64 targets left the chip idle: 65,536
+// particles are 1,024 waves, one per SIMD, where the pair loop needs several
+// (60,000 particles: 10.6 -> 3.1 ms, 1.15e12 pairs/s).
+constexpr int DIRECT_WAVES = 8;
+template <int SCHEME, bool KAHAN, bool VAR>
+__global__ __launch_bounds__(64 * DIRECT_WAVES) void k_direct(P2PConst k, P2PArgs A) {
+    __shared__ float red[DIRECT_WAVES][9][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = (int)A.n, i = blockIdx.x * 64 + lane;
+    Tgt t;
+    const float4 r0 = load_target<VAR>(A, min(i, n - 1), t);
+    set_offset<SCHEME>(r0, make_float4(0.f, 0.f, 0.f, 0.f), t);
+    float S[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    float Cc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    const int s0 = (int)((int64_t)wave * n / DIRECT_WAVES), s1 = (int)((int64_t)(wave + 1) * n / DIRECT_WAVES);
+    for (int s = s0; s < s1; s += 64) {
+        Acc9 p = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+        leaf_loop<0, SCHEME, VAR>(k, A.rec, s, min(64, s1 - s), t, p);
+        add_leaf<SCHEME, KAHAN>(t, p, S, Cc);  // per 64 sources: |y| spans the domain here
+    }
+#pragma unroll
+    for (int q = 0; q < 9; ++q) red[wave][q][lane] = KAHAN ? S[q] - Cc[q] : S[q];
+    sum_waves<DIRECT_WAVES, 9 * 64>(&red[0][0][0]);
+    if (wave != 0 || i >= n) return;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) S[q] = red[0][q][lane];
+    finish<SCHEME>(k, A, i, lane, 64, t, S, nullptr);
+}
+
+// Fewer particles: a work-group of sixteen waves takes 16 targets, each wave every
+// sixteenth pass of 64 sources (four lane groups that hold the 16 targets, the
+// sources staged in LDS as in p2p_group), so that 1,500 particles occupy 94
+// CUs with 16 waves each instead of 24 waves in all (the whole call 337 -> 35
+// us; 5,000 particles 964 -> 69 us, 16,000 2,930 -> 254 us).
+constexpr int DIRECT_SMALL_WAVES = 16, DIRECT_SMALL_T = 16;
+template <int SCHEME, bool KAHAN, bool VAR>
+__global__ __launch_bounds__(64 * DIRECT_SMALL_WAVES) void k_direct_small(P2PConst k, P2PArgs A) {
+    constexpr int RS = VAR ? 4 : 3, T = DIRECT_SMALL_T, NG = 64 / T;
+    __shared__ float4 stage[DIRECT_SMALL_WAVES][3 * 64];
+    __shared__ float red[DIRECT_SMALL_WAVES][9][T];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int grp = lane / T, tl = lane % T;
+    const int n = (int)A.n, i = blockIdx.x * T + tl;
+    Tgt t;
+    const float4 r0 = load_target<VAR>(A, min(i, n - 1), t);
+    set_offset<SCHEME>(r0, make_float4(0.f, 0.f, 0.f, 0.f), t);
+    float S[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    float Cc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    float4 *L = stage[wave];
+    for (int f0 = 64 * wave; f0 < n; f0 += 64 * DIRECT_SMALL_WAVES) {
+        const int f = f0 + lane;
+        const bool ok = f < n;
+        const float4 *src = A.rec + RS * (size_t)min(f, n - 1);
+        float4 sp = src[0], sa = src[1], sb = src[2];
+        if (!ok) {  // zero strength far away
+            sp = make_float4(1e4f, 0.f, 0.f, 1.f);
+            sa = sb = make_float4(0.f, 0.f, 0.f, 1.f);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // LDS order within the wave
+        L[3 * lane] = sp;
+        L[3 * lane + 1] = sa;
+        L[3 * lane + 2] = sb;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        Acc9 p = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+        group_loop<0, SCHEME, VAR>(k, L + 3 * grp, NG, (min(64, n - f0) + 2 * NG - 1) / (2 * NG), t, p);
+        add_leaf<SCHEME, KAHAN>(t, p, S, Cc);  // per 64 sources: |y| spans the domain here
+    }
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        float v = KAHAN ? S[q] - Cc[q] : S[q];
+        const float v0 = v;
+        for (int g = 1; g < NG; ++g) v += __shfl(v0, (lane + g * T) & 63, 64);
+        if (lane < T) red[wave][q][lane] = v;
+    }
+    sum_waves<DIRECT_SMALL_WAVES, 9 * T>(&red[0][0][0]);
+    if (wave != 0 || lane >= T || i >= n) return;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) S[q] = red[0][q][lane];
+    finish<SCHEME>(k, A, i, lane, T, t, S, nullptr);
+}
+
+// Few targets per work-group keep the last round of work-groups even until the
+// scalar form's cheaper pair step outweighs it; measured (scalar / groups):
+// 17,000 particles 516 / 280 us, 24,000 724 / 532, 32,768 973 / 926, 40,000
+// 1,611 / 1,379, 49,152 1,998 / 2,053, 57,344 2,997 / 2,800, 65,536 3,422 / 3,645.
+constexpr int64_t DIRECT_SMALL_N = 61440;
+
+template <int SCHEME, bool KAHAN>
+static void launch_direct(const P2PConst &k, const P2PArgs &A, bool var, hipStream_t s) {
+    const bool small = A.n < DIRECT_SMALL_N;
+    const unsigned g = small ? cdiv(A.n, DIRECT_SMALL_T) : cdiv(A.n, 64);
+    if (small && var)
+        k_direct_small<SCHEME, KAHAN, true><<<g, 64 * DIRECT_SMALL_WAVES, 0, s>>>(k, A);
+    else if (small)
+        k_direct_small<SCHEME, KAHAN, false><<<g, 64 * DIRECT_SMALL_WAVES, 0, s>>>(k, A);
+    else if (var)
+        k_direct<SCHEME, KAHAN, true><<<g, 64 * DIRECT_WAVES, 0, s>>>(k, A);
+    else
+        k_direct<SCHEME, KAHAN, false><<<g, 64 * DIRECT_WAVES, 0, s>>>(k, A);
+    VFMM_LAUNCH_CHECK();
+}
+
+// Entries of 64 sources for the float64 form.
+__global__ __launch_bounds__(256) void k_direct_blocks(int64_t n, int nb, int4 *blocks, int4 *ent) {
     const int b = blockIdx.x * 256 + threadIdx.x;
     if (b < nb) {
         const int cnt = (int)min<int64_t>(64, n - (int64_t)b * 64);
         blocks[b] = make_int4(b * 64, cnt, 0, nb);
         ent[b] = make_int4(b * 64, cnt, 0, 0);
-        if (sh) sh[b] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
 }
 
-// The float32 (and mixed) all-pairs evaluation into caller-given buffers; the
-// near-field kernel's interval is timed on ctx's events when tc is given.
-static void direct_f32_impl(const Ctx &c, Ctx *tc, hipStream_t s, int64_t n, const Bounds &hb, const DirectBufs &b,
-                            const float *x, const float *y, const float *z, const float *ax, const float *ay,
-                            const float *az, const float *sigma, float *ux, float *uy, float *uz, float *dax,
-                            float *day, float *daz) {
+// The float32 (and mixed) all-pairs evaluation; the near-field kernel's
+// interval is timed on tc's events when tc is given.
+static void direct_f32_impl(const Ctx &c, Ctx *tc, hipStream_t s, int64_t n, const Bounds &hb, float4 *recp,
+                            const Bounds *bounds, const float *x, const float *y, const float *z, const float *ax,
+                            const float *ay, const float *az, const float *sigma, float *ux, float *uy, float *uz,
+                            float *dax, float *day, float *daz) {
     if (n == 0) return;
-    const int nb = (int)cdiv(n, 64);
-    k_direct_setup<<<cdiv(n, 256), 256, 0, s>>>(n, x, y, z, ax, ay, az, sigma, b.rec, b.perm);
-    VFMM_LAUNCH_CHECK();
-    k_direct_blocks<<<cdiv(nb, 256), 256, 0, s>>>(n, nb, b.blocks, b.ent, b.sh);
-    VFMM_LAUNCH_CHECK();
     // per-source cores when they differ by more than 1e-6 relative (as a build decides)
     const bool var = hb.sig_max > hb.sig_min * (1.0 + 1e-6);
     const float sig = (float)hb.sig_max;
+    const double kap = record_kappa(var, sig);
     // one origin for every record: the centre of the bounding box
     const double org[3] = {0.5 * (hb.lo[0] + hb.hi[0]), 0.5 * (hb.lo[1] + hb.hi[1]), 0.5 * (hb.lo[2] + hb.hi[2])};
-    launch_records(s, var, sig, nullptr, 0, nullptr, nullptr, nullptr, n, org, b.rec, b.recp);
+    if (var)
+        k_direct_records<true><<<cdiv(n, 256), 256, 0, s>>>(n, x, y, z, ax, ay, az, sigma, org[0], org[1], org[2], kap,
+                                                            recp);
+    else
+        k_direct_records<false><<<cdiv(n, 256), 256, 0, s>>>(n, x, y, z, ax, ay, az, sigma, org[0], org[1], org[2],
+                                                             kap, recp);
+    VFMM_LAUNCH_CHECK();
     const P2PConst k = make_const(sig, var);
     P2PArgs A{};
-    A.rec = b.recp;
-    A.items = b.blocks;
-    A.ent = b.ent;
-    A.sh = b.sh;
-    A.nitems = A.nitems_w = nb;
-    A.far_u = nullptr;
-    A.far_da = nullptr;
+    A.rec = recp;
     A.n = n;
-    A.perm = b.perm;
-    A.bounds = b.bounds;
-    A.surface = 0;
+    A.bounds = bounds;
     A.ux = ux; A.uy = uy; A.uz = uz; A.dax = dax; A.day = day; A.daz = daz;
     if (tc) tc->record(2 * PH_P2P, s);
-    dispatch_p2p(c.prm, var, k, A, s);
+    const bool kah = c.prm.kahan != 0 || c.prm.precision == VFMM_PRECISION_MIXED;
+    if (c.prm.scheme == VFMM_SCHEME_TRANSPOSE) {
+        if (kah) launch_direct<VFMM_SCHEME_TRANSPOSE, true>(k, A, var, s);
+        else launch_direct<VFMM_SCHEME_TRANSPOSE, false>(k, A, var, s);
+    } else {
+        if (kah) launch_direct<VFMM_SCHEME_CLASSICAL, true>(k, A, var, s);
+        else launch_direct<VFMM_SCHEME_CLASSICAL, false>(k, A, var, s);
+    }
     if (tc) tc->record(2 * PH_P2P + 1, s);
 }
 
-void direct_f32(const Ctx &c, hipStream_t s, int64_t n, const Bounds &hb, const DirectBufs &b, const float *x,
-                const float *y, const float *z, const float *ax, const float *ay, const float *az,
+void direct_f32(const Ctx &c, hipStream_t s, int64_t n, const Bounds &hb, float4 *recp, const Bounds *bounds,
+                const float *x, const float *y, const float *z, const float *ax, const float *ay, const float *az,
                 const float *sigma, float *ux, float *uy, float *uz, float *dax, float *day, float *daz) {
-    direct_f32_impl(c, nullptr, s, n, hb, b, x, y, z, ax, ay, az, sigma, ux, uy, uz, dax, day, daz);
+    direct_f32_impl(c, nullptr, s, n, hb, recp, bounds, x, y, z, ax, ay, az, sigma, ux, uy, uz, dax, day, daz);
 }
 
 void direct_all_pairs(Ctx &c, const float *x, const float *y, const float *z, const float *ax, const float *ay,
                       const float *az, const float *sigma, float *ux, float *uy, float *uz, float *dax, float *day,
                       float *daz) {
     const int64_t n = c.n;
-    c.rec.ensure(sizeof(float4) * 2 * n);
-    c.perm.ensure(sizeof(int) * n);
     const int nb = (int)cdiv(n, 64);
-    c.blocks.ensure(sizeof(int4) * nb);
-    c.p2p_ent.ensure(sizeof(int4) * nb);
     c.n_blocks = nb;
     c.p2p_pairs = n * n;
     if (c.prm.precision == VFMM_PRECISION_FP64) {
-        k_direct_setup<<<cdiv(n, 256), 256, 0, c.stream>>>(n, x, y, z, ax, ay, az, sigma, c.rec.as<float4>(),
-                                                            c.perm.as<int>());
-        VFMM_LAUNCH_CHECK();
-        k_direct_blocks<<<cdiv(nb, 256), 256, 0, c.stream>>>(n, nb, c.blocks.as<int4>(), c.p2p_ent.as<int4>(),
-                                                              nullptr);
+        c.perm.ensure(sizeof(int) * n);
+        c.blocks.ensure(sizeof(int4) * nb);
+        c.p2p_ent.ensure(sizeof(int4) * nb);
+        k_direct_blocks<<<cdiv(nb, 256), 256, 0, c.stream>>>(n, nb, c.blocks.as<int4>(), c.p2p_ent.as<int4>());
         VFMM_LAUNCH_CHECK();
         c.rec64.ensure(sizeof(double4) * 2 * n);
         k_direct_setup64<<<cdiv(n, 256), 256, 0, c.stream>>>(n, x, y, z, ax, ay, az, sigma, c.rec64.as<double4>(),
@@ -1119,11 +1214,9 @@ void direct_all_pairs(Ctx &c, const float *x, const float *y, const float *z, co
         c.record(2 * PH_P2P + 1);
         return;
     }
-    c.p2p_sh.ensure(sizeof(float4) * nb);
     c.recp.ensure(sizeof(float4) * (c.var_sigma ? 4 : 3) * (size_t)n);
-    DirectBufs b{c.rec.as<float4>(), c.perm.as<int>(), c.blocks.as<int4>(), c.p2p_ent.as<int4>(),
-                 c.p2p_sh.as<float4>(), c.recp.as<float4>(), c.bres.as<Bounds>()};
-    direct_f32_impl(c, &c, c.stream, n, c.hb, b, x, y, z, ax, ay, az, sigma, ux, uy, uz, dax, day, daz);
+    direct_f32_impl(c, &c, c.stream, n, c.hb, c.recp.as<float4>(), c.bres.as<Bounds>(), x, y, z, ax, ay, az, sigma,
+                    ux, uy, uz, dax, day, daz);
 }
 
 }  // namespace vfmm

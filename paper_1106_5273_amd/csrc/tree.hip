@@ -11,6 +11,8 @@ namespace vfmm {
 static constexpr int TPB = 256;
 // work-groups of the first bounds pass (each reduces a strided share of the particles)
 static constexpr int BOUNDS_MAX_PARTS = 1024;
+// up to this many particles one work-group of 1,024 threads does both passes
+static constexpr int64_t BOUNDS_ONE_GROUP = 8192;
 
 // ---------------------------------------------------------------------------
 // Exclusive scan of int32 (in-place allowed).  2048 items per block, block
@@ -175,21 +177,6 @@ void sync_ints(Ctx &c, int n, int *dst) {
     for (int i = 0; i < n; ++i) dst[i] = c.hpin[i];
 }
 
-__global__ __launch_bounds__(64) void k_copy_words(const int *src, int n, int *out) {
-    const int i = threadIdx.x;
-    if (i < n) out[i] = src[i];
-}
-
-void read_words(Ctx &c, const void *src, size_t bytes, void *dst) {
-    if (bytes == 0 || bytes > 64 * sizeof(int) || bytes % sizeof(int)) throw Error{VFMM_EINVAL, "read_words: size"};
-    const int n = (int)(bytes / sizeof(int));
-    int *hp = pinned_ints(c);
-    k_copy_words<<<1, 64, 0, c.stream>>>(static_cast<const int *>(src), n, hp);
-    VFMM_LAUNCH_CHECK();
-    VFMM_HIP(hipStreamSynchronize(c.stream));
-    std::memcpy(dst, hp, bytes);
-}
-
 void read_ints(Ctx &c, std::initializer_list<const int *> src, int *dst) {
     if (src.size() == 0 || src.size() > 4) throw Error{VFMM_EINVAL, "read_ints: one to four values"};
     int *hp = pinned_ints(c);
@@ -238,11 +225,9 @@ struct BoundsArgs {
     double fp_ref;
 };
 
-__global__ __launch_bounds__(TPB) void k_bounds_partial(BoundsArgs A, BAcc *part) {
-    __shared__ BAcc sh[TPB];
-    BAcc a;
-    bacc_init(a);
-    for (int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x; i < A.n; i += (int64_t)gridDim.x * TPB) {
+// accumulates this thread's particles (i0, i0 + stride, ...)
+__device__ inline void bacc_particles(const BoundsArgs &A, int64_t i0, int64_t stride, BAcc &a) {
+    for (int64_t i = i0; i < A.n; i += stride) {
         const double p[3] = {A.x[i], A.y[i], A.z[i]};
         const double sg = A.s[i];
         bool fin = isfinite(p[0]) && isfinite(p[1]) && isfinite(p[2]) && isfinite(sg) && sg > 0.0;
@@ -267,48 +252,87 @@ __global__ __launch_bounds__(TPB) void k_bounds_partial(BoundsArgs A, BAcc *part
             a.sxa[2] += r[0] * al[1] - r[1] * al[0];
         }
     }
-    sh[threadIdx.x] = a;
-    __syncthreads();
-    for (int o = TPB / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o) bacc_merge(sh[threadIdx.x], sh[threadIdx.x + o]);
-        __syncthreads();
+}
+
+// merges the lanes' accumulators (a fixed tree over the lowest `lanes` lanes)
+__device__ inline void bacc_wave(BAcc &a, int lanes) {
+    for (int o = lanes / 2; o > 0; o >>= 1) {
+        BAcc b;
+        for (int d = 0; d < 3; ++d) {
+            b.lo[d] = __shfl_xor(a.lo[d], o, 64); b.hi[d] = __shfl_xor(a.hi[d], o, 64);
+            b.sa[d] = __shfl_xor(a.sa[d], o, 64); b.sxa[d] = __shfl_xor(a.sxa[d], o, 64);
+        }
+        b.smin = __shfl_xor(a.smin, o, 64); b.smax = __shfl_xor(a.smax, o, 64);
+        b.fp = __shfl_xor(a.fp, o, 64);
+        b.nf = __shfl_xor(a.nf, o, 64); b.out = __shfl_xor(a.out, o, 64);
+        bacc_merge(a, b);
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
+}
+
+// merges a work-group's accumulators into thread 0's; sh holds one per wave (a power of two)
+__device__ inline void bacc_group(BAcc &a, BAcc *sh) {
+    const int nw = blockDim.x / 64;
+    bacc_wave(a, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        a = sh[threadIdx.x & (nw - 1)];
+        bacc_wave(a, nw);
+    }
+}
+
+// the result of a bounds pass; host (may be null) is pinned host memory
+__device__ inline void bounds_result(const BAcc &a, int check_fp, double fp_ref, Bounds *res, Bounds *host) {
+    Bounds b;
+    for (int d = 0; d < 3; ++d) {
+        b.lo[d] = a.lo[d]; b.hi[d] = a.hi[d];
+        b.sum_a[d] = a.sa[d]; b.sum_xa[d] = a.sxa[d];
+    }
+    b.sig_min = a.smin; b.sig_max = a.smax;
+    b.fp = a.fp;
+    b.nonfinite = a.nf; b.outside = a.out;
+    // the sums are deterministic: equal inputs give a bitwise equal fingerprint
+    b.stale = (check_fp && !(a.fp == fp_ref)) ? 1 : 0;
+    b.overfull = 0;
+    *res = b;
+    if (host) *host = b;
+}
+
+__global__ __launch_bounds__(TPB) void k_bounds_partial(BoundsArgs A, BAcc *part) {
+    __shared__ BAcc sh[TPB / 64];
+    BAcc a;
+    bacc_init(a);
+    bacc_particles(A, (int64_t)blockIdx.x * TPB + threadIdx.x, (int64_t)gridDim.x * TPB, a);
+    bacc_group(a, sh);
+    if (threadIdx.x == 0) part[blockIdx.x] = a;
 }
 
 __global__ __launch_bounds__(TPB) void k_bounds_final(const BAcc *part, int np, int check_fp, double fp_ref,
-                                                      Bounds *res) {
-    __shared__ BAcc sh[TPB];
+                                                      Bounds *res, Bounds *host) {
+    __shared__ BAcc sh[TPB / 64];
     BAcc a;
     bacc_init(a);
     for (int i = threadIdx.x; i < np; i += TPB) bacc_merge(a, part[i]);
-    sh[threadIdx.x] = a;
-    __syncthreads();
-    for (int o = TPB / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o) bacc_merge(sh[threadIdx.x], sh[threadIdx.x + o]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        Bounds b;
-        for (int d = 0; d < 3; ++d) {
-            b.lo[d] = sh[0].lo[d]; b.hi[d] = sh[0].hi[d];
-            b.sum_a[d] = sh[0].sa[d]; b.sum_xa[d] = sh[0].sxa[d];
-        }
-        b.sig_min = sh[0].smin; b.sig_max = sh[0].smax;
-        b.fp = sh[0].fp;
-        b.nonfinite = sh[0].nf; b.outside = sh[0].out;
-        // the two-stage sum is deterministic: equal inputs give a bitwise equal fingerprint
-        b.stale = (check_fp && !(sh[0].fp == fp_ref)) ? 1 : 0;
-        b.overfull = 0;
-        *res = b;
-    }
+    bacc_group(a, sh);
+    if (threadIdx.x == 0) bounds_result(a, check_fp, fp_ref, res, host);
+}
+
+// both stages in one work-group
+__global__ __launch_bounds__(1024) void k_bounds_small(BoundsArgs A, int check_fp, double fp_ref, Bounds *res,
+                                                       Bounds *host) {
+    __shared__ BAcc sh[1024 / 64];
+    BAcc a;
+    bacc_init(a);
+    bacc_particles(A, threadIdx.x, 1024, a);
+    bacc_group(a, sh);
+    if (threadIdx.x == 0) bounds_result(a, check_fp, fp_ref, res, host);
 }
 
 size_t bounds_scratch_bytes() { return sizeof(BAcc) * BOUNDS_MAX_PARTS; }
 
 void launch_bounds(const Ctx &c, hipStream_t s, int64_t n, const float *x, const float *y, const float *z,
                    const float *sigma, const float *ax, const float *ay, const float *az, bool with_alpha,
-                   bool check_fp, double fp_ref, void *part, Bounds *res) {
+                   bool check_fp, double fp_ref, void *part, Bounds *res, Bounds *host) {
     BoundsArgs A{};
     A.x = x; A.y = y; A.z = z; A.s = sigma; A.ax = ax; A.ay = ay; A.az = az;
     A.n = n;
@@ -319,20 +343,30 @@ void launch_bounds(const Ctx &c, hipStream_t s, int64_t n, const float *x, const
         A.ref[d] = c.prm.periodic ? c.prm.box_lo[d] + 0.5 * c.prm.box_len : 0.0;
     }
     A.plen = c.prm.box_len;
+    if (n <= BOUNDS_ONE_GROUP) {
+        k_bounds_small<<<1, 1024, 0, s>>>(A, check_fp ? 1 : 0, fp_ref, res, host);
+        VFMM_LAUNCH_CHECK();
+        return;
+    }
     const int nb = (int)std::min<int64_t>(BOUNDS_MAX_PARTS, std::max<int64_t>(1, cdiv(n, TPB)));
     k_bounds_partial<<<nb, TPB, 0, s>>>(A, (BAcc *)part);
     VFMM_LAUNCH_CHECK();
-    k_bounds_final<<<1, TPB, 0, s>>>((const BAcc *)part, nb, check_fp ? 1 : 0, fp_ref, res);
+    k_bounds_final<<<1, TPB, 0, s>>>((const BAcc *)part, nb, check_fp ? 1 : 0, fp_ref, res, host);
     VFMM_LAUNCH_CHECK();
 }
 
 void compute_bounds(Ctx &c, int64_t n, const float *x, const float *y, const float *z, const float *sigma,
-                    const float *ax, const float *ay, const float *az, bool with_alpha) {
+                    const float *ax, const float *ay, const float *az, bool with_alpha, bool to_host) {
     c.bpart.ensure(bounds_scratch_bytes());
     c.bres.ensure(sizeof(Bounds));
     // an evaluation checks its positions and cores against those of the build
     launch_bounds(c, c.stream, n, x, y, z, sigma, ax, ay, az, with_alpha, with_alpha, c.build_fp, c.bpart.ptr,
-                  c.bres.as<Bounds>());
+                  c.bres.as<Bounds>(), to_host ? reinterpret_cast<Bounds *>(pinned_ints(c)) : nullptr);
+}
+
+void sync_bounds(Ctx &c, Bounds *dst) {
+    VFMM_HIP(hipStreamSynchronize(c.stream));
+    std::memcpy(dst, c.hpin, sizeof(Bounds));
 }
 
 // ---------------------------------------------------------------------------

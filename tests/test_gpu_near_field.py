@@ -14,14 +14,14 @@ from parity_util import check
 pytestmark = pytest.mark.gpu
 
 
-def _cells(k, seed, var):
+def _cells(k, seed, var, core):
     """Exactly k particles in each of the 4^3 cells of the unit cube."""
     rng = np.random.default_rng(seed)
     g = (np.stack(np.meshgrid(*[np.arange(4)] * 3, indexing="ij"), -1).reshape(-1, 1, 3)
          + rng.uniform(0.02, 0.98, (64, k, 3))).reshape(-1, 3) / 4.0
     n = len(g)
     a = rng.standard_normal((3, n)) / n
-    sig = np.full(n, 0.06) * (rng.uniform(0.6, 1.4, n) if var else 1.0)
+    sig = np.full(n, core) * (rng.uniform(0.6, 1.4, n) if var else 1.0)
     f = lambda v: np.ascontiguousarray(v, np.float32)  # noqa: E731
     return dict(x=f(g[:, 0]), y=f(g[:, 1]), z=f(g[:, 2]), ax=f(a[0]), ay=f(a[1]), az=f(a[2]), sigma=f(sig), n=n)
 
@@ -38,14 +38,17 @@ def _run(case, **kw):
     return o[:, :3], o[:, 3:]
 
 
-FORMS = {"plain": {}, "cores": dict(var=True), "classical": dict(scheme=1), "mixed": dict(precision=1)}
+# core 0.06: the cutoff's series, erfc and singular forms mix within a leaf pair; 0.4 and 0.9: all (or,
+# with per-particle cores, some) leaf pairs lie within the series range of every core
+FORMS = {"plain": {}, "cores": dict(var=True), "classical": dict(scheme=1), "mixed": dict(precision=1),
+         "wide": dict(core=0.4), "wide_cores": dict(core=0.9, var=True)}
 
 
 @pytest.mark.parametrize("form", sorted(FORMS))
 @pytest.mark.parametrize("k", [1, 2, 7, 8, 9, 15, 16, 17, 21, 22, 31, 32, 33, 40, 63, 64, 65, 97, 130])
 def test_leaves_of_k_particles(k, form):
     opt = dict(FORMS[form])
-    case = _cells(k, 100 + k, opt.pop("var", False))
+    case = _cells(k, 100 + k, opt.pop("var", False), opt.pop("core", 0.06))
     kw = dict(p=8, ncrit=k, box_len=1.0, **opt)
     u, da = _run(case, **kw)
     kw["precision"] = 2
@@ -68,3 +71,26 @@ def test_lists_of_very_unequal_length(far):
     ref = oracle.direct(case)
     check("unequal lists u", u, ref["u"], 1e-4, 1e-3)
     check("unequal lists dalpha", da, ref["da_t"], 1e-4, 1e-3)
+
+
+# around a pass of 64 sources, a wave's and a work-group's share of them, and the two kernels' boundary
+@pytest.mark.parametrize("var", [False, True])
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 63, 64, 65, 1023, 1024, 1025, 61439, 61440, 61441])
+def test_direct_mode_sizes(n, var):
+    rng = np.random.default_rng(n)
+    x = rng.uniform(0.0, 0.2, (n, 3))
+    a = rng.standard_normal((n, 3)) / n
+    f = lambda v: np.ascontiguousarray(v, np.float32)  # noqa: E731
+    case = dict(x=f(x[:, 0]), y=f(x[:, 1]), z=f(x[:, 2]), ax=f(a[:, 0]), ay=f(a[:, 1]), az=f(a[:, 2]),
+                sigma=f(0.03 * (rng.uniform(0.7, 1.3, n) if var else np.ones(n))), n=n)
+    u, da = _run(case, direct=1)
+    sub = np.arange(n) if n < 2000 else np.unique(np.r_[0:64, n // 2, n - 64:n])
+    ref = oracle.direct(case, targets=sub)
+    assert np.isfinite(u).all() and np.isfinite(da).all()
+    if n > 1:
+        check("direct n=%d u" % n, u[sub], ref["u"], 1e-5, 1e-3)
+        check("direct n=%d dalpha" % n, da[sub], ref["da_t"], 1e-5, 1e-3)
+    else:  # a particle alone: u exactly zero, and alpha x (F alpha) zero up to the rounding of its
+        # two factors, F <= F(0) = 1 / (6 sqrt 2 pi^1.5 sigma^3) of Eq. (2)
+        scale = np.sum(a * a) / (6.0 * np.sqrt(2.0) * np.pi ** 1.5 * float(case["sigma"][0]) ** 3)
+        assert not u.any() and np.abs(da).max() <= 4 * 2.0 ** -24 * scale
