@@ -575,9 +575,9 @@ static void far_prealloc_p(Ctx &c) {
     c.Lexp.ensure(bytes);
     c.far_u.ensure(rs * 3 * (size_t)c.n);
     c.far_da.ensure(rs * 3 * (size_t)c.n);
+    c.near.ensure(rs * 6 * (size_t)std::max(c.n_partial, 1));  // the near-field parts
     if (c.prm.precision == VFMM_PRECISION_FP64) c.rec64.ensure(sizeof(double4) * 2 * (size_t)c.n);
     else {
-        c.near.ensure(sizeof(float) * 6 * (size_t)std::max(c.n_partial, 1));  // the near-field parts
         c.recp.ensure(sizeof(float4) * (c.var_sigma ? 4 : 3) * (size_t)c.n);
     }
 }

@@ -658,23 +658,32 @@ __global__ __launch_bounds__(256) void k_p2p_records(const int *__restrict__ lea
 }
 
 // ---------------------------------------------------------------------------
-// Float64 reference form: the same work blocks and lists, one lane per
-// target, every quantity in double and the cutoff always in its full form:
+// Float64 reference form: the same work items and lists, every quantity in
+// double and the cutoff always in its full form:
 //   F = P(3/2, x)/rho^3,  H = P(5/2, x)/rho^5,  x = c^2 rho^2,  c = 1/(sqrt 2 sigma_j)
-// of the source's own core (stored in the fourth component of its record).
-// For x < 2 the power series of the lower incomplete gamma function,
+// of the source's own core (c^2 and c^3 in the fourth components of its record).
+// For x < 3 the power series of the lower incomplete gamma function,
 //   P(a, x) = x^a e^{-x} sum_k x^k / Gamma(a + k + 1),
 // divided by rho^{2a}, gives F and H without cancellation (finite at rho = 0);
-// for x >= 2, 1 - P(3/2, x) = erfc(s) + (2/sqrt pi) s e^{-x}, s = sqrt x, and
-// P(5/2, x) = P(3/2, x) - (4/(3 sqrt pi)) s^3 e^{-x}.
+// the sum for a = 5/2 is a fitted polynomial (relative error 5e-18), the one for
+// 3/2 follows from it.  For x >= 3, with u = x^{-1/2},
+//   1 - P(3/2, x) = e^{-x} (u Pe(u) + (2/sqrt pi) / u),  Pe(1/s) = s erfcx(s),
+// Pe fitted for 3 <= x <= 41 (it changes P by less than 2e-17), and
+// P(5/2, x) = P(3/2, x) - (4/(3 sqrt pi)) x^{3/2} e^{-x}; beyond x = 41 both are 1
+// to double precision.  Bound by float64 VALU issue (4 clocks an instruction):
+// about 75 instructions per pair in place of the library's exp, erfc and sqrt
+// and a series of up to 60 divisions (64^3 lattice, 2.47e9 pairs: 21.4 -> 7.3 ms).
 // ---------------------------------------------------------------------------
 struct P2P64Args {
     const double4 *__restrict__ rec;
-    const int4 *__restrict__ blocks;
+    const int4 *__restrict__ items;
+    const int *__restrict__ item_out;
+    const int4 *__restrict__ blocks;  // (target start, targets, first partial result, parts)
     const int4 *__restrict__ ent;
-    int nblocks;
+    int nitems, nblocks;
     int B;
     double len;
+    double *near;  // partial results, [6][targets] per item
     const double *__restrict__ far_u;
     const double *__restrict__ far_da;
     int64_t n;
@@ -685,82 +694,167 @@ struct P2P64Args {
     float *ux, *uy, *uz, *dax, *day, *daz;
 };
 
-__device__ inline void cutoff64(double r2, double c, double c2, double &F, double &H) {
-    const double x = c2 * r2;
-    const double isqpi = 0.56418958354775628695;  // 1/sqrt(pi)
-    const double e = exp(-x);
-    if (x < 2.0) {
-        double t = 4.0 / 3.0 * isqpi, u = 8.0 / 15.0 * isqpi;  // 1/Gamma(5/2), 1/Gamma(7/2)
-        double st = t, su = u;
-        for (int k = 1; k < 60; ++k) {
-            t *= x / (k + 1.5);
-            u *= x / (k + 2.5);
-            st += t;
-            su += u;
-            if (t < 1e-18 * st) break;
-        }
-        F = c * c2 * e * st;
-        H = c2 * c2 * c * e * su;
-    } else {
-        const double sx = sqrt(x);
-        const double rho = sqrt(r2);
-        const double q3 = erfc(sx) + 2.0 * isqpi * sx * e;
-        const double g = 1.0 - q3;
-        const double g5 = g - 4.0 / 3.0 * isqpi * sx * x * e;
-        const double ir = 1.0 / rho, ir2 = ir * ir;
-        F = g * ir * ir2;
-        H = g5 * ir * ir2 * ir2;
+// a b + k with the constant k in scalar registers: left to itself the compiler
+// keeps the polynomials' constants in vector registers (168 in all, three waves
+// per SIMD) and copies each into the accumulator first (a v_mov_b64 per v_fmac_f64)
+__device__ __forceinline__ double fma_const(double a, double b, double k) {
+    double d;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(k));
+    return d;
+}
+
+// e^{-x}, x >= 0: 2^n e^r with |r| <= ln 2 / 2 and e^r by its Taylor sum
+__device__ __forceinline__ double exp_minus(double x) {
+    const double n = __builtin_rint(-1.4426950408889634 * x);
+    double r = fma(n, -6.93147180369123816490e-01, -x);
+    r = fma(n, -1.90821492927058770002e-10, r);
+    double p = 1.0 / 6227020800.0;
+    p = fma_const(p, r, 1.0 / 479001600.0);
+    p = fma_const(p, r, 1.0 / 39916800.0);
+    p = fma_const(p, r, 1.0 / 3628800.0);
+    p = fma_const(p, r, 1.0 / 362880.0);
+    p = fma_const(p, r, 1.0 / 40320.0);
+    p = fma_const(p, r, 1.0 / 5040.0);
+    p = fma_const(p, r, 1.0 / 720.0);
+    p = fma_const(p, r, 1.0 / 120.0);
+    p = fma_const(p, r, 1.0 / 24.0);
+    p = fma_const(p, r, 1.0 / 6.0);
+    p = fma_const(p, r, 0.5);
+    p = fma_const(p, r, 1.0);
+    p = fma_const(p, r, 1.0);
+    return ldexp(p, (int)n);
+}
+
+// P(3/2, x)/x^{3/2} and P(5/2, x)/x^{5/2}
+__device__ __forceinline__ void cutoff64(double x, double &F, double &H) {
+    // x^{-1/2}: the hardware's estimate and one third-order step
+    double u = __builtin_amdgcn_rsq(x);
+    const double d = fma(-x * u, u, 1.0);
+    u = fma(u * d, fma(d, 0.375, 0.5), u);
+    const double u2 = u * u;
+    F = u2 * u;
+    H = F * u2;
+    const bool near = x < 3.0;
+    if (!__any(x < 41.0)) return;
+    const double e = exp_minus(x);
+    if (__any(!near)) {
+        const double t = fma(u, 4.7486029380327639523, -1.7416071845478640612);
+        double pe = 1.0154139291334610343e-8;
+        pe = fma_const(pe, t, -6.78240140967600289e-8);
+        pe = fma_const(pe, t, 1.3629171185641934622e-7);
+        pe = fma_const(pe, t, 4.9343870167675321161e-7);
+        pe = fma_const(pe, t, -4.8554535549403367007e-6);
+        pe = fma_const(pe, t, 0.000018420223593917519055);
+        pe = fma_const(pe, t, -0.000019826846639273996918);
+        pe = fma_const(pe, t, -0.00022522551963893404409);
+        pe = fma_const(pe, t, 0.0016910379992956190884);
+        pe = fma_const(pe, t, -0.0042781108341645073393);
+        pe = fma_const(pe, t, -0.03159513100524058218);
+        pe = fma_const(pe, t, 0.53210276267808352717);
+        const double q = fma(u, pe, 1.1283791670955125739 * (x * u));  // (1 - P(3/2, x)) e^x
+        F *= fma(-e, q, 1.0);
+        H = u2 * fma(-0.75225277806367504925, e, F);  // 4 / (3 sqrt pi)
+    }
+    if (__any(near)) {
+        double s = 2.473165037961738643e-15;
+        s = fma_const(s, x, -1.1889376396170663998e-14);
+        s = fma_const(s, x, 3.5903357402350888376e-13);
+        s = fma_const(s, x, 2.2329913611558775379e-12);
+        s = fma_const(s, x, 4.5659993236357083032e-11);
+        s = fma_const(s, x, 5.7934352867643122933e-10);
+        s = fma_const(s, x, 7.3161834843850830295e-9);
+        s = fma_const(s, x, 8.4027546810691893533e-8);
+        s = fma_const(s, x, 8.8240441348206060814e-7);
+        s = fma_const(s, x, 8.382754048318247031e-6);
+        s = fma_const(s, x, 0.000071253456606512365563);
+        s = fma_const(s, x, 0.00053440090733175414279);
+        s = fma_const(s, x, 0.0034736059016923648073);
+        s = fma_const(s, x, 0.019104832458751436672);
+        s = fma_const(s, x, 0.085971746064420295029);
+        s = fma_const(s, x, 0.30090111122547001809);
+        const double Fs = e * fma(x, s, 0.75225277806367504925);  // 1/Gamma(5/2)
+        F = near ? Fs : F;
+        H = near ? e * s : H;
     }
 }
 
 template <int SCHEME>
-__global__ __launch_bounds__(64) void k_p2p64(P2P64Args A) {
-    const int lane = threadIdx.x;
-    const int b = blockIdx.x;
-    if (b >= A.nblocks) return;
-    const int4 blk = A.blocks[b];
-    const bool valid = lane < blk.y;
-    const int i = blk.x + (valid ? lane : 0);
+__device__ __forceinline__ void pair64(double xi, double yi, double zi, double ai0, double ai1, double ai2, double4 sp,
+                                       double4 sa, bool ok, double *S) {
+    const double dx = xi - sp.x, dy = yi - sp.y, dz = zi - sp.z;
+    double F, H;
+    cutoff64((dx * dx + dy * dy + dz * dz) * sp.w, F, H);
+    F *= ok ? sa.w : 0.0;              // c^3
+    H *= ok ? sa.w * sp.w : 0.0;       // c^5
+    const double c0 = sa.y * dz - sa.z * dy;
+    const double c1 = sa.z * dx - sa.x * dz;
+    const double c2 = sa.x * dy - sa.y * dx;
+    S[0] += F * c0;
+    S[1] += F * c1;
+    S[2] += F * c2;
+    S[3] += F * sa.x;
+    S[4] += F * sa.y;
+    S[5] += F * sa.z;
+    if (SCHEME == VFMM_SCHEME_TRANSPOSE) {
+        const double hd = H * (ai0 * c0 + ai1 * c1 + ai2 * c2);
+        S[6] += hd * dx;
+        S[7] += hd * dy;
+        S[8] += hd * dz;
+    } else {
+        const double hd = H * (ai0 * dx + ai1 * dy + ai2 * dz);
+        S[6] += hd * c0;
+        S[7] += hd * c1;
+        S[8] += hd * c2;
+    }
+}
+
+// One wave per item, as in the float32 form; the lane groups of a small block
+// take every ng-th source of each entry.
+template <int SCHEME>
+__global__ __launch_bounds__(256) void k_p2p64(P2P64Args A) {
+    const int item = xcd_logical(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
+    if (item >= A.nitems) return;
+    const int lane = threadIdx.x & 63;
+    const int4 it = A.items[item];
+    const int t0 = __builtin_amdgcn_readfirstlane(it.x), tc = __builtin_amdgcn_readfirstlane(it.y);
+    const int l0 = __builtin_amdgcn_readfirstlane(it.z), lc = __builtin_amdgcn_readfirstlane(it.w);
+    const int ng = p2p_groups(tc);
+    const int g0 = ng > 1 ? (int)(((float)lane + 0.5f) / (float)tc) : 0;
+    const int tl = lane - g0 * tc;
+    const bool member = ng > 1 ? g0 < ng : lane < tc;  // lanes past the last group (or target) add nothing
+    const int i = t0 + min(tl, tc - 1);
     const double4 xp = A.rec[2 * (size_t)i];
     const double4 xa = A.rec[2 * (size_t)i + 1];
     const double fp = 12.566370614359172954;  // 4 pi
     const double ai0 = xa.x * fp, ai1 = xa.y * fp, ai2 = xa.z * fp;
     double S[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     const int W = 2 * A.B + 1;
-    for (int e = 0; e < blk.w; ++e) {
-        const int4 en = A.ent[blk.z + e];
+    for (int e = l0; e < l0 + lc; ++e) {
+        const int4 en = A.ent[e];
+        const int s0 = __builtin_amdgcn_readfirstlane(en.x), sc = __builtin_amdgcn_readfirstlane(en.y);
         const double xi = xp.x - (double)(en.z % W - A.B) * A.len;
         const double yi = xp.y - (double)((en.z / W) % W - A.B) * A.len;
         const double zi = xp.z - (double)(en.z / (W * W) - A.B) * A.len;
-        for (int j = en.x; j < en.x + en.y; ++j) {
-            const double4 sp = A.rec[2 * (size_t)j], sa = A.rec[2 * (size_t)j + 1];
-            const double dx = xi - sp.x, dy = yi - sp.y, dz = zi - sp.z;
-            double F, H;
-            const double cj = sp.w;  // 1/(sqrt 2 sigma_j), stored in the float64 records
-            cutoff64(dx * dx + dy * dy + dz * dz, cj, cj * cj, F, H);
-            const double c0 = sa.y * dz - sa.z * dy;
-            const double c1 = sa.z * dx - sa.x * dz;
-            const double c2 = sa.x * dy - sa.y * dx;
-            S[0] += F * c0;
-            S[1] += F * c1;
-            S[2] += F * c2;
-            S[3] += F * sa.x;
-            S[4] += F * sa.y;
-            S[5] += F * sa.z;
-            if (SCHEME == VFMM_SCHEME_TRANSPOSE) {
-                const double hd = H * (ai0 * c0 + ai1 * c1 + ai2 * c2);
-                S[6] += hd * dx;
-                S[7] += hd * dy;
-                S[8] += hd * dz;
-            } else {
-                const double hd = H * (ai0 * dx + ai1 * dy + ai2 * dz);
-                S[6] += hd * c0;
-                S[7] += hd * c1;
-                S[8] += hd * c2;
+        if (ng == 1) {
+            for (int j = s0; j < s0 + sc; ++j)
+                pair64<SCHEME>(xi, yi, zi, ai0, ai1, ai2, A.rec[2 * (size_t)j], A.rec[2 * (size_t)j + 1], true, S);
+        } else {
+            for (int j0 = 0; j0 < sc; j0 += ng) {
+                const bool ok = member && j0 + g0 < sc;
+                const int j = s0 + (ok ? j0 + g0 : 0);
+                pair64<SCHEME>(xi, yi, zi, ai0, ai1, ai2, A.rec[2 * (size_t)j], A.rec[2 * (size_t)j + 1], ok, S);
             }
         }
     }
-    if (!valid) return;
+    if (ng > 1) {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+            double v = S[q];
+            for (int g = 1; g < ng; ++g) v += __shfl(S[q], (lane + g * tc) & 63, 64);
+            S[q] = v;
+        }
+    }
+    if (lane >= tc) return;
     double d0, d1, d2;
     if (SCHEME == VFMM_SCHEME_TRANSPOSE) {
         d0 = ai1 * S[5] - ai2 * S[4];
@@ -771,40 +865,59 @@ __global__ __launch_bounds__(64) void k_p2p64(P2P64Args A) {
         d1 = S[5] * ai0 - S[3] * ai2;
         d2 = S[3] * ai1 - S[4] * ai0;
     }
-    d0 -= 3.0 * S[6];
-    d1 -= 3.0 * S[7];
-    d2 -= 3.0 * S[8];
-    double u0 = S[0], u1 = S[1], u2 = S[2];
-    if (A.far_u) {
-        u0 += A.far_u[i];
-        u1 += A.far_u[A.n + i];
-        u2 += A.far_u[2 * A.n + i];
-        d0 += A.far_da[i];
-        d1 += A.far_da[A.n + i];
-        d2 += A.far_da[2 * A.n + i];
-    }
-    if (A.surface) {
-        u0 -= A.bounds->sum_xa[0] * A.inv3V;
-        u1 -= A.bounds->sum_xa[1] * A.inv3V;
-        u2 -= A.bounds->sum_xa[2] * A.inv3V;
-    }
-    if (A.bounds->stale) u0 = u1 = u2 = d0 = d1 = d2 = __builtin_nan("");  // positions differ from the build's
-    const int o = A.perm[i];
-    A.ux[o] = (float)u0;
-    A.uy[o] = (float)u1;
-    A.uz[o] = (float)u2;
-    A.dax[o] = (float)d0;
-    A.day[o] = (float)d1;
-    A.daz[o] = (float)d2;
+    double *near = A.near + 6 * (size_t)A.item_out[item];
+    near[lane] = S[0];
+    near[tc + lane] = S[1];
+    near[2 * tc + lane] = S[2];
+    near[3 * tc + lane] = d0 - 3.0 * S[6];
+    near[4 * tc + lane] = d1 - 3.0 * S[7];
+    near[5 * tc + lane] = d2 - 3.0 * S[8];
 }
 
-static void launch_p2p64(Ctx &c, P2P64Args A) {
-    if (A.nblocks == 0) return;
-    if (c.prm.scheme == VFMM_SCHEME_TRANSPOSE)
-        k_p2p64<VFMM_SCHEME_TRANSPOSE><<<A.nblocks, 64, 0, c.stream>>>(A);
-    else
-        k_p2p64<VFMM_SCHEME_CLASSICAL><<<A.nblocks, 64, 0, c.stream>>>(A);
-    VFMM_LAUNCH_CHECK();
+// the parts of a block in list order, the far field and the zero-mean term,
+// rounded to float32 once
+__global__ __launch_bounds__(256) void k_finalize64(P2P64Args A) {
+    const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (b >= A.nblocks) return;
+    const int4 blk = A.blocks[b];
+    if (lane >= blk.y) return;
+    const int64_t i = blk.x + lane;
+    const double *q = A.near + 6 * (size_t)blk.z + lane;
+    double v[6] = {0, 0, 0, 0, 0, 0};
+    for (int p = 0; p < blk.w; ++p)
+#pragma unroll
+        for (int c = 0; c < 6; ++c) v[c] += q[(size_t)(6 * p + c) * blk.y];
+    if (A.far_u)
+        for (int c = 0; c < 3; ++c) {
+            v[c] += A.far_u[c * A.n + i];
+            v[3 + c] += A.far_da[c * A.n + i];
+        }
+    if (A.surface)
+        for (int c = 0; c < 3; ++c) v[c] -= A.bounds->sum_xa[c] * A.inv3V;
+    if (A.bounds->stale)  // positions differ from the build's
+        for (int c = 0; c < 6; ++c) v[c] = __builtin_nan("");
+    const int o = A.perm[i];
+    A.ux[o] = (float)v[0];
+    A.uy[o] = (float)v[1];
+    A.uz[o] = (float)v[2];
+    A.dax[o] = (float)v[3];
+    A.day[o] = (float)v[4];
+    A.daz[o] = (float)v[5];
+}
+
+static void launch_p2p64(Ctx &c, const P2P64Args &A) {
+    c.record(2 * PH_P2P);
+    if (A.nitems > 0) {
+        const unsigned g = xcd_grid(cdiv(A.nitems, 4));
+        if (c.prm.scheme == VFMM_SCHEME_TRANSPOSE)
+            k_p2p64<VFMM_SCHEME_TRANSPOSE><<<g, 256, 0, c.stream>>>(A);
+        else
+            k_p2p64<VFMM_SCHEME_CLASSICAL><<<g, 256, 0, c.stream>>>(A);
+        VFMM_LAUNCH_CHECK();
+        k_finalize64<<<cdiv(A.nblocks, 4), 256, 0, c.stream>>>(A);
+        VFMM_LAUNCH_CHECK();
+    }
+    c.record(2 * PH_P2P + 1);
 }
 
 // The launch constant of the scaled form (the cutoff's constants are cutoff_ce).
@@ -959,9 +1072,13 @@ void p2p_and_finalize(Ctx &c, float *ux, float *uy, float *uz, float *dax, float
     if (c.prm.precision == VFMM_PRECISION_FP64) {
         P2P64Args A{};
         A.rec = c.rec64.as<double4>();
-        A.blocks = c.blocks.as<int4>();
+        A.items = c.items.as<int4>();
+        A.item_out = c.item_out.as<int>();
+        A.blocks = c.pblocks.as<int4>();
         A.ent = c.p2p_ent.as<int4>();
-        A.nblocks = c.n_blocks;
+        A.nitems = c.n_items;
+        A.nblocks = c.n_pblocks;
+        A.near = c.near.as<double>();
         A.B = c.img_B;
         A.len = c.prm.periodic ? c.prm.box_len : 0.0;
         A.far_u = c.far_u.as<double>();
@@ -972,9 +1089,7 @@ void p2p_and_finalize(Ctx &c, float *ux, float *uy, float *uz, float *dax, float
         A.surface = (c.prm.periodic && c.prm.zero_mean) ? 1 : 0;
         A.inv3V = c.prm.periodic ? 1.0 / (3.0 * c.prm.box_len * c.prm.box_len * c.prm.box_len) : 0.0;
         A.ux = ux; A.uy = uy; A.uz = uz; A.dax = dax; A.day = day; A.daz = daz;
-        c.record(2 * PH_P2P);
         launch_p2p64(c, A);
-        c.record(2 * PH_P2P + 1);
         return;
     }
     // the same near-field parts and finalize as the other evaluation orders,
@@ -993,8 +1108,9 @@ __global__ __launch_bounds__(256) void k_direct_setup64(int64_t n, const float *
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
     const double k = 0.079577471545947667884;  // 1/(4 pi)
-    rec[2 * i] = make_double4(x[i], y[i], z[i], 0.70710678118654752440 / (double)s[i]);  // 1/(sqrt 2 sigma)
-    rec[2 * i + 1] = make_double4((double)ax[i] * k, (double)ay[i] * k, (double)az[i] * k, 0.0);
+    const double c = 0.70710678118654752440 / (double)s[i];  // 1/(sqrt 2 sigma)
+    rec[2 * i] = make_double4(x[i], y[i], z[i], c * c);
+    rec[2 * i + 1] = make_double4((double)ax[i] * k, (double)ay[i] * k, (double)az[i] * k, c * c * c);
     perm[i] = (int)i;
 }
 
@@ -1129,14 +1245,22 @@ static void launch_direct(const P2PConst &k, const P2PArgs &A, bool var, hipStre
     VFMM_LAUNCH_CHECK();
 }
 
-// Entries of 64 sources for the float64 form.
-__global__ __launch_bounds__(256) void k_direct_blocks(int64_t n, int nb, int4 *blocks, int4 *ent) {
-    const int b = blockIdx.x * 256 + threadIdx.x;
-    if (b < nb) {
-        const int cnt = (int)min<int64_t>(64, n - (int64_t)b * 64);
-        blocks[b] = make_int4(b * 64, cnt, 0, nb);
+// Blocks of 64 targets, entries of 64 sources and np items per block for the
+// float64 form.
+__global__ __launch_bounds__(256) void k_direct_blocks(int64_t n, int nb, int np, int4 *blocks, int4 *ent, int4 *items,
+                                                       int *item_out) {
+    const int j = blockIdx.x * 256 + threadIdx.x;
+    if (j >= nb * np) return;
+    const int b = j / np, p = j % np;
+    const int cnt = (int)min<int64_t>(64, n - (int64_t)b * 64);
+    const int u0 = b * 64 * np;
+    if (p == 0) {
+        blocks[b] = make_int4(b * 64, cnt, u0, np);
         ent[b] = make_int4(b * 64, cnt, 0, 0);
     }
+    const int e0 = (int)((int64_t)p * nb / np), e1 = (int)((int64_t)(p + 1) * nb / np);
+    items[j] = make_int4(b * 64, cnt, e0, e1 - e0);
+    item_out[j] = u0 + p * cnt;
 }
 
 // The float32 (and mixed) all-pairs evaluation; the near-field kernel's
@@ -1191,10 +1315,16 @@ void direct_all_pairs(Ctx &c, const float *x, const float *y, const float *z, co
     c.n_blocks = nb;
     c.p2p_pairs = n * n;
     if (c.prm.precision == VFMM_PRECISION_FP64) {
+        const int np = std::max(1, std::min(nb, 8192 / nb));  // at least about 8,192 waves
         c.perm.ensure(sizeof(int) * n);
-        c.blocks.ensure(sizeof(int4) * nb);
+        c.pblocks.ensure(sizeof(int4) * nb);
         c.p2p_ent.ensure(sizeof(int4) * nb);
-        k_direct_blocks<<<cdiv(nb, 256), 256, 0, c.stream>>>(n, nb, c.blocks.as<int4>(), c.p2p_ent.as<int4>());
+        c.items.ensure(sizeof(int4) * (size_t)nb * np);
+        c.item_out.ensure(sizeof(int) * (size_t)nb * np);
+        c.near.ensure(sizeof(double) * 6 * 64 * (size_t)nb * np);
+        k_direct_blocks<<<cdiv((size_t)nb * np, 256), 256, 0, c.stream>>>(n, nb, np, c.pblocks.as<int4>(),
+                                                                          c.p2p_ent.as<int4>(), c.items.as<int4>(),
+                                                                          c.item_out.as<int>());
         VFMM_LAUNCH_CHECK();
         c.rec64.ensure(sizeof(double4) * 2 * n);
         k_direct_setup64<<<cdiv(n, 256), 256, 0, c.stream>>>(n, x, y, z, ax, ay, az, sigma, c.rec64.as<double4>(),
@@ -1202,16 +1332,18 @@ void direct_all_pairs(Ctx &c, const float *x, const float *y, const float *z, co
         VFMM_LAUNCH_CHECK();
         P2P64Args A{};
         A.rec = c.rec64.as<double4>();
-        A.blocks = c.blocks.as<int4>();
+        A.items = c.items.as<int4>();
+        A.item_out = c.item_out.as<int>();
+        A.blocks = c.pblocks.as<int4>();
         A.ent = c.p2p_ent.as<int4>();
+        A.nitems = nb * np;
         A.nblocks = nb;
+        A.near = c.near.as<double>();
         A.n = n;
         A.perm = c.perm.as<int>();
         A.bounds = c.bres.as<Bounds>();
         A.ux = ux; A.uy = uy; A.uz = uz; A.dax = dax; A.day = day; A.daz = daz;
-        c.record(2 * PH_P2P);
         launch_p2p64(c, A);
-        c.record(2 * PH_P2P + 1);
         return;
     }
     c.recp.ensure(sizeof(float4) * (c.var_sigma ? 4 : 3) * (size_t)n);

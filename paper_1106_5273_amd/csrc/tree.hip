@@ -559,8 +559,8 @@ void gather_strengths(Ctx &c, const float *ax, const float *ay, const float *az,
 }
 
 // float64 records for the float64 form: positions from the sorted float32
-// records (exact), c = 1/(sqrt 2 sigma) of each core, strengths from the
-// caller's arrays scaled in float64
+// records (exact), c^2 and c^3 with c = 1/(sqrt 2 sigma) of each core, strengths
+// from the caller's arrays scaled in float64
 __global__ __launch_bounds__(TPB) void k_gather_rec64(const int *perm, int64_t n, const float *ax, const float *ay,
                                                       const float *az, const float4 *rec, double4 *rec64) {
     const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
@@ -568,8 +568,9 @@ __global__ __launch_bounds__(TPB) void k_gather_rec64(const int *perm, int64_t n
     const int j = perm[i];
     const double k = 0.079577471545947667884;  // 1/(4 pi)
     const float4 p = rec[2 * i];
-    rec64[2 * i] = make_double4(p.x, p.y, p.z, 0.70710678118654752440 / (double)p.w);  // 1/(sqrt 2 sigma)
-    rec64[2 * i + 1] = make_double4((double)ax[j] * k, (double)ay[j] * k, (double)az[j] * k, 0.0);
+    const double c = 0.70710678118654752440 / (double)p.w;  // 1/(sqrt 2 sigma)
+    rec64[2 * i] = make_double4(p.x, p.y, p.z, c * c);
+    rec64[2 * i + 1] = make_double4((double)ax[j] * k, (double)ay[j] * k, (double)az[j] * k, c * c * c);
 }
 
 void gather_records64(Ctx &c, const float *ax, const float *ay, const float *az) {

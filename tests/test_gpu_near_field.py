@@ -94,3 +94,18 @@ def test_direct_mode_sizes(n, var):
         # two factors, F <= F(0) = 1 / (6 sqrt 2 pi^1.5 sigma^3) of Eq. (2)
         scale = np.sum(a * a) / (6.0 * np.sqrt(2.0) * np.pi ** 1.5 * float(case["sigma"][0]) ** 3)
         assert not u.any() and np.abs(da).max() <= 4 * 2.0 ** -24 * scale
+
+
+@pytest.mark.parametrize("x", [0.0, 1e-12, 0.3, 2.9999, 3.0001, 8.0, 40.99, 41.01, 300.0])
+def test_float64_cutoff_at_its_branches(x):
+    """Two particles at (rho / (sqrt 2 sigma))^2 = x.  The float64 form is exact to its one rounding to float32:
+    2^-24 of each component, here of the largest."""
+    sig = 0.05
+    d = np.sqrt(x) * np.sqrt(2.0) * sig * np.array([0.6, 0.0, 0.8])
+    f = lambda *v: np.array(v, np.float32)  # noqa: E731
+    case = dict(x=f(0.1, 0.1 + d[0]), y=f(0.2, 0.2), z=f(0.3, 0.3 + d[2]), ax=f(0.7, -0.3), ay=f(0.2, 0.9),
+                az=f(-0.4, 0.5), sigma=f(sig, 1.2 * sig), n=2)
+    u, da = _run(case, direct=1, precision=2)
+    ref = oracle.direct(case)
+    for got, want in ((u, ref["u"]), (da, ref["da_t"])):
+        assert np.abs(got - want).max() <= 1.01 * 2.0 ** -24 * np.abs(want).max()
