@@ -62,6 +62,9 @@ struct Ctx {
     DevBuf lkey, lkey2, lval, lval2;     // list sort
     DevBuf m2l_off, m2l_src;             // CSR by target cell: int offsets[ncells+1], int2 (src, img)
     DevBuf m2l_tgt;                      // target cell of each CSR entry
+    unsigned m2l_lds_set = 0;            // per-pair M2L kernels (degree, precision) whose dynamic LDS has been allowed
+    int m2l_part = 0, m2l_nparts = 0;    // per-pair M2L: sources per part, part slots
+    DevBuf m2l_parts, m2l_partial;       // int4 (target, first, end) per slot, V2[3 NC(p)] partial sums
     DevBuf p2p_off, p2p_ent;             // CSR by target cell: int offsets, int4 (start, count, img, variant)
     DevBuf p2p_sh;                       // float4 per P2P entry: scaled offset between the two leaf centres
     DevBuf blocks;                       // int4 (tgt start, tgt count, list off, list count)
@@ -176,6 +179,7 @@ void traverse_and_lists(Ctx &c);
 // far.hip
 void far_field(Ctx &c);
 void far_prealloc(Ctx &c);
+void m2l_pair_plan(Ctx &c);
 // m2lb.hip
 void m2lb_plan(Ctx &c);
 void m2lb_run(Ctx &c);

@@ -208,166 +208,301 @@ __global__ __launch_bounds__((XferCfg<P>::THREADS)) void k_m2m(int c0, int c1, c
 }
 
 // ---------------------------------------------------------------------------
-// M2L: one work-group per target cell; each thread owns one real output row
-// (Re or Im of Lt_k^l, l >= 0; (P+1)^2 rows) for all three potentials, and
-// the source cells of the target's list are staged in LDS two at a time
-// (Sec. 3.6: a block per target cell, source cells loaded to shared memory
-// and processed sequentially).
+// M2L, one translation at a time (Sec. 3.6), for trees whose translations do
+// not group densely and for the float64 form.
 //   Lt_k^l(A) = (-1)^{k+l} lambda^{-(k+1)} sum_{n,m} Mt_n^m(B) I_{n+k}^{m-l}((c_A - c_B)/s_B),
 //   lambda = s_B/s_A.
-// With I^{-mu} = (-1)^mu conj(I^mu) and Mt^{-m} = (-1)^m conj(Mt^m), the terms
-// of +-m combine into Re/Im rows that read two staged tables:
-//   X_N^M = (Re I_N^M, -Im I_N^M),  Y_N^M = (Im I_N^M, Re I_N^M),  |M| <= 2P.
+// With I^{-mu} = (-1)^mu conj(I^mu), Mt^{-m} = (-1)^m conj(Mt^m), z1 = I_{n+k}^{m-l},
+// z2 = (-1)^l I_{n+k}^{m+l}, the terms of +-m are
+//   Re: Mr (z1r + z2r) - Mi (z1i + z2i),   Im: Mr (z1i - z2i) + Mi (z1r - z2r).
+// Target lists are cut into parts (m2l_pair_plan), a work-group each, whose
+// partial sums k_m2l_add adds to the local expansions in list order: with a
+// work-group per target the 64 targets of a 3,000-particle tree ran on 64 CUs,
+// its longest list of 43 sources in one serial loop (235 -> 18 us).  A
+// work-group stages SB sources at a time in LDS (the harmonics |M| <= N <= 2P of
+// each, a column of one order per thread, and the multipoles), and a subgroup
+// of LP threads takes each source.  A thread holds one order l and KB
+// consecutive degrees k of the output, real and imaginary, for the three
+// potentials; with KB > 1 it walks n downwards at fixed m, so that each harmonic
+// that it reads serves KB degrees (n + k = N), and so does each multipole.  In float64 the
+// kernel is bound by LDS reads, so KB = 3 (64^3, 1.43 million translations: 7.5
+// ms; KB = 2 8.6, KB = 1 16.8, a thread per real output row 16.2 ms); in float32
+// the walk's registers outweigh them, so KB = 1 with n outermost (70,516
+// translations at p = 8: 0.18 ms; KB = 2 0.30, KB = 3 0.33 ms, a thread per real
+// output row 0.44 ms).
 // ---------------------------------------------------------------------------
+__host__ __device__ constexpr int m2l_kb(bool dbl) { return dbl ? 3 : 1; }
+__host__ __device__ constexpr int m2l_lanes(int P, bool dbl) {  // threads per source
+    int n = 0;
+    for (int l = 0; l <= P; ++l) n += (P + m2l_kb(dbl) - l) / m2l_kb(dbl);
+    return n;
+}
+__host__ __device__ constexpr int m2l_sources(int P, bool dbl) {  // sources staged at once
+    const int s = (dbl ? 192 : 320) / m2l_lanes(P, dbl);
+    return s < 8 ? s : 8;
+}
+
 template <int P, class R = float>
 struct M2LCfg {
     static constexpr int NCP = NC(P);
-    static constexpr int ROWS = (P + 1) * (P + 1);
-    static constexpr int THREADS = ((ROWS + 63) / 64) * 64;
+    static constexpr int KB = m2l_kb(sizeof(R) == 8);
+    static constexpr int LP = m2l_lanes(P, sizeof(R) == 8);
+    static constexpr int SB = m2l_sources(P, sizeof(R) == 8);
+    static constexpr int THREADS = ((SB * LP + 63) / 64) * 64;
     static constexpr int Q = 2 * P;
-    static constexpr int IW = 4 * P + 1;                 // M in [-2P, 2P]
-    static constexpr int ISZ = (Q + 1) * IW;             // per table
-    static constexpr int SB = sizeof(R) == 8 ? 1 : 2;    // sources staged at once
+    // I_N^M at PAD + N (N + 1) + M; a thread's lowest degrees may lie below l, whose
+    // (unused) sums read up to two elements in front
+    static constexpr int PAD = 2;
+    static constexpr int ISZ = PAD + (Q + 1) * (Q + 1);
+    using V2 = typename VT<R>::V2;
+    static constexpr size_t LDS = sizeof(V2) * SB * (ISZ + 3 * NCP) + sizeof(R) * SB;
 };
 
 template <int P, class R>
-__global__ __launch_bounds__((M2LCfg<P, R>::THREADS)) void k_m2l(int ncells, const int *off, const int2 *src,
-                                                               const float4 *geo,
+__global__ __launch_bounds__((M2LCfg<P, R>::THREADS)) void k_m2l(const int4 *parts, const int2 *src, const float4 *geo,
                                                                const typename VT<R>::V2 *__restrict__ Mexp,
-                                                               typename VT<R>::V2 *__restrict__ Lexp, int B,
+                                                               typename VT<R>::V2 *__restrict__ partial, int B,
                                                                float len) {
     using C = M2LCfg<P, R>;
     using V2 = typename VT<R>::V2;
-    __shared__ V2 Xs[C::SB][C::ISZ];
-    __shared__ V2 Ys[C::SB][C::ISZ];
-    __shared__ V2 Ms[C::SB][3][C::NCP];
-    __shared__ R lam[C::SB];
-    const int tgt = blockIdx.x;
-    if (tgt >= ncells) return;
-    const int o0 = off[tgt], o1 = off[tgt + 1];
-    if (o0 == o1) return;
+    constexpr int KB = C::KB, NCP = C::NCP;
+    extern __shared__ double2 smem[];
+    V2 *Is = reinterpret_cast<V2 *>(smem);   // [SB][ISZ]
+    V2 *Ms = Is + C::SB * C::ISZ;            // [SB][3][NCP]
+    R *lam = reinterpret_cast<R *>(Ms + C::SB * 3 * NCP);
+    const int4 part = parts[blockIdx.x];  // (target, first entry, end entry)
+    const int tgt = part.x;
+    if (tgt < 0) return;
+    const int o0 = part.y, o1 = part.z;
     const int tid = threadIdx.x;
-    for (int i = tid; i < C::SB * C::ISZ; i += C::THREADS) {
-        (&Xs[0][0])[i] = V2{R(0), R(0)};
-        (&Ys[0][0])[i] = V2{R(0), R(0)};
-    }
     const float4 ga = geo[tgt];
-    // row of this thread
-    const bool active = tid < C::ROWS;
-    int k = 0, l = 0;
-    bool isIm = false;
-    if (active) {
-        k = (int)sqrtf((float)tid);
-        while ((k + 1) * (k + 1) <= tid) ++k;
-        while (k * k > tid) --k;
-        const int j = tid - k * k;
-        l = (j + 1) / 2;
-        isIm = (j > 0) && ((j & 1) == 0);
+    const int sub = tid / C::LP;
+    int j = tid % C::LP, l = 0;
+    for (int cnt = (P + KB) / KB; j >= cnt; cnt = (P - l + KB) / KB) {
+        j -= cnt;
+        ++l;
     }
-    const R sig = (l & 1) ? R(-1) : R(1);
-    const R sp = isIm ? -sig : sig;
-    R acc[3] = {R(0), R(0), R(0)};
+    const int kt = P - KB * j;  // this thread's degrees: kt, kt - 1, .. (those >= l)
+    const R sg = (l & 1) ? R(-1) : R(1);
+    R re[KB][3], im[KB][3];
+#pragma unroll
+    for (int q = 0; q < KB; ++q)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) re[q][c] = im[q][c] = R(0);
     const int W = 2 * B + 1;
     for (int e0 = o0; e0 < o1; e0 += C::SB) {
+        const int nb = min(C::SB, o1 - e0);
         __syncthreads();
-        // ---- stage up to SB sources ----
-        for (int s = 0; s < C::SB; ++s) {
-            const int e = e0 + s;
-            if (e >= o1) break;
-            const int2 ent = src[e];
+        // ---- stage nb sources ----
+        for (int i = tid; i < nb * (C::Q + 1); i += C::THREADS) {
+            const int s = i / (C::Q + 1), M = i % (C::Q + 1);
+            const int2 ent = src[e0 + s];
             const float4 gb = geo[ent.x];
-            const int col = tid - s * (C::Q + 1);
-            if (col >= 0 && col <= C::Q) {
-                const R ix = (R)(ent.y % W - B), iy = (R)((ent.y / W) % W - B), iz = (R)(ent.y / (W * W) - B);
-                const R inv = R(1) / R(gb.w);
-                const R dx = (R(ga.x) - R(gb.x) - ix * R(len)) * inv;
-                const R dy = (R(ga.y) - R(gb.y) - iy * R(len)) * inv;
-                const R dz = (R(ga.z) - R(gb.z) - iz * R(len)) * inv;
-                const R r2 = dx * dx + dy * dy + dz * dz;
-                const R ir2 = R(1) / r2;
-                // I_M^M by the diagonal recurrence, then upward in N
-                R cr = rsqr(r2), ci = R(0);
-                for (int mm = 1; mm <= col; ++mm) {
-                    const R f = -(R)(2 * mm - 1) * ir2;
-                    const R nr = f * (dx * cr - dy * ci);
-                    const R ni = f * (dx * ci + dy * cr);
-                    cr = nr;
-                    ci = ni;
-                }
-                const int M = col;
-                V2 *X = Xs[s], *Y = Ys[s];
-                auto put = [&](int N, R vr, R vi) {
-                    X[N * C::IW + C::Q + M] = V2{vr, -vi};
-                    Y[N * C::IW + C::Q + M] = V2{vi, vr};
-                    if (M > 0) {
-                        // I^{-M} = (-1)^M conj(I^M)
-                        const R sr = (M & 1) ? -vr : vr, si = (M & 1) ? vi : -vi;
-                        X[N * C::IW + C::Q - M] = V2{sr, -si};
-                        Y[N * C::IW + C::Q - M] = V2{si, sr};
-                    }
-                };
-                put(M, cr, ci);
-                R pr = cr, pi = ci;
-                R qr = R(0), qi = R(0);
-                if (M + 1 <= C::Q) {
-                    const R a0 = (R)(2 * M + 1) * dz * ir2;
-                    qr = a0 * cr;
-                    qi = a0 * ci;
-                    put(M + 1, qr, qi);
-                }
-                for (int N = M + 2; N <= C::Q; ++N) {
-                    const R a = (R)(2 * N - 1) * dz;
-                    const R b = (R)((N - 1) * (N - 1) - M * M);
-                    const R vr = (a * qr - b * pr) * ir2;
-                    const R vi = (a * qi - b * pi) * ir2;
-                    put(N, vr, vi);
-                    pr = qr; pi = qi; qr = vr; qi = vi;
-                }
+            const R ix = (R)(ent.y % W - B), iy = (R)((ent.y / W) % W - B), iz = (R)(ent.y / (W * W) - B);
+            const R inv = R(1) / R(gb.w);
+            const R dx = (R(ga.x) - R(gb.x) - ix * R(len)) * inv;
+            const R dy = (R(ga.y) - R(gb.y) - iy * R(len)) * inv;
+            const R dz = (R(ga.z) - R(gb.z) - iz * R(len)) * inv;
+            const R r2 = dx * dx + dy * dy + dz * dz;
+            const R ir2 = R(1) / r2;
+            // I_M^M by the diagonal recurrence, then upward in N
+            R cr = rsqr(r2), ci = R(0);
+            for (int mm = 1; mm <= M; ++mm) {
+                const R f = -(R)(2 * mm - 1) * ir2;
+                const R nr = f * (dx * cr - dy * ci);
+                const R ni = f * (dx * ci + dy * cr);
+                cr = nr;
+                ci = ni;
             }
-            for (int i = tid; i < 3 * C::NCP; i += C::THREADS)
-                Ms[s][i / C::NCP][i % C::NCP] = Mexp[(size_t)ent.x * 3 * C::NCP + i];
-            if (tid == 0) lam[s] = R(ga.w) / R(gb.w);  // 1/lambda
+            V2 *I = Is + s * C::ISZ + C::PAD;
+            auto put = [&](int N, R vr, R vi) {
+                I[N * (N + 1) + M] = V2{vr, vi};
+                if (M > 0) I[N * (N + 1) - M] = (M & 1) ? V2{-vr, vi} : V2{vr, -vi};  // (-1)^M conj
+            };
+            put(M, cr, ci);
+            R pr = cr, pi = ci;
+            R qr = R(0), qi = R(0);
+            if (M + 1 <= C::Q) {
+                const R a0 = (R)(2 * M + 1) * dz * ir2;
+                qr = a0 * cr;
+                qi = a0 * ci;
+                put(M + 1, qr, qi);
+            }
+            for (int N = M + 2; N <= C::Q; ++N) {
+                const R a = (R)(2 * N - 1) * dz;
+                const R b = (R)((N - 1) * (N - 1) - M * M);
+                const R vr = (a * qr - b * pr) * ir2;
+                const R vi = (a * qi - b * pi) * ir2;
+                put(N, vr, vi);
+                pr = qr; pi = qi; qr = vr; qi = vi;
+            }
+            if (M == 0) lam[s] = R(ga.w) / R(gb.w);  // 1/lambda
+        }
+        for (int i = tid; i < nb * 3 * NCP; i += C::THREADS) {
+            const int s = i / (3 * NCP), q = i % (3 * NCP);
+            Ms[i] = Mexp[(size_t)src[e0 + s].x * 3 * NCP + q];
         }
         __syncthreads();
-        if (!active) continue;
-        for (int s = 0; s < C::SB; ++s) {
-            if (e0 + s >= o1) break;
-            const V2 *Wt = isIm ? Ys[s] : Xs[s];
-            R a0 = R(0), a1 = R(0), a2 = R(0);
+        if (sub >= nb) continue;
+        const V2 *I = Is + sub * C::ISZ + C::PAD, *Mt = Ms + sub * 3 * NCP;
+        R ar[KB][3], ai[KB][3];
+#pragma unroll
+        for (int q = 0; q < KB; ++q)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) ar[q][c] = ai[q][c] = R(0);
+        if constexpr (KB == 1) {
 #pragma unroll
             for (int n = P; n >= 0; --n) {
-                const V2 *row = Wt + (n + k) * C::IW + C::Q;
+                const V2 *row = I + (n + kt) * (n + kt + 1);
                 {
-                    const R w = row[-l].x;
-                    a0 += Ms[s][0][CIDX(n, 0)].x * w;
-                    a1 += Ms[s][1][CIDX(n, 0)].x * w;
-                    a2 += Ms[s][2][CIDX(n, 0)].x * w;
+                    const V2 z = row[-l];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        const R w = Mt[c * NCP + CIDX(n, 0)].x;
+                        ar[0][c] = fmar(w, z.x, ar[0][c]);
+                        ai[0][c] = fmar(w, z.y, ai[0][c]);
+                    }
                 }
 #pragma unroll
                 for (int m = 1; m <= n; ++m) {
-                    const V2 w1 = row[m - l], w2 = row[m + l];
-                    const R A1 = fmar(sp, w2.x, w1.x);
-                    const R B1 = fmar(sp, w2.y, w1.y);
-                    const V2 m0 = Ms[s][0][CIDX(n, m)], m1 = Ms[s][1][CIDX(n, m)], m2 = Ms[s][2][CIDX(n, m)];
-                    a0 = fmar(m0.x, A1, fmar(m0.y, B1, a0));
-                    a1 = fmar(m1.x, A1, fmar(m1.y, B1, a1));
-                    a2 = fmar(m2.x, A1, fmar(m2.y, B1, a2));
+                    const V2 z1 = row[m - l], z2 = row[m + l];
+                    const R ur = fmar(sg, z2.x, z1.x), ui = fmar(sg, z2.y, z1.y);
+                    const R vr = fmar(-sg, z2.x, z1.x), vi = fmar(-sg, z2.y, z1.y);
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        const V2 w = Mt[c * NCP + CIDX(n, m)];
+                        ar[0][c] = fmar(w.x, ur, fmar(-w.y, ui, ar[0][c]));
+                        ai[0][c] = fmar(w.x, vi, fmar(w.y, vr, ai[0][c]));
+                    }
                 }
             }
-            const R sc = powr(lam[s], k + 1);
-            acc[0] += sc * a0;
-            acc[1] += sc * a1;
-            acc[2] += sc * a2;
+        } else {
+#pragma unroll
+            for (int m = 0; m <= P; ++m) {
+                // z1 + z2 and z1 - z2 of the KB degrees N = n + kt - q
+                V2 u[KB], v[KB];
+                auto get = [&](int N, V2 &a, V2 &b) {
+                    const V2 *row = I + N * (N + 1) + m;
+                    const V2 z1 = row[-l];
+                    if (m == 0) {  // one term, not two
+                        a = z1;
+                        b = z1;
+                    } else {
+                        const V2 z2 = row[l];
+                        a = V2{fmar(sg, z2.x, z1.x), fmar(sg, z2.y, z1.y)};
+                        b = V2{fmar(-sg, z2.x, z1.x), fmar(-sg, z2.y, z1.y)};
+                    }
+                };
+#pragma unroll
+                for (int q = 0; q < KB - 1; ++q) get(P + kt - q, u[q], v[q]);
+#pragma unroll
+                for (int n = P; n >= m; --n) {
+                    get(n + kt - (KB - 1), u[KB - 1], v[KB - 1]);
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        const V2 w = Mt[c * NCP + CIDX(n, m)];
+#pragma unroll
+                        for (int q = 0; q < KB; ++q) {
+                            if (m == 0) {
+                                ar[q][c] = fmar(w.x, u[q].x, ar[q][c]);
+                                ai[q][c] = fmar(w.x, u[q].y, ai[q][c]);
+                            } else {
+                                ar[q][c] = fmar(w.x, u[q].x, fmar(-w.y, u[q].y, ar[q][c]));
+                                ai[q][c] = fmar(w.x, v[q].y, fmar(w.y, v[q].x, ai[q][c]));
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int q = 0; q < KB - 1; ++q) {
+                        u[q] = u[q + 1];
+                        v[q] = v[q + 1];
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < KB; ++q) {
+            const R sc = powr(lam[sub], kt - q + 1);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                re[q][c] = fmar(sc, ar[q][c], re[q][c]);
+                im[q][c] = fmar(sc, ai[q][c], im[q][c]);
+            }
         }
     }
-    if (active) {
-        const R sg = ((k + l) & 1) ? R(-1) : R(1);
-        const int coef = CIDX(k, l);
-        for (int c = 0; c < 3; ++c) {
-            R *dst = reinterpret_cast<R *>(&Lexp[((size_t)tgt * 3 + c) * C::NCP + coef]) + (isIm ? 1 : 0);
-            *dst += sg * acc[c];
+    // the subgroups' sums, added in order
+    __syncthreads();
+    static_assert(3 * NCP <= C::ISZ, "the sums fit the harmonics' space");
+    if (sub < C::SB)
+#pragma unroll
+        for (int q = 0; q < KB; ++q)
+            if (kt - q >= l)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) Is[(sub * 3 + c) * NCP + CIDX(kt - q, l)] = V2{re[q][c], im[q][c]};
+    __syncthreads();
+    for (int i = tid; i < 3 * NCP; i += C::THREADS) {
+        V2 w = Is[i];
+        for (int t = 1; t < C::SB; ++t) {
+            const V2 x = Is[t * 3 * NCP + i];
+            w.x += x.x;
+            w.y += x.y;
         }
+        int kk, ll;
+        decode_nm(i % NCP, kk, ll);
+        const R f = ((kk + ll) & 1) ? R(-1) : R(1);
+        partial[(size_t)blockIdx.x * 3 * NCP + i] = V2{f * w.x, ll == 0 ? R(0) : f * w.y};
     }
+}
+
+// slot of part p of target t's list; distinct for all parts of all targets
+__device__ inline int m2l_slot(const int *off, int t, int part) { return off[t] / part + t; }
+
+// (target, first entry, end entry, 0) of every part; the other slots hold target -1
+__global__ __launch_bounds__(TPB) void k_m2l_parts(int ncells, const int *off, int part, int4 *parts) {
+    const int t = blockIdx.x * (TPB / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (t >= ncells) return;
+    const int o0 = off[t], o1 = off[t + 1], s0 = m2l_slot(off, t, part);
+    const int s1 = t + 1 < ncells ? m2l_slot(off, t + 1, part) : o1 / part + ncells;
+    for (int s = s0 + lane; s < s1; s += 64) {
+        const int e = o0 + (s - s0) * part;
+        parts[s] = e < o1 ? make_int4(t, e, min(e + part, o1), 0) : make_int4(-1, 0, 0, 0);
+    }
+}
+
+// Lt(t) += its parts' sums, in list order
+template <class V2>
+__global__ __launch_bounds__(TPB) void k_m2l_add(const int *off, int part, int nc3, const V2 *__restrict__ partial,
+                                                 V2 *__restrict__ Lexp) {
+    const int t = blockIdx.x;
+    const int np = (off[t + 1] - off[t] + part - 1) / part;
+    if (np == 0) return;
+    const V2 *p = partial + (size_t)m2l_slot(off, t, part) * nc3;
+    for (int i = threadIdx.x; i < nc3; i += TPB) {
+        V2 v = Lexp[(size_t)t * nc3 + i];
+        for (int q = 0; q < np; ++q) {
+            const V2 w = p[(size_t)q * nc3 + i];
+            v.x += w.x;
+            v.y += w.y;
+        }
+        Lexp[(size_t)t * nc3 + i] = v;
+    }
+}
+
+// Parts of the target lists for the translations one at a time: the sources of
+// one pass where the whole list would otherwise leave CUs idle, else four
+// passes, growing with the list so that the partial sums stay within the size
+// of the expansions.
+void m2l_pair_plan(Ctx &c) {
+    if (c.n_m2l == 0) return;
+    const int sb = m2l_sources(c.prm.p, c.prm.precision == VFMM_PRECISION_FP64);
+    c.m2l_part = c.n_m2l < 65536 ? sb : (int)std::max<int64_t>(4 * sb, c.n_m2l / 65536 / sb * sb);
+    c.m2l_nparts = (int)(c.n_m2l / c.m2l_part) + c.ncells;
+    const size_t vs = c.prm.precision == VFMM_PRECISION_FP64 ? sizeof(double2) : sizeof(float2);
+    c.m2l_parts.ensure(sizeof(int4) * (size_t)c.m2l_nparts);
+    c.m2l_partial.ensure(vs * 3 * NC(c.prm.p) * (size_t)c.m2l_nparts);
+    k_m2l_parts<<<cdiv(c.ncells, TPB / 64), TPB, 0, c.stream>>>(c.ncells, c.m2l_off.as<int>(), c.m2l_part,
+                                                                c.m2l_parts.as<int4>());
+    VFMM_LAUNCH_CHECK();
 }
 
 // ---------------------------------------------------------------------------
@@ -634,10 +769,20 @@ static void far_field_t(Ctx &c) {
     if (c.n_m2l > 0 && c.m2lb_ok && sizeof(S) == 4) {
         m2lb_run(c);
     } else if (c.n_m2l > 0) {
-        k_m2l<P, S><<<c.ncells, M2LCfg<P, S>::THREADS, 0, s>>>(c.ncells, c.m2l_off.as<int>(), c.m2l_src.as<int2>(),
-                                                                c.c_geo.as<float4>(), c.Mexp.as<V2>(),
-                                                                c.Lexp.as<V2>(), c.img_B,
-                                                                c.prm.periodic ? (float)c.prm.box_len : 0.f);
+        using MC = M2LCfg<P, S>;
+        const unsigned bit = 1u << (P / 2 + (sizeof(S) == 8 ? 8 : 0));
+        if (MC::LDS > 64 * 1024 && !(c.m2l_lds_set & bit)) {  // once per context (a context lives on one device)
+            VFMM_HIP(hipFuncSetAttribute((const void *)k_m2l<P, S>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         (int)MC::LDS));
+            c.m2l_lds_set |= bit;
+        }
+        k_m2l<P, S><<<c.m2l_nparts, MC::THREADS, MC::LDS, s>>>(c.m2l_parts.as<int4>(), c.m2l_src.as<int2>(),
+                                                                   c.c_geo.as<float4>(), c.Mexp.as<V2>(),
+                                                                   c.m2l_partial.as<V2>(), c.img_B,
+                                                                   c.prm.periodic ? (float)c.prm.box_len : 0.f);
+        VFMM_LAUNCH_CHECK();
+        k_m2l_add<V2><<<c.ncells, TPB, 0, s>>>(c.m2l_off.as<int>(), c.m2l_part, 3 * NCP, c.m2l_partial.as<V2>(),
+                                               c.Lexp.as<V2>());
         VFMM_LAUNCH_CHECK();
     }
     c.record(2 * PH_M2L + 1);
