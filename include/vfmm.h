@@ -31,8 +31,8 @@
  *   failure on that context.
  * - The context owns the tree, expansions, interaction lists and scratch space
  *   in device memory, and 256 bytes of pinned host memory (hipHostMalloc) that
- *   the build reads its sizes through.  These only grow; vfmm_destroy frees
- *   them.
+ *   the build reads its sizes through (7 KB more once vfmm_energy_spectrum has
+ *   been called).  These only grow; vfmm_destroy frees them.
  * - A context is not thread safe; calls on one context must not overlap.
  * - Depth.  Morton keys hold 21 bits per axis (Sec. 3.2), so a cell is split
  *   at most 21 times (fewer in a batch, whose keys also carry the problem id).

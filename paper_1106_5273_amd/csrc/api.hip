@@ -38,6 +38,8 @@ void Ctx::release_all() {
     ev_fork = ev_join = nullptr;
     if (hpin) (void)hipHostFree(hpin);
     hpin = nullptr;
+    if (hspec) (void)hipHostFree(hspec);
+    hspec = nullptr;
 }
 
 static bool supported_p(int p) { return p == 4 || p == 6 || p == 8 || p == 10 || p == 12; }

@@ -107,8 +107,9 @@ struct Ctx {
     bool rbf_ev_ok = false, gauss_timed = false;
     int64_t gauss_pairs = 0;             // particle pairs of one Gaussian sum on this tree
     uint64_t gauss_build_id = ~0ull;     // build the pair count belongs to
-    // energy spectrum: complex float64 [3][n^3] field, partial and final shell sums
+    // energy spectrum: complex float64 [n^3] (u + i v) and [n^2][n/2 + 1] (w) fields, partial shell sums
     DevBuf spec;
+    double *hspec = nullptr;             // pinned host memory that the spectrum's sums are written to
     // autotuner scratch
     DevBuf tune_ref, tune_out, tune_part;
 
