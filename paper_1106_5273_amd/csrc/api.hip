@@ -147,6 +147,7 @@ static void do_build(Ctx &c, int64_t n, const float *x, const float *y, const fl
     c.record(2 * PH_BOUNDS_SORT);
     c.n = n;
     c.overfull_leaves = 0;
+    c.parted = false;
     if (n == 0) {
         c.ncells = c.nleaves = c.n_p2p = c.n_blocks = 0;
         c.n_m2l = c.p2p_pairs = 0;
@@ -202,7 +203,10 @@ static void do_build(Ctx &c, int64_t n, const float *x, const float *y, const fl
     }
     upload_lattice(c);
     build_tree(c, n, x, y, z, sigma);
-    if (c.n_src_part >= 0 && c.n_src_part < n) partition_sources(c, c.n_src_part);
+    if (c.n_src_part >= 0 && c.n_src_part < n) {
+        partition_sources(c, c.n_src_part);
+        c.parted = true;
+    }
     c.record(2 * PH_TRAVERSE);
     traverse_and_lists(c);
     c.m2lb_ok = false;
@@ -638,6 +642,10 @@ vfmm_status fmm_evaluate_targets(vfmm_ctx *ctx, int64_t n, const float *ax, cons
             VFMM_HIP(hipMemsetAsync(AY + n, 0, sizeof(float) * m, c.stream));
             VFMM_HIP(hipMemsetAsync(AZ + n, 0, sizeof(float) * m, c.stream));
         }
+        struct Mark {
+            bool &on;
+            ~Mark() { on = false; }
+        } mark{c.tg_eval = true};
         vfmm::do_evaluate(c, N, X, Y, Z, AX, AY, AZ, S, O, O + N, O + 2 * N, O + 3 * N, O + 4 * N, O + 5 * N);
         for (int k = 0; k < 6; ++k) copy_d2d(c, op[k], O + k * N, n);
         for (int k = 0; k < 3; ++k) copy_d2d(c, tp[k], O + k * N + n, m);

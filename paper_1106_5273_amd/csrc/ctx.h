@@ -27,7 +27,8 @@ struct Ctx {
     int ncells = 0, nleaves = 0;
     int n_p2p = 0, n_blocks = 0;
     int n_pblocks = 0;                   // near-field blocks (a leaf's targets, cut to fill waves)
-    int n_items = 0, n_items_w = 0;      // P2P work items (parts of a block's list); the first n_items_w take whole waves
+    int item0[5] = {};                   // P2P work items (parts of a block's list) by kind: whole waves, lane groups, and
+                                         // the same for target points (velocity alone); item0[4] is their number
     int n_partial = 0;                   // float[6] partial results of the items
     int64_t n_m2l = 0, p2p_pairs = 0;
     int img_B = 0, img_codes = 1;
@@ -68,7 +69,7 @@ struct Ctx {
     DevBuf p2p_off, p2p_ent;             // CSR by target cell: int offsets, int4 (start, count, img, variant)
     DevBuf p2p_sh;                       // float4 per P2P entry: scaled offset between the two leaf centres
     DevBuf blocks;                       // int4 (tgt start, tgt count, list off, list count)
-    DevBuf pblocks;                      // int4 per near-field block (tgt start, tgt count, first partial result, parts)
+    DevBuf pblocks;                      // int4 per near-field block (tgt start, tgt count, first partial result, parts and kind)
     DevBuf items, item_out;              // int4 per part (tgt start, tgt count, first entry, entries), first partial result
     DevBuf pairs64;                      // int64 reduction scratch
     DevBuf gpart;                        // per-work-group partial pair and source counts of the P2P list
@@ -98,6 +99,8 @@ struct Ctx {
     // separate target points: combined inputs/outputs x y z sigma ax ay az + 6 outputs, float[13 (n + m)]
     DevBuf tgt;
     int64_t tg_n = -1, tg_m = 0;         // particles and targets of the last fmm_build_targets (-1: none)
+    bool tg_eval = false;                // an evaluation by fmm_evaluate_targets is being enqueued
+    bool parted = false;                 // the tree's leaves hold their sources in front (c_nsrc)
     int64_t n_src_part = -1;             // >= 0: callers' indices below it are sources, the rest targets
     DevBuf c_nsrc;                       // per leaf: sources in front of its targets (partitioned builds)
     DevBuf part;                         // partition scratch
@@ -144,6 +147,10 @@ struct Ctx {
     }
     void record(int i) { record(i, stream); }
 };
+
+// Sources per leaf when the evaluation needs no stretching at the target points
+// (fmm_evaluate_targets), else null.
+inline const int *eval_sources(const Ctx &c) { return c.tg_eval && c.parted ? c.c_nsrc.as<int>() : nullptr; }
 
 // tree.hip
 // bytes of the partial-sum buffer of the bounds pass (any n)
@@ -196,6 +203,10 @@ void direct_all_pairs(Ctx &c, const float *x, const float *y, const float *z, co
 void direct_f32(const Ctx &c, hipStream_t s, int64_t n, const Bounds &hb, float4 *recp, const Bounds *bounds,
                 const float *x, const float *y, const float *z, const float *ax, const float *ay, const float *az,
                 const float *sigma, float *ux, float *uy, float *uz, float *dax, float *day, float *daz);
+// The fourth component of a near-field block: its parts, and a flag for blocks
+// of target points that are no particles (velocity alone).
+constexpr int PBLOCK_VELOCITY = 1 << 30;
+constexpr int PBLOCK_PARTS = PBLOCK_VELOCITY - 1;
 // Lane groups of a near-field block of tc targets: more than 32 targets take the
 // wave alone; fewer are held by several groups of tc lanes each (at most 16),
 // which take different sources.

@@ -53,8 +53,8 @@ __device__ inline void decode_nm(int t, int &n, int &m) {
 // P2M: one wave per leaf, particles staged CH at a time.
 // ---------------------------------------------------------------------------
 template <int P, class R>
-__global__ __launch_bounds__(64) void k_p2m(const int *leaves, const int *start, const int *count, const float4 *geo,
-                                            const typename VT<R>::V4 *rec, typename VT<R>::V2 *Mexp) {
+__global__ __launch_bounds__(64) void k_p2m(const int *leaves, const int *start, const int *count, const int *nsrc,
+                                            const float4 *geo, const typename VT<R>::V4 *rec, typename VT<R>::V2 *Mexp) {
     using V2 = typename VT<R>::V2;
     using V4 = typename VT<R>::V4;
     constexpr int NCP = NC(P);
@@ -67,7 +67,7 @@ __global__ __launch_bounds__(64) void k_p2m(const int *leaves, const int *start,
     const int cell = leaves[blockIdx.x];
     const float4 g = geo[cell];
     const R inv = R(1) / R(g.w);
-    const int s0 = start[cell], cnt = count[cell];
+    const int s0 = start[cell], cnt = nsrc ? nsrc[cell] : count[cell];  // target points carry no strength
     constexpr int NT = (NCP + 63) / 64;
     V2 acc[NT][3];
 #pragma unroll
@@ -749,8 +749,9 @@ static void far_field_t(Ctx &c) {
     // a fill kernel rather than a memset, so that the evaluation can be captured in a graph
     k_zero<<<cdiv(cdiv(bytes, 16), 256), 256, 0, s>>>(c.Lexp.as<float>(), (int64_t)(bytes / 4));
     VFMM_LAUNCH_CHECK();
-    k_p2m<P, S><<<c.nleaves, 64, 0, s>>>(c.leaves.as<int>(), c.c_start.as<int>(), c.c_count.as<int>(),
-                                          c.c_geo.as<float4>(), rec, c.Mexp.as<V2>());
+    const int *nsrc = eval_sources(c);
+    k_p2m<P, S><<<c.nleaves, 64, 0, s>>>(c.leaves.as<int>(), c.c_start.as<int>(), c.c_count.as<int>(), nsrc,
+                                         c.c_geo.as<float4>(), rec, c.Mexp.as<V2>());
     VFMM_LAUNCH_CHECK();
     for (int l = c.depth - 1; l >= 0; --l) {
         const int c0 = c.lvl_off[l], c1 = c.lvl_off[l + 1];

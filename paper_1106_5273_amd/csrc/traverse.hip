@@ -304,20 +304,22 @@ __device__ inline int remainder_blocks(int r) {
     return best;
 }
 
-// block b of a leaf of cnt targets: its first target and size (false past the last)
-__device__ inline bool leaf_block(int cnt, int b, int k, int &t0, int &tc) {
-    const int full = cnt / 64, r = cnt % 64;
-    if (b < full) {
-        t0 = 64 * b;
-        tc = 64;
-        return true;
+// The near-field blocks of a leaf of cnt targets, of which the first ns are
+// particles and the rest target points without strength (their blocks compute
+// the velocity alone): f(first target, targets, whether target points).
+template <class F>
+__device__ inline void leaf_blocks(int cnt, int ns, F f) {
+    for (int half = 0; half < 2; ++half) {
+        const int lo = half ? ns : 0, c = half ? cnt - ns : ns;
+        const int full = c / 64, r = c % 64;
+        for (int b = 0; b < full; ++b) f(lo + 64 * b, 64, half != 0);
+        if (r == 0) continue;
+        const int k = remainder_blocks(r);
+        for (int q = 0; q < k; ++q) {
+            const int a = q * r / k, e = (q + 1) * r / k;
+            f(lo + 64 * full + a, e - a, half != 0);
+        }
     }
-    if (r == 0 || b >= full + k) return false;
-    const int q = b - full;
-    const int lo = q * r / k, hi = (q + 1) * r / k;
-    t0 = 64 * full + lo;
-    tc = hi - lo;
-    return true;
 }
 
 // parts of the list (lc entries) of a block of tc targets: whole-wave blocks
@@ -331,45 +333,50 @@ __device__ inline int list_parts(const LeafWork &W, int tc, int lc) {
     return max(1, min(most, (int)(srcs / ((float)p2p_groups(tc) * W.part) + 0.5f)));
 }
 
-// per leaf: its blocks of 64 (Gaussian sums, float64 form), its near-field
-// blocks, the parts of blocks that take whole waves and of those that take
-// lane groups, and the float[6] outputs of the parts
-__global__ __launch_bounds__(TPB) void k_leaf_counts(const int *leaves, int nl, const int *count, const int *loff,
-                                                     const unsigned long long *tot, int64_t nent, int *out) {
+// per leaf: its blocks of 64 (Gaussian sums), its near-field blocks, the parts
+// by kind (whole waves, lane groups, the same for target points), and the
+// float[6] outputs of the parts
+constexpr int LEAF_SUMS = 7;
+
+__global__ __launch_bounds__(TPB) void k_leaf_counts(const int *leaves, int nl, const int *count, const int *nsrc,
+                                                     const int *loff, const unsigned long long *tot, int64_t nent,
+                                                     int *out) {
     const int i = blockIdx.x * TPB + threadIdx.x;
     if (i >= nl) return;
     const LeafWork W = leaf_work(tot, nent);
     const int cell = leaves[i];
     const int cnt = count[cell], lc = loff[cell + 1] - loff[cell];
-    const int k = remainder_blocks(max(1, cnt % 64));
-    int nb = 0, nw = 0, ng = 0, nu = 0, t0, tc;
-    for (; leaf_block(cnt, nb, k, t0, tc); ++nb) {
-        const int np = list_parts(W, tc, lc);
-        (tc > 32 ? nw : ng) += np;
-        nu += np * tc;
-    }
-    out[i] = (cnt + 63) / 64;
-    out[nl + i] = nb;
-    out[2 * nl + i] = nw;
-    out[3 * nl + i] = ng;
-    out[4 * nl + i] = nu;
+    int s[LEAF_SUMS] = {(cnt + 63) / 64, 0, 0, 0, 0, 0, 0};
+    leaf_blocks(cnt, nsrc ? nsrc[cell] : cnt, [&](int, int tc, bool pts) {
+        const int np = list_parts(W, tc, lc), kind = (pts ? 2 : 0) + (tc > 32 ? 0 : 1);
+        ++s[1];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s[2 + k] += k == kind ? np : 0;
+        s[6] += np * tc;
+    });
+#pragma unroll
+    for (int k = 0; k < LEAF_SUMS; ++k) out[k * nl + i] = s[k];
 }
 
-// the five totals and the pair count, straight to pinned host memory
+// the totals and the pair count, straight to pinned host memory
 __global__ void k_leaf_totals(const int *cnt, const int *off, int nl, const int *tot, int *out) {
-    for (int k = 0; k < 5; ++k) out[k] = off[(k + 1) * nl - 1] + cnt[(k + 1) * nl - 1] - off[k * nl];
-    out[5] = tot[0];
-    out[6] = tot[1];
+    for (int k = 0; k < LEAF_SUMS; ++k) out[k] = off[(k + 1) * nl - 1] + cnt[(k + 1) * nl - 1] - off[k * nl];
+    out[LEAF_SUMS] = tot[0];
+    out[LEAF_SUMS + 1] = tot[1];
 }
+
+struct ItemKinds {
+    int first[4];
+};
 
 // blocks of 64 (target start, targets, first entry, entries); near-field blocks
-// (target start, targets, first output, parts) and one work item per part
-// (target start, targets, first entry, entries) with its first output: items
-// [0, nw) take whole waves (more than 32 targets), the rest lane groups
+// (target start, targets, first output, parts and kind) and one work item per
+// part (target start, targets, first entry, entries) with its first output, the
+// items of kind k from K.first[k] on
 __global__ __launch_bounds__(TPB) void k_leaf_items(const int *leaves, int nl, const int *start, const int *count,
-                                                    const int *loff, const unsigned long long *tot, int64_t nent,
-                                                    const int *off, int nw, int4 *blocks, int4 *pblocks,
-                                                    int4 *items, int *item_out) {
+                                                    const int *nsrc, const int *loff, const unsigned long long *tot,
+                                                    int64_t nent, const int *off, ItemKinds K, int4 *blocks,
+                                                    int4 *pblocks, int4 *items, int *item_out) {
     // one wave per leaf: a leaf may have hundreds of parts
     const int i = blockIdx.x * (TPB / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (i >= nl) return;
@@ -379,22 +386,26 @@ __global__ __launch_bounds__(TPB) void k_leaf_items(const int *leaves, int nl, c
     const int l0 = loff[cell], lc = loff[cell + 1] - l0;
     for (int k = 64 * lane, b = off[i] + lane; k < cnt; k += 64 * 64, b += 64)
         blocks[b] = make_int4(s + k, min(64, cnt - k), l0, lc);
-    const int k = remainder_blocks(max(1, cnt % 64));
-    const int pb = off[nl + i] - off[nl];
-    int iw = off[2 * nl + i] - off[2 * nl], ig = nw + off[3 * nl + i] - off[3 * nl];
-    int u = off[4 * nl + i] - off[4 * nl], t0, tc;
-    for (int q = 0; leaf_block(cnt, q, k, t0, tc); ++q) {
-        const int np = list_parts(W, tc, lc);
-        if (lane == 0) pblocks[pb + q] = make_int4(s + t0, tc, u, np);
-        int &it = tc > 32 ? iw : ig;
+    int pb = off[nl + i] - off[nl], u = off[6 * nl + i] - off[6 * nl];
+    int it[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) it[k] = K.first[k] + off[(2 + k) * nl + i] - off[(2 + k) * nl];
+    leaf_blocks(cnt, nsrc ? nsrc[cell] : cnt, [&](int t0, int tc, bool pts) {
+        const int np = list_parts(W, tc, lc), kind = (pts ? 2 : 0) + (tc > 32 ? 0 : 1);
+        int i0 = it[0];
+#pragma unroll
+        for (int k = 1; k < 4; ++k) i0 = k == kind ? it[k] : i0;
+        if (lane == 0) pblocks[pb] = make_int4(s + t0, tc, u, np | (pts ? PBLOCK_VELOCITY : 0));
         for (int p = lane; p < np; p += 64) {
             const int e0 = (int)((int64_t)p * lc / np), e1 = (int)((int64_t)(p + 1) * lc / np);
-            items[it + p] = make_int4(s + t0, tc, l0 + e0, e1 - e0);
-            item_out[it + p] = u + p * tc;
+            items[i0 + p] = make_int4(s + t0, tc, l0 + e0, e1 - e0);
+            item_out[i0 + p] = u + p * tc;
         }
-        it += np;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) it[k] += k == kind ? np : 0;
+        ++pb;
         u += np * tc;
-    }
+    });
 }
 
 static int bits_for(int64_t v) {
@@ -532,7 +543,7 @@ void traverse_and_lists(Ctx &c) {
         E.geo = c.c_geo.as<float4>();
         E.kappa = c.var_sigma ? 1.0 : p2p_kappa(c.sigma_uniform);  // per-source cores: unscaled offsets
         E.len64 = c.prm.periodic ? c.prm.box_len : 0.0;
-        E.nsrc = c.n_src_part >= 0 && c.n_src_part < c.n ? c.c_nsrc.as<int>() : nullptr;
+        E.nsrc = c.parted ? c.c_nsrc.as<int>() : nullptr;
         E.sh = f32 ? c.p2p_sh.as<float4>() : nullptr;
         const int ngb = (int)cdiv(n_p2p, TPB);
         c.gpart.ensure(2 * sizeof(unsigned long long) * (size_t)ngb);
@@ -544,32 +555,41 @@ void traverse_and_lists(Ctx &c) {
     }
     // ---- P2P work: blocks of <= 64 targets, their lists in parts ----
     const int nl = c.nleaves;
-    c.c_tmp.ensure(sizeof(int) * (10 * (size_t)nl + 2));
-    int *cnt = c.c_tmp.as<int>(), *off = cnt + 5 * (size_t)nl;
+    c.c_tmp.ensure(sizeof(int) * (2 * LEAF_SUMS * (size_t)nl + 2));
+    int *cnt = c.c_tmp.as<int>(), *off = cnt + LEAF_SUMS * (size_t)nl;
+    const int *nsrc = c.parted ? c.c_nsrc.as<int>() : nullptr;
     const unsigned long long *tot = c.pairs64.as<unsigned long long>();
-    k_leaf_counts<<<cdiv(nl, TPB), TPB, 0, s>>>(c.leaves.as<int>(), nl, c.c_count.as<int>(), c.p2p_off.as<int>(), tot,
-                                                n_p2p, cnt);
+    k_leaf_counts<<<cdiv(nl, TPB), TPB, 0, s>>>(c.leaves.as<int>(), nl, c.c_count.as<int>(), nsrc, c.p2p_off.as<int>(),
+                                                tot, n_p2p, cnt);
     VFMM_LAUNCH_CHECK();
-    scan_excl_i32(c, cnt, off, 5 * (int64_t)nl);
+    scan_excl_i32(c, cnt, off, LEAF_SUMS * (int64_t)nl);
     k_leaf_totals<<<1, 1, 0, s>>>(cnt, off, nl, c.pairs64.as<int>(), pinned_ints(c));
     VFMM_LAUNCH_CHECK();
-    int h7[7];
-    sync_ints(c, 7, h7);
-    c.n_blocks = h7[0];
-    c.n_pblocks = h7[1];
-    c.n_items_w = h7[2];
-    c.n_items = h7[2] + h7[3];
-    c.n_partial = h7[4];
-    c.p2p_pairs = (int64_t)((unsigned long long)(uint32_t)h7[5] | ((unsigned long long)(uint32_t)h7[6] << 32));
-    if (c.n_pblocks < 0 || c.n_items < 0 || c.n_partial < 0)
+    int h[LEAF_SUMS + 2];
+    sync_ints(c, LEAF_SUMS + 2, h);
+    c.n_blocks = h[0];
+    c.n_pblocks = h[1];
+    ItemKinds K{};
+    int64_t items = 0;
+    for (int k = 0; k < 4; ++k) {
+        c.item0[k] = K.first[k] = (int)items;
+        items += h[2 + k];
+        if (h[2 + k] < 0) items = INT64_MAX / 2;
+    }
+    c.item0[4] = (int)items;
+    c.n_partial = h[6];
+    c.p2p_pairs = (int64_t)((unsigned long long)(uint32_t)h[LEAF_SUMS] |
+                            ((unsigned long long)(uint32_t)h[LEAF_SUMS + 1] << 32));
+    if (c.n_pblocks < 0 || items > INT32_MAX || c.n_partial < 0)
         throw Error{VFMM_ENOMEM, "near-field work items exceed 2^31 entries"};
     c.blocks.ensure(sizeof(int4) * (size_t)std::max(c.n_blocks, 1));
     c.pblocks.ensure(sizeof(int4) * (size_t)std::max(c.n_pblocks, 1));
-    c.items.ensure(sizeof(int4) * (size_t)std::max(c.n_items, 1));
-    c.item_out.ensure(sizeof(int) * (size_t)std::max(c.n_items, 1));
+    c.items.ensure(sizeof(int4) * (size_t)std::max<int64_t>(items, 1));
+    c.item_out.ensure(sizeof(int) * (size_t)std::max<int64_t>(items, 1));
     k_leaf_items<<<cdiv(nl, TPB / 64), TPB, 0, s>>>(c.leaves.as<int>(), nl, c.c_start.as<int>(), c.c_count.as<int>(),
-                                               c.p2p_off.as<int>(), tot, n_p2p, off, c.n_items_w, c.blocks.as<int4>(),
-                                               c.pblocks.as<int4>(), c.items.as<int4>(), c.item_out.as<int>());
+                                                    nsrc, c.p2p_off.as<int>(), tot, n_p2p, off, K,
+                                                    c.blocks.as<int4>(), c.pblocks.as<int4>(), c.items.as<int4>(),
+                                                    c.item_out.as<int>());
     VFMM_LAUNCH_CHECK();
 }
 

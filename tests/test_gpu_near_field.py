@@ -109,3 +109,31 @@ def test_float64_cutoff_at_its_branches(x):
     ref = oracle.direct(case)
     for got, want in ((u, ref["u"]), (da, ref["da_t"])):
         assert np.abs(got - want).max() <= 1.01 * 2.0 ** -24 * np.abs(want).max()
+
+
+# sources and points per leaf around a wave and a lane group; leaves without sources and without points
+@pytest.mark.parametrize("form", ["plain", "cores", "classical", "mixed", "periodic"])
+@pytest.mark.parametrize("ks,kt", [(1, 0), (1, 1), (0, 5), (31, 33), (33, 31), (64, 1), (1, 65), (40, 97)])
+def test_points_beside_particles(ks, kt, form):
+    """Points get the velocity alone, particles velocity and stretching, from one tree."""
+    import torch
+    import paper_1106_5273_amd as vf
+    opt = {"periodic": dict(periodic=1)}.get(form) or dict(FORMS.get(form, {}))
+    var = opt.pop("var", False)
+    case = _cells(ks, 11 + ks, var, 0.06) if ks else _cells(1, 5, var, 0.06)
+    if ks == 0:  # one particle in eight leaves, points in all
+        case = {k: (np.ascontiguousarray(v[:8]) if k != "n" else 8) for k, v in case.items()}
+    pts = _cells(kt, 17 + kt, False, 0.06) if kt else None
+    res = []
+    for prec in (opt.pop("precision", 0), 2):
+        t = vf.case_to_device(case)
+        T = [torch.from_numpy(pts[k]).cuda() for k in "xyz"] if kt else [torch.empty(0, device="cuda")] * 3
+        with vf.Context(p=8, ncrit=ks + kt, box_len=1.0, precision=prec, **opt) as ctx:
+            ctx.build_targets(t[0], t[1], t[2], t[6], *T)
+            out = ctx.evaluate_targets(t[3], t[4], t[5])
+            torch.cuda.synchronize()
+        res.append([v.cpu().numpy().astype(np.float64) for v in out])
+    for name, lo, hi in (("u", 0, 3), ("dalpha", 3, 6), ("points", 6, 9)):
+        got, ref = (np.stack(r[lo:hi], 1) for r in res)
+        if len(got):
+            check("%d+%d %s, %s" % (ks, kt, form, name), got, ref, 1e-5, 1e-3)
