@@ -29,6 +29,7 @@ struct Ctx {
     int n_pblocks = 0;                   // near-field blocks (a leaf's targets, cut to fill waves)
     int item0[5] = {};                   // P2P work items (parts of a block's list) by kind: whole waves, lane groups, and
                                          // the same for target points (velocity alone); item0[4] is their number
+    int n_long = 0;                      // blocks of more than LONG_PARTS parts (pblong)
     int n_partial = 0;                   // float[6] partial results of the items
     int64_t n_m2l = 0, p2p_pairs = 0;
     int img_B = 0, img_codes = 1;
@@ -69,6 +70,7 @@ struct Ctx {
     DevBuf p2p_off, p2p_ent;             // CSR by target cell: int offsets, int4 (start, count, img, variant)
     DevBuf p2p_sh;                       // float4 per P2P entry: scaled offset between the two leaf centres
     DevBuf blocks;                       // int4 (tgt start, tgt count, list off, list count)
+    DevBuf pblong;                       // int[n_long]
     DevBuf pblocks;                      // int4 per near-field block (tgt start, tgt count, first partial result, parts and kind)
     DevBuf items, item_out;              // int4 per part (tgt start, tgt count, first entry, entries), first partial result
     DevBuf pairs64;                      // int64 reduction scratch
@@ -207,6 +209,14 @@ void direct_f32(const Ctx &c, hipStream_t s, int64_t n, const Bounds &hb, float4
 // of target points that are no particles (velocity alone).
 constexpr int PBLOCK_VELOCITY = 1 << 30;
 constexpr int PBLOCK_PARTS = PBLOCK_VELOCITY - 1;
+// Blocks of more parts than this have them summed by a work-group into the first
+// (k_sum_parts) before the outputs are put together, where one wave takes a block.
+constexpr int LONG_PARTS = 32;
+// the partial results of a block that are left to add
+__host__ __device__ inline int parts_left(int w) {
+    const int np = w & PBLOCK_PARTS;
+    return np > LONG_PARTS ? 1 : np;
+}
 // Lane groups of a near-field block of tc targets: more than 32 targets take the
 // wave alone; fewer are held by several groups of tc lanes each (at most 16),
 // which take different sources.

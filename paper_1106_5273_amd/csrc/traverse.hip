@@ -334,9 +334,9 @@ __device__ inline int list_parts(const LeafWork &W, int tc, int lc) {
 }
 
 // per leaf: its blocks of 64 (Gaussian sums), its near-field blocks, the parts
-// by kind (whole waves, lane groups, the same for target points), and the
-// float[6] outputs of the parts
-constexpr int LEAF_SUMS = 7;
+// by kind (whole waves, lane groups, the same for target points), the float[6]
+// outputs of the parts, and the blocks of many parts
+constexpr int LEAF_SUMS = 8;
 
 __global__ __launch_bounds__(TPB) void k_leaf_counts(const int *leaves, int nl, const int *count, const int *nsrc,
                                                      const int *loff, const unsigned long long *tot, int64_t nent,
@@ -346,13 +346,14 @@ __global__ __launch_bounds__(TPB) void k_leaf_counts(const int *leaves, int nl, 
     const LeafWork W = leaf_work(tot, nent);
     const int cell = leaves[i];
     const int cnt = count[cell], lc = loff[cell + 1] - loff[cell];
-    int s[LEAF_SUMS] = {(cnt + 63) / 64, 0, 0, 0, 0, 0, 0};
+    int s[LEAF_SUMS] = {(cnt + 63) / 64, 0, 0, 0, 0, 0, 0, 0};
     leaf_blocks(cnt, nsrc ? nsrc[cell] : cnt, [&](int, int tc, bool pts) {
         const int np = list_parts(W, tc, lc), kind = (pts ? 2 : 0) + (tc > 32 ? 0 : 1);
         ++s[1];
 #pragma unroll
         for (int k = 0; k < 4; ++k) s[2 + k] += k == kind ? np : 0;
         s[6] += np * tc;
+        s[7] += np > LONG_PARTS;
     });
 #pragma unroll
     for (int k = 0; k < LEAF_SUMS; ++k) out[k * nl + i] = s[k];
@@ -376,7 +377,7 @@ struct ItemKinds {
 __global__ __launch_bounds__(TPB) void k_leaf_items(const int *leaves, int nl, const int *start, const int *count,
                                                     const int *nsrc, const int *loff, const unsigned long long *tot,
                                                     int64_t nent, const int *off, ItemKinds K, int4 *blocks,
-                                                    int4 *pblocks, int4 *items, int *item_out) {
+                                                    int4 *pblocks, int *pblong, int4 *items, int *item_out) {
     // one wave per leaf: a leaf may have hundreds of parts
     const int i = blockIdx.x * (TPB / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (i >= nl) return;
@@ -386,7 +387,7 @@ __global__ __launch_bounds__(TPB) void k_leaf_items(const int *leaves, int nl, c
     const int l0 = loff[cell], lc = loff[cell + 1] - l0;
     for (int k = 64 * lane, b = off[i] + lane; k < cnt; k += 64 * 64, b += 64)
         blocks[b] = make_int4(s + k, min(64, cnt - k), l0, lc);
-    int pb = off[nl + i] - off[nl], u = off[6 * nl + i] - off[6 * nl];
+    int pb = off[nl + i] - off[nl], u = off[6 * nl + i] - off[6 * nl], ib = off[7 * nl + i] - off[7 * nl];
     int it[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) it[k] = K.first[k] + off[(2 + k) * nl + i] - off[(2 + k) * nl];
@@ -395,7 +396,11 @@ __global__ __launch_bounds__(TPB) void k_leaf_items(const int *leaves, int nl, c
         int i0 = it[0];
 #pragma unroll
         for (int k = 1; k < 4; ++k) i0 = k == kind ? it[k] : i0;
-        if (lane == 0) pblocks[pb] = make_int4(s + t0, tc, u, np | (pts ? PBLOCK_VELOCITY : 0));
+        if (lane == 0) {
+            pblocks[pb] = make_int4(s + t0, tc, u, np | (pts ? PBLOCK_VELOCITY : 0));
+            if (np > LONG_PARTS) pblong[ib] = pb;
+        }
+        ib += np > LONG_PARTS;
         for (int p = lane; p < np; p += 64) {
             const int e0 = (int)((int64_t)p * lc / np), e1 = (int)((int64_t)(p + 1) * lc / np);
             items[i0 + p] = make_int4(s + t0, tc, l0 + e0, e1 - e0);
@@ -578,18 +583,20 @@ void traverse_and_lists(Ctx &c) {
     }
     c.item0[4] = (int)items;
     c.n_partial = h[6];
+    c.n_long = h[7];
     c.p2p_pairs = (int64_t)((unsigned long long)(uint32_t)h[LEAF_SUMS] |
                             ((unsigned long long)(uint32_t)h[LEAF_SUMS + 1] << 32));
     if (c.n_pblocks < 0 || items > INT32_MAX || c.n_partial < 0)
         throw Error{VFMM_ENOMEM, "near-field work items exceed 2^31 entries"};
     c.blocks.ensure(sizeof(int4) * (size_t)std::max(c.n_blocks, 1));
+    c.pblong.ensure(sizeof(int) * (size_t)std::max(c.n_long, 1));
     c.pblocks.ensure(sizeof(int4) * (size_t)std::max(c.n_pblocks, 1));
     c.items.ensure(sizeof(int4) * (size_t)std::max<int64_t>(items, 1));
     c.item_out.ensure(sizeof(int) * (size_t)std::max<int64_t>(items, 1));
     k_leaf_items<<<cdiv(nl, TPB / 64), TPB, 0, s>>>(c.leaves.as<int>(), nl, c.c_start.as<int>(), c.c_count.as<int>(),
                                                     nsrc, c.p2p_off.as<int>(), tot, n_p2p, off, K,
-                                                    c.blocks.as<int4>(), c.pblocks.as<int4>(), c.items.as<int4>(),
-                                                    c.item_out.as<int>());
+                                                    c.blocks.as<int4>(), c.pblocks.as<int4>(), c.pblong.as<int>(),
+                                                    c.items.as<int4>(), c.item_out.as<int>());
     VFMM_LAUNCH_CHECK();
 }
 

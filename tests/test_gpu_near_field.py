@@ -73,6 +73,25 @@ def test_lists_of_very_unequal_length(far):
     check("unequal lists dalpha", da, ref["da_t"], 1e-4, 1e-3)
 
 
+# one block (of 1 to 63 targets) whose list holds a whole cluster: its parts are summed by work-groups
+@pytest.mark.parametrize("precision", [0, 2])
+@pytest.mark.parametrize("far", [1, 5, 22, 33, 63])
+def test_blocks_of_many_parts(far, precision):
+    rng = np.random.default_rng(70 + far)
+    n = 30000 + far
+    x = np.concatenate([0.5 + 0.01 * rng.standard_normal((30000, 3)), 0.42 + 0.002 * rng.standard_normal((far, 3))])
+    a = rng.standard_normal((n, 3)) / n
+    f = lambda v: np.ascontiguousarray(v, np.float32)  # noqa: E731
+    case = dict(x=f(x[:, 0]), y=f(x[:, 1]), z=f(x[:, 2]), ax=f(a[:, 0]), ay=f(a[:, 1]), az=f(a[:, 2]),
+                sigma=f(np.full(n, 0.004)), n=n)
+    # theta 0.3: the lone block's near field holds most of the cluster
+    u, da = _run(case, p=10, ncrit=64, box_len=1.0, theta=0.3, precision=precision)
+    sub = np.concatenate([np.arange(0, 30000, 997), np.arange(30000, n)])
+    ref = oracle.direct(case, targets=sub)
+    check("many parts u", u[sub], ref["u"], 1e-4, 1e-3)
+    check("many parts dalpha", da[sub], ref["da_t"], 1e-4, 1e-3)
+
+
 # around a pass of 64 sources, a wave's and a work-group's share of them, and the two kernels' boundary
 @pytest.mark.parametrize("var", [False, True])
 @pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 63, 64, 65, 1023, 1024, 1025, 61439, 61440, 61441])
