@@ -446,82 +446,265 @@ __global__ __launch_bounds__(TPB) void k_problem_boxes(const int64_t *off, const
 
 // ---------------------------------------------------------------------------
 // Stable LSD radix sort of (uint64 key, uint32 value), 8-bit digits.
-// Ranking inside a tile uses wave ballots over the digit bits, so equal
-// digits keep their input order: the sort is stable and deterministic.
+// A wave takes consecutive items, 64 at a time, and ranks equal digits with
+// ballots over the digit's bits after a running count per digit of its own, so
+// equal digits keep their input order (stable, deterministic) and the waves meet
+// only once per pass, to add up their counts.
 // ---------------------------------------------------------------------------
-static constexpr int RS_ITEMS = 16;
-static constexpr int RS_TILE = TPB * RS_ITEMS;
-
-__global__ __launch_bounds__(TPB) void k_rs_hist(const uint64_t *keys, int64_t n, int shift, int *hist, int nblk) {
-    __shared__ int h[256];
-    h[threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * RS_TILE;
-    for (int i = 0; i < RS_ITEMS; ++i) {
-        const int64_t k = base + (int64_t)i * TPB + threadIdx.x;
-        if (k < n) atomicAdd(&h[(keys[k] >> shift) & 255], 1);
-    }
-    __syncthreads();
-    hist[threadIdx.x * nblk + blockIdx.x] = h[threadIdx.x];
+// orders a wave's own LDS accesses (no other wave touches the counts meanwhile)
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
-__global__ __launch_bounds__(TPB) void k_rs_scatter(const uint64_t *kin, const uint32_t *vin, uint64_t *kout,
-                                                    uint32_t *vout, int64_t n, int shift, const int *offs,
-                                                    int nblk) {
-    __shared__ int base_off[256];
-    __shared__ int wcnt[TPB / 64][256];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    base_off[tid] = offs[tid * nblk + blockIdx.x];
+// off[r] = items of this wave before item r (of this lane) with the same digit;
+// cnt[256]: the wave's counts per digit
+template <int ITEMS>
+__device__ __forceinline__ void rank_digits(const uint64_t *key, const bool *valid, int shift, int *cnt, int *off) {
+    const int lane = threadIdx.x & 63;
+    for (int j = lane; j < 256; j += 64) cnt[j] = 0;
+    wave_fence();
     const uint64_t lt = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
-    const int64_t base = (int64_t)blockIdx.x * RS_TILE;
-    for (int r = 0; r < RS_ITEMS; ++r) {
-        for (int j = 0; j < TPB / 64; ++j) wcnt[j][tid] = 0;
-        const int64_t k = base + (int64_t)r * TPB + tid;
-        const bool valid = k < n;
-        const uint64_t key = valid ? kin[k] : 0ull;
-        const uint32_t val = valid ? vin[k] : 0u;
-        const int d = (int)((key >> shift) & 255);
-        uint64_t m = __ballot(valid);
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const int d = (int)((key[r] >> shift) & 255);
+        uint64_t m = __ballot(valid[r]);
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
             const uint64_t mb = __ballot((d >> b) & 1);
             m &= ((d >> b) & 1) ? mb : ~mb;
         }
-        const int rank = __popcll(m & lt);
+        const int rank = __popcll(m & lt), prev = cnt[d];
+        wave_fence();
+        if (valid[r] && rank == 0) cnt[d] = prev + __popcll(m);
+        wave_fence();
+        off[r] = prev + rank;
+    }
+}
+
+// exclusive sum of v over the 256 threads t = 0 .. 255 (four whole waves; every
+// thread of the work-group calls it); sh: int[4]
+__device__ __forceinline__ int scan_256(int v, int t, int *sh) {
+    int incl = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(incl, o, 64);
+        if ((t & 63) >= o) incl += u;
+    }
+    if (t < 256 && (t & 63) == 63) sh[t >> 6] = incl;
+    __syncthreads();
+    int base = 0;
+    if (t < 256)
+        for (int w = 0; w < (t >> 6); ++w) base += sh[w];
+    return base + incl - v;
+}
+
+// Up to RS_GROUP items: all passes in one work-group, the items in registers and
+// exchanged through LDS.  A pass over several work-groups is a histogram, a scan
+// and a scatter, 3 launches of 2 to 11 us each for 3,000 items; here it is about 3 us.
+static constexpr int RS_GROUP = 8192;
+
+template <int ITEMS>
+__global__ __launch_bounds__(1024) void k_rs_group(uint64_t *key, uint32_t *val, int n, int passes) {
+    __shared__ uint64_t buf[1024 * ITEMS];
+    __shared__ int cnt[16][256];
+    __shared__ int sh[4];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int i0 = w * 64 * ITEMS + lane;
+    uint64_t k[ITEMS];
+    uint32_t v[ITEMS];
+    int off[ITEMS];
+    bool valid[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {  // padded with the largest key: stays behind the items
+        const int i = i0 + 64 * r;
+        valid[r] = true;
+        k[r] = i < n ? key[i] : ~0ull;
+        v[r] = i < n ? val[i] : 0u;
+    }
+    for (int p = 0; p < passes; ++p) {
+        const int shift = 8 * p;
+        rank_digits<ITEMS>(k, valid, shift, cnt[w], off);
         __syncthreads();
-        if (valid && rank == 0) wcnt[w][d] = __popcll(m);
-        __syncthreads();
-        if (valid) {
-            int pre = 0;
-            for (int j = 0; j < w; ++j) pre += wcnt[j][d];
-            const int pos = base_off[d] + pre + rank;
-            kout[pos] = key;
-            vout[pos] = val;
+        int c[16], tot = 0;
+        if (t < 256) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) c[j] = cnt[j][t];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) tot += c[j];
+        }
+        int base = scan_256(tot, t, sh);
+        if (t < 256) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                cnt[j][t] = base;
+                base += c[j];
+            }
         }
         __syncthreads();
-        int add = 0;
-        for (int j = 0; j < TPB / 64; ++j) add += wcnt[j][tid];
-        base_off[tid] += add;
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            off[r] += cnt[w][(int)((k[r] >> shift) & 255)];
+            buf[off[r]] = k[r];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) k[r] = buf[i0 + 64 * r];
+        __syncthreads();
+        uint32_t *vb = reinterpret_cast<uint32_t *>(buf);
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) vb[off[r]] = v[r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) v[r] = vb[i0 + 64 * r];
         __syncthreads();
     }
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const int i = i0 + 64 * r;
+        if (i < n) {
+            key[i] = k[r];
+            val[i] = v[r];
+        }
+    }
+}
+
+// Larger sorts: tiles of 256 * ITEMS items.  Up to RS_ROWS tiles the scatter sums
+// the histograms (one row of 256 per tile) itself; more are scanned digit by digit
+// in launches between the two (SCANNED).  The tile's items are put in order in LDS
+// first, so that a digit's run leaves in consecutive addresses.
+static constexpr int RS_ROWS = 64;
+
+template <bool SCANNED>
+__global__ __launch_bounds__(TPB) void k_rs_hist(const uint64_t *keys, int64_t n, int shift, int items, int *hist) {
+    __shared__ int h[256];
+    h[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * items * TPB;
+    for (int i = 0; i < items; ++i) {
+        const int64_t k = base + (int64_t)i * TPB + threadIdx.x;
+        if (k < n) atomicAdd(&h[(keys[k] >> shift) & 255], 1);
+    }
+    __syncthreads();
+    hist[SCANNED ? (size_t)threadIdx.x * gridDim.x + blockIdx.x : (size_t)blockIdx.x * 256 + threadIdx.x] =
+        h[threadIdx.x];
+}
+
+template <int ITEMS, bool SCANNED>
+__global__ __launch_bounds__(TPB) void k_rs_scatter(const uint64_t *kin, const uint32_t *vin, uint64_t *kout,
+                                                    uint32_t *vout, int64_t n, int shift, const int *offs) {
+    __shared__ uint64_t lk[TPB * ITEMS];
+    __shared__ uint32_t lv[TPB * ITEMS];
+    __shared__ int cnt[TPB / 64][256];
+    __shared__ int dst[256];
+    __shared__ int sh[2][4];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int64_t base = (int64_t)blockIdx.x * (TPB * ITEMS);
+    uint64_t k[ITEMS];
+    uint32_t v[ITEMS];
+    int off[ITEMS];
+    bool valid[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const int64_t i = base + w * 64 * ITEMS + 64 * r + lane;
+        valid[r] = i < n;
+        k[r] = valid[r] ? kin[i] : 0ull;
+        v[r] = valid[r] ? vin[i] : 0u;
+    }
+    int gbase;  // output position of the tile's first item of digit t
+    if (SCANNED) {
+        gbase = offs[(size_t)t * gridDim.x + blockIdx.x];
+    } else {
+        int before = 0, total = 0;
+        for (int b0 = 0; b0 < (int)gridDim.x; b0 += 16) {
+            int h[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) h[j] = b0 + j < (int)gridDim.x ? offs[(b0 + j) * 256 + t] : 0;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                total += h[j];
+                before += b0 + j < (int)blockIdx.x ? h[j] : 0;
+            }
+        }
+        gbase = scan_256(total, t, sh[0]) + before;
+    }
+    rank_digits<ITEMS>(k, valid, shift, cnt[w], off);
+    __syncthreads();
+    int c[TPB / 64], tot = 0;
+#pragma unroll
+    for (int j = 0; j < TPB / 64; ++j) {
+        c[j] = cnt[j][t];
+        tot += c[j];
+    }
+    int lbase = scan_256(tot, t, sh[1]);
+    dst[t] = gbase - lbase;
+#pragma unroll
+    for (int j = 0; j < TPB / 64; ++j) {
+        cnt[j][t] = lbase;
+        lbase += c[j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        if (!valid[r]) continue;
+        const int o = off[r] + cnt[w][(int)((k[r] >> shift) & 255)];
+        lk[o] = k[r];
+        lv[o] = v[r];
+    }
+    __syncthreads();
+    const int m = (int)min((int64_t)(TPB * ITEMS), n - base);
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const int i = r * TPB + t;
+        if (i >= m) continue;
+        const uint64_t key = lk[i];
+        const int o = dst[(int)((key >> shift) & 255)] + i;
+        kout[o] = key;
+        vout[o] = lv[i];
+    }
+}
+
+template <int ITEMS, bool SCANNED>
+static void rs_pass(Ctx &c, const DevBuf &kA, const DevBuf &vA, const DevBuf &kB, const DevBuf &vB, int64_t n,
+                    int shift) {
+    const int nblk = (int)cdiv(n, TPB * ITEMS);
+    int *hist = c.hist.as<int>();
+    k_rs_hist<SCANNED><<<nblk, TPB, 0, c.stream>>>(kA.as<uint64_t>(), n, shift, ITEMS, hist);
+    VFMM_LAUNCH_CHECK();
+    if (SCANNED) scan_excl_i32(c, hist, hist, 256LL * nblk);
+    k_rs_scatter<ITEMS, SCANNED><<<nblk, TPB, 0, c.stream>>>(kA.as<uint64_t>(), vA.as<uint32_t>(), kB.as<uint64_t>(),
+                                                             vB.as<uint32_t>(), n, shift, hist);
+    VFMM_LAUNCH_CHECK();
 }
 
 // Sorts keyA/valA (n items, significant bits [0, nbits)); result ends in keyA/valA.
 static void radix_sort(Ctx &c, DevBuf &kA, DevBuf &vA, DevBuf &kB, DevBuf &vB, int64_t n, int nbits) {
     if (n <= 1) return;
-    const int nblk = (int)cdiv(n, RS_TILE);
-    c.hist.ensure(sizeof(int) * 256 * (size_t)nblk);
+    const int passes = (nbits + 7) / 8;
+    if (n <= RS_GROUP) {
+        uint64_t *k = kA.as<uint64_t>();
+        uint32_t *v = vA.as<uint32_t>();
+        if (n <= 1024)
+            k_rs_group<1><<<1, 1024, 0, c.stream>>>(k, v, (int)n, passes);
+        else if (n <= 4096)
+            k_rs_group<4><<<1, 1024, 0, c.stream>>>(k, v, (int)n, passes);
+        else
+            k_rs_group<8><<<1, 1024, 0, c.stream>>>(k, v, (int)n, passes);
+        VFMM_LAUNCH_CHECK();
+        return;
+    }
     kB.ensure(sizeof(uint64_t) * n);
     vB.ensure(sizeof(uint32_t) * n);
-    const int passes = (nbits + 7) / 8;
+    c.hist.ensure(sizeof(int) * 256 * (size_t)std::max<int64_t>(RS_ROWS, cdiv(n, 16 * TPB)));
     for (int p = 0; p < passes; ++p) {
-        const int shift = 8 * p;
-        k_rs_hist<<<nblk, TPB, 0, c.stream>>>(kA.as<uint64_t>(), n, shift, c.hist.as<int>(), nblk);
-        VFMM_LAUNCH_CHECK();
-        scan_excl_i32(c, c.hist.as<int>(), c.hist.as<int>(), 256LL * nblk);
-        k_rs_scatter<<<nblk, TPB, 0, c.stream>>>(kA.as<uint64_t>(), vA.as<uint32_t>(), kB.as<uint64_t>(),
-                                                 vB.as<uint32_t>(), n, shift, c.hist.as<int>(), nblk);
-        VFMM_LAUNCH_CHECK();
+        if (n <= RS_ROWS * 4 * TPB)
+            rs_pass<4, false>(c, kA, vA, kB, vB, n, 8 * p);
+        else if (n <= RS_ROWS * 8 * TPB)
+            rs_pass<8, false>(c, kA, vA, kB, vB, n, 8 * p);
+        else if (n <= RS_ROWS * 16 * TPB)
+            rs_pass<16, false>(c, kA, vA, kB, vB, n, 8 * p);
+        else
+            rs_pass<16, true>(c, kA, vA, kB, vB, n, 8 * p);
         std::swap(kA, kB);
         std::swap(vA, vB);
     }
@@ -710,12 +893,17 @@ __global__ __launch_bounds__(TPB) void k_make_children(int c0, int c1, int lvl, 
 
 // Centres from the key prefix of the first particle; leaves get their tight
 // radius (max distance of a particle from the cube centre) and bounding box.
+// Sixteen lanes per cell: one thread per leaf reads its records one after
+// another, 32 bytes apart (140 us for 64 rings of 1,000 particles each with 64
+// per leaf, 24 us for 3,000 particles; now 12 and 5).
+static constexpr int GEO_LANES = 16;
+
 __global__ __launch_bounds__(TPB) void k_leaf_geometry(int ncell, const RootBox *boxes, int KL, const int *start,
                                                        const int *count,
                                                        const int *level, const int *nchild, const uint64_t *keys,
                                                        const float4 *rec, float4 *geo, float *rad, float4 *blo,
                                                        float4 *bhi) {
-    const int cell = blockIdx.x * TPB + threadIdx.x;
+    const int cell = blockIdx.x * (TPB / GEO_LANES) + threadIdx.x / GEO_LANES, sub = threadIdx.x % GEO_LANES;
     if (cell >= ncell) return;
     const int lvl = level[cell];
     const int s = start[cell];
@@ -735,24 +923,35 @@ __global__ __launch_bounds__(TPB) void k_leaf_geometry(int ncell, const RootBox 
     g.y = (float)(box.lo[1] + (q[1] + 0.5) * size);
     g.z = (float)(box.lo[2] + (q[2] + 0.5) * size);
     g.w = (float)size;
-    geo[cell] = g;
-    if (nchild[cell] == 0) {
-        float r2 = 0.f;
-        float4 lo = make_float4(3.4e38f, 3.4e38f, 3.4e38f, 0.f), hi = make_float4(-3.4e38f, -3.4e38f, -3.4e38f, 0.f);
-        const int cnt = count[cell];
-        for (int i = s; i < s + cnt; ++i) {
-            const float4 p = rec[2 * i];
-            const float dx = p.x - g.x, dy = p.y - g.y, dz = p.z - g.z;
-            r2 = fmaxf(r2, dx * dx + dy * dy + dz * dz);
-            lo.x = fminf(lo.x, p.x); lo.y = fminf(lo.y, p.y); lo.z = fminf(lo.z, p.z);
-            hi.x = fmaxf(hi.x, p.x); hi.y = fmaxf(hi.y, p.y); hi.z = fmaxf(hi.z, p.z);
-            hi.w = fmaxf(hi.w, p.w);  // the cell's largest core
-        }
-        // round the radius up by a few ulps so float rounding never makes it short
-        rad[cell] = sqrtf(r2) * (1.0f + 4.0e-7f);
-        blo[cell] = lo;
-        bhi[cell] = hi;
+    if (sub == 0) geo[cell] = g;
+    if (nchild[cell] != 0) return;
+    float r2 = 0.f;
+    float4 lo = make_float4(3.4e38f, 3.4e38f, 3.4e38f, 0.f), hi = make_float4(-3.4e38f, -3.4e38f, -3.4e38f, 0.f);
+    const int end = s + count[cell];
+    for (int i = s + sub; i < end; i += GEO_LANES) {
+        const float4 p = rec[2 * (size_t)i];
+        const float dx = p.x - g.x, dy = p.y - g.y, dz = p.z - g.z;
+        r2 = fmaxf(r2, dx * dx + dy * dy + dz * dz);
+        lo.x = fminf(lo.x, p.x); lo.y = fminf(lo.y, p.y); lo.z = fminf(lo.z, p.z);
+        hi.x = fmaxf(hi.x, p.x); hi.y = fmaxf(hi.y, p.y); hi.z = fmaxf(hi.z, p.z);
+        hi.w = fmaxf(hi.w, p.w);  // the cell's largest core
     }
+#pragma unroll
+    for (int o = GEO_LANES / 2; o > 0; o >>= 1) {
+        r2 = fmaxf(r2, __shfl_xor(r2, o, GEO_LANES));
+        lo.x = fminf(lo.x, __shfl_xor(lo.x, o, GEO_LANES));
+        lo.y = fminf(lo.y, __shfl_xor(lo.y, o, GEO_LANES));
+        lo.z = fminf(lo.z, __shfl_xor(lo.z, o, GEO_LANES));
+        hi.x = fmaxf(hi.x, __shfl_xor(hi.x, o, GEO_LANES));
+        hi.y = fmaxf(hi.y, __shfl_xor(hi.y, o, GEO_LANES));
+        hi.z = fmaxf(hi.z, __shfl_xor(hi.z, o, GEO_LANES));
+        hi.w = fmaxf(hi.w, __shfl_xor(hi.w, o, GEO_LANES));
+    }
+    if (sub != 0) return;
+    // round the radius up by a few ulps so float rounding never makes it short
+    rad[cell] = sqrtf(r2) * (1.0f + 4.0e-7f);
+    blo[cell] = lo;
+    bhi[cell] = hi;
 }
 
 // Internal cells, one level at a time bottom-up: radius bounded by the
@@ -897,7 +1096,7 @@ void build_tree(Ctx &c, int64_t n, const float *x, const float *y, const float *
     c.c_rad.ensure(sizeof(float) * nc);
     c.c_lo.ensure(sizeof(float4) * nc);
     c.c_hi.ensure(sizeof(float4) * nc);
-    k_leaf_geometry<<<cdiv(nc, TPB), TPB, 0, s>>>(nc, c.pbox.as<RootBox>(), KL, c.c_start.as<int>(), c.c_count.as<int>(),
+    k_leaf_geometry<<<cdiv(nc * (int64_t)GEO_LANES, TPB), TPB, 0, s>>>(nc, c.pbox.as<RootBox>(), KL, c.c_start.as<int>(), c.c_count.as<int>(),
                                                    c.c_level.as<int>(), c.c_nchild.as<int>(), keys,
                                                    c.rec.as<float4>(), c.c_geo.as<float4>(), c.c_rad.as<float>(),
                                                    c.c_lo.as<float4>(), c.c_hi.as<float4>());
