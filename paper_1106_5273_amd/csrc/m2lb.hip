@@ -33,6 +33,9 @@ static constexpr int TPB = 256;
 static constexpr int ITEM_GROUPS = 24;
 static constexpr int TABLE_KEY_BITS = 24;  // offset keys up to this width are numbered through a direct table
 static constexpr size_t MAX_TABLE_BYTES = size_t(8) << 30;  // operator table cap (else the per-pair kernel)
+// translations below which the per-pair M2L runs at once: its 6 ns for each (p = 10)
+// stay below the 0.2 ms of the batched plan's 25 launches and 6 waits
+static constexpr int MIN_BATCHED = 8192;
 static constexpr int MIN_GROUP_FILL = 8;  // translations per (block, key) group below which per-pair M2L runs
 
 void sort_pairs_u64(Ctx &c, DevBuf &kA, DevBuf &vA, DevBuf &kB, DevBuf &vB, int64_t n, int nbits);
@@ -930,6 +933,7 @@ static void m2lb_plan_p(Ctx &c) {
     const int64_t n = c.n_m2l;
     c.m2lb_ok = false;
     if (n == 0) return;
+    if (c.prm.m2l_mode == 0 && n < MIN_BATCHED) return;
     // ---- offsets and ranges ----
     c.mb_eq.ensure(sizeof(int4) * n);
     c.pairs64.ensure(64);
@@ -988,6 +992,8 @@ static void m2lb_plan_p(Ctx &c) {
                                                 c.mb_kid.as<int>(), c.mb_ukey.as<uint64_t>());
         VFMM_LAUNCH_CHECK();
     }
+    // every key has a group: the rule on the groups' fill below fails already
+    if (c.prm.m2l_mode == 0 && n < (int64_t)MIN_GROUP_FILL * nkeys) return;
     c.lkey.ensure(sizeof(uint64_t) * n);
     c.lval.ensure(sizeof(uint32_t) * n);
     int *flag = c.mb_flag.as<int>(), *pos = c.mb_pos.as<int>();
