@@ -52,15 +52,15 @@ __device__ inline int interact(const TravArgs &A, int a, int b, int img) {
     float sx, sy, sz;
     img_shift(img, A.B, A.len, sx, sy, sz);
     const float4 ga = A.geo[a], gb = A.geo[b];
+    const float ra = A.rad[a], rb = A.rad[b];
+    const int na = A.nchild[a], nb = A.nchild[b];
     const float dx = ga.x - gb.x - sx, dy = ga.y - gb.y - sy, dz = ga.z - gb.z - sz;
     const float D = sqrtf(dx * dx + dy * dy + dz * dz);
-    const float ra = A.rad[a], rb = A.rad[b];
     // the MAC and the core gap, both failing on (near-)ties; with per-source
     // cores the gap is measured in the largest core of the source cell b
     const float gap = A.hi ? A.sgap * A.hi[b].w : A.gap;
-    if (ra + rb < A.theta * D * (1.0f - TIE_TOL) && D - ra - rb >= gap + TIE_TOL * D) return 0;
-    if (A.nchild[a] == 0 && A.nchild[b] == 0) return 1;
-    return 2;
+    const bool far = ra + rb < A.theta * D * (1.0f - TIE_TOL) && D - ra - rb >= gap + TIE_TOL * D;
+    return far ? 0 : na == 0 && nb == 0 ? 1 : 2;
 }
 
 // Children pairs of a frontier pair (Algorithm 1): split A when its radius is
@@ -75,26 +75,48 @@ __device__ inline void split_pair(const TravArgs &A, int a, int b, bool &splitA,
     cnt = A.nchild[s];
 }
 
-__global__ __launch_bounds__(TPB) void k_trav_count(TravArgs A, const int4 *fr, int nf, int split, int *cnt) {
-    const int i = blockIdx.x * TPB + threadIdx.x;
-    if (i >= nf) return;
-    const int4 pr = fr[i];
-    int c[3] = {0, 0, 0};
-    if (!split) {
-        c[interact(A, pr.x, pr.y, pr.z)]++;
-    } else {
-        bool sa;
-        int first, n;
-        split_pair(A, pr.x, pr.y, sa, first, n);
-        for (int k = 0; k < n; ++k) {
-            const int a = sa ? first + k : pr.x;
-            const int b = sa ? pr.y : first + k;
-            c[interact(A, a, b, pr.z)]++;
+// Eight lanes per frontier pair, one per child pair: lane o's cells and decision
+// (3: no such child pair), and its lanes' ballots.  With a thread per frontier
+// pair the child pairs' loads followed one another and their entries were
+// written 16 bytes at a time, 128 bytes apart.
+struct ChildPair {
+    int a, b, img, kind;
+    int sh;                 // first lane of the frontier pair
+    unsigned below;         // mask of the lanes before this one among the eight
+    unsigned bal[3];        // per kind: which of the eight lanes
+};
+
+__device__ inline ChildPair child_pair(const TravArgs &A, const int4 *fr, int nf, int split, int i, int o) {
+    ChildPair c;
+    c.kind = 3;
+    c.a = c.b = c.img = 0;
+    if (i < nf) {
+        const int4 pr = fr[i];
+        c.a = pr.x;
+        c.b = pr.y;
+        c.img = pr.z;
+        int n = 1;
+        if (split) {
+            bool sa;
+            int first;
+            split_pair(A, pr.x, pr.y, sa, first, n);
+            if (sa) c.a = first + o;
+            else c.b = first + o;
         }
+        if (o < n) c.kind = interact(A, c.a, c.b, c.img);
     }
-    cnt[i] = c[0];
-    cnt[nf + i] = c[1];
-    cnt[2 * nf + i] = c[2];
+    c.sh = (threadIdx.x & 63) & ~7;
+    c.below = (1u << o) - 1u;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) c.bal[k] = (unsigned)(__ballot(c.kind == k) >> c.sh) & 0xffu;
+    return c;
+}
+
+__global__ __launch_bounds__(TPB) void k_trav_count(TravArgs A, const int4 *fr, int nf, int split, int *cnt) {
+    const unsigned g = blockIdx.x * TPB + threadIdx.x;  // below 2^31 + 2^8: frontiers hold at most 2^28 pairs
+    const int i = (int)(g >> 3), o = (int)(g & 7u);
+    const ChildPair c = child_pair(A, fr, nf, split, i, o);
+    if (i < nf && o < 3) cnt[o * nf + i] = __popc(o == 0 ? c.bal[0] : o == 1 ? c.bal[1] : c.bal[2]);
 }
 
 __global__ void k_trav_totals(const int *cnt, const int *off, int nf, int *tot) {
@@ -103,24 +125,123 @@ __global__ void k_trav_totals(const int *cnt, const int *off, int nf, int *tot) 
 
 __global__ __launch_bounds__(TPB) void k_trav_write(TravArgs A, const int4 *fr, int nf, int split, const int *off,
                                                     int4 *m2l, int m2l_base, int4 *p2p, int p2p_base, int4 *next) {
-    const int i = blockIdx.x * TPB + threadIdx.x;
-    if (i >= nf) return;
-    const int4 pr = fr[i];
-    int o[3] = {off[i] - off[0] + m2l_base, off[nf + i] - off[nf] + p2p_base, off[2 * nf + i] - off[2 * nf]};
-    auto emit = [&](int a, int b) {
-        const int k = interact(A, a, b, pr.z);
-        const int4 e = make_int4(a, b, pr.z, 0);
-        if (k == 0) m2l[o[0]++] = e;
-        else if (k == 1) p2p[o[1]++] = e;
-        else next[o[2]++] = e;
-    };
-    if (!split) {
-        emit(pr.x, pr.y);
-    } else {
-        bool sa;
-        int first, n;
-        split_pair(A, pr.x, pr.y, sa, first, n);
-        for (int k = 0; k < n; ++k) emit(sa ? first + k : pr.x, sa ? pr.y : first + k);
+    const unsigned g = blockIdx.x * TPB + threadIdx.x;  // below 2^31 + 2^8: frontiers hold at most 2^28 pairs
+    const int i = (int)(g >> 3), o = (int)(g & 7u);
+    const ChildPair c = child_pair(A, fr, nf, split, i, o);
+    if (c.kind == 3) return;
+    const int4 e = make_int4(c.a, c.b, c.img, 0);
+    if (c.kind == 0)
+        m2l[m2l_base + off[i] - off[0] + __popc(c.bal[0] & c.below)] = e;
+    else if (c.kind == 1)
+        p2p[p2p_base + off[nf + i] - off[nf] + __popc(c.bal[1] & c.below)] = e;
+    else
+        next[off[2 * nf + i] - off[2 * nf] + __popc(c.bal[2] & c.below)] = e;
+}
+
+// The first generations in one work-group, while the frontier holds at most
+// TRAV_GROUP pairs: a generation is otherwise a count, one or two scan launches,
+// the totals, a wait and a write, 35 us however few its pairs are.  1,024 pairs at
+// a time, a thread each; the entries' order is the same.
+static constexpr int TRAV_GROUP = 4096;
+
+struct TravGroupArgs {
+    int4 *fr[2];  // frontiers, of 8 TRAV_GROUP pairs
+    int4 *m2l, *p2p;
+    int m2l_cap, p2p_cap;
+    int nroot, ncode;
+    int *host;  // pinned: pairs left, their frontier, M2L and P2P entries, whether the pairs are to be split
+};
+
+__global__ __launch_bounds__(1024) void k_trav_group(TravArgs A, TravGroupArgs G) {
+    __shared__ unsigned long long wsum[16];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    int nf = G.nroot * G.ncode, cur = 0, split = 0, nm = 0, np = 0;
+    for (int i = t; i < nf; i += 1024) G.fr[0][i] = make_int4(i / G.ncode, i / G.ncode, i % G.ncode, 0);
+    __syncthreads();
+    while (nf > 0 && nf <= TRAV_GROUP) {
+        const int4 *fr = G.fr[cur];
+        int4 *nx = G.fr[cur ^ 1];
+        int gm = nm, gp = np, gn = 0;
+        bool fits = true;
+        for (int base = 0; base < nf; base += 1024) {
+            const int i = base + t;
+            int4 pr = make_int4(0, 0, 0, 0);
+            int first = 0, n = 0;
+            bool sa = false;
+            if (i < nf) {
+                pr = fr[i];
+                n = 1;
+                if (split) split_pair(A, pr.x, pr.y, sa, first, n);
+            }
+            auto cell_a = [&](int k) { return split && sa ? first + k : pr.x; };
+            auto cell_b = [&](int k) { return split && !sa ? first + k : pr.y; };
+            unsigned kinds = 0xffffu;  // two bits per child pair, 3: none
+            if (i < nf) {
+                kinds = 0;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {  // all loads in flight together
+                    const int kk = min(k, n - 1);
+                    const int v = interact(A, cell_a(kk), cell_b(kk), pr.z);
+                    kinds |= (unsigned)(k < n ? v : 3) << (2 * k);
+                }
+            }
+            // counts of the three kinds in 21-bit fields
+            unsigned long long mine = 0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const unsigned v = (kinds >> (2 * k)) & 3u;
+                if (v < 3u) mine += 1ull << (21 * v);
+            }
+            unsigned long long incl = mine;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const unsigned long long u = __shfl_up(incl, o, 64);
+                if (lane >= o) incl += u;
+            }
+            if (lane == 63) wsum[w] = incl;
+            __syncthreads();
+            unsigned long long pre = incl - mine, tot = 0;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const unsigned long long v = wsum[j];
+                pre += j < w ? v : 0;
+                tot += v;
+            }
+            __syncthreads();
+            const int f21 = (1 << 21) - 1;
+            const int tm = (int)(tot & f21), tp = (int)((tot >> 21) & f21), tn = (int)(tot >> 42);
+            if (gm + tm > G.m2l_cap || gp + tp > G.p2p_cap) {  // the caller grows the lists and repeats the generation
+                fits = false;
+                break;
+            }
+            int om = gm + (int)(pre & f21), op = gp + (int)((pre >> 21) & f21), on = gn + (int)(pre >> 42);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const unsigned v = (kinds >> (2 * k)) & 3u;
+                if (v == 3u) continue;
+                const int4 e = make_int4(cell_a(k), cell_b(k), pr.z, 0);
+                if (v == 0u) G.m2l[om++] = e;
+                else if (v == 1u) G.p2p[op++] = e;
+                else nx[on++] = e;
+            }
+            gm += tm;
+            gp += tp;
+            gn += tn;
+        }
+        if (!fits) break;
+        __syncthreads();  // the new frontier is read by other threads
+        nm = gm;
+        np = gp;
+        nf = gn;
+        cur ^= 1;
+        split = 1;
+    }
+    if (t == 0) {
+        G.host[0] = nf;
+        G.host[1] = cur;
+        G.host[2] = nm;
+        G.host[3] = np;
+        G.host[4] = split;
     }
 }
 
@@ -482,20 +603,43 @@ void traverse_and_lists(Ctx &c) {
     const int ncode = c.img_codes;
     c.images_traversed = ncode;
 
-    int nf = ncode * c.nprob;
-    c.frA.ensure(sizeof(int4) * (size_t)nf);
-    k_trav_init<<<cdiv(nf, TPB), TPB, 0, s>>>(c.frA.as<int4>(), c.nprob, ncode);
-    VFMM_LAUNCH_CHECK();
+    int nf = ncode * c.nprob, split = 0;
     int64_t n_m2l = 0, n_p2p = 0;
-    c.m2l_raw.ensure(sizeof(int4) * 1024);
-    c.p2p_raw.ensure(sizeof(int4) * 1024);
-    int split = 0;
+    c.m2l_raw.ensure(sizeof(int4) * (1 << 16));
+    c.p2p_raw.ensure(sizeof(int4) * (1 << 16));
+    if (nf <= TRAV_GROUP) {
+        c.frA.ensure(sizeof(int4) * 8 * TRAV_GROUP);
+        c.frB.ensure(sizeof(int4) * 8 * TRAV_GROUP);
+        TravGroupArgs G{};
+        G.fr[0] = c.frA.as<int4>();
+        G.fr[1] = c.frB.as<int4>();
+        G.m2l = c.m2l_raw.as<int4>();
+        G.p2p = c.p2p_raw.as<int4>();
+        G.m2l_cap = (int)std::min<size_t>(c.m2l_raw.cap / sizeof(int4), INT32_MAX / 2);
+        G.p2p_cap = (int)std::min<size_t>(c.p2p_raw.cap / sizeof(int4), INT32_MAX / 2);
+        G.nroot = c.nprob;
+        G.ncode = ncode;
+        G.host = pinned_ints(c);
+        k_trav_group<<<1, 1024, 0, s>>>(A, G);
+        VFMM_LAUNCH_CHECK();
+        int h[5];
+        sync_ints(c, 5, h);
+        nf = h[0];
+        if (h[1]) std::swap(c.frA, c.frB);
+        n_m2l = h[2];
+        n_p2p = h[3];
+        split = h[4];
+    } else {
+        c.frA.ensure(sizeof(int4) * (size_t)nf);
+        k_trav_init<<<cdiv(nf, TPB), TPB, 0, s>>>(c.frA.as<int4>(), c.nprob, ncode);
+        VFMM_LAUNCH_CHECK();
+    }
     int h_tot[4];
     while (nf > 0) {
         c.tcnt.ensure(sizeof(int) * 6 * (size_t)nf + 64);
         int *cnt = c.tcnt.as<int>();
         int *off = cnt + 3 * (size_t)nf;
-        k_trav_count<<<cdiv(nf, TPB), TPB, 0, s>>>(A, c.frA.as<int4>(), nf, split, cnt);
+        k_trav_count<<<cdiv(8 * (int64_t)nf, TPB), TPB, 0, s>>>(A, c.frA.as<int4>(), nf, split, cnt);
         VFMM_LAUNCH_CHECK();
         scan_excl_i32(c, cnt, off, 3LL * nf);
         k_trav_totals<<<1, 1, 0, s>>>(cnt, off, nf, pinned_ints(c));  // straight to pinned host memory
@@ -510,7 +654,7 @@ void traverse_and_lists(Ctx &c) {
         grow_keep4(c, c.m2l_raw, sizeof(int4) * (size_t)(n_m2l + tm), sizeof(int4) * (size_t)n_m2l);
         grow_keep4(c, c.p2p_raw, sizeof(int4) * (size_t)(n_p2p + tp), sizeof(int4) * (size_t)n_p2p);
         c.frB.ensure(sizeof(int4) * (size_t)std::max(tn, 1));
-        k_trav_write<<<cdiv(nf, TPB), TPB, 0, s>>>(A, c.frA.as<int4>(), nf, split, off, c.m2l_raw.as<int4>(),
+        k_trav_write<<<cdiv(8 * (int64_t)nf, TPB), TPB, 0, s>>>(A, c.frA.as<int4>(), nf, split, off, c.m2l_raw.as<int4>(),
                                                     (int)n_m2l, c.p2p_raw.as<int4>(), (int)n_p2p,
                                                     c.frB.as<int4>());
         VFMM_LAUNCH_CHECK();

@@ -4,6 +4,7 @@
 // key; at most 21 levels).
 #include "ctx.h"
 
+#include <algorithm>
 #include <cstring>
 
 namespace vfmm {
@@ -891,6 +892,129 @@ __global__ __launch_bounds__(TPB) void k_make_children(int c0, int c1, int lvl, 
     }
 }
 
+// The top levels in one work-group, while a level has at most TREE_GROUP cells:
+// per level one launch instead of a count, a scan, a wait for the total and a
+// write (25 us), and for a small tree the leaf list too (3,000 particles: 16
+// launches and 4 waits, 110 us, become one launch and one wait).  Each of the
+// 1,024 threads takes an octant of a cell, 128 cells at a time; a child's place is
+// the number of non-empty octants before it.
+static constexpr int TREE_GROUP = 512;
+
+struct TreeGroupArgs {
+    const uint64_t *keys;
+    const int64_t *off;  // batched problems: first particle of each (else null)
+    int nroot, n, ncrit, KL;
+    int cap;  // cells that the arrays hold
+    int *start, *count, *parent, *child, *nchild, *level, *leaves;
+    Bounds *res;
+    // pinned: [0] whether the tree is complete, [1] level offsets, [2] leaves,
+    // [3] leaves over ncrit, [4 ...] the offsets
+    int *host;
+};
+
+__global__ __launch_bounds__(1024) void k_tree_group(TreeGroupArgs T) {
+    __shared__ int wsum[16];
+    __shared__ int sh_over;
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6, o = t & 7;
+    for (int b = t; b < T.nroot; b += 1024) {
+        T.start[b] = T.off ? (int)T.off[b] : 0;
+        T.count[b] = T.off ? (int)(T.off[b + 1] - T.off[b]) : T.n;
+        T.parent[b] = -1;
+        T.level[b] = 0;
+    }
+    if (t == 0) {
+        sh_over = 0;
+        T.host[4] = 0;
+        T.host[5] = T.nroot;
+    }
+    __syncthreads();
+    // this wave's sum of the lower waves' counts, and the total
+    auto add_up = [&](int mine, int &pre) {
+        if (lane == 0) wsum[w] = mine;
+        __syncthreads();
+        int tot = 0;
+        pre = 0;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int v = wsum[j];
+            pre += j < w ? v : 0;
+            tot += v;
+        }
+        __syncthreads();
+        return tot;
+    };
+    int c0 = 0, c1 = T.nroot, lvl = 0, done = 0, over = 0;
+    while (c1 - c0 <= TREE_GROUP) {
+        int next = c1, level_over = 0;
+        bool fits = true;
+        for (int base = c0; base < c1; base += 128) {
+            const int cell = base + t / 8;
+            const bool valid = cell < c1;
+            const int s = valid ? T.start[cell] : 0, cnt = valid ? T.count[cell] : 0;
+            const bool big = valid && cnt > T.ncrit, split = big && lvl < T.KL;
+            // keys resolve no finer than level KL: such a leaf keeps all its particles
+            if (big && !split && o == 0) ++level_over;
+            const int e = split ? octant_end(T.keys, s, s + cnt, o, lvl + 1, T.KL) : s;
+            const int prev = __shfl_up(e, 1, 8);
+            const int lo = o == 0 ? s : prev;
+            const bool nonempty = split && e > lo;
+            const unsigned long long bal = __ballot(nonempty);
+            int pre;
+            const int tot = add_up(__popcll(bal), pre);
+            if (next + tot > T.cap) {  // the caller grows the arrays and repeats the level
+                fits = false;
+                break;
+            }
+            const int sh = lane & ~7;
+            const int first = next + pre + __popcll(bal & ((1ull << sh) - 1));
+            const unsigned mine = (unsigned)(bal >> sh) & 0xffu;
+            if (valid && o == 0) {
+                T.nchild[cell] = __popc(mine);
+                T.child[cell] = mine == 0 ? -1 : first;
+            }
+            if (nonempty) {
+                const int ch = first + __popc(mine & ((1u << o) - 1));
+                T.start[ch] = lo;
+                T.count[ch] = e - lo;
+                T.parent[ch] = cell;
+                T.level[ch] = lvl + 1;
+            }
+            next += tot;
+        }
+        if (!fits) break;
+        over += level_over;
+        __syncthreads();  // the children are read by other threads
+        if (next == c1) {
+            done = 1;
+            break;
+        }
+        c0 = c1;
+        c1 = next;
+        ++lvl;
+        if (t == 0) T.host[5 + lvl] = next;
+    }
+    if (over) atomicAdd(&sh_over, over);
+    int leaves = 0;
+    if (done)
+        for (int base = 0; base < c1; base += 1024) {
+            const int cell = base + t;
+            const bool leaf = cell < c1 && T.nchild[cell] == 0;
+            const unsigned long long bal = __ballot(leaf);
+            int pre;
+            const int tot = add_up(__popcll(bal), pre);
+            if (leaf) T.leaves[leaves + pre + __popcll(bal & ((1ull << lane) - 1))] = cell;
+            leaves += tot;
+        }
+    __syncthreads();
+    if (t == 0) {
+        T.res->overfull = sh_over;
+        T.host[0] = done;
+        T.host[1] = lvl + 2;
+        T.host[2] = leaves;
+        T.host[3] = sh_over;
+    }
+}
+
 // Centres from the key prefix of the first particle; leaves get their tight
 // radius (max distance of a particle from the cube centre) and bounding box.
 // Sixteen lanes per cell: one thread per leaf reads its records one after
@@ -957,10 +1081,8 @@ __global__ __launch_bounds__(TPB) void k_leaf_geometry(int ncell, const RootBox 
 // Internal cells, one level at a time bottom-up: radius bounded by the
 // children's spheres, bounding box the union of the children's boxes, largest
 // core (the box's fourth component) the largest of the children's.
-__global__ __launch_bounds__(TPB) void k_internal_geometry(int c0, int c1, const int *child, const int *nchild,
-                                                           const float4 *geo, float *rad, float4 *blo, float4 *bhi) {
-    const int cell = c0 + blockIdx.x * TPB + threadIdx.x;
-    if (cell >= c1) return;
+__device__ inline void internal_geometry(int cell, const int *child, const int *nchild, const float4 *geo, float *rad,
+                                         float4 *blo, float4 *bhi) {
     const int nc = nchild[cell];
     if (nc == 0) return;
     const float4 g = geo[cell];
@@ -979,6 +1101,29 @@ __global__ __launch_bounds__(TPB) void k_internal_geometry(int c0, int c1, const
     rad[cell] = r * (1.0f + 4.0e-7f);
     blo[cell] = lo;
     bhi[cell] = hi;
+}
+
+__global__ __launch_bounds__(TPB) void k_internal_geometry(int c0, int c1, const int *child, const int *nchild,
+                                                           const float4 *geo, float *rad, float4 *blo, float4 *bhi) {
+    const int cell = c0 + blockIdx.x * TPB + threadIdx.x;
+    if (cell < c1) internal_geometry(cell, child, nchild, geo, rad, blo, bhi);
+}
+
+// all levels of a tree of at most TREE_GEO_GROUP cells in one work-group
+static constexpr int TREE_GEO_GROUP = 2048;
+
+struct LevelOffsets {
+    int v[26];
+};
+
+__global__ __launch_bounds__(1024) void k_internal_geometry_group(LevelOffsets L, int depth, const int *child,
+                                                                  const int *nchild, const float4 *geo, float *rad,
+                                                                  float4 *blo, float4 *bhi) {
+    for (int l = depth - 1; l >= 0; --l) {
+        for (int cell = L.v[l] + threadIdx.x; cell < L.v[l + 1]; cell += 1024)
+            internal_geometry(cell, child, nchild, geo, rad, blo, bhi);
+        __syncthreads();
+    }
 }
 
 __global__ __launch_bounds__(TPB) void k_leaf_flags(int ncell, const int *nchild, int *flag) {
@@ -1052,16 +1197,49 @@ void build_tree(Ctx &c, int64_t n, const float *x, const float *y, const float *
     for (DevBuf *b : arrs) b->ensure(sizeof(int) * cap);
     cap = std::min(c.c_start.cap, std::min(c.c_count.cap, c.c_parent.cap)) / sizeof(int);
     for (DevBuf *b : arrs) cap = std::min(cap, b->cap / sizeof(int));
-    k_roots<<<cdiv(nprob, TPB), TPB, 0, s>>>(nprob, nprob > 1 ? c.poff.as<int64_t>() : nullptr, (int)n,
-                                              c.c_start.as<int>(), c.c_count.as<int>(), c.c_parent.as<int>(),
-                                              c.c_level.as<int>());
-    VFMM_LAUNCH_CHECK();
     c.lvl_off.assign(1, 0);
     c.lvl_off.push_back(nprob);
     int lvl = 0;
     const uint64_t *keys = c.keyA.as<uint64_t>();
+    const int64_t *poff = nprob > 1 ? c.poff.as<int64_t>() : nullptr;
+    bool done = false;
+    if (nprob <= TREE_GROUP) {
+        TreeGroupArgs T{};
+        T.keys = keys;
+        T.off = poff;
+        T.nroot = nprob;
+        T.n = (int)n;
+        T.ncrit = c.prm.ncrit;
+        T.KL = KL;
+        T.cap = (int)std::min<size_t>(cap, INT32_MAX);
+        T.start = c.c_start.as<int>();
+        T.count = c.c_count.as<int>();
+        T.parent = c.c_parent.as<int>();
+        T.child = c.c_child.as<int>();
+        T.nchild = c.c_nchild.as<int>();
+        T.level = c.c_level.as<int>();
+        c.leaves.ensure(sizeof(int) * cap);
+        T.leaves = c.leaves.as<int>();
+        T.res = c.bres.as<Bounds>();
+        T.host = pinned_ints(c);
+        k_tree_group<<<1, 1024, 0, s>>>(T);
+        VFMM_LAUNCH_CHECK();
+        int h[32];
+        sync_ints(c, 32, h);
+        done = h[0] != 0;
+        c.lvl_off.assign(h + 4, h + 4 + h[1]);
+        lvl = h[1] - 2;
+        if (done) {
+            c.nleaves = h[2];
+            c.overfull_leaves = h[3];
+        }
+    } else {
+        k_roots<<<cdiv(nprob, TPB), TPB, 0, s>>>(nprob, poff, (int)n, c.c_start.as<int>(), c.c_count.as<int>(),
+                                                  c.c_parent.as<int>(), c.c_level.as<int>());
+        VFMM_LAUNCH_CHECK();
+    }
     int h_tot[2];
-    for (;;) {
+    while (!done) {
         const int c0 = c.lvl_off[lvl], c1 = c.lvl_off[lvl + 1];
         const int nl = c1 - c0;
         c.c_tmp.ensure(sizeof(int) * (2 * (size_t)nl + 2));
@@ -1101,7 +1279,15 @@ void build_tree(Ctx &c, int64_t n, const float *x, const float *y, const float *
                                                    c.rec.as<float4>(), c.c_geo.as<float4>(), c.c_rad.as<float>(),
                                                    c.c_lo.as<float4>(), c.c_hi.as<float4>());
     VFMM_LAUNCH_CHECK();
-    for (int l = c.depth - 1; l >= 0; --l) {
+    if (nc <= TREE_GEO_GROUP) {
+        LevelOffsets L{};
+        std::copy(c.lvl_off.begin(), c.lvl_off.end(), L.v);
+        k_internal_geometry_group<<<1, 1024, 0, s>>>(L, c.depth, c.c_child.as<int>(), c.c_nchild.as<int>(),
+                                                     c.c_geo.as<float4>(), c.c_rad.as<float>(), c.c_lo.as<float4>(),
+                                                     c.c_hi.as<float4>());
+        VFMM_LAUNCH_CHECK();
+    }
+    for (int l = nc <= TREE_GEO_GROUP ? -1 : c.depth - 1; l >= 0; --l) {
         const int c0 = c.lvl_off[l], c1 = c.lvl_off[l + 1];
         k_internal_geometry<<<cdiv(c1 - c0, TPB), TPB, 0, s>>>(c0, c1, c.c_child.as<int>(), c.c_nchild.as<int>(),
                                                                 c.c_geo.as<float4>(), c.c_rad.as<float>(),
@@ -1109,6 +1295,10 @@ void build_tree(Ctx &c, int64_t n, const float *x, const float *y, const float *
         VFMM_LAUNCH_CHECK();
     }
     // ---- leaf list ----
+    if (done) {
+        c.record(2 * PH_TREE + 1);
+        return;
+    }
     c.c_tmp.ensure(sizeof(int) * (2 * (size_t)nc + 2));
     int *flag = c.c_tmp.as<int>();
     int *pos = flag + nc + 1;
