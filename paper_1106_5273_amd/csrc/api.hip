@@ -14,7 +14,7 @@ void Ctx::release_all() {
     DevBuf *bufs[] = {&bpart, &bres, &keyA, &keyB, &valA, &valB, &hist, &scanA, &scanB, &scanC, &perm, &rec, &rec64,
                       &c_start, &c_count, &c_parent, &c_child, &c_nchild, &c_level, &c_geo, &c_rad, &c_lo, &c_hi,
                       &c_tmp, &leaves, &frA, &frB, &tcnt, &m2l_raw, &p2p_raw, &lkey, &lkey2, &lval, &lval2,
-                      &m2l_off, &m2l_src, &p2p_off, &p2p_ent, &p2p_sh, &recp, &tgt, &c_nsrc, &part, &blocks, &pblocks, &pblong, &items, &item_out, &pairs64, &Mexp, &Lexp, &lat_op, &far_u,
+                      &m2l_off, &m2l_src, &p2p_off, &p2p_ent, &p2p_sh, &recp, &tgt, &c_nsrc, &part, &blocks, &pblocks, &pblong, &mb_kord, &mb_inv, &mb_koff, &mb_ksec, &mb_dst, &mb_coff, &mb_roff, &mb_rsrc, &mb_cols, &items, &item_out, &pairs64, &Mexp, &Lexp, &lat_op, &far_u,
                       &far_da, &near, &dsurf, &rk, &m2l_tgt, &m2l_parts, &m2l_partial, &mb_eq, &mb_flag, &mb_pos, &mb_kid, &mb_ukey,
                       &mb_tab, &mb_bcells, &mb_ent, &mb_groups, &mb_blk, &mb_items, &mb_mr, &mb_partial, &mb_cls, &mb_cellbs, &mb_gcnt, &mb_gid, &mb_goff, &mb_gcur, &mb_bkt, &mb_order, &mb_slots, &gpart, &pid, &pbox, &poff, &tune_ref, &tune_out, &tune_part, &rbf, &spec};
     for (DevBuf *b : bufs) b->release();
@@ -213,7 +213,7 @@ static void do_build(Ctx &c, int64_t n, const float *x, const float *y, const fl
     if (c.prm.m2l_mode != 1 && c.prm.precision != VFMM_PRECISION_FP64) m2lb_plan(c);
     if (!c.m2lb_ok) {  // the per-pair M2L runs instead
         if (!c.m2l_csr) build_m2l_csr(c);
-        m2l_pair_plan(c);
+        m2l_pair_plan(c, c.m2l_off.as<int>(), c.n_m2l);
     }
     far_prealloc(c);
     m2lb_prealloc(c);

@@ -89,8 +89,12 @@ struct Ctx {
     bool mb_x6 = false;                  // the plan's operator table is in the split bf16 form
     int mb_nsplit = 3;                   // bf16 parts per operand the split form multiplies (3 or 2)
     int m2lbx3_lds_set = 0;              // dynamic LDS allowed for the two-part split kernel
+    unsigned m2lbk_lds_set = 0;          // keyed split kernels (degree, parts) whose dynamic LDS has been allowed
     int mb_nblk = 0, mb_nkeys = 0, mb_ngroups = 0, mb_nitems = 0;
     int mb_fmt[4] = {0, 0, 0, 0};
+    bool mb_keyed = false;               // the plan's groups are by operator alone (m2lb_plan_keyed)
+    int64_t mb_ncols = 0, mb_nrest = 0;  // its translations, and those left to the per-pair kernel
+    DevBuf mb_kord, mb_inv, mb_koff, mb_ksec, mb_dst, mb_coff, mb_roff, mb_rsrc, mb_cols;
     DevBuf mb_eq, mb_flag, mb_pos, mb_kid, mb_ukey, mb_tab, mb_bcells, mb_ent, mb_groups, mb_blk, mb_items,
         mb_mr, mb_partial, mb_cls, mb_cellbs, mb_gcnt, mb_gid, mb_goff, mb_gcur, mb_bkt, mb_order, mb_slots;
     // outputs of the far field, sorted order: float [3n] each
@@ -172,6 +176,8 @@ void gather_strengths(Ctx &c, const float *ax, const float *ay, const float *az,
 void gather_records64(Ctx &c, const float *ax, const float *ay, const float *az);
 void partition_sources(Ctx &c, int64_t n_src);
 void build_m2l_csr(Ctx &c);
+// off[t] = first of the n sorted keys >= t, t = 0 .. nc
+void csr_bounds(Ctx &c, const uint64_t *key, int64_t n, int nc, int *off);
 void p2p_prepare(Ctx &c);
 void p2p_near(Ctx &c, hipStream_t s);
 void finalize_near_far(Ctx &c, float *ux, float *uy, float *uz, float *dax, float *day, float *daz);
@@ -189,7 +195,7 @@ void traverse_and_lists(Ctx &c);
 // far.hip
 void far_field(Ctx &c);
 void far_prealloc(Ctx &c);
-void m2l_pair_plan(Ctx &c);
+void m2l_pair_plan(Ctx &c, const int *off, int64_t n);
 // m2lb.hip
 void m2lb_plan(Ctx &c);
 void m2lb_run(Ctx &c);

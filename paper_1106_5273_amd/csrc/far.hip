@@ -492,16 +492,15 @@ __global__ __launch_bounds__(TPB) void k_m2l_add(const int *off, int part, int n
 // one pass where the whole list would otherwise leave CUs idle, else four
 // passes, growing with the list so that the partial sums stay within the size
 // of the expansions.
-void m2l_pair_plan(Ctx &c) {
-    if (c.n_m2l == 0) return;
+void m2l_pair_plan(Ctx &c, const int *off, int64_t n) {
+    if (n == 0) return;
     const int sb = m2l_sources(c.prm.p, c.prm.precision == VFMM_PRECISION_FP64);
-    c.m2l_part = c.n_m2l < 65536 ? sb : (int)std::max<int64_t>(4 * sb, c.n_m2l / 65536 / sb * sb);
-    c.m2l_nparts = (int)(c.n_m2l / c.m2l_part) + c.ncells;
+    c.m2l_part = n < 65536 ? sb : (int)std::max<int64_t>(4 * sb, n / 65536 / sb * sb);
+    c.m2l_nparts = (int)(n / c.m2l_part) + c.ncells;
     const size_t vs = c.prm.precision == VFMM_PRECISION_FP64 ? sizeof(double2) : sizeof(float2);
     c.m2l_parts.ensure(sizeof(int4) * (size_t)c.m2l_nparts);
     c.m2l_partial.ensure(vs * 3 * NC(c.prm.p) * (size_t)c.m2l_nparts);
-    k_m2l_parts<<<cdiv(c.ncells, TPB / 64), TPB, 0, c.stream>>>(c.ncells, c.m2l_off.as<int>(), c.m2l_part,
-                                                                c.m2l_parts.as<int4>());
+    k_m2l_parts<<<cdiv(c.ncells, TPB / 64), TPB, 0, c.stream>>>(c.ncells, off, c.m2l_part, c.m2l_parts.as<int4>());
     VFMM_LAUNCH_CHECK();
 }
 
@@ -767,9 +766,11 @@ static void far_field_t(Ctx &c) {
     }
     c.record(2 * PH_LATTICE + 1);
     c.record(2 * PH_M2L);
-    if (c.n_m2l > 0 && c.m2lb_ok && sizeof(S) == 4) {
-        m2lb_run(c);
-    } else if (c.n_m2l > 0) {
+    const bool batched = c.n_m2l > 0 && c.m2lb_ok && sizeof(S) == 4;
+    if (batched) m2lb_run(c);
+    if (batched ? c.mb_keyed && c.mb_nrest > 0 : c.n_m2l > 0) {  // all translations, or those the plan left out
+        const int2 *src = batched ? c.mb_rsrc.as<int2>() : c.m2l_src.as<int2>();
+        const int *off = batched ? c.mb_roff.as<int>() : c.m2l_off.as<int>();
         using MC = M2LCfg<P, S>;
         const unsigned bit = 1u << (P / 2 + (sizeof(S) == 8 ? 8 : 0));
         if (MC::LDS > 64 * 1024 && !(c.m2l_lds_set & bit)) {  // once per context (a context lives on one device)
@@ -777,12 +778,12 @@ static void far_field_t(Ctx &c) {
                                          (int)MC::LDS));
             c.m2l_lds_set |= bit;
         }
-        k_m2l<P, S><<<c.m2l_nparts, MC::THREADS, MC::LDS, s>>>(c.m2l_parts.as<int4>(), c.m2l_src.as<int2>(),
+        k_m2l<P, S><<<c.m2l_nparts, MC::THREADS, MC::LDS, s>>>(c.m2l_parts.as<int4>(), src,
                                                                    c.c_geo.as<float4>(), c.Mexp.as<V2>(),
                                                                    c.m2l_partial.as<V2>(), c.img_B,
                                                                    c.prm.periodic ? (float)c.prm.box_len : 0.f);
         VFMM_LAUNCH_CHECK();
-        k_m2l_add<V2><<<c.ncells, TPB, 0, s>>>(c.m2l_off.as<int>(), c.m2l_part, 3 * NCP, c.m2l_partial.as<V2>(),
+        k_m2l_add<V2><<<c.ncells, TPB, 0, s>>>(off, c.m2l_part, 3 * NCP, c.m2l_partial.as<V2>(),
                                                c.Lexp.as<V2>());
         VFMM_LAUNCH_CHECK();
     }

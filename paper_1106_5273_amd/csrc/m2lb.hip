@@ -708,20 +708,26 @@ __device__ __forceinline__ vf4 mfma_bf16(u32x4 a, u32x4 b, vf4 c) {
                                                   0, 0, 0);
 }
 
-template <int P, int NS>
+//
+// KEYED: the groups of one operator's translations whatever their targets
+// (m2lb_plan_keyed).  The 64 columns then belong to different targets, so every
+// group's products are written at once, column by column in order of the targets
+// (dsts: the column's place, -1 for none), for k_m2lb_columns to add up.
+template <int P, int NS, bool KEYED>
 __global__ __launch_bounds__(MbxCfg<P>::WAVES * 64) void k_m2lb_x6(const int4 *__restrict__ items,
                                                                   const int *__restrict__ order,
                                                                   const int4 *__restrict__ groups,
                                                                   const int *__restrict__ slots,
                                                                   const float *__restrict__ Mr,
-                                                                  const uint32_t *__restrict__ tab, int nitems,
+                                                                  const uint32_t *__restrict__ tab,
+                                                                  const int *__restrict__ dsts, int nitems,
                                                                   float *__restrict__ partial) {
     using C = MbCfg<P>;
     using X = MbxCfg<P>;
     constexpr int NT = X::WAVES * 64;
     const int li = xcd_logical(blockIdx.x, gridDim.x);
     if (li >= nitems) return;
-    const int item = order[li];
+    const int item = KEYED ? li : order[li];
     extern __shared__ float smem[];
     uint16_t *Bs = reinterpret_cast<uint16_t *>(smem);                     // [2][NS][64][BSX]
     const int tid = threadIdx.x;
@@ -753,10 +759,11 @@ __global__ __launch_bounds__(MbxCfg<P>::WAVES * 64) void k_m2lb_x6(const int4 *_
             for (int sp = 0; sp < NS; ++sp)
                 A[j][kb][sp] = T4[(((size_t)(ra0 + j) * X::KB + kb) * 3 + sp) * 64 + lane];
     };
+    int key = 0;
     if (g0 < g1) {
-        const int key0 = __builtin_amdgcn_readfirstlane(groups[g0].x);
+        key = __builtin_amdgcn_readfirstlane(groups[g0].x);
 #pragma unroll
-        for (int kb = 0; kb < X::KB; ++kb) load_a(key0, kb);
+        for (int kb = 0; kb < X::KB; ++kb) load_a(key, kb);
     }
     // float4 number q = tid + NT i of a staged tile: column q / (RP/4), inputs 4 (q % (RP/4)) ..;
     // the source cell of every column of a group comes from its dense slot table (the
@@ -791,6 +798,10 @@ __global__ __launch_bounds__(MbxCfg<P>::WAVES * 64) void k_m2lb_x6(const int4 *_
     for (int g = g0; g < g1; ++g) {
         const bool more = g + 1 < g1;
         const int nkey = more ? __builtin_amdgcn_readfirstlane(groups[g + 1].x) : 0;
+        int col[2] = {-1, -1};
+        if (KEYED)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) col[b] = dsts[(size_t)g * 64 + 16 * (cb0 + b) + i16];
         __syncthreads();  // the previous group's tiles are no longer read
 #pragma unroll
         for (int i = 0; i < X::F4; ++i) put(0, i, pre[i]);
@@ -827,7 +838,19 @@ __global__ __launch_bounds__(MbxCfg<P>::WAVES * 64) void k_m2lb_x6(const int4 *_
 #pragma unroll
                         for (int b = 0; b < 2; ++b)
                             acc[c][j][b] = mfma_bf16(A[j][kb][TA[t]], Bv[b][TB[t]], acc[c][j][b]);
-                if (c == 2 && more) load_a(nkey, kb);  // this k block's last use in this group
+                // this k block's last use in this group (groups of one operator follow each other)
+                if (c == 2 && more && !(KEYED && nkey == key)) load_a(nkey, kb);
+            }
+            if (KEYED) {
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        if (col[b] >= 0)
+                            *reinterpret_cast<vf4 *>(partial + ((size_t)col[b] * 3 + c) * C::RP + 16 * (ra0 + j) +
+                                                     4 * kq) = acc[c][j][b];
+                        acc[c][j][b] = vf4{0.f, 0.f, 0.f, 0.f};
+                    }
             }
             if (c < 2) {
 #pragma unroll
@@ -835,7 +858,9 @@ __global__ __launch_bounds__(MbxCfg<P>::WAVES * 64) void k_m2lb_x6(const int4 *_
                 __syncthreads();
             }
         }
+        key = nkey;
     }
+    if (KEYED) return;
     // D fragment: lane holds rows 16 a + 4 kq + v of target column 16 b + i16
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -913,9 +938,237 @@ __global__ __launch_bounds__(TPB) void k_m2lb_reduce(const int *blk_item0, const
     }
 }
 
+// Lt(t) += the columns of the keyed form, which hold the translations to each
+// target one after another: COL_GROUPS groups of threads (a thread per two rows)
+// take every COL_GROUPS-th column with 16 in flight, then the groups are added in
+// order.  Bound by reading the columns (1.5 KB each at p = 10).
+static constexpr int COL_GROUPS = 4;
+
+template <int P, typename A>
+__global__ __launch_bounds__(COL_GROUPS * 3 * NRP(P) / 2) void k_m2lb_columns(const int *__restrict__ coff,
+                                                                            const float *__restrict__ cols,
+                                                                            float2 *Lexp) {
+    constexpr int R = NR(P), RP = NRP(P), NCP = NC(P), HP = 3 * RP / 2;
+    __shared__ A red[COL_GROUPS][2][HP];
+    const int t = blockIdx.x, c0 = coff[t], c1 = coff[t + 1];
+    if (c0 == c1) return;
+    const int grp = threadIdx.x / HP, h = threadIdx.x % HP;
+    const float2 *p = reinterpret_cast<const float2 *>(cols) + h;
+    A v0 = A(0), v1 = A(0);
+    for (int i0 = c0 + grp; i0 < c1; i0 += 16 * COL_GROUPS) {
+        float2 w[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            w[u] = i0 + COL_GROUPS * u < c1 ? p[(size_t)(i0 + COL_GROUPS * u) * HP] : make_float2(0.f, 0.f);
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            v0 += (A)w[u].x;
+            v1 += (A)w[u].y;
+        }
+    }
+    red[grp][0][h] = v0;
+    red[grp][1][h] = v1;
+    __syncthreads();
+    if (grp > 0) return;
+    for (int g = 1; g < COL_GROUPS; ++g) {
+        v0 += red[g][0][h];
+        v1 += red[g][1][h];
+    }
+    const int comp = h / (RP / 2), r0 = 2 * (h % (RP / 2));
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        if (r0 + q >= R) continue;
+        int k, l, im;
+        decode_row(r0 + q, k, l, im);
+        float *dst = reinterpret_cast<float *>(&Lexp[((size_t)t * 3 + comp) * NCP + CIDX(k, l)]) + im;
+        *dst = (float)((A)*dst + (q ? v1 : v0));
+    }
+}
+
+// ---- plan of the keyed form ----
+// keys of fewer translations than this go to the per-pair kernel: their operator
+// and their group cost what about ten translations one at a time cost
+static constexpr int KEYED_MIN = 10;
+
+__global__ __launch_bounds__(TPB) void k_kid_keys(int64_t n, const int *kid, uint64_t *key, uint32_t *val) {
+    const int64_t e = (int64_t)blockIdx.x * TPB + threadIdx.x;
+    if (e >= n) return;
+    key[e] = (uint64_t)kid[e];
+    val[e] = (uint32_t)e;
+}
+
+// per key: its groups of 64, whether it is used, its translations that are left out
+__global__ __launch_bounds__(TPB) void k_key_sections(int nkeys, const int *koff, int *sec) {
+    const int k = blockIdx.x * TPB + threadIdx.x;
+    if (k >= nkeys) return;
+    const int cnt = koff[k + 1] - koff[k];
+    const bool used = cnt >= KEYED_MIN;
+    sec[k] = used ? (cnt + 63) / 64 : 0;
+    sec[nkeys + k] = used;
+    sec[2 * nkeys + k] = used ? 0 : cnt;
+}
+
+__global__ void k_key_totals(const int *sec, const int *off, int nkeys, int *out) {
+    for (int k = 0; k < 3; ++k) out[k] = off[(k + 1) * nkeys - 1] + sec[(k + 1) * nkeys - 1] - off[k * nkeys];
+}
+
+// entry i of the list by target: whether it is left out, and its position from its raw index
+__global__ __launch_bounds__(TPB) void k_rest_flags(int64_t n, const uint32_t *order, const int *kid, const int *used,
+                                                    int *flag, int *inv) {
+    const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t e = order[i];
+    flag[i] = used[kid[e]] ? 0 : 1;
+    inv[e] = (int)i;
+}
+
+// offsets per target of the columns and of the entries left out
+__global__ __launch_bounds__(TPB) void k_rest_offsets(int nc, int64_t n, int nrest, const int *off, const int *pos,
+                                                      int *coff, int *roff) {
+    const int t = blockIdx.x * TPB + threadIdx.x;
+    if (t > nc) return;
+    const int o = off[t], r = o < n ? pos[o] : nrest;
+    roff[t] = r;
+    coff[t] = o - r;
+}
+
+__global__ __launch_bounds__(TPB) void k_rest_gather(int64_t n, const int *flag, const int *pos, const int2 *src,
+                                                     int2 *rsrc) {
+    const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
+    if (i < n && flag[i]) rsrc[pos[i]] = src[i];
+}
+
+// a translation per thread, in key order: its group's key, source and column
+__global__ __launch_bounds__(TPB) void k_key_slots(int64_t n, const uint32_t *kord, const int *kid, const int *koff,
+                                                   int nkeys, const int *sec, const int *off, const int4 *raw,
+                                                   const int *inv, const int *pos, const uint64_t *ukey,
+                                                   int4 *groups, int *slots, int *dsts, uint64_t *used_key) {
+    const int64_t j = (int64_t)blockIdx.x * TPB + threadIdx.x;
+    if (j >= n) return;
+    const uint32_t e = kord[j];
+    const int k = kid[e];
+    if (!sec[nkeys + k]) return;
+    const int r = (int)j - koff[k];
+    const int g = off[k] + r / 64;
+    const int u = off[nkeys + k] - off[nkeys];
+    if (r == 0) used_key[u] = ukey[k];
+    if (r % 64 == 0) groups[g] = make_int4(u, 0, 0, 0);
+    const int i = inv[e];
+    slots[(size_t)g * 64 + r % 64] = raw[e].y;
+    dsts[(size_t)g * 64 + r % 64] = i - pos[i];
+}
+
+__global__ __launch_bounds__(TPB) void k_key_items(int nitems, int per, int ng, int4 *items) {
+    const int i = blockIdx.x * TPB + threadIdx.x;
+    if (i < nitems) items[i] = make_int4(0, i * per, min(ng, (i + 1) * per), 0);
+}
+
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
+// The keyed form of the plan, where the targets of a block share too few
+// operators to fill groups of 64 (irregular trees): the groups take the
+// translations of one operator whatever their targets, at the price of writing
+// every translation's result and reading it again for its target's sum; rare
+// operators go to the per-pair kernel.  Taken where the costs below, in ns as
+// measured at p = 10 (a group 32, a column's bytes at 5 TB/s 0.6, an operator's
+// bytes at 4.2 TB/s 23, a pair 6; scaled by their work to other degrees), say so:
+// 1.8 million translations of 29,744 operators (100,003 clustered particles)
+// filled 162,850 groups by block to a sixth, 32,000 by key: 5.75 -> 2.43 ms, and
+// the plan 0.33 ms shorter with 6,800 operators left; a jittered 80^3 lattice, 37
+// of 64 filled by block, stays there, and so do 64 rings' 70,516 translations one
+// at a time (0.29 ms; by key 0.16, for a plan of 0.17 more).
+static constexpr size_t MAX_COLUMN_BYTES = size_t(8) << 30;
+
+template <int P>
+static bool m2lb_plan_keyed(Ctx &c, int64_t n, int nkeys, int ng_block, const KeyFmt &f) {
+    using C = MbCfg<P>;
+    hipStream_t s = c.stream;
+    const double t_group = (double)C::RTI * (C::RP / 32), t_col = 24.0 * C::RP / 5000.0;
+    const double t_key = 4.0 * (double)C::OPX / 4200.0, t_pair = 6.0 * std::pow(C::R / 121.0, 1.5);
+    const double t_plan = 2e5 + 0.11 * (double)n;  // twenty launches, two sorts
+    const bool by_block = n >= (int64_t)MIN_GROUP_FILL * ng_block;
+    const double other = by_block ? 1.1 * t_group * ng_block + t_key * nkeys : t_pair * (double)n;
+    if (t_plan + t_col * (double)n + t_group * (double)n / 64 > other) return false;  // whatever the keys are
+    c.mb_koff.ensure(sizeof(int) * ((size_t)nkeys + 1));
+    c.mb_ksec.ensure(sizeof(int) * 6 * (size_t)nkeys);
+    int *koff = c.mb_koff.as<int>(), *sec = c.mb_ksec.as<int>(), *off = sec + 3 * (size_t)nkeys;
+    const int *kid = c.mb_kid.as<int>();
+    c.lkey.ensure(sizeof(uint64_t) * n);
+    c.lval.ensure(sizeof(uint32_t) * n);
+    k_kid_keys<<<cdiv(n, TPB), TPB, 0, s>>>(n, kid, c.lkey.as<uint64_t>(), c.lval.as<uint32_t>());
+    VFMM_LAUNCH_CHECK();
+    int kbits = 1;
+    while ((1 << kbits) < nkeys) ++kbits;
+    sort_pairs_u64(c, c.lkey, c.lval, c.lkey2, c.lval2, n, kbits);
+    csr_bounds(c, c.lkey.as<uint64_t>(), n, nkeys, koff);
+    k_key_sections<<<cdiv(nkeys, TPB), TPB, 0, s>>>(nkeys, koff, sec);
+    VFMM_LAUNCH_CHECK();
+    scan_excl_i32(c, sec, off, 3LL * nkeys);
+    k_key_totals<<<1, 1, 0, s>>>(sec, off, nkeys, pinned_ints(c));
+    VFMM_LAUNCH_CHECK();
+    int h[3];
+    sync_ints(c, 3, h);
+    const int ng = h[0], nused = h[1], nrest = h[2];
+    const int64_t ncols = n - nrest;
+    const double keyed = t_plan + t_group * ng + t_col * (double)ncols + t_key * nused + t_pair * nrest;
+    const size_t tab_bytes = sizeof(uint32_t) * C::OPX * (size_t)nused;
+    if (keyed > other || ng == 0 || tab_bytes > MAX_TABLE_BYTES ||
+        sizeof(float) * 3 * C::RP * (size_t)ncols > MAX_COLUMN_BYTES)
+        return false;
+    std::swap(c.lval, c.mb_kord);  // kept while the list by target is sorted
+    c.m2l_csr = false;
+    build_m2l_csr(c);              // leaves the list's order in lval
+    c.mb_inv.ensure(sizeof(int) * n);
+    c.mb_coff.ensure(sizeof(int) * ((size_t)c.ncells + 1));
+    c.mb_roff.ensure(sizeof(int) * ((size_t)c.ncells + 1));
+    c.mb_rsrc.ensure(sizeof(int2) * (size_t)std::max(nrest, 1));
+    c.mb_groups.ensure(sizeof(int4) * (size_t)ng);
+    c.mb_slots.ensure(sizeof(int) * 64 * (size_t)ng);
+    c.mb_dst.ensure(sizeof(int) * 64 * (size_t)ng);
+    int *flag = c.mb_flag.as<int>(), *pos = c.mb_pos.as<int>(), *inv = c.mb_inv.as<int>();
+    k_rest_flags<<<cdiv(n, TPB), TPB, 0, s>>>(n, c.lval.as<uint32_t>(), kid, sec + nkeys, flag, inv);
+    VFMM_LAUNCH_CHECK();
+    scan_excl_i32(c, flag, pos, n);
+    k_rest_offsets<<<cdiv(c.ncells + 1, TPB), TPB, 0, s>>>(c.ncells, n, nrest, c.m2l_off.as<int>(), pos,
+                                                           c.mb_coff.as<int>(), c.mb_roff.as<int>());
+    VFMM_LAUNCH_CHECK();
+    if (nrest > 0) {
+        k_rest_gather<<<cdiv(n, TPB), TPB, 0, s>>>(n, flag, pos, c.m2l_src.as<int2>(), c.mb_rsrc.as<int2>());
+        VFMM_LAUNCH_CHECK();
+        m2l_pair_plan(c, c.mb_roff.as<int>(), nrest);
+    }
+    k_fill_i32<<<cdiv(64 * (int64_t)ng, TPB), TPB, 0, s>>>(64 * (int64_t)ng, c.ncells, c.mb_slots.as<int>());
+    VFMM_LAUNCH_CHECK();
+    k_fill_i32<<<cdiv(64 * (int64_t)ng, TPB), TPB, 0, s>>>(64 * (int64_t)ng, -1, c.mb_dst.as<int>());
+    VFMM_LAUNCH_CHECK();
+    c.lkey.ensure(sizeof(uint64_t) * (size_t)nused);
+    k_key_slots<<<cdiv(n, TPB), TPB, 0, s>>>(n, c.mb_kord.as<uint32_t>(), kid, koff, nkeys, sec, off,
+                                              c.m2l_raw.as<int4>(), inv, pos, c.mb_ukey.as<uint64_t>(),
+                                              c.mb_groups.as<int4>(), c.mb_slots.as<int>(), c.mb_dst.as<int>(),
+                                              c.lkey.as<uint64_t>());
+    VFMM_LAUNCH_CHECK();
+    // a few items per CU: one operator's groups stay together, the last round is short
+    const int per = std::max(1, std::min(ITEM_GROUPS, ng / 2048));
+    c.mb_nitems = (int)cdiv(ng, per);
+    c.mb_items.ensure(sizeof(int4) * (size_t)c.mb_nitems);
+    k_key_items<<<cdiv(c.mb_nitems, TPB), TPB, 0, s>>>(c.mb_nitems, per, ng, c.mb_items.as<int4>());
+    VFMM_LAUNCH_CHECK();
+    c.mb_tab.ensure(tab_bytes);
+    k_m2lb_optab<P, 1><<<nused, 256, 0, s>>>(nused, c.lkey.as<uint64_t>(), f, c.mb_tab.as<float>());
+    VFMM_LAUNCH_CHECK();
+    c.mb_x6 = true;
+    c.mb_keyed = true;
+    c.mb_nsplit = c.prm.m2l_form == 3 ? 2 : 3;
+    c.mb_nkeys = nused;
+    c.mb_nblk = 0;
+    c.mb_ngroups = ng;
+    c.mb_ncols = ncols;
+    c.mb_nrest = nrest;
+    c.m2lb_ok = true;
+    return true;
+}
+
 // Product form of the batched M2L: split bf16 products when asked for
 // (m2l_form 2: six products, 3: three) and the padded inputs make whole k
 // blocks of 32.
@@ -932,6 +1185,7 @@ static void m2lb_plan_p(Ctx &c) {
     hipStream_t s = c.stream;
     const int64_t n = c.n_m2l;
     c.m2lb_ok = false;
+    c.mb_keyed = false;
     if (n == 0) return;
     if (c.prm.m2l_mode == 0 && n < MIN_BATCHED) return;
     // ---- offsets and ranges ----
@@ -1062,6 +1316,8 @@ static void m2lb_plan_p(Ctx &c) {
     // all present or not; measured on gfx950 a group costs about as much as
     // 6-7 translations of the per-pair kernel, so sparse groups (irregular
     // trees: many offsets, few targets sharing each) go to the per-pair M2L.
+    if constexpr (C::X6)
+        if (c.prm.m2l_mode == 0 && x6 && n < 32 * (int64_t)ng && m2lb_plan_keyed<P>(c, n, nkeys, ng, f)) return;
     if (c.prm.m2l_mode == 0 && n < (int64_t)MIN_GROUP_FILL * ng) return;
     c.mb_groups.ensure(sizeof(int4) * ng);
     k_gk_groups<<<cdiv(T, TPB), TPB, 0, s>>>(T, gcnt, gid, x6 ? nullptr : goff, nkeys, c.mb_groups.as<int4>(), gcur);
@@ -1141,7 +1397,10 @@ template <int P>
 static void m2lb_prealloc_p(Ctx &c) {
     constexpr int R = NR(P), RP = NRP(P);
     c.mb_mr.ensure(sizeof(float) * (size_t)(c.ncells + 1) * 3 * RP);
-    c.mb_partial.ensure(sizeof(float) * (size_t)std::max(c.mb_nitems, 1) * 3 * R * 64);
+    if (c.mb_keyed)
+        c.mb_cols.ensure(sizeof(float) * 3 * RP * (size_t)c.mb_ncols);
+    else
+        c.mb_partial.ensure(sizeof(float) * (size_t)std::max(c.mb_nitems, 1) * 3 * R * 64);
 }
 
 void m2lb_prealloc(Ctx &c) {
@@ -1164,27 +1423,42 @@ static void m2lb_run_p(Ctx &c) {
     c.mb_mr.ensure(sizeof(float) * mr_total);
     k_m2lb_mreal<P><<<cdiv(mr_total, TPB), TPB, 0, s>>>(c.ncells, c.Mexp.as<float2>(), c.mb_mr.as<float>());
     VFMM_LAUNCH_CHECK();
-    c.mb_partial.ensure(sizeof(float) * (size_t)c.mb_nitems * 3 * R * 64);
+    m2lb_prealloc_p<P>(c);
     if (c.mb_x6) {
         using X = MbxCfg<P>;
-        auto launch = [&](auto ns) {
+        auto launch = [&](auto ns, auto by_key) {
             constexpr int NS = decltype(ns)::value;
+            constexpr bool KEYED = decltype(by_key)::value;
             const size_t lds = m2lb_x6_lds_bytes<P, NS>();
             int &set = NS == 3 ? c.m2lbx_lds_set : c.m2lbx3_lds_set;
-            if (set < (int)lds) {  // once per context (a context lives on one device)
-                VFMM_HIP(hipFuncSetAttribute((const void *)k_m2lb_x6<P, NS>,
+            const unsigned bit = 1u << (P / 2 + (NS == 3 ? 8 : 0));
+            // once per context (a context lives on one device)
+            if (KEYED ? !(c.m2lbk_lds_set & bit) : set < (int)lds) {
+                VFMM_HIP(hipFuncSetAttribute((const void *)k_m2lb_x6<P, NS, KEYED>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-                set = (int)lds;
+                if (KEYED)
+                    c.m2lbk_lds_set |= bit;
+                else
+                    set = (int)lds;
             }
-            k_m2lb_x6<P, NS><<<xcd_grid(c.mb_nitems), X::WAVES * 64, lds, s>>>(
+            k_m2lb_x6<P, NS, KEYED><<<xcd_grid(c.mb_nitems), X::WAVES * 64, lds, s>>>(
                 c.mb_items.as<int4>(), c.mb_order.as<int>(), c.mb_groups.as<int4>(), c.mb_slots.as<int>(),
                 c.mb_mr.as<float>(),
-                c.mb_tab.as<uint32_t>(), c.mb_nitems, c.mb_partial.as<float>());
+                c.mb_tab.as<uint32_t>(), c.mb_dst.as<int>(), c.mb_nitems,
+                (KEYED ? c.mb_cols : c.mb_partial).template as<float>());
         };
-        if (c.mb_nsplit == 2)
-            launch(std::integral_constant<int, 2>{});
-        else
-            launch(std::integral_constant<int, 3>{});
+        auto launch_form = [&](auto by_key) {
+            if (c.mb_nsplit == 2)
+                launch(std::integral_constant<int, 2>{}, by_key);
+            else
+                launch(std::integral_constant<int, 3>{}, by_key);
+        };
+        if constexpr (MbCfg<P>::X6) {
+            if (c.mb_keyed)
+                launch_form(std::true_type{});
+            else
+                launch_form(std::false_type{});
+        }
     } else {
         const size_t lds = m2lb_lds_bytes<P>();
         if (c.m2lb_lds_set < (int)lds) {  // once per context (a context lives on one device)
@@ -1199,6 +1473,17 @@ static void m2lb_run_p(Ctx &c) {
                                                            c.mb_partial.as<float>());
     }
     VFMM_LAUNCH_CHECK();
+    if (c.mb_keyed) {
+        constexpr int NT = COL_GROUPS * 3 * RP / 2;
+        if (c.prm.precision == VFMM_PRECISION_MIXED)
+            k_m2lb_columns<P, double><<<c.ncells, NT, 0, s>>>(c.mb_coff.as<int>(), c.mb_cols.as<float>(),
+                                                              c.Lexp.as<float2>());
+        else
+            k_m2lb_columns<P, float><<<c.ncells, NT, 0, s>>>(c.mb_coff.as<int>(), c.mb_cols.as<float>(),
+                                                             c.Lexp.as<float2>());
+        VFMM_LAUNCH_CHECK();
+        return;
+    }
     const int nblk = c.mb_nblk;
     int *blk_item0 = c.mb_blk.as<int>() + nblk, *blk_nitem = blk_item0 + nblk;
     const dim3 rgrid(nblk, 3, cdiv(R, RC));

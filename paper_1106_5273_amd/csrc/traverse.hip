@@ -550,6 +550,11 @@ static void grow_keep4(Ctx &c, DevBuf &b, size_t bytes, size_t used) {
     b = nb;
 }
 
+void csr_bounds(Ctx &c, const uint64_t *key, int64_t n, int nc, int *off) {
+    k_csr_bounds<<<cdiv(nc + 1, TPB), TPB, 0, c.stream>>>(key, n, nc, off);
+    VFMM_LAUNCH_CHECK();
+}
+
 // Builds CSR offsets (ncells+1) for a raw (tgt, src, img) list and the
 // stable order that sorts it by target.
 static void csr_by_target(Ctx &c, const int4 *raw, int64_t n, DevBuf &off) {
@@ -565,8 +570,7 @@ static void csr_by_target(Ctx &c, const int4 *raw, int64_t n, DevBuf &off) {
     k_list_keys<<<cdiv(n, TPB), TPB, 0, s>>>(raw, n, c.lkey.as<uint64_t>(), c.lval.as<uint32_t>());
     VFMM_LAUNCH_CHECK();
     sort_pairs_u64(c, c.lkey, c.lval, c.lkey2, c.lval2, n, bits_for(nc));
-    k_csr_bounds<<<cdiv(nc + 1, TPB), TPB, 0, s>>>(c.lkey.as<uint64_t>(), n, nc, off.as<int>());
-    VFMM_LAUNCH_CHECK();
+    csr_bounds(c, c.lkey.as<uint64_t>(), n, nc, off.as<int>());
 }
 
 // M2L list in CSR order by target cell (stable: traversal order within a

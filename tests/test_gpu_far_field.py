@@ -33,3 +33,33 @@ def test_translations_one_at_a_time_match_batched(n, ncrit, p):
     assert s1["m2l_groups"] == 0 and s2["m2l_groups"] > 0 and s1["m2l_entries"] == s2["m2l_entries"]
     check("n=%d p=%d, %d translations, u" % (n, p, s1["m2l_entries"]), u1, u2, 1e-5, 1e-3)
     check("n=%d p=%d dalpha" % (n, p), d1, d2, 1e-5, 1e-3)
+
+
+def _clustered(n, seed):
+    """Two dense clusters and a sparse background: few targets of a block share an operator."""
+    rng = np.random.default_rng(seed)
+    x = np.concatenate([0.4 + 0.03 * rng.standard_normal((n // 2, 3)), 0.65 + 0.05 * rng.standard_normal((n // 2, 3)),
+                        rng.uniform(0.0, 1.0, (n - 2 * (n // 2) + n // 50, 3))])
+    x = np.clip(x, 0.0, 0.999)
+    a = rng.standard_normal(x.shape) / len(x)
+    f = lambda v: np.ascontiguousarray(v, np.float32)  # noqa: E731
+    return dict(x=f(x[:, 0]), y=f(x[:, 1]), z=f(x[:, 2]), ax=f(a[:, 0]), ay=f(a[:, 1]), az=f(a[:, 2]),
+                sigma=f(np.full(len(x), 0.002)), n=len(x))
+
+
+@pytest.mark.parametrize("opt", [dict(p=6), dict(p=8), dict(p=10), dict(p=10, precision=1), dict(p=8, precision=1),
+                                 dict(p=10, periodic=1, box_len=1.0, images=3), dict(p=10, m2l_form=3),
+                                 dict(p=8, m2l_form=3)], ids=lambda o: "-".join("%s%s" % kv for kv in o.items()))
+def test_groups_by_operator_match_one_at_a_time(opt):
+    """Irregular trees: groups of one operator's translations whatever their targets, rare operators one at a
+    time.  m2l_form 3 drops terms of 2^-16 of the operator's and the multipoles' size: the evaluation's 1e-4."""
+    case = _clustered(40000, 3)
+    u0, d0, s0 = _run(case, ncrit=32, **opt)
+    one = dict(opt, m2l_mode=1)
+    u1, d1, s1 = _run(case, ncrit=32, **one)
+    _, _, s2 = _run(case, ncrit=32, **dict(opt, m2l_mode=2))
+    assert 0 < s0["m2l_groups"] < s2["m2l_groups"] and s0["m2l_keys"] < s2["m2l_keys"]  # neither of the other forms
+    assert s0["m2l_entries"] == s1["m2l_entries"]
+    tol = 1e-4 if opt.get("m2l_form") == 3 else 1e-5
+    check("%s, %d translations, u" % (opt, s0["m2l_entries"]), u0, u1, tol, 1e-3)
+    check("%s dalpha" % opt, d0, d1, tol, 1e-3)
