@@ -115,32 +115,78 @@ __global__ __launch_bounds__(64) void k_p2m(const int *leaves, const int *start,
 }
 
 // ---------------------------------------------------------------------------
-// M2M: one work-group per parent cell of one level, one thread per
-// (potential, coefficient n >= m >= 0) of the parent.
+// M2M: one work-group per parent cell of one level, one thread per (child,
+// coefficient n >= m >= 0 of the parent) for the three potentials.
 //   Mt_n^m(P) = sum_children sum_{k,l} conj(R_k^l(d)) (s_c/s_P)^{n-k} Mt_{n-k}^{m-l}(c),
 //   d = (c - P)/s_P.
-// Children are staged one at a time in LDS as full-order tables (m from -n
-// to n, negative orders expanded once) with the size ratio folded into the
-// child's coefficients, so the inner loop is a plain complex multiply-add.
+// The children are staged in LDS as full-order tables (m from -n to n, negative
+// orders expanded once) with the size ratio folded into the child's
+// coefficients, so the inner loop is a plain complex multiply-add; the children
+// of a coefficient are neighbouring lanes, summed by shuffles.  The first wave
+// or two take the harmonics, a lane per child and order, the others stage.
 // S is the storage type of the expansions, R the arithmetic type (the mixed
 // precision form keeps float storage and accumulates in double).
+// Bound by latency at the coarse levels and by LDS reads at the fine ones (32
+// bytes for the three potentials' terms).  One child after another with a thread
+// per potential: 33 us a level of 1 to 8 cells at p = 8 and 0.33 ms for the five
+// levels of 80^3 particles at p = 10; now 8 us and 0.21 ms.
 // ---------------------------------------------------------------------------
-template <int P>
+template <int P, class R = float>
 struct XferCfg {
     static constexpr int NCP = NC(P);
     static constexpr int W = 2 * P + 1;                       // full-order row width
-    static constexpr int THREADS = ((3 * NCP + 63) / 64) * 64;
+    static constexpr int ROWS = (P + 1) * W;
+    static constexpr int CH = sizeof(R) == 8 ? 4 : 8;         // children staged at once by M2M
+    static constexpr int M2M_HARM = ((CH * (P + 1) + 63) / 64) * 64;  // threads that take the harmonics
+    static constexpr int L2L_HARM = ((8 * (P + 1) + 63) / 64) * 64;
+    static constexpr int M2M_THREADS = ((CH * NCP + 63) / 64) * 64 + 64;
+    static constexpr int L2L_THREADS = ((8 * NCP + 63) / 64) * 64 + 64;
 };
 
+// The orders +-m of R(d) (common.h regular_harmonics, one order's recursion) into
+// the full-order table T; CONJ: its conjugate
+template <int P, class R, bool CONJ, class V2>
+__device__ inline void harmonics_order(R x, R y, R z, int m, V2 *T) {
+    constexpr int W = 2 * P + 1;
+    const R r2 = x * x + y * y + z * z;
+    R cr = R(1), ci = R(0);  // R_m^m
+    for (int k = 1; k <= m; ++k) {
+        const R f = R(-1) / R(2 * k);
+        const R nr = f * (x * cr - y * ci);
+        const R ni = f * (x * ci + y * cr);
+        cr = nr;
+        ci = ni;
+    }
+    auto put = [&](int n, R vr, R vi) {
+        const R v = CONJ ? -vi : vi;
+        T[n * W + P + m] = V2{vr, v};
+        if (m > 0) T[n * W + P - m] = (m & 1) ? V2{-vr, v} : V2{vr, -v};
+    };
+    put(m, cr, ci);
+    R pr = R(0), pi = R(0);  // R_{n-2}^m
+    for (int n = m + 1; n <= P; ++n) {
+        const R inv = R(1) / R(n * n - m * m);
+        const R a = R(2 * n - 1) * z;
+        // R_{m+1}^m = z R_m^m
+        const R vr = n == m + 1 ? z * cr : (a * cr - r2 * pr) * inv;
+        const R vi = n == m + 1 ? z * ci : (a * ci - r2 * pi) * inv;
+        put(n, vr, vi);
+        pr = cr;
+        pi = ci;
+        cr = vr;
+        ci = vi;
+    }
+}
+
 template <int P, class R, class S>
-__global__ __launch_bounds__((XferCfg<P>::THREADS)) void k_m2m(int c0, int c1, const int *child, const int *nchild,
-                                                               const float4 *geo, typename VT<S>::V2 *Mexp) {
+__global__ __launch_bounds__((XferCfg<P, R>::M2M_THREADS)) void k_m2m(int c0, int c1, const int *child,
+                                                                     const int *nchild, const float4 *geo,
+                                                                     typename VT<S>::V2 *Mexp) {
     using V2 = typename VT<R>::V2;
-    using C = XferCfg<P>;
-    constexpr int NCP = C::NCP, W = C::W;
-    __shared__ V2 Mf[3][P + 1][W];   // child multipole, scaled by (s_c/s_P)^n, full orders
-    __shared__ V2 Rf[P + 1][W];      // conj R_k^l(d), full orders
-    __shared__ V2 Rh[8][NCP];        // R_k^l(d) of every child, l >= 0
+    using C = XferCfg<P, R>;
+    constexpr int NCP = C::NCP, W = C::W, CH = C::CH;
+    __shared__ V2 Mf[CH][3][C::ROWS];   // child multipole, scaled by (s_c/s_P)^n, full orders
+    __shared__ V2 Rf[CH][C::ROWS];      // conj R_k^l(d), full orders
     const int cell = c0 + blockIdx.x;
     if (cell >= c1) return;
     const int nc = nchild[cell];
@@ -148,62 +194,67 @@ __global__ __launch_bounds__((XferCfg<P>::THREADS)) void k_m2m(int c0, int c1, c
     const int f = child[cell];
     const float4 gp = geo[cell];
     const int tid = threadIdx.x;
-    const bool active = tid < 3 * NCP;
-    const int comp = active ? tid / NCP : 0;
-    int n = 0, m = 0;
-    decode_nm(active ? tid % NCP : 0, n, m);
     const R inv = R(1) / R(gp.w);
-    // the regular harmonics of the eight child offsets, one lane each (the
-    // recursion is serial; the children's run side by side)
-    if (tid < nc) {
-        const float4 gc = geo[f + tid];
-        V2 Rl[NCP];
-        regular_harmonics<P, R, V2>((R(gc.x) - R(gp.x)) * inv, (R(gc.y) - R(gp.y)) * inv,
-                                    (R(gc.z) - R(gp.z)) * inv, Rl);
+    const int ch = tid % CH, q = tid / CH;  // the high coefficients, whose sums are longest, share waves
+    const bool active = q < NCP;
+    int n = 0, m = 0;
+    decode_nm(active ? q : 0, n, m);
+    V2 acc[3];
 #pragma unroll
-        for (int q = 0; q < NCP; ++q) Rh[tid][q] = Rl[q];
-    }
-    V2 acc = V2{R(0), R(0)};
-    for (int k = 0; k < nc; ++k) {
-        const float4 gc = geo[f + k];
-        __syncthreads();
-        if (tid < NCP) {
-            int a, b;
-            decode_nm(tid, a, b);
-            const V2 v = Rh[k][tid];
-            Rf[a][P + b] = V2{v.x, -v.y};                                   // conj R^b
-            if (b > 0) Rf[a][P - b] = (b & 1) ? V2{-v.x, -v.y} : V2{v.x, v.y};  // conj R^{-b}
+    for (int c = 0; c < 3; ++c) acc[c] = V2{R(0), R(0)};
+    for (int k0 = 0; k0 < nc; k0 += CH) {
+        const int nk = min(CH, nc - k0);
+        if (k0 > 0) __syncthreads();
+        if (tid < C::M2M_HARM) {
+            const int k = tid % CH;
+            if (k < nk && tid / CH <= P) {
+                const float4 gc = geo[f + k0 + k];
+                harmonics_order<P, R, true>((R(gc.x) - R(gp.x)) * inv, (R(gc.y) - R(gp.y)) * inv,
+                                            (R(gc.z) - R(gp.z)) * inv, tid / CH, Rf[k]);
+            }
+        } else {
+            for (int i = tid - C::M2M_HARM; i < nk * 3 * NCP; i += C::M2M_THREADS - C::M2M_HARM) {
+                const int k = i / (3 * NCP), cc = i / NCP % 3;
+                int a, b;
+                decode_nm(i % NCP, a, b);
+                const auto v = Mexp[(size_t)(f + k0) * 3 * NCP + i];
+                const R sc = powr(R(geo[f + k0 + k].w) * inv, a);
+                const R vr = sc * R(v.x), vi = sc * R(v.y);
+                Mf[k][cc][a * W + P + b] = V2{vr, vi};
+                if (b > 0) Mf[k][cc][a * W + P - b] = (b & 1) ? V2{-vr, vi} : V2{vr, -vi};
+            }
         }
-        const R rt = R(gc.w) * inv;
-        for (int i = tid; i < 3 * NCP; i += C::THREADS) {
-            const int cc = i / NCP;
-            int a, b;
-            decode_nm(i % NCP, a, b);
-            const auto v = Mexp[((size_t)(f + k) * 3 + cc) * NCP + i % NCP];
-            const R sc = powr(rt, a);
-            const R vr = sc * R(v.x), vi = sc * R(v.y);
-            Mf[cc][a][P + b] = V2{vr, vi};
-            if (b > 0) Mf[cc][a][P - b] = (b & 1) ? V2{-vr, vi} : V2{vr, -vi};
-        }
         __syncthreads();
-        if (active) {
+        if (active && ch < nk) {
             // sum from high source degree n - kk to low: kk from 0 up
             for (int kk = 0; kk <= n; ++kk) {
                 const int nm = n - kk;
                 const int lo = max(-kk, m - nm), hi = min(kk, m + nm);
+                const V2 *r = &Rf[ch][kk * W + P], *v = &Mf[ch][0][nm * W + P + m];
                 for (int l = lo; l <= hi; ++l) {
-                    const V2 r = Rf[kk][P + l];
-                    const V2 v = Mf[comp][nm][P + m - l];
-                    acc.x = fmar(r.x, v.x, fmar(-r.y, v.y, acc.x));
-                    acc.y = fmar(r.x, v.y, fmar(r.y, v.x, acc.y));
+                    const V2 h = r[l];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        const V2 w = v[c * C::ROWS - l];
+                        acc[c].x = fmar(h.x, w.x, fmar(-h.y, w.y, acc[c].x));
+                        acc[c].y = fmar(h.x, w.y, fmar(h.y, w.x, acc[c].y));
+                    }
                 }
             }
         }
     }
-    if (active) {
-        auto &dst = Mexp[((size_t)cell * 3 + comp) * NCP + CIDX(n, m)];
-        dst.x = (S)acc.x;
-        dst.y = (S)acc.y;
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int o = CH / 2; o > 0; o >>= 1) {
+            acc[c].x += __shfl_xor(acc[c].x, o, CH);
+            acc[c].y += __shfl_xor(acc[c].y, o, CH);
+        }
+    if (active && ch < 3) {
+        const V2 v = ch == 0 ? acc[0] : ch == 1 ? acc[1] : acc[2];
+        auto &dst = Mexp[((size_t)cell * 3 + ch) * NCP + q];
+        dst.x = (S)v.x;
+        dst.y = (S)v.y;
     }
 }
 
@@ -505,67 +556,78 @@ void m2l_pair_plan(Ctx &c, const int *off, int64_t n) {
 }
 
 // ---------------------------------------------------------------------------
-// L2L: one work-group per child cell of one level, one thread per
-// (potential, coefficient k >= l >= 0) of the child (storage S, arithmetic R
-// as in M2M); parent expansion and R(d) staged as full-order tables.
+// L2L: one work-group per parent cell of one level, one thread per (child,
+// coefficient k >= l >= 0) for the three potentials (storage S, arithmetic R as in
+// M2M); the parent's expansion, staged once, and each child's R(d) as full-order
+// tables.
 //   Lt_k^l(c) = (s_c/s_P)^{k+1} sum_{n >= k, m} Lt_n^m(P) R_{n-k}^{m-l}(d),  d = (c - P)/s_P.
+// A work-group per child with a thread per potential: 0.27 ms for the five levels
+// of 80^3 particles at p = 10; now 0.12.
 // ---------------------------------------------------------------------------
 template <int P, class R, class S>
-__global__ __launch_bounds__((XferCfg<P>::THREADS)) void k_l2l(int c0, int c1, const int *parent, const float4 *geo,
-                                                               typename VT<S>::V2 *Lexp) {
+__global__ __launch_bounds__((XferCfg<P, R>::L2L_THREADS)) void k_l2l(int c0, int c1, const int *child,
+                                                                     const int *nchild, const float4 *geo,
+                                                                     typename VT<S>::V2 *Lexp) {
     using V2 = typename VT<R>::V2;
-    using C = XferCfg<P>;
+    using C = XferCfg<P, R>;
     constexpr int NCP = C::NCP, W = C::W;
-    __shared__ V2 Lf[3][P + 1][W];
-    __shared__ V2 Rf[P + 1][W];
+    __shared__ V2 Lf[3][C::ROWS];
+    __shared__ V2 Rf[8][C::ROWS];
     const int cell = c0 + blockIdx.x;
     if (cell >= c1) return;
-    const int par = parent[cell];
-    const float4 gp = geo[par], gc = geo[cell];
+    const int nc = nchild[cell];
+    if (nc == 0) return;
+    const int f = child[cell];
+    const float4 gp = geo[cell];
     const int tid = threadIdx.x;
     const R inv = R(1) / R(gp.w);
-    if (tid == 0) {
-        V2 Rl[NCP];
-        regular_harmonics<P, R, V2>((R(gc.x) - R(gp.x)) * inv, (R(gc.y) - R(gp.y)) * inv, (R(gc.z) - R(gp.z)) * inv,
-                                    Rl);
-#pragma unroll
-        for (int q = 0; q < NCP; ++q) {
+    if (tid < C::L2L_HARM) {
+        const int j = tid % 8;
+        if (j < nc && tid / 8 <= P) {
+            const float4 gc = geo[f + j];
+            harmonics_order<P, R, false>((R(gc.x) - R(gp.x)) * inv, (R(gc.y) - R(gp.y)) * inv,
+                                         (R(gc.z) - R(gp.z)) * inv, tid / 8, Rf[j]);
+        }
+    } else {
+        for (int i = tid - C::L2L_HARM; i < 3 * NCP; i += C::L2L_THREADS - C::L2L_HARM) {
+            const int cc = i / NCP;
             int a, b;
-            decode_nm(q, a, b);
-            const V2 v = Rl[q];
-            Rf[a][P + b] = v;
-            if (b > 0) Rf[a][P - b] = (b & 1) ? V2{-v.x, v.y} : V2{v.x, -v.y};
+            decode_nm(i % NCP, a, b);
+            const auto v = Lexp[(size_t)cell * 3 * NCP + i];
+            const R vr = R(v.x), vi = R(v.y);
+            Lf[cc][a * W + P + b] = V2{vr, vi};
+            if (b > 0) Lf[cc][a * W + P - b] = (b & 1) ? V2{-vr, vi} : V2{vr, -vi};
         }
     }
-    for (int i = tid; i < 3 * NCP; i += C::THREADS) {
-        const int cc = i / NCP;
-        int a, b;
-        decode_nm(i % NCP, a, b);
-        const auto v = Lexp[((size_t)par * 3 + cc) * NCP + i % NCP];
-        const R vr = R(v.x), vi = R(v.y);
-        Lf[cc][a][P + b] = V2{vr, vi};
-        if (b > 0) Lf[cc][a][P - b] = (b & 1) ? V2{-vr, vi} : V2{vr, -vi};
-    }
     __syncthreads();
-    if (tid >= 3 * NCP) return;
-    const int comp = tid / NCP;
+    const int ch = tid % 8, q = tid / 8;
+    if (q >= NCP || ch >= nc) return;
     int k, l;
-    decode_nm(tid % NCP, k, l);
-    V2 acc = V2{R(0), R(0)};
+    decode_nm(q, k, l);
+    V2 acc[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) acc[c] = V2{R(0), R(0)};
     for (int n = P; n >= k; --n) {
         const int dn = n - k;
         const int lo = max(-n, l - dn), hi = min(n, l + dn);
+        const V2 *L = &Lf[0][n * W + P], *r = &Rf[ch][dn * W + P - l];
         for (int m = lo; m <= hi; ++m) {
-            const V2 L = Lf[comp][n][P + m];
-            const V2 r = Rf[dn][P + m - l];
-            acc.x = fmar(L.x, r.x, fmar(-L.y, r.y, acc.x));
-            acc.y = fmar(L.x, r.y, fmar(L.y, r.x, acc.y));
+            const V2 h = r[m];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const V2 w = L[c * C::ROWS + m];
+                acc[c].x = fmar(w.x, h.x, fmar(-w.y, h.y, acc[c].x));
+                acc[c].y = fmar(w.x, h.y, fmar(w.y, h.x, acc[c].y));
+            }
         }
     }
-    const R sc = powr(R(gc.w) * inv, k + 1);
-    auto &dst = Lexp[((size_t)cell * 3 + comp) * NCP + tid % NCP];
-    dst.x = (S)((R)dst.x + sc * acc.x);
-    dst.y = (S)((R)dst.y + sc * acc.y);
+    const R sc = powr(R(geo[f + ch].w) * inv, k + 1);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        auto &dst = Lexp[((size_t)(f + ch) * 3 + c) * NCP + q];
+        dst.x = (S)((R)dst.x + sc * acc[c].x);
+        dst.y = (S)((R)dst.y + sc * acc[c].y);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -754,7 +816,7 @@ static void far_field_t(Ctx &c) {
     VFMM_LAUNCH_CHECK();
     for (int l = c.depth - 1; l >= 0; --l) {
         const int c0 = c.lvl_off[l], c1 = c.lvl_off[l + 1];
-        k_m2m<P, RA, S><<<c1 - c0, XferCfg<P>::THREADS, 0, s>>>(c0, c1, c.c_child.as<int>(), c.c_nchild.as<int>(),
+        k_m2m<P, RA, S><<<c1 - c0, XferCfg<P, RA>::M2M_THREADS, 0, s>>>(c0, c1, c.c_child.as<int>(), c.c_nchild.as<int>(),
                                                 c.c_geo.as<float4>(), c.Mexp.as<V2>());
         VFMM_LAUNCH_CHECK();
     }
@@ -789,10 +851,11 @@ static void far_field_t(Ctx &c) {
     }
     c.record(2 * PH_M2L + 1);
     c.record(2 * PH_L2L_L2P);
-    for (int l = 1; l <= c.depth; ++l) {
+    for (int l = 0; l < c.depth; ++l) {  // from the cells of level l to their children
         const int c0 = c.lvl_off[l], c1 = c.lvl_off[l + 1];
-        k_l2l<P, RA, S><<<c1 - c0, XferCfg<P>::THREADS, 0, s>>>(c0, c1, c.c_parent.as<int>(), c.c_geo.as<float4>(),
-                                                c.Lexp.as<V2>());
+        k_l2l<P, RA, S><<<c1 - c0, XferCfg<P, RA>::L2L_THREADS, 0, s>>>(c0, c1, c.c_child.as<int>(),
+                                                                        c.c_nchild.as<int>(), c.c_geo.as<float4>(),
+                                                                        c.Lexp.as<V2>());
         VFMM_LAUNCH_CHECK();
     }
     k_l2p<P, S><<<c.nleaves, 64, 0, s>>>(c.leaves.as<int>(), c.c_start.as<int>(), c.c_count.as<int>(),

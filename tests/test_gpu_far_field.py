@@ -5,6 +5,7 @@ Tolerance: the two differ by float32 rounding alone, for which the near field's 
 import numpy as np
 import pytest
 
+import oracle
 import workloads as wl
 from parity_util import check
 
@@ -63,3 +64,14 @@ def test_groups_by_operator_match_one_at_a_time(opt):
     tol = 1e-4 if opt.get("m2l_form") == 3 else 1e-5
     check("%s, %d translations, u" % (opt, s0["m2l_entries"]), u0, u1, tol, 1e-3)
     check("%s dalpha" % opt, d0, d1, tol, 1e-3)
+
+
+@pytest.mark.parametrize("precision", [0, 1, 2])
+@pytest.mark.parametrize("p", [8, 10, 12])
+def test_deep_tree_of_few_children(p, precision):
+    """Parents of one to eight children over many levels, against the direct sum (the evaluation's 1e-4)."""
+    case = _clustered(3000, 9)
+    u, d, _ = _run(case, p=p, ncrit=4, theta=0.4, precision=precision)
+    ref = oracle.direct(case)
+    check("p=%d precision %d u" % (p, precision), u, ref["u"], 1e-4, 1e-3)
+    check("p=%d precision %d dalpha" % (p, precision), d, ref["da_t"], 1e-4, 1e-3)
