@@ -14,7 +14,8 @@ void Ctx::release_all() {
     DevBuf *bufs[] = {&bpart, &bres, &keyA, &keyB, &valA, &valB, &hist, &scanA, &scanB, &scanC, &perm, &rec, &rec64,
                       &c_start, &c_count, &c_parent, &c_child, &c_nchild, &c_level, &c_geo, &c_rad, &c_lo, &c_hi,
                       &c_tmp, &leaves, &frA, &frB, &tcnt, &m2l_raw, &p2p_raw, &lkey, &lkey2, &lval, &lval2,
-                      &m2l_off, &m2l_src, &p2p_off, &p2p_ent, &p2p_sh, &recp, &tgt, &c_nsrc, &part, &blocks, &pblocks, &pblong, &mb_kord, &mb_inv, &mb_koff, &mb_ksec, &mb_dst, &mb_coff, &mb_roff, &mb_rsrc, &mb_cols, &items, &item_out, &pairs64, &Mexp, &Lexp, &lat_op, &far_u,
+                      &m2l_off, &m2l_src, &p2p_off, &p2p_ent, &p2p_sh, &recp, &tgt, &c_nsrc, &part, &blocks, &pblocks, &pblong, &mb_kord, &mb_inv, &mb_koff, &mb_ksec, &mb_dst, &mb_coff, &mb_roff, &mb_rsrc, &mb_cols, &mb_toff, &mb_kgroups,
+                      &mb_kslots, &mb_kitem, &mb_fill, &mb_low, &mb_lowkid, &items, &item_out, &pairs64, &Mexp, &Lexp, &lat_op, &far_u,
                       &far_da, &near, &dsurf, &rk, &m2l_tgt, &m2l_parts, &m2l_partial, &mb_eq, &mb_flag, &mb_pos, &mb_kid, &mb_ukey,
                       &mb_tab, &mb_bcells, &mb_ent, &mb_groups, &mb_blk, &mb_items, &mb_mr, &mb_partial, &mb_cls, &mb_cellbs, &mb_gcnt, &mb_gid, &mb_goff, &mb_gcur, &mb_bkt, &mb_order, &mb_slots, &gpart, &pid, &pbox, &poff, &tune_ref, &tune_out, &tune_part, &rbf, &spec};
     for (DevBuf *b : bufs) b->release();
@@ -886,7 +887,7 @@ vfmm_status vfmm_get_stats(const vfmm_ctx *ctx, vfmm_stats *out) {
     if (c.m2lb_ok) {
         out->m2l_keys = c.mb_nkeys;
         out->m2l_groups = c.mb_ngroups;
-        out->m2l_items = c.mb_nitems;
+        out->m2l_items = c.mb_nitems + (c.mb_keyed ? c.mb_kitems : 0);
         out->m2l_split = c.mb_x6 ? (c.mb_nsplit == 2 ? 2 : 1) : 0;
     }
     out->overfull_leaves = c.overfull_leaves;

@@ -92,9 +92,13 @@ struct Ctx {
     unsigned m2lbk_lds_set = 0;          // keyed split kernels (degree, parts) whose dynamic LDS has been allowed
     int mb_nblk = 0, mb_nkeys = 0, mb_ngroups = 0, mb_nitems = 0;
     int mb_fmt[4] = {0, 0, 0, 0};
-    bool mb_keyed = false;               // the plan's groups are by operator alone (m2lb_plan_keyed)
-    int64_t mb_ncols = 0, mb_nrest = 0;  // its translations, and those left to the per-pair kernel
-    DevBuf mb_kord, mb_inv, mb_koff, mb_ksec, mb_dst, mb_coff, mb_roff, mb_rsrc, mb_cols;
+    // translations grouped by operator alone (keyed_lists): all that are batched, or those of
+    // blocks' thinly filled groups
+    bool mb_keyed = false;
+    int64_t mb_ncols = 0, mb_nrest = 0;  // these translations, and those left to the per-pair kernel
+    int mb_kitems = 0, mb_kng = 0;       // their work items and groups
+    DevBuf mb_kord, mb_inv, mb_koff, mb_ksec, mb_toff, mb_dst, mb_coff, mb_roff, mb_rsrc, mb_cols, mb_kgroups,
+        mb_kslots, mb_kitem, mb_fill, mb_low, mb_lowkid;
     DevBuf mb_eq, mb_flag, mb_pos, mb_kid, mb_ukey, mb_tab, mb_bcells, mb_ent, mb_groups, mb_blk, mb_items,
         mb_mr, mb_partial, mb_cls, mb_cellbs, mb_gcnt, mb_gid, mb_goff, mb_gcur, mb_bkt, mb_order, mb_slots;
     // outputs of the far field, sorted order: float [3n] each
@@ -176,6 +180,8 @@ void gather_strengths(Ctx &c, const float *ax, const float *ay, const float *az,
 void gather_records64(Ctx &c, const float *ax, const float *ay, const float *az);
 void partition_sources(Ctx &c, int64_t n_src);
 void build_m2l_csr(Ctx &c);
+// CSR offsets (ncells + 1) of a raw (tgt, src, img, -) list; leaves the stable order by target in lval
+void csr_by_target(Ctx &c, const int4 *raw, int64_t n, DevBuf &off);
 // off[t] = first of the n sorted keys >= t, t = 0 .. nc
 void csr_bounds(Ctx &c, const uint64_t *key, int64_t n, int nc, int *off);
 void p2p_prepare(Ctx &c);

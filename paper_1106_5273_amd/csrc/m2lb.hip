@@ -280,7 +280,8 @@ __global__ __launch_bounds__(TPB) void k_gk_groups(int64_t T, const int *cnt, co
     const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
     if (i >= T) return;
     cursor[i] = 0;
-    if (cnt[i] > 0) groups[gid[i]] = make_int4((int)(i % nkeys), eoff ? eoff[i] : 0, cnt[i], (int)(i / nkeys));
+    // without entry lists (eoff null): the row of its slot table
+    if (cnt[i] > 0) groups[gid[i]] = make_int4((int)(i % nkeys), eoff ? eoff[i] : gid[i], cnt[i], (int)(i / nkeys));
 }
 
 __global__ __launch_bounds__(TPB) void k_gk_scatter(int64_t n, const int4 *raw, const int2 *cell_bs, const int *kid,
@@ -770,8 +771,9 @@ __global__ __launch_bounds__(MbxCfg<P>::WAVES * 64) void k_m2lb_x6(const int4 *_
     // current group's until its last potential, then the next group's)
     int scol[X::F4];
     auto load_cols = [&](int g) {
+        const int row = __builtin_amdgcn_readfirstlane(groups[g].y);
 #pragma unroll
-        for (int i = 0; i < X::F4; ++i) scol[i] = slots[(size_t)g * 64 + (tid + NT * i) / (C::RP / 4)];
+        for (int i = 0; i < X::F4; ++i) scol[i] = slots[(size_t)row * 64 + (tid + NT * i) / (C::RP / 4)];
     };
     auto src4 = [&](int i, int c) {
         return reinterpret_cast<const vf4 *>(Mr + ((size_t)scol[i] * 3 + c) * C::RP +
@@ -985,7 +987,7 @@ __global__ __launch_bounds__(COL_GROUPS * 3 * NRP(P) / 2) void k_m2lb_columns(co
     }
 }
 
-// ---- plan of the keyed form ----
+// ---- lists of the keyed form ----
 // keys of fewer translations than this go to the per-pair kernel: their operator
 // and their group cost what about ten translations one at a time cost
 static constexpr int KEYED_MIN = 10;
@@ -998,18 +1000,20 @@ __global__ __launch_bounds__(TPB) void k_kid_keys(int64_t n, const int *kid, uin
 }
 
 // per key: its groups of 64, whether it is used, its translations that are left out
-__global__ __launch_bounds__(TPB) void k_key_sections(int nkeys, const int *koff, int *sec) {
+__global__ __launch_bounds__(TPB) void k_key_sections(int nkeys, int least, const int *koff, int *sec) {
     const int k = blockIdx.x * TPB + threadIdx.x;
     if (k >= nkeys) return;
     const int cnt = koff[k + 1] - koff[k];
-    const bool used = cnt >= KEYED_MIN;
+    const bool used = cnt >= least;
     sec[k] = used ? (cnt + 63) / 64 : 0;
     sec[nkeys + k] = used;
     sec[2 * nkeys + k] = used ? 0 : cnt;
 }
 
-__global__ void k_key_totals(const int *sec, const int *off, int nkeys, int *out) {
-    for (int k = 0; k < 3; ++k) out[k] = off[(k + 1) * nkeys - 1] + sec[(k + 1) * nkeys - 1] - off[k * nkeys];
+// totals of `sections` sections of n counts from their exclusive scan
+__global__ void k_section_totals(const int *cnt, const int *off, int n, int sections, int *out) {
+    for (int k = 0; k < sections; ++k)
+        out[k] = off[(size_t)(k + 1) * n - 1] + cnt[(size_t)(k + 1) * n - 1] - off[(size_t)k * n];
 }
 
 // entry i of the list by target: whether it is left out, and its position from its raw index
@@ -1032,13 +1036,16 @@ __global__ __launch_bounds__(TPB) void k_rest_offsets(int nc, int64_t n, int nre
     coff[t] = o - r;
 }
 
-__global__ __launch_bounds__(TPB) void k_rest_gather(int64_t n, const int *flag, const int *pos, const int2 *src,
-                                                     int2 *rsrc) {
+__global__ __launch_bounds__(TPB) void k_rest_gather(int64_t n, const int *flag, const int *pos, const uint32_t *order,
+                                                     const int4 *raw, int2 *rsrc) {
     const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    if (i < n && flag[i]) rsrc[pos[i]] = src[i];
+    if (i >= n || !flag[i]) return;
+    const int4 e = raw[order[i]];
+    rsrc[pos[i]] = make_int2(e.y, e.z);
 }
 
-// a translation per thread, in key order: its group's key, source and column
+// a translation per thread, in key order: its group's key (renumbered if used_key
+// takes the used keys), its source and its column
 __global__ __launch_bounds__(TPB) void k_key_slots(int64_t n, const uint32_t *kord, const int *kid, const int *koff,
                                                    int nkeys, const int *sec, const int *off, const int4 *raw,
                                                    const int *inv, const int *pos, const uint64_t *ukey,
@@ -1050,9 +1057,9 @@ __global__ __launch_bounds__(TPB) void k_key_slots(int64_t n, const uint32_t *ko
     if (!sec[nkeys + k]) return;
     const int r = (int)j - koff[k];
     const int g = off[k] + r / 64;
-    const int u = off[nkeys + k] - off[nkeys];
-    if (r == 0) used_key[u] = ukey[k];
-    if (r % 64 == 0) groups[g] = make_int4(u, 0, 0, 0);
+    const int u = used_key ? off[nkeys + k] - off[nkeys] : k;
+    if (r == 0 && used_key) used_key[u] = ukey[k];
+    if (r % 64 == 0) groups[g] = make_int4(u, g, 0, 0);
     const int i = inv[e];
     slots[(size_t)g * 64 + r % 64] = raw[e].y;
     dsts[(size_t)g * 64 + r % 64] = i - pos[i];
@@ -1063,37 +1070,78 @@ __global__ __launch_bounds__(TPB) void k_key_items(int nitems, int per, int ng, 
     if (i < nitems) items[i] = make_int4(0, i * per, min(ng, (i + 1) * per), 0);
 }
 
+// ---- the thinly filled groups of blocks ----
+// groups by block of fewer translations than this, where enough of them are, give
+// theirs to groups by operator
+static constexpr int LOW_FILL = 24;
+static constexpr int FULL_FILL = 56;  // groups filled so far on average are not looked at
+
+// per group (a wave each): whether it stays, and its translations if it does not
+__global__ __launch_bounds__(TPB) void k_group_fill(int ng, int nc, const int *slots, int *out) {
+    const int g = blockIdx.x * (TPB / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (g >= ng) return;
+    const int fill = __popcll(__ballot(slots[(size_t)g * 64 + lane] != nc));
+    if (lane != 0) return;
+    out[g] = fill >= LOW_FILL;
+    out[ng + g] = fill >= LOW_FILL ? 0 : fill;
+}
+
+// the groups that stay, and the translations (target, source, -, -) of the others with their keys
+__global__ __launch_bounds__(TPB) void k_group_split(int ng, int nc, const int4 *groups, const int *slots,
+                                                     const int *bcells, const int *cnt, const int *off, int4 *stay,
+                                                     int4 *low, int *lowkid) {
+    const int g = blockIdx.x * (TPB / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (g >= ng) return;
+    const int4 gr = groups[g];
+    if (cnt[g]) {
+        if (lane == 0) stay[off[g]] = gr;
+        return;
+    }
+    const int src = slots[(size_t)g * 64 + lane];
+    const unsigned long long bal = __ballot(src != nc);
+    if (src == nc) return;
+    const int j = off[ng + g] - off[ng] + __popcll(bal & ((1ull << lane) - 1));
+    low[j] = make_int4(bcells[(size_t)gr.w * 64 + lane], src, 0, 0);
+    lowkid[j] = gr.x;
+}
+
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-// The keyed form of the plan, where the targets of a block share too few
-// operators to fill groups of 64 (irregular trees): the groups take the
-// translations of one operator whatever their targets, at the price of writing
-// every translation's result and reading it again for its target's sum; rare
-// operators go to the per-pair kernel.  Taken where the costs below, in ns as
-// measured at p = 10 (a group 32, a column's bytes at 5 TB/s 0.6, an operator's
-// bytes at 4.2 TB/s 23, a pair 6; scaled by their work to other degrees), say so:
+// Groups by operator, where the targets of a block share too few to fill groups
+// of 64 (irregular trees): they take the translations of one operator whatever
+// their targets, at the price of writing every translation's result and reading it
+// again for its target's sum.  Either for all translations, operators of fewer
+// than KEYED_MIN going to the per-pair kernel, or only for those of the blocks'
+// groups filled below LOW_FILL, the others staying.  The plan takes the form of
+// least cost, in ns as measured at p = 10 and scaled by their work to other
+// degrees: a group 32 (by block, with its partial sums, a tenth more), a column's
+// bytes at 5 TB/s 0.6, an operator's bytes at 4.2 TB/s 23, a pair one at a time 6.
 // 1.8 million translations of 29,744 operators (100,003 clustered particles)
 // filled 162,850 groups by block to a sixth, 32,000 by key: 5.75 -> 2.43 ms, and
-// the plan 0.33 ms shorter with 6,800 operators left; a jittered 80^3 lattice, 37
-// of 64 filled by block, stays there, and so do 64 rings' 70,516 translations one
-// at a time (0.29 ms; by key 0.16, for a plan of 0.17 more).
+// the plan 0.33 ms shorter with 6,800 operators left.  A jittered 80^3 lattice, 37
+// of 64 filled on average, gives up a fifth of its groups and 4 % of its
+// translations: 11.4 -> 10.4 ms, for a plan of 0.3 more.  64 rings' 70,516 translations stay with the
+// per-pair kernel (0.29 ms; by key 0.16, for a plan of 0.17 more).
 static constexpr size_t MAX_COLUMN_BYTES = size_t(8) << 30;
 
+struct M2lCosts {
+    double group, col, key, pair;
+};
+
 template <int P>
-static bool m2lb_plan_keyed(Ctx &c, int64_t n, int nkeys, int ng_block, const KeyFmt &f) {
+static M2lCosts m2l_costs() {
     using C = MbCfg<P>;
+    return {(double)C::RTI * (C::RP / 32), 24.0 * C::RP / 5000.0, 4.0 * (double)C::OPX / 4200.0,
+            6.0 * std::pow(C::R / 121.0, 1.5)};
+}
+
+// Key order, sections and their totals h = (groups, used keys, left out) of n translations with key ids kid.
+static void keyed_sections(Ctx &c, int64_t n, const int *kid, int nkeys, int least, int h[3]) {
     hipStream_t s = c.stream;
-    const double t_group = (double)C::RTI * (C::RP / 32), t_col = 24.0 * C::RP / 5000.0;
-    const double t_key = 4.0 * (double)C::OPX / 4200.0, t_pair = 6.0 * std::pow(C::R / 121.0, 1.5);
-    const double t_plan = 2e5 + 0.11 * (double)n;  // twenty launches, two sorts
-    const bool by_block = n >= (int64_t)MIN_GROUP_FILL * ng_block;
-    const double other = by_block ? 1.1 * t_group * ng_block + t_key * nkeys : t_pair * (double)n;
-    if (t_plan + t_col * (double)n + t_group * (double)n / 64 > other) return false;  // whatever the keys are
     c.mb_koff.ensure(sizeof(int) * ((size_t)nkeys + 1));
     c.mb_ksec.ensure(sizeof(int) * 6 * (size_t)nkeys);
-    int *koff = c.mb_koff.as<int>(), *sec = c.mb_ksec.as<int>(), *off = sec + 3 * (size_t)nkeys;
-    const int *kid = c.mb_kid.as<int>();
+    int *sec = c.mb_ksec.as<int>(), *off = sec + 3 * (size_t)nkeys;
     c.lkey.ensure(sizeof(uint64_t) * n);
     c.lval.ensure(sizeof(uint32_t) * n);
     k_kid_keys<<<cdiv(n, TPB), TPB, 0, s>>>(n, kid, c.lkey.as<uint64_t>(), c.lval.as<uint32_t>());
@@ -1101,72 +1149,132 @@ static bool m2lb_plan_keyed(Ctx &c, int64_t n, int nkeys, int ng_block, const Ke
     int kbits = 1;
     while ((1 << kbits) < nkeys) ++kbits;
     sort_pairs_u64(c, c.lkey, c.lval, c.lkey2, c.lval2, n, kbits);
-    csr_bounds(c, c.lkey.as<uint64_t>(), n, nkeys, koff);
-    k_key_sections<<<cdiv(nkeys, TPB), TPB, 0, s>>>(nkeys, koff, sec);
+    csr_bounds(c, c.lkey.as<uint64_t>(), n, nkeys, c.mb_koff.as<int>());
+    k_key_sections<<<cdiv(nkeys, TPB), TPB, 0, s>>>(nkeys, least, c.mb_koff.as<int>(), sec);
     VFMM_LAUNCH_CHECK();
     scan_excl_i32(c, sec, off, 3LL * nkeys);
-    k_key_totals<<<1, 1, 0, s>>>(sec, off, nkeys, pinned_ints(c));
+    k_section_totals<<<1, 1, 0, s>>>(sec, off, nkeys, 3, pinned_ints(c));
     VFMM_LAUNCH_CHECK();
-    int h[3];
     sync_ints(c, 3, h);
-    const int ng = h[0], nused = h[1], nrest = h[2];
-    const int64_t ncols = n - nrest;
-    const double keyed = t_plan + t_group * ng + t_col * (double)ncols + t_key * nused + t_pair * nrest;
-    const size_t tab_bytes = sizeof(uint32_t) * C::OPX * (size_t)nused;
-    if (keyed > other || ng == 0 || tab_bytes > MAX_TABLE_BYTES ||
-        sizeof(float) * 3 * C::RP * (size_t)ncols > MAX_COLUMN_BYTES)
-        return false;
-    std::swap(c.lval, c.mb_kord);  // kept while the list by target is sorted
-    c.m2l_csr = false;
-    build_m2l_csr(c);              // leaves the list's order in lval
+}
+
+// Groups, slots and columns after keyed_sections; used_key (may be null) takes the used keys.
+static void keyed_lists(Ctx &c, int64_t n, const int4 *raw, const int *kid, int nkeys, const int h[3],
+                        uint64_t *used_key) {
+    hipStream_t s = c.stream;
+    const int ng = h[0], nrest = h[2];
+    const int *koff = c.mb_koff.as<int>(), *sec = c.mb_ksec.as<int>(), *off = sec + 3 * (size_t)nkeys;
+    std::swap(c.lval, c.mb_kord);            // kept while the list by target is sorted
+    csr_by_target(c, raw, n, c.mb_toff);     // leaves that order in lval
     c.mb_inv.ensure(sizeof(int) * n);
+    c.mb_flag.ensure(sizeof(int) * (n + 1));
+    c.mb_pos.ensure(sizeof(int) * (n + 1));
     c.mb_coff.ensure(sizeof(int) * ((size_t)c.ncells + 1));
     c.mb_roff.ensure(sizeof(int) * ((size_t)c.ncells + 1));
     c.mb_rsrc.ensure(sizeof(int2) * (size_t)std::max(nrest, 1));
-    c.mb_groups.ensure(sizeof(int4) * (size_t)ng);
-    c.mb_slots.ensure(sizeof(int) * 64 * (size_t)ng);
+    c.mb_kgroups.ensure(sizeof(int4) * (size_t)ng);
+    c.mb_kslots.ensure(sizeof(int) * 64 * (size_t)ng);
     c.mb_dst.ensure(sizeof(int) * 64 * (size_t)ng);
     int *flag = c.mb_flag.as<int>(), *pos = c.mb_pos.as<int>(), *inv = c.mb_inv.as<int>();
     k_rest_flags<<<cdiv(n, TPB), TPB, 0, s>>>(n, c.lval.as<uint32_t>(), kid, sec + nkeys, flag, inv);
     VFMM_LAUNCH_CHECK();
     scan_excl_i32(c, flag, pos, n);
-    k_rest_offsets<<<cdiv(c.ncells + 1, TPB), TPB, 0, s>>>(c.ncells, n, nrest, c.m2l_off.as<int>(), pos,
+    k_rest_offsets<<<cdiv(c.ncells + 1, TPB), TPB, 0, s>>>(c.ncells, n, nrest, c.mb_toff.as<int>(), pos,
                                                            c.mb_coff.as<int>(), c.mb_roff.as<int>());
     VFMM_LAUNCH_CHECK();
     if (nrest > 0) {
-        k_rest_gather<<<cdiv(n, TPB), TPB, 0, s>>>(n, flag, pos, c.m2l_src.as<int2>(), c.mb_rsrc.as<int2>());
+        k_rest_gather<<<cdiv(n, TPB), TPB, 0, s>>>(n, flag, pos, c.lval.as<uint32_t>(), raw, c.mb_rsrc.as<int2>());
         VFMM_LAUNCH_CHECK();
         m2l_pair_plan(c, c.mb_roff.as<int>(), nrest);
     }
-    k_fill_i32<<<cdiv(64 * (int64_t)ng, TPB), TPB, 0, s>>>(64 * (int64_t)ng, c.ncells, c.mb_slots.as<int>());
+    k_fill_i32<<<cdiv(64 * (int64_t)ng, TPB), TPB, 0, s>>>(64 * (int64_t)ng, c.ncells, c.mb_kslots.as<int>());
     VFMM_LAUNCH_CHECK();
     k_fill_i32<<<cdiv(64 * (int64_t)ng, TPB), TPB, 0, s>>>(64 * (int64_t)ng, -1, c.mb_dst.as<int>());
     VFMM_LAUNCH_CHECK();
-    c.lkey.ensure(sizeof(uint64_t) * (size_t)nused);
-    k_key_slots<<<cdiv(n, TPB), TPB, 0, s>>>(n, c.mb_kord.as<uint32_t>(), kid, koff, nkeys, sec, off,
-                                              c.m2l_raw.as<int4>(), inv, pos, c.mb_ukey.as<uint64_t>(),
-                                              c.mb_groups.as<int4>(), c.mb_slots.as<int>(), c.mb_dst.as<int>(),
-                                              c.lkey.as<uint64_t>());
+    k_key_slots<<<cdiv(n, TPB), TPB, 0, s>>>(n, c.mb_kord.as<uint32_t>(), kid, koff, nkeys, sec, off, raw, inv, pos,
+                                              c.mb_ukey.as<uint64_t>(), c.mb_kgroups.as<int4>(),
+                                              c.mb_kslots.as<int>(), c.mb_dst.as<int>(), used_key);
     VFMM_LAUNCH_CHECK();
-    // a few items per CU: one operator's groups stay together, the last round is short
+    // several items per CU: one operator's groups stay together, the last round is short
     const int per = std::max(1, std::min(ITEM_GROUPS, ng / 2048));
-    c.mb_nitems = (int)cdiv(ng, per);
-    c.mb_items.ensure(sizeof(int4) * (size_t)c.mb_nitems);
-    k_key_items<<<cdiv(c.mb_nitems, TPB), TPB, 0, s>>>(c.mb_nitems, per, ng, c.mb_items.as<int4>());
+    c.mb_kitems = (int)cdiv(ng, per);
+    c.mb_kitem.ensure(sizeof(int4) * (size_t)c.mb_kitems);
+    k_key_items<<<cdiv(c.mb_kitems, TPB), TPB, 0, s>>>(c.mb_kitems, per, ng, c.mb_kitem.as<int4>());
     VFMM_LAUNCH_CHECK();
+    c.mb_keyed = true;
+    c.mb_kng = ng;
+    c.mb_ncols = n - nrest;
+    c.mb_nrest = nrest;
+}
+
+// All translations by operator, if that costs less than `other`.
+template <int P>
+static bool m2lb_plan_keyed(Ctx &c, int64_t n, int nkeys, double other, const KeyFmt &f) {
+    using C = MbCfg<P>;
+    const M2lCosts t = m2l_costs<P>();
+    const double plan = 2e5 + 0.11 * (double)n;  // twenty launches, two sorts
+    if (plan + t.col * (double)n + t.group * (double)n / 64 > other) return false;  // whatever the keys are
+    int h[3];
+    keyed_sections(c, n, c.mb_kid.as<int>(), nkeys, KEYED_MIN, h);
+    const int ng = h[0], nused = h[1], nrest = h[2];
+    const int64_t ncols = n - nrest;
+    const size_t tab_bytes = sizeof(uint32_t) * C::OPX * (size_t)nused;
+    if (ng == 0 || tab_bytes > MAX_TABLE_BYTES || sizeof(float) * 3 * C::RP * (size_t)ncols > MAX_COLUMN_BYTES ||
+        plan + t.group * ng + t.col * (double)ncols + t.key * nused + t.pair * nrest > other)
+        return false;
+    c.mb_low.ensure(sizeof(uint64_t) * (size_t)nused);
+    keyed_lists(c, n, c.m2l_raw.as<int4>(), c.mb_kid.as<int>(), nkeys, h, c.mb_low.as<uint64_t>());
     c.mb_tab.ensure(tab_bytes);
-    k_m2lb_optab<P, 1><<<nused, 256, 0, s>>>(nused, c.lkey.as<uint64_t>(), f, c.mb_tab.as<float>());
+    k_m2lb_optab<P, 1><<<nused, 256, 0, c.stream>>>(nused, c.mb_low.as<uint64_t>(), f, c.mb_tab.as<float>());
     VFMM_LAUNCH_CHECK();
     c.mb_x6 = true;
-    c.mb_keyed = true;
     c.mb_nsplit = c.prm.m2l_form == 3 ? 2 : 3;
     c.mb_nkeys = nused;
     c.mb_nblk = 0;
+    c.mb_nitems = 0;
     c.mb_ngroups = ng;
-    c.mb_ncols = ncols;
-    c.mb_nrest = nrest;
     c.m2lb_ok = true;
     return true;
+}
+
+// The blocks' ng groups (mb_groups, mb_slots) and how they are to run: leaves true
+// where a plan by operator alone has taken over; else takes the thinly filled
+// groups out (ng is then what stays) if that pays.
+template <int P>
+static bool m2lb_fill_plan(Ctx &c, int64_t n, int nkeys, int &ng, const KeyFmt &f) {
+    using C = MbCfg<P>;
+    hipStream_t s = c.stream;
+    const M2lCosts t = m2l_costs<P>();
+    c.mb_fill.ensure(sizeof(int) * 4 * (size_t)ng);
+    int *cnt = c.mb_fill.as<int>(), *off = cnt + 2 * (size_t)ng;
+    k_group_fill<<<cdiv(ng, TPB / 64), TPB, 0, s>>>(ng, c.ncells, c.mb_slots.as<int>(), cnt);
+    VFMM_LAUNCH_CHECK();
+    scan_excl_i32(c, cnt, off, 2LL * ng);
+    k_section_totals<<<1, 1, 0, s>>>(cnt, off, ng, 2, pinned_ints(c));
+    VFMM_LAUNCH_CHECK();
+    int h2[2];
+    sync_ints(c, 2, h2);
+    const int stay = h2[0], nlow = h2[1];
+    const double block = 1.1 * t.group * ng, tab = t.key * nkeys;
+    const double split = 1.1 * t.group * stay + t.group * (nlow / 64.0 + std::min(nkeys, nlow) / 2.0) +
+                         (t.col + 0.15) * nlow + 3.5e5;
+    const bool low = stay > 0 && nlow > 0 && split < block &&
+                     sizeof(float) * 3 * C::RP * (size_t)nlow <= MAX_COLUMN_BYTES;
+    if (m2lb_plan_keyed<P>(c, n, nkeys, (low ? split : block) + tab, f)) return true;
+    if (!low) return false;
+    c.mb_low.ensure(sizeof(int4) * (size_t)nlow);
+    c.mb_lowkid.ensure(sizeof(int) * (size_t)nlow);
+    c.mb_kgroups.ensure(sizeof(int4) * (size_t)stay);
+    k_group_split<<<cdiv(ng, TPB / 64), TPB, 0, s>>>(ng, c.ncells, c.mb_groups.as<int4>(), c.mb_slots.as<int>(),
+                                                     c.mb_bcells.as<int>(), cnt, off, c.mb_kgroups.as<int4>(),
+                                                     c.mb_low.as<int4>(), c.mb_lowkid.as<int>());
+    VFMM_LAUNCH_CHECK();
+    std::swap(c.mb_groups, c.mb_kgroups);
+    ng = stay;
+    int h[3];
+    keyed_sections(c, nlow, c.mb_lowkid.as<int>(), nkeys, 1, h);
+    keyed_lists(c, nlow, c.mb_low.as<int4>(), c.mb_lowkid.as<int>(), nkeys, h, nullptr);
+    return false;
 }
 
 // Product form of the batched M2L: split bf16 products when asked for
@@ -1311,14 +1419,21 @@ static void m2lb_plan_p(Ctx &c) {
     VFMM_LAUNCH_CHECK();
     scan_excl_i32(c, gcur, gid, T);
     read_ints(c, {gid + T - 1, gcur + T - 1}, h2);
-    const int ng = h2[0] + h2[1];
+    int ng = h2[0] + h2[1];
     // A group costs a full 64-target operator product whether its targets are
     // all present or not; measured on gfx950 a group costs about as much as
     // 6-7 translations of the per-pair kernel, so sparse groups (irregular
     // trees: many offsets, few targets sharing each) go to the per-pair M2L.
-    if constexpr (C::X6)
-        if (c.prm.m2l_mode == 0 && x6 && n < 32 * (int64_t)ng && m2lb_plan_keyed<P>(c, n, nkeys, ng, f)) return;
-    if (c.prm.m2l_mode == 0 && n < (int64_t)MIN_GROUP_FILL * ng) return;
+    if (c.prm.m2l_mode == 0 && n < (int64_t)MIN_GROUP_FILL * ng) {
+        if constexpr (C::X6)
+            if (x6) m2lb_plan_keyed<P>(c, n, nkeys, m2l_costs<P>().pair * (double)n, f);
+        return;
+    }
+    if constexpr (C::X6)  // so thin that the groups by block need not be laid out to tell
+        if (c.prm.m2l_mode == 0 && x6 && n < LOW_FILL * (int64_t)ng) {
+            const M2lCosts t = m2l_costs<P>();
+            if (m2lb_plan_keyed<P>(c, n, nkeys, 1.1 * t.group * ng + t.key * nkeys, f)) return;
+        }
     c.mb_groups.ensure(sizeof(int4) * ng);
     k_gk_groups<<<cdiv(T, TPB), TPB, 0, s>>>(T, gcnt, gid, x6 ? nullptr : goff, nkeys, c.mb_groups.as<int4>(), gcur);
     VFMM_LAUNCH_CHECK();
@@ -1329,6 +1444,8 @@ static void m2lb_plan_p(Ctx &c) {
         k_gk_slots<<<cdiv(n, TPB), TPB, 0, s>>>(n, c.m2l_raw.as<int4>(), c.mb_cellbs.as<int2>(), c.mb_kid.as<int>(),
                                                  nkeys, gid, c.mb_slots.as<int>());
         VFMM_LAUNCH_CHECK();
+        if constexpr (C::X6)
+            if (c.prm.m2l_mode == 0 && n < FULL_FILL * (int64_t)ng && m2lb_fill_plan<P>(c, n, nkeys, ng, f)) return;
     } else {  // the float32-product kernel reads each group's entry list
         c.mb_ent.ensure(sizeof(int2) * n);
         k_gk_scatter<<<cdiv(n, TPB), TPB, 0, s>>>(n, c.m2l_raw.as<int4>(), c.mb_cellbs.as<int2>(),
@@ -1377,7 +1494,7 @@ static void m2lb_plan_p(Ctx &c) {
     c.mb_fmt[1] = f.bdl;
     c.mb_fmt[2] = f.oq;
     c.mb_fmt[3] = f.odl;
-    c.mb_ngroups = ng;
+    c.mb_ngroups = ng + (c.mb_keyed ? c.mb_kng : 0);
     c.mb_nitems = nitems;
     c.m2lb_ok = true;
 }
@@ -1397,9 +1514,8 @@ template <int P>
 static void m2lb_prealloc_p(Ctx &c) {
     constexpr int R = NR(P), RP = NRP(P);
     c.mb_mr.ensure(sizeof(float) * (size_t)(c.ncells + 1) * 3 * RP);
-    if (c.mb_keyed)
-        c.mb_cols.ensure(sizeof(float) * 3 * RP * (size_t)c.mb_ncols);
-    else
+    if (c.mb_keyed) c.mb_cols.ensure(sizeof(float) * 3 * RP * (size_t)c.mb_ncols);
+    if (c.mb_nitems > 0)
         c.mb_partial.ensure(sizeof(float) * (size_t)std::max(c.mb_nitems, 1) * 3 * R * 64);
 }
 
@@ -1441,11 +1557,13 @@ static void m2lb_run_p(Ctx &c) {
                 else
                     set = (int)lds;
             }
-            k_m2lb_x6<P, NS, KEYED><<<xcd_grid(c.mb_nitems), X::WAVES * 64, lds, s>>>(
-                c.mb_items.as<int4>(), c.mb_order.as<int>(), c.mb_groups.as<int4>(), c.mb_slots.as<int>(),
-                c.mb_mr.as<float>(),
-                c.mb_tab.as<uint32_t>(), c.mb_dst.as<int>(), c.mb_nitems,
-                (KEYED ? c.mb_cols : c.mb_partial).template as<float>());
+            const int nitems = KEYED ? c.mb_kitems : c.mb_nitems;
+            k_m2lb_x6<P, NS, KEYED><<<xcd_grid(nitems), X::WAVES * 64, lds, s>>>(
+                (KEYED ? c.mb_kitem : c.mb_items).template as<int4>(), c.mb_order.as<int>(),
+                (KEYED ? c.mb_kgroups : c.mb_groups).template as<int4>(),
+                (KEYED ? c.mb_kslots : c.mb_slots).template as<int>(), c.mb_mr.as<float>(), c.mb_tab.as<uint32_t>(),
+                c.mb_dst.as<int>(), nitems, (KEYED ? c.mb_cols : c.mb_partial).template as<float>());
+            VFMM_LAUNCH_CHECK();
         };
         auto launch_form = [&](auto by_key) {
             if (c.mb_nsplit == 2)
@@ -1454,10 +1572,8 @@ static void m2lb_run_p(Ctx &c) {
                 launch(std::integral_constant<int, 3>{}, by_key);
         };
         if constexpr (MbCfg<P>::X6) {
-            if (c.mb_keyed)
-                launch_form(std::true_type{});
-            else
-                launch_form(std::false_type{});
+            if (c.mb_nitems > 0) launch_form(std::false_type{});
+            if (c.mb_keyed) launch_form(std::true_type{});
         }
     } else {
         const size_t lds = m2lb_lds_bytes<P>();
@@ -1482,7 +1598,6 @@ static void m2lb_run_p(Ctx &c) {
             k_m2lb_columns<P, float><<<c.ncells, NT, 0, s>>>(c.mb_coff.as<int>(), c.mb_cols.as<float>(),
                                                              c.Lexp.as<float2>());
         VFMM_LAUNCH_CHECK();
-        return;
     }
     const int nblk = c.mb_nblk;
     int *blk_item0 = c.mb_blk.as<int>() + nblk, *blk_nitem = blk_item0 + nblk;

@@ -557,7 +557,7 @@ void csr_bounds(Ctx &c, const uint64_t *key, int64_t n, int nc, int *off) {
 
 // Builds CSR offsets (ncells+1) for a raw (tgt, src, img) list and the
 // stable order that sorts it by target.
-static void csr_by_target(Ctx &c, const int4 *raw, int64_t n, DevBuf &off) {
+void csr_by_target(Ctx &c, const int4 *raw, int64_t n, DevBuf &off) {
     hipStream_t s = c.stream;
     const int nc = c.ncells;
     off.ensure(sizeof(int) * ((size_t)nc + 1));

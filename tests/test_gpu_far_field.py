@@ -75,3 +75,28 @@ def test_deep_tree_of_few_children(p, precision):
     ref = oracle.direct(case)
     check("p=%d precision %d u" % (p, precision), u, ref["u"], 1e-4, 1e-3)
     check("p=%d precision %d dalpha" % (p, precision), d, ref["da_t"], 1e-4, 1e-3)
+
+
+@pytest.mark.parametrize("opt", [dict(p=8), dict(p=10), dict(p=10, precision=1), dict(p=10, m2l_form=3),
+                                 dict(p=10, periodic=1, images=3)],
+                         ids=lambda o: "-".join("%s%s" % kv for kv in o.items()))
+def test_thin_groups_by_operator_match_one_at_a_time(opt):
+    """A jittered lattice: groups by block, those of few targets by operator.  m2l_form 3: the evaluation's 1e-4."""
+    m = 64
+    rng = np.random.default_rng(2)
+    x = (np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 3)
+         + 0.5 + rng.uniform(-0.3, 0.3, (m ** 3, 3))) / m
+    a = rng.standard_normal((3, m ** 3)) / m ** 3
+    f = lambda v: np.ascontiguousarray(v, np.float32)  # noqa: E731
+    case = dict(x=f(x[:, 0]), y=f(x[:, 1]), z=f(x[:, 2]), ax=f(a[0]), ay=f(a[1]), az=f(a[2]),
+                sigma=f(np.full(m ** 3, 0.01)), n=m ** 3)
+    kw = dict(opt, ncrit=24, box_len=1.0)
+    u0, d0, s0 = _run(case, **kw)
+    u1, d1, _ = _run(case, **dict(kw, m2l_mode=1))
+    _, _, s2 = _run(case, **dict(kw, m2l_mode=2))
+    print("groups %d (by block alone %d), keys %d of %d" % (s0["m2l_groups"], s2["m2l_groups"], s0["m2l_keys"],
+                                                            s2["m2l_keys"]))
+    assert 0 < s0["m2l_groups"] < s2["m2l_groups"]
+    tol = 1e-4 if opt.get("m2l_form") == 3 else 1e-5
+    check("%s u" % opt, u0, u1, tol, 1e-3)
+    check("%s dalpha" % opt, d0, d1, tol, 1e-3)
