@@ -12,7 +12,7 @@ static std::string g_create_error;
 
 void Ctx::release_all() {
     DevBuf *bufs[] = {&bpart, &bres, &keyA, &keyB, &valA, &valB, &hist, &scanA, &scanB, &scanC, &perm, &rec, &rec64,
-                      &c_start, &c_count, &c_parent, &c_child, &c_nchild, &c_level, &c_geo, &c_rad, &c_lo, &c_hi,
+                      &c_start, &c_count, &c_parent, &c_child, &c_nchild, &c_level, &c_geo, &c_geo64, &c_rad, &c_lo, &c_hi,
                       &c_tmp, &leaves, &frA, &frB, &tcnt, &m2l_raw, &p2p_raw, &lkey, &lkey2, &lval, &lval2,
                       &m2l_off, &m2l_src, &p2p_off, &p2p_ent, &p2p_sh, &recp, &tgt, &c_nsrc, &part, &blocks, &pblocks, &pblong, &mb_kord, &mb_inv, &mb_koff, &mb_ksec, &mb_dst, &mb_coff, &mb_roff, &mb_rsrc, &mb_cols, &mb_toff, &mb_kgroups,
                       &mb_kslots, &mb_kitem, &mb_fill, &mb_low, &mb_lowkid, &items, &item_out, &pairs64, &Mexp, &Lexp, &lat_op, &far_u,
@@ -211,7 +211,7 @@ static void do_build(Ctx &c, int64_t n, const float *x, const float *y, const fl
     c.record(2 * PH_TRAVERSE);
     traverse_and_lists(c);
     c.m2lb_ok = false;
-    if (c.prm.m2l_mode != 1 && c.prm.precision != VFMM_PRECISION_FP64) m2lb_plan(c);
+    if (m2l_batched(c.prm)) m2lb_plan(c);
     if (!c.m2lb_ok) {  // the per-pair M2L runs instead
         if (!c.m2l_csr) build_m2l_csr(c);
         m2l_pair_plan(c, c.m2l_off.as<int>(), c.n_m2l);
@@ -987,12 +987,22 @@ vfmm_status vfmm_copy_expansions(vfmm_ctx *ctx, int32_t *level, int32_t *parent,
             std::vector<float4> g(nc);
             std::vector<float> r(nc);
             VFMM_HIP(hipMemcpy(g.data(), c.c_geo.ptr, sizeof(float4) * nc, hipMemcpyDeviceToHost));
+            std::vector<double4> g64;
+            if (c.prm.precision == VFMM_PRECISION_FP64) {
+                g64.resize(nc);
+                VFMM_HIP(hipMemcpy(g64.data(), c.c_geo64.ptr, sizeof(double4) * nc, hipMemcpyDeviceToHost));
+            }
             VFMM_HIP(hipMemcpy(r.data(), c.c_rad.ptr, sizeof(float) * nc, hipMemcpyDeviceToHost));
             for (int i = 0; i < nc; ++i) {
                 geo[5 * i] = g[i].x;
                 geo[5 * i + 1] = g[i].y;
                 geo[5 * i + 2] = g[i].z;
                 geo[5 * i + 3] = g[i].w;
+                if (!g64.empty()) {
+                    geo[5 * i] = g64[i].x;
+                    geo[5 * i + 1] = g64[i].y;
+                    geo[5 * i + 2] = g64[i].z;
+                }
                 geo[5 * i + 4] = r[i];
             }
         }

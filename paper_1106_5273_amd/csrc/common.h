@@ -96,6 +96,15 @@ struct RootBox {
     float len;
 };
 
+// Vector types of the compute precision R (float: the product path; double:
+// the FP64 reference form of the precision parameter).
+template <class R> struct VT;
+template <> struct VT<float> { using V2 = float2; using V4 = float4; };
+template <> struct VT<double> { using V2 = double2; using V4 = double4; };
+
+__device__ inline float rsqr(float a) { return rsqrtf(a); }
+__device__ inline double rsqr(double a) { return 1.0 / sqrt(a); }
+
 // ---------------------------------------------------------------------------
 // Coefficient layout: complex coefficients c_n^m with 0 <= m <= n <= P are
 // stored at index n(n+1)/2 + m; negative orders follow from

@@ -52,6 +52,7 @@ struct Ctx {
     DevBuf recp;                         // float4[3n]: float32 near-field records (scaled, leaf-local)
     // cells
     DevBuf c_start, c_count, c_parent, c_child, c_nchild, c_level;  // int
+    DevBuf c_geo64;                      // double4 in the float64 form: the same, centres not rounded to float32
     DevBuf c_geo;                        // float4 (cx, cy, cz, size)
     DevBuf c_rad;                        // float tight radius
     DevBuf c_lo, c_hi;                   // float4 particle bounding box
@@ -160,6 +161,11 @@ struct Ctx {
 
 // Sources per leaf when the evaluation needs no stretching at the target points
 // (fmm_evaluate_targets), else null.
+// Whether the operator-batched M2L may run: not in mode 1, and in the float64 form by its own rule alone.
+inline bool m2l_batched(const vfmm_params &p) {
+    return p.m2l_mode != 1 && !(p.precision == VFMM_PRECISION_FP64 && p.m2l_mode != 0);
+}
+
 inline const int *eval_sources(const Ctx &c) { return c.tg_eval && c.parted ? c.c_nsrc.as<int>() : nullptr; }
 
 // tree.hip

@@ -14,12 +14,6 @@ namespace vfmm {
 
 static constexpr int TPB = 256;
 
-// Vector types of the compute precision R (float: the product path; double:
-// the FP64 reference form of the precision parameter).
-template <class R> struct VT;
-template <> struct VT<float> { using V2 = float2; using V4 = float4; };
-template <> struct VT<double> { using V2 = double2; using V4 = double4; };
-
 template <class V2>
 __device__ inline V2 cmul(V2 a, V2 b) { return V2{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
 template <class V2>
@@ -27,8 +21,6 @@ __device__ inline V2 cconj(V2 a) { return V2{a.x, -a.y}; }
 
 __device__ inline float fmar(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ inline double fmar(double a, double b, double c) { return fma(a, b, c); }
-__device__ inline float rsqr(float a) { return rsqrtf(a); }
-__device__ inline double rsqr(double a) { return 1.0 / sqrt(a); }
 
 // rt^e for a ratio of cell sizes (a power of two) and an integer e >= 0
 __device__ inline float powr(float rt, int e) { return __builtin_amdgcn_exp2f((float)e * __log2f(rt)); }
@@ -54,7 +46,8 @@ __device__ inline void decode_nm(int t, int &n, int &m) {
 // ---------------------------------------------------------------------------
 template <int P, class R>
 __global__ __launch_bounds__(64) void k_p2m(const int *leaves, const int *start, const int *count, const int *nsrc,
-                                            const float4 *geo, const typename VT<R>::V4 *rec, typename VT<R>::V2 *Mexp) {
+                                            const typename VT<R>::V4 *geo, const typename VT<R>::V4 *rec,
+                                            typename VT<R>::V2 *Mexp) {
     using V2 = typename VT<R>::V2;
     using V4 = typename VT<R>::V4;
     constexpr int NCP = NC(P);
@@ -65,7 +58,7 @@ __global__ __launch_bounds__(64) void k_p2m(const int *leaves, const int *start,
     __shared__ V4 al[CH];
     const int lane = threadIdx.x;
     const int cell = leaves[blockIdx.x];
-    const float4 g = geo[cell];
+    const auto g = geo[cell];
     const R inv = R(1) / R(g.w);
     const int s0 = start[cell], cnt = nsrc ? nsrc[cell] : count[cell];  // target points carry no strength
     constexpr int NT = (NCP + 63) / 64;
@@ -180,7 +173,7 @@ __device__ inline void harmonics_order(R x, R y, R z, int m, V2 *T) {
 
 template <int P, class R, class S>
 __global__ __launch_bounds__((XferCfg<P, R>::M2M_THREADS)) void k_m2m(int c0, int c1, const int *child,
-                                                                     const int *nchild, const float4 *geo,
+                                                                     const int *nchild, const typename VT<S>::V4 *geo,
                                                                      typename VT<S>::V2 *Mexp) {
     using V2 = typename VT<R>::V2;
     using C = XferCfg<P, R>;
@@ -192,7 +185,7 @@ __global__ __launch_bounds__((XferCfg<P, R>::M2M_THREADS)) void k_m2m(int c0, in
     const int nc = nchild[cell];
     if (nc == 0) return;
     const int f = child[cell];
-    const float4 gp = geo[cell];
+    const auto gp = geo[cell];
     const int tid = threadIdx.x;
     const R inv = R(1) / R(gp.w);
     const int ch = tid % CH, q = tid / CH;  // the high coefficients, whose sums are longest, share waves
@@ -208,7 +201,7 @@ __global__ __launch_bounds__((XferCfg<P, R>::M2M_THREADS)) void k_m2m(int c0, in
         if (tid < C::M2M_HARM) {
             const int k = tid % CH;
             if (k < nk && tid / CH <= P) {
-                const float4 gc = geo[f + k0 + k];
+                const auto gc = geo[f + k0 + k];
                 harmonics_order<P, R, true>((R(gc.x) - R(gp.x)) * inv, (R(gc.y) - R(gp.y)) * inv,
                                             (R(gc.z) - R(gp.z)) * inv, tid / CH, Rf[k]);
             }
@@ -310,7 +303,8 @@ struct M2LCfg {
 };
 
 template <int P, class R>
-__global__ __launch_bounds__((M2LCfg<P, R>::THREADS)) void k_m2l(const int4 *parts, const int2 *src, const float4 *geo,
+__global__ __launch_bounds__((M2LCfg<P, R>::THREADS)) void k_m2l(const int4 *parts, const int2 *src,
+                                                               const typename VT<R>::V4 *geo,
                                                                const typename VT<R>::V2 *__restrict__ Mexp,
                                                                typename VT<R>::V2 *__restrict__ partial, int B,
                                                                float len) {
@@ -326,7 +320,7 @@ __global__ __launch_bounds__((M2LCfg<P, R>::THREADS)) void k_m2l(const int4 *par
     if (tgt < 0) return;
     const int o0 = part.y, o1 = part.z;
     const int tid = threadIdx.x;
-    const float4 ga = geo[tgt];
+    const auto ga = geo[tgt];
     const int sub = tid / C::LP;
     int j = tid % C::LP, l = 0;
     for (int cnt = (P + KB) / KB; j >= cnt; cnt = (P - l + KB) / KB) {
@@ -348,7 +342,7 @@ __global__ __launch_bounds__((M2LCfg<P, R>::THREADS)) void k_m2l(const int4 *par
         for (int i = tid; i < nb * (C::Q + 1); i += C::THREADS) {
             const int s = i / (C::Q + 1), M = i % (C::Q + 1);
             const int2 ent = src[e0 + s];
-            const float4 gb = geo[ent.x];
+            const auto gb = geo[ent.x];
             const R ix = (R)(ent.y % W - B), iy = (R)((ent.y / W) % W - B), iz = (R)(ent.y / (W * W) - B);
             const R inv = R(1) / R(gb.w);
             const R dx = (R(ga.x) - R(gb.x) - ix * R(len)) * inv;
@@ -566,7 +560,7 @@ void m2l_pair_plan(Ctx &c, const int *off, int64_t n) {
 // ---------------------------------------------------------------------------
 template <int P, class R, class S>
 __global__ __launch_bounds__((XferCfg<P, R>::L2L_THREADS)) void k_l2l(int c0, int c1, const int *child,
-                                                                     const int *nchild, const float4 *geo,
+                                                                     const int *nchild, const typename VT<S>::V4 *geo,
                                                                      typename VT<S>::V2 *Lexp) {
     using V2 = typename VT<R>::V2;
     using C = XferCfg<P, R>;
@@ -578,13 +572,13 @@ __global__ __launch_bounds__((XferCfg<P, R>::L2L_THREADS)) void k_l2l(int c0, in
     const int nc = nchild[cell];
     if (nc == 0) return;
     const int f = child[cell];
-    const float4 gp = geo[cell];
+    const auto gp = geo[cell];
     const int tid = threadIdx.x;
     const R inv = R(1) / R(gp.w);
     if (tid < C::L2L_HARM) {
         const int j = tid % 8;
         if (j < nc && tid / 8 <= P) {
-            const float4 gc = geo[f + j];
+            const auto gc = geo[f + j];
             harmonics_order<P, R, false>((R(gc.x) - R(gp.x)) * inv, (R(gc.y) - R(gp.y)) * inv,
                                          (R(gc.z) - R(gp.z)) * inv, tid / 8, Rf[j]);
         }
@@ -638,8 +632,8 @@ __global__ __launch_bounds__((XferCfg<P, R>::L2L_THREADS)) void k_l2l(int c0, in
 // against R_{n-1} and R_{n-2}.
 // ---------------------------------------------------------------------------
 template <int P, class R>
-__global__ __launch_bounds__(64) void k_l2p(const int *leaves, const int *start, const int *count, const float4 *geo,
-                                            const typename VT<R>::V4 *rec, const typename VT<R>::V2 *Lexp,
+__global__ __launch_bounds__(64) void k_l2p(const int *leaves, const int *start, const int *count,
+                                            const typename VT<R>::V4 *geo, const typename VT<R>::V4 *rec, const typename VT<R>::V2 *Lexp,
                                             int64_t n_all, R *far_u, R *far_da, int scheme) {
     using V2 = typename VT<R>::V2;
     using V4 = typename VT<R>::V4;
@@ -650,7 +644,7 @@ __global__ __launch_bounds__(64) void k_l2p(const int *leaves, const int *start,
     const int lane = threadIdx.x;
     for (int i = lane; i < 3 * NCP; i += 64) Ls[i / NCP][i % NCP] = Lexp[(size_t)cell * 3 * NCP + i];
     __syncthreads();
-    const float4 g = geo[cell];
+    const auto g = geo[cell];
     const R inv = R(1) / R(g.w);
     const int s0 = start[cell], cnt = count[cell];
     for (int b = 0; b < cnt; b += 64) {
@@ -806,18 +800,19 @@ static void far_field_t(Ctx &c) {
     c.far_u.ensure(sizeof(S) * 3 * (size_t)c.n);
     c.far_da.ensure(sizeof(S) * 3 * (size_t)c.n);
     const V4 *rec = (sizeof(S) == 8) ? reinterpret_cast<const V4 *>(c.rec64.ptr) : reinterpret_cast<const V4 *>(c.rec.ptr);
+    const V4 *geo = reinterpret_cast<const V4 *>(sizeof(S) == 8 ? c.c_geo64.ptr : c.c_geo.ptr);
     c.record(2 * PH_P2M_M2M);
     // a fill kernel rather than a memset, so that the evaluation can be captured in a graph
     k_zero<<<cdiv(cdiv(bytes, 16), 256), 256, 0, s>>>(c.Lexp.as<float>(), (int64_t)(bytes / 4));
     VFMM_LAUNCH_CHECK();
     const int *nsrc = eval_sources(c);
     k_p2m<P, S><<<c.nleaves, 64, 0, s>>>(c.leaves.as<int>(), c.c_start.as<int>(), c.c_count.as<int>(), nsrc,
-                                         c.c_geo.as<float4>(), rec, c.Mexp.as<V2>());
+                                         geo, rec, c.Mexp.as<V2>());
     VFMM_LAUNCH_CHECK();
     for (int l = c.depth - 1; l >= 0; --l) {
         const int c0 = c.lvl_off[l], c1 = c.lvl_off[l + 1];
         k_m2m<P, RA, S><<<c1 - c0, XferCfg<P, RA>::M2M_THREADS, 0, s>>>(c0, c1, c.c_child.as<int>(), c.c_nchild.as<int>(),
-                                                c.c_geo.as<float4>(), c.Mexp.as<V2>());
+                                                geo, c.Mexp.as<V2>());
         VFMM_LAUNCH_CHECK();
     }
     c.record(2 * PH_P2M_M2M + 1);
@@ -828,7 +823,7 @@ static void far_field_t(Ctx &c) {
     }
     c.record(2 * PH_LATTICE + 1);
     c.record(2 * PH_M2L);
-    const bool batched = c.n_m2l > 0 && c.m2lb_ok && sizeof(S) == 4;
+    const bool batched = c.n_m2l > 0 && c.m2lb_ok;
     if (batched) m2lb_run(c);
     if (batched ? c.mb_keyed && c.mb_nrest > 0 : c.n_m2l > 0) {  // all translations, or those the plan left out
         const int2 *src = batched ? c.mb_rsrc.as<int2>() : c.m2l_src.as<int2>();
@@ -841,7 +836,7 @@ static void far_field_t(Ctx &c) {
             c.m2l_lds_set |= bit;
         }
         k_m2l<P, S><<<c.m2l_nparts, MC::THREADS, MC::LDS, s>>>(c.m2l_parts.as<int4>(), src,
-                                                                   c.c_geo.as<float4>(), c.Mexp.as<V2>(),
+                                                                   geo, c.Mexp.as<V2>(),
                                                                    c.m2l_partial.as<V2>(), c.img_B,
                                                                    c.prm.periodic ? (float)c.prm.box_len : 0.f);
         VFMM_LAUNCH_CHECK();
@@ -854,12 +849,12 @@ static void far_field_t(Ctx &c) {
     for (int l = 0; l < c.depth; ++l) {  // from the cells of level l to their children
         const int c0 = c.lvl_off[l], c1 = c.lvl_off[l + 1];
         k_l2l<P, RA, S><<<c1 - c0, XferCfg<P, RA>::L2L_THREADS, 0, s>>>(c0, c1, c.c_child.as<int>(),
-                                                                        c.c_nchild.as<int>(), c.c_geo.as<float4>(),
+                                                                        c.c_nchild.as<int>(), geo,
                                                                         c.Lexp.as<V2>());
         VFMM_LAUNCH_CHECK();
     }
     k_l2p<P, S><<<c.nleaves, 64, 0, s>>>(c.leaves.as<int>(), c.c_start.as<int>(), c.c_count.as<int>(),
-                                          c.c_geo.as<float4>(), rec, c.Lexp.as<V2>(), c.n, c.far_u.as<S>(),
+                                          geo, rec, c.Lexp.as<V2>(), c.n, c.far_u.as<S>(),
                                           c.far_da.as<S>(), c.prm.scheme);
     VFMM_LAUNCH_CHECK();
     c.record(2 * PH_L2L_L2P + 1);

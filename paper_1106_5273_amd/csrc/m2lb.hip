@@ -33,9 +33,12 @@ static constexpr int TPB = 256;
 static constexpr int ITEM_GROUPS = 24;
 static constexpr int TABLE_KEY_BITS = 24;  // offset keys up to this width are numbered through a direct table
 static constexpr size_t MAX_TABLE_BYTES = size_t(8) << 30;  // operator table cap (else the per-pair kernel)
-// translations below which the per-pair M2L runs at once: its 6 ns for each (p = 10)
-// stay below the 0.2 ms of the batched plan's 25 launches and 6 waits
-static constexpr int MIN_BATCHED = 8192;
+// time (ns) of all translations one at a time below which they run so at once: the
+// batched plan's 25 launches and 6 waits take 0.2 ms, in float64, where groups cost
+// four times as much, with lists by operator 0.4
+static constexpr double MIN_PAIR_NS = 2.5e5, MIN_PAIR_NS_F64 = 6e5;
+// the same for the float64 products, whose group costs as much as 17 translations one at a time
+static constexpr int MIN_FILL_F64 = 24;
 static constexpr int MIN_GROUP_FILL = 8;  // translations per (block, key) group below which per-pair M2L runs
 
 void sort_pairs_u64(Ctx &c, DevBuf &kA, DevBuf &vA, DevBuf &kB, DevBuf &vB, int64_t n, int nbits);
@@ -361,19 +364,19 @@ __global__ __launch_bounds__(TPB) void k_items(int ng, const int4 *groups, const
 // ---------------------------------------------------------------------------
 // Mt in real row order, padded, k-permuted: Mr[cell][comp][NRP] (extra zero cell at the end)
 // ---------------------------------------------------------------------------
-template <int P>
-__global__ __launch_bounds__(TPB) void k_m2lb_mreal(int ncells, const float2 *Mexp, float *Mr) {
-    constexpr int R = NR(P), RP = NRP(P), NCP = NC(P);
+template <int P, class R>
+__global__ __launch_bounds__(TPB) void k_m2lb_mreal(int ncells, const typename VT<R>::V2 *Mexp, R *Mr) {
+    constexpr int ROWS = NR(P), RP = NRP(P), NCP = NC(P);
     const int64_t idx = (int64_t)blockIdx.x * TPB + threadIdx.x;
     const int64_t total = (int64_t)(ncells + 1) * 3 * RP;
     if (idx >= total) return;
     const int r = kperm((int)(idx % RP));  // row held at this position
     const int64_t cc = idx / RP;           // cell*3 + comp
-    float v = 0.f;
-    if (r < R && cc < (int64_t)ncells * 3) {
+    R v = R(0);
+    if (r < ROWS && cc < (int64_t)ncells * 3) {
         int n, m, im;
         decode_row(r, n, m, im);
-        const float2 z = Mexp[cc * NCP + CIDX(n, m)];
+        const auto z = Mexp[cc * NCP + CIDX(n, m)];
         v = im ? z.y : z.x;
     }
     Mr[idx] = v;
@@ -403,6 +406,7 @@ struct MbCfg {
 // FORM 0 (float32 products): MFMA A-fragment order [key][row tile a][chunk]
 // [lane][e] = T[16 a + lane % 16][16 chunk + 4 e + lane / 16], zero outside
 // R x R, so a lane reads the operands of four k steps as one float4.
+// In double (R) the same order serves the float64 products.
 // FORM 1 (three-way bfloat16 split): T = T0 + T1 + T2 with T0 = bf16(T),
 // T1 = bf16(T - T0), T2 = bf16(T - T0 - T1) (24 significant bits), stored
 // [key][row tile a][k block kb][split s][lane][e] = Ts[16 a + lane % 16]
@@ -414,11 +418,12 @@ __device__ inline uint32_t bf16_bits_rne(float x) {
     return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;  // finite inputs only
 }
 
-template <int P, int FORM>
+template <int P, int FORM, class R = float>
 __global__ __launch_bounds__(256) void k_m2lb_optab(int nkeys, const uint64_t *__restrict__ ukey, KeyFmt f,
-                                                    float *__restrict__ tab) {
+                                                    R *__restrict__ tab) {
     using C = MbCfg<P>;
-    __shared__ float2 Is[(C::Q + 1) * C::IW];  // full orders M in [-Q, Q]
+    using V2 = typename VT<R>::V2;
+    __shared__ V2 Is[(C::Q + 1) * C::IW];  // full orders M in [-Q, Q]
     __shared__ int rinfo[C::RP];
     const int key = blockIdx.x;
     if (key >= nkeys) return;
@@ -428,7 +433,7 @@ __global__ __launch_bounds__(256) void k_m2lb_optab(int nkeys, const uint64_t *_
         if (r < C::R) decode_row(r, k, l, im);
         rinfo[r] = k | (l << 8) | (im << 16);
     }
-    for (int i = tid; i < (C::Q + 1) * C::IW; i += 256) Is[i] = make_float2(0.f, 0.f);
+    for (int i = tid; i < (C::Q + 1) * C::IW; i += 256) Is[i] = V2{R(0), R(0)};
     const uint64_t kv = ukey[key];
     const uint64_t mq = (1ull << f.bq) - 1;
     const int dl = (int)(kv >> (3 * f.bq)) - f.odl;
@@ -436,66 +441,66 @@ __global__ __launch_bounds__(256) void k_m2lb_optab(int nkeys, const uint64_t *_
     if (tid <= C::Q) {
         // irregular harmonics I_N^M((c_A - c_B)/s_B), (c_A - c_B)/s_B = -q 2^(min(dl,0) - 2)
         const int M = tid;
-        const float sc = -ldexpf(1.0f, min(dl, 0) - 2);
-        const float dx = (float)((int)((kv >> (2 * f.bq)) & mq) - f.oq) * sc;
-        const float dy = (float)((int)((kv >> f.bq) & mq) - f.oq) * sc;
-        const float dz = (float)((int)(kv & mq) - f.oq) * sc;
-        const float r2 = dx * dx + dy * dy + dz * dz;
-        const float ir2 = 1.0f / r2;
-        float cr = rsqrtf(r2), ci = 0.f;
+        const R sc = -ldexp(R(1), min(dl, 0) - 2);
+        const R dx = (R)((int)((kv >> (2 * f.bq)) & mq) - f.oq) * sc;
+        const R dy = (R)((int)((kv >> f.bq) & mq) - f.oq) * sc;
+        const R dz = (R)((int)(kv & mq) - f.oq) * sc;
+        const R r2 = dx * dx + dy * dy + dz * dz;
+        const R ir2 = R(1) / r2;
+        R cr = rsqr(r2), ci = R(0);
         for (int mm = 1; mm <= M; ++mm) {
-            const float fc = -(float)(2 * mm - 1) * ir2;
-            const float nr = fc * (dx * cr - dy * ci);
-            const float ni = fc * (dx * ci + dy * cr);
+            const R fc = -(R)(2 * mm - 1) * ir2;
+            const R nr = fc * (dx * cr - dy * ci);
+            const R ni = fc * (dx * ci + dy * cr);
             cr = nr;
             ci = ni;
         }
-        auto put = [&](int N, float vr, float vi) {
-            Is[N * C::IW + C::Q + M] = make_float2(vr, vi);
-            if (M > 0) Is[N * C::IW + C::Q - M] = (M & 1) ? make_float2(-vr, vi) : make_float2(vr, -vi);
+        auto put = [&](int N, R vr, R vi) {
+            Is[N * C::IW + C::Q + M] = V2{vr, vi};
+            if (M > 0) Is[N * C::IW + C::Q - M] = (M & 1) ? V2{-vr, vi} : V2{vr, -vi};
         };
         put(M, cr, ci);
-        float pr = cr, pi = ci, qr = 0.f, qi = 0.f;
+        R pr = cr, pi = ci, qr = R(0), qi = R(0);
         if (M + 1 <= C::Q) {
-            const float a0 = (float)(2 * M + 1) * dz * ir2;
+            const R a0 = (R)(2 * M + 1) * dz * ir2;
             qr = a0 * cr;
             qi = a0 * ci;
             put(M + 1, qr, qi);
         }
         for (int N = M + 2; N <= C::Q; ++N) {
-            const float a = (float)(2 * N - 1) * dz;
-            const float b = (float)((N - 1) * (N - 1) - M * M);
-            const float vr = (a * qr - b * pr) * ir2;
-            const float vi = (a * qi - b * pi) * ir2;
+            const R a = (R)(2 * N - 1) * dz;
+            const R b = (R)((N - 1) * (N - 1) - M * M);
+            const R vr = (a * qr - b * pr) * ir2;
+            const R vi = (a * qi - b * pi) * ir2;
             put(N, vr, vi);
             pr = qr; pi = qi; qr = vr; qi = vi;
         }
     }
     __syncthreads();
-    auto value = [&](int r, int c) -> float {
-        float v = 0.f;
+    auto value = [&](int r, int c) -> R {
+        R v = R(0);
         if (r < C::R && c < C::R) {
             const int ri = rinfo[r], ci = rinfo[c];
             const int k = ri & 255, l = (ri >> 8) & 255, im = (ri >> 16) & 1;
             const int n = ci & 255, m = (ci >> 8) & 255, imc = (ci >> 16) & 1;
-            const float2 x = Is[(n + k) * C::IW + C::Q + m - l];
-            const float2 y = Is[(n + k) * C::IW + C::Q + m + l];
-            const float sg = (l & 1) ? -1.f : 1.f;
+            const V2 x = Is[(n + k) * C::IW + C::Q + m - l];
+            const V2 y = Is[(n + k) * C::IW + C::Q + m + l];
+            const R sg = (l & 1) ? R(-1) : R(1);
             if (m == 0) v = im ? x.y : x.x;
             else if (!im) v = imc ? (-x.y - sg * y.y) : (x.x + sg * y.x);
             else v = imc ? (x.x - sg * y.x) : (x.y - sg * y.y);
-            v *= (((k + l) & 1) ? -1.f : 1.f) * ldexpf(1.0f, dl * (k + 1));
+            v *= (((k + l) & 1) ? R(-1) : R(1)) * ldexp(R(1), dl * (k + 1));
         }
         return v;
     };
     if (FORM == 0) {
-        float *T = tab + (size_t)key * C::OP;
+        R *T = tab + (size_t)key * C::OP;
         for (int idx = tid; idx < (int)C::OP; idx += 256) {
             const int e = idx & 3, lane = (idx >> 2) & 63;
             const int chunk = (idx >> 8) % C::KC, a = (idx >> 8) / C::KC;
             T[idx] = value(16 * a + (lane & 15), 16 * chunk + 4 * e + (lane >> 4));
         }
-    } else {
+    } else if constexpr (FORM == 1) {
         // one thread per (a, kb, lane, pair of e): two values packed per 32-bit word and split
         uint32_t *T = reinterpret_cast<uint32_t *>(tab) + (size_t)key * C::OPX;
         constexpr int KB = C::RP / 32;
@@ -891,6 +896,152 @@ static size_t m2lb_lds_bytes() {
     return sizeof(float) * 2 * 64 * C::BS + sizeof(int) * 64;
 }
 
+// The float64 form: the groups, slot tables and items of the split form, products
+// [16 rows x 4 inputs] x [4 inputs x 16 targets] on v_mfma_f64_16x16x4f64 with the
+// operator in double.  A work-group of RTI waves takes one item; a wave owns one
+// row tile of the three potentials and all 64 targets (192 accumulator registers at
+// three potentials would leave none for a second tile), streams its operator rows
+// from the table a chunk of 16 inputs ahead, and shares the 64 targets' multipoles,
+// staged one potential at a time in two LDS buffers.  An instruction holds the
+// matrix core for 64 cycles, so two waves per SIMD hide the loads.  One at a time
+// the 1.43 million translations of 64^3 particles took 7.4 ms (5.2 ns each, 17 TF/s).
+template <int P>
+struct Mb64Cfg {
+    using C = MbCfg<P>;
+    static constexpr int THREADS = 64 * C::RTI;
+    static constexpr int BS = C::RP + 2;                          // LDS column stride (double)
+    static constexpr int D2 = 64 * C::RP / 2 / THREADS;           // staged double2 per thread and potential
+    static constexpr size_t LDS = sizeof(double) * 2 * 64 * BS;
+    static constexpr bool OK = LDS <= 160 * 1024 && C::RT == C::RP;
+};
+
+typedef double vd4 __attribute__((ext_vector_type(4)));
+typedef double vd2 __attribute__((ext_vector_type(2)));
+
+template <int P, bool KEYED>
+__global__ __launch_bounds__(Mb64Cfg<P>::THREADS) void k_m2lb_f64(const int4 *__restrict__ items,
+                                                                 const int *__restrict__ order,
+                                                                 const int4 *__restrict__ groups,
+                                                                 const int *__restrict__ slots,
+                                                                 const double *__restrict__ Mr,
+                                                                 const double *__restrict__ tab,
+                                                                 const int *__restrict__ dsts, int nitems,
+                                                                 double *__restrict__ partial) {
+    using C = MbCfg<P>;
+    using X = Mb64Cfg<P>;
+    const int li = xcd_logical(blockIdx.x, gridDim.x);
+    if (li >= nitems) return;
+    const int item = KEYED ? li : order[li];
+    extern __shared__ double Bd[];  // [2][64][BS]
+    const int tid = threadIdx.x, a = tid >> 6, lane = tid & 63, i16 = lane & 15, kq = lane >> 4;
+    const int4 it = items[item];
+    const int g0 = __builtin_amdgcn_readfirstlane(it.y), g1 = __builtin_amdgcn_readfirstlane(it.z);
+    vd4 acc[3][4];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[c][b] = vd4{0., 0., 0., 0.};
+    // chunk ch of this wave's operator rows: k steps 4 ch .. 4 ch + 3
+    auto load_a = [&](int key, int ch, vd4 &A) {
+        A = reinterpret_cast<const vd4 *>(tab + (size_t)key * C::OP)[((size_t)a * C::KC + ch) * 64 + lane];
+    };
+    // double2 number q = tid + THREADS i of a staged tile: column q / (RP/2), inputs 2 (q % (RP/2)) ..
+    int scol[X::D2];
+    auto load_cols = [&](int g) {
+        const int row = __builtin_amdgcn_readfirstlane(groups[g].y);
+#pragma unroll
+        for (int i = 0; i < X::D2; ++i) scol[i] = slots[(size_t)row * 64 + (tid + X::THREADS * i) / (C::RP / 2)];
+    };
+    auto src2 = [&](int i, int c) {
+        return *reinterpret_cast<const vd2 *>(Mr + ((size_t)scol[i] * 3 + c) * C::RP +
+                                              2 * ((tid + X::THREADS * i) % (C::RP / 2)));
+    };
+    auto put = [&](int buf, int i, vd2 x) {
+        const int q = tid + X::THREADS * i;
+        *reinterpret_cast<vd2 *>(Bd + (size_t)buf * 64 * X::BS + (q / (C::RP / 2)) * X::BS + 2 * (q % (C::RP / 2))) = x;
+    };
+    if (g0 >= g1) return;
+    int key = __builtin_amdgcn_readfirstlane(groups[g0].x);
+    vd4 A;
+    load_a(key, 0, A);
+    vd2 nxt[X::D2];
+    load_cols(g0);
+#pragma unroll
+    for (int i = 0; i < X::D2; ++i) nxt[i] = src2(i, 0);
+    for (int g = g0; g < g1; ++g) {
+        const bool more = g + 1 < g1;
+        const int nkey = more ? __builtin_amdgcn_readfirstlane(groups[g + 1].x) : key;
+        int col[4] = {-1, -1, -1, -1};
+        if (KEYED)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) col[b] = dsts[(size_t)g * 64 + 16 * b + i16];
+        __syncthreads();  // the previous group's tiles are no longer read
+#pragma unroll
+        for (int i = 0; i < X::D2; ++i) put(0, i, nxt[i]);
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double *Bc = Bd + (size_t)(c & 1) * 64 * X::BS + i16 * X::BS + 4 * kq;
+            if (c < 2) {
+#pragma unroll
+                for (int i = 0; i < X::D2; ++i) nxt[i] = src2(i, c + 1);
+            } else if (more) {
+                load_cols(g + 1);
+#pragma unroll
+                for (int i = 0; i < X::D2; ++i) nxt[i] = src2(i, 0);
+            }
+#pragma unroll 2
+            for (int ch = 0; ch < C::KC; ++ch) {
+                vd4 An;  // the next chunk's rows, of the next group's key after the last
+                const bool last = ch + 1 == C::KC;
+                load_a(c == 2 && last ? nkey : key, last ? 0 : ch + 1, An);
+                vd4 Bv[4];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const vd2 *q = reinterpret_cast<const vd2 *>(Bc + 16 * b * X::BS + 16 * ch);
+                    const vd2 lo = q[0], hi = q[1];
+                    Bv[b] = vd4{lo[0], lo[1], hi[0], hi[1]};
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int b = 0; b < 4; ++b)
+                        acc[c][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[e], Bv[b][e], acc[c][b], 0, 0, 0);
+                A = An;
+            }
+            if (KEYED) {
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    if (col[b] >= 0)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            partial[((size_t)col[b] * 3 + c) * C::RP + 16 * a + 4 * v + kq] = acc[c][b][v];
+                    acc[c][b] = vd4{0., 0., 0., 0.};
+                }
+            }
+            if (c < 2) {
+#pragma unroll
+                for (int i = 0; i < X::D2; ++i) put((c + 1) & 1, i, nxt[i]);
+                __syncthreads();
+            }
+        }
+        key = nkey;
+    }
+    if (KEYED) return;
+    // D fragment: lane holds rows 16 a + 4 v + kq of target column 16 b + i16
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        double *out = partial + ((size_t)item * 3 + c) * C::R * 64;
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = 16 * a + 4 * v + kq;
+                if (row < C::R) out[(size_t)row * 64 + 16 * b + i16] = acc[c][b][v];
+            }
+    }
+}
+
 // per block: sum the items' partials in item order and add to Lt.  One thread
 // per (potential, row, target slot) of a block; blockIdx.y strides over blocks.
 // Per target block, potential and chunk of RC rows: the items' partial sums of
@@ -900,9 +1051,9 @@ static size_t m2lb_lds_bytes() {
 // the read-modify-write of Lexp touches each cell's coefficients together.
 static constexpr int RC = 64;  // rows per work-group
 
-template <int P, typename A>
+template <int P, typename A, typename T = float>
 __global__ __launch_bounds__(TPB) void k_m2lb_reduce(const int *blk_item0, const int *blk_nitem, const int *blk_cells,
-                                                     const float *partial, float2 *Lexp) {
+                                                     const T *partial, typename VT<T>::V2 *Lexp) {
     // A: accumulator type (double in the mixed precision form)
     constexpr int R = NR(P), NCP = NC(P);
     __shared__ A tile[RC][65];
@@ -914,13 +1065,13 @@ __global__ __launch_bounds__(TPB) void k_m2lb_reduce(const int *blk_item0, const
     for (int rr = wave; rr < RC; rr += TPB / 64) {
         const int r = r0 + rr;
         if (r >= R) break;
-        const float *p = partial + ((size_t)blk_item0[b] * 3 * R + (size_t)comp * R + r) * 64 + lane;
+        const T *p = partial + ((size_t)blk_item0[b] * 3 * R + (size_t)comp * R + r) * 64 + lane;
         // up to 16 items' loads in flight, added in item order
         A acc = A(0);
         for (int i0 = 0; i0 < ni; i0 += 16) {
-            float v[16];
+            T v[16];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) v[u] = i0 + u < ni ? p[(size_t)(i0 + u) * stride] : 0.f;
+            for (int u = 0; u < 16; ++u) v[u] = i0 + u < ni ? p[(size_t)(i0 + u) * stride] : T(0);
 #pragma unroll
             for (int u = 0; u < 16; ++u)
                 if (i0 + u < ni) acc += (A)v[u];
@@ -935,8 +1086,8 @@ __global__ __launch_bounds__(TPB) void k_m2lb_reduce(const int *blk_item0, const
     for (int slot = wave; slot < 64; slot += TPB / 64) {
         const int cell = blk_cells[(size_t)b * 64 + slot];
         if (cell < 0) continue;
-        float *dst = reinterpret_cast<float *>(&Lexp[((size_t)cell * 3 + comp) * NCP + CIDX(k, l)]) + im;
-        *dst = (float)((A)*dst + tile[lane][slot]);
+        T *dst = reinterpret_cast<T *>(&Lexp[((size_t)cell * 3 + comp) * NCP + CIDX(k, l)]) + im;
+        *dst = (T)((A)*dst + tile[lane][slot]);
     }
 }
 
@@ -946,22 +1097,23 @@ __global__ __launch_bounds__(TPB) void k_m2lb_reduce(const int *blk_item0, const
 // order.  Bound by reading the columns (1.5 KB each at p = 10).
 static constexpr int COL_GROUPS = 4;
 
-template <int P, typename A>
+template <int P, typename A, typename T = float>
 __global__ __launch_bounds__(COL_GROUPS * 3 * NRP(P) / 2) void k_m2lb_columns(const int *__restrict__ coff,
-                                                                            const float *__restrict__ cols,
-                                                                            float2 *Lexp) {
+                                                                            const T *__restrict__ cols,
+                                                                            typename VT<T>::V2 *Lexp) {
+    using V2 = typename VT<T>::V2;
     constexpr int R = NR(P), RP = NRP(P), NCP = NC(P), HP = 3 * RP / 2;
     __shared__ A red[COL_GROUPS][2][HP];
     const int t = blockIdx.x, c0 = coff[t], c1 = coff[t + 1];
     if (c0 == c1) return;
     const int grp = threadIdx.x / HP, h = threadIdx.x % HP;
-    const float2 *p = reinterpret_cast<const float2 *>(cols) + h;
+    const V2 *p = reinterpret_cast<const V2 *>(cols) + h;
     A v0 = A(0), v1 = A(0);
     for (int i0 = c0 + grp; i0 < c1; i0 += 16 * COL_GROUPS) {
-        float2 w[16];
+        V2 w[16];
 #pragma unroll
         for (int u = 0; u < 16; ++u)
-            w[u] = i0 + COL_GROUPS * u < c1 ? p[(size_t)(i0 + COL_GROUPS * u) * HP] : make_float2(0.f, 0.f);
+            w[u] = i0 + COL_GROUPS * u < c1 ? p[(size_t)(i0 + COL_GROUPS * u) * HP] : V2{T(0), T(0)};
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
             v0 += (A)w[u].x;
@@ -982,8 +1134,8 @@ __global__ __launch_bounds__(COL_GROUPS * 3 * NRP(P) / 2) void k_m2lb_columns(co
         if (r0 + q >= R) continue;
         int k, l, im;
         decode_row(r0 + q, k, l, im);
-        float *dst = reinterpret_cast<float *>(&Lexp[((size_t)t * 3 + comp) * NCP + CIDX(k, l)]) + im;
-        *dst = (float)((A)*dst + (q ? v1 : v0));
+        T *dst = reinterpret_cast<T *>(&Lexp[((size_t)t * 3 + comp) * NCP + CIDX(k, l)]) + im;
+        *dst = (T)((A)*dst + (q ? v1 : v0));
     }
 }
 
@@ -991,6 +1143,7 @@ __global__ __launch_bounds__(COL_GROUPS * 3 * NRP(P) / 2) void k_m2lb_columns(co
 // keys of fewer translations than this go to the per-pair kernel: their operator
 // and their group cost what about ten translations one at a time cost
 static constexpr int KEYED_MIN = 10;
+static constexpr int KEYED_MIN_F64 = 40;  // float64: 160 ns against 5.1 each, less 1.2 of column bytes
 
 __global__ __launch_bounds__(TPB) void k_kid_keys(int64_t n, const int *kid, uint64_t *key, uint32_t *val) {
     const int64_t e = (int64_t)blockIdx.x * TPB + threadIdx.x;
@@ -1130,8 +1283,11 @@ struct M2lCosts {
 };
 
 template <int P>
-static M2lCosts m2l_costs() {
+static M2lCosts m2l_costs(bool dbl = false) {
     using C = MbCfg<P>;
+    if (dbl)  // a group 125 at p = 10 (eight waves), a pair 5.1
+        return {125.0 * ((C::RTI + 3) / 4) / 2.0 * C::KC / 8.0, 48.0 * C::RP / 5000.0, 8.0 * (double)C::OP / 4200.0,
+                5.1 * C::R / 121.0};
     return {(double)C::RTI * (C::RP / 32), 24.0 * C::RP / 5000.0, 4.0 * (double)C::OPX / 4200.0,
             6.0 * std::pow(C::R / 121.0, 1.5)};
 }
@@ -1211,23 +1367,29 @@ static void keyed_lists(Ctx &c, int64_t n, const int4 *raw, const int *kid, int 
 template <int P>
 static bool m2lb_plan_keyed(Ctx &c, int64_t n, int nkeys, double other, const KeyFmt &f) {
     using C = MbCfg<P>;
-    const M2lCosts t = m2l_costs<P>();
+    const bool dbl = c.prm.precision == VFMM_PRECISION_FP64;
+    const M2lCosts t = m2l_costs<P>(dbl);
+    const size_t rs = dbl ? sizeof(double) : sizeof(float);
     const double plan = 2e5 + 0.11 * (double)n;  // twenty launches, two sorts
     if (plan + t.col * (double)n + t.group * (double)n / 64 > other) return false;  // whatever the keys are
     int h[3];
-    keyed_sections(c, n, c.mb_kid.as<int>(), nkeys, KEYED_MIN, h);
+    keyed_sections(c, n, c.mb_kid.as<int>(), nkeys, dbl ? KEYED_MIN_F64 : KEYED_MIN, h);
     const int ng = h[0], nused = h[1], nrest = h[2];
     const int64_t ncols = n - nrest;
-    const size_t tab_bytes = sizeof(uint32_t) * C::OPX * (size_t)nused;
-    if (ng == 0 || tab_bytes > MAX_TABLE_BYTES || sizeof(float) * 3 * C::RP * (size_t)ncols > MAX_COLUMN_BYTES ||
+    const size_t tab_bytes = (dbl ? sizeof(double) * C::OP : sizeof(uint32_t) * C::OPX) * (size_t)nused;
+    if (ng == 0 || tab_bytes > MAX_TABLE_BYTES || rs * 3 * C::RP * (size_t)ncols > MAX_COLUMN_BYTES ||
         plan + t.group * ng + t.col * (double)ncols + t.key * nused + t.pair * nrest > other)
         return false;
     c.mb_low.ensure(sizeof(uint64_t) * (size_t)nused);
     keyed_lists(c, n, c.m2l_raw.as<int4>(), c.mb_kid.as<int>(), nkeys, h, c.mb_low.as<uint64_t>());
     c.mb_tab.ensure(tab_bytes);
-    k_m2lb_optab<P, 1><<<nused, 256, 0, c.stream>>>(nused, c.mb_low.as<uint64_t>(), f, c.mb_tab.as<float>());
+    if (dbl)
+        k_m2lb_optab<P, 0, double><<<nused, 256, 0, c.stream>>>(nused, c.mb_low.as<uint64_t>(), f,
+                                                                c.mb_tab.as<double>());
+    else
+        k_m2lb_optab<P, 1><<<nused, 256, 0, c.stream>>>(nused, c.mb_low.as<uint64_t>(), f, c.mb_tab.as<float>());
     VFMM_LAUNCH_CHECK();
-    c.mb_x6 = true;
+    c.mb_x6 = !dbl;
     c.mb_nsplit = c.prm.m2l_form == 3 ? 2 : 3;
     c.mb_nkeys = nused;
     c.mb_nblk = 0;
@@ -1295,7 +1457,9 @@ static void m2lb_plan_p(Ctx &c) {
     c.m2lb_ok = false;
     c.mb_keyed = false;
     if (n == 0) return;
-    if (c.prm.m2l_mode == 0 && n < MIN_BATCHED) return;
+    if (c.prm.precision == VFMM_PRECISION_FP64 && !Mb64Cfg<P>::OK) return;  // p = 12: two tiles exceed the LDS
+    const bool dbl = c.prm.precision == VFMM_PRECISION_FP64;
+    if (c.prm.m2l_mode == 0 && m2l_costs<P>(dbl).pair * (double)n < (dbl ? MIN_PAIR_NS_F64 : MIN_PAIR_NS)) return;
     // ---- offsets and ranges ----
     c.mb_eq.ensure(sizeof(int4) * n);
     c.pairs64.ensure(64);
@@ -1403,9 +1567,9 @@ static void m2lb_plan_p(Ctx &c) {
     int *gcnt = c.mb_gcnt.as<int>(), *gid = c.mb_gid.as<int>(), *goff = c.mb_goff.as<int>(),
         *gcur = c.mb_gcur.as<int>();
     using C = MbCfg<P>;
-    const bool x6 = m2lb_split_form(c, C::X6);
+    const bool x6 = !dbl && m2lb_split_form(c, C::X6), dense = x6 || dbl;  // dense: slot tables, no entry lists
     VFMM_HIP(hipMemsetAsync(gcnt, 0, sizeof(int) * (size_t)T, s));
-    if (x6) {
+    if (dense) {
         k_gk_mark<<<cdiv(n, TPB), TPB, 0, s>>>(n, c.m2l_raw.as<int4>(), c.mb_cellbs.as<int2>(), c.mb_kid.as<int>(),
                                                 nkeys, gcnt);
         VFMM_LAUNCH_CHECK();
@@ -1420,6 +1584,10 @@ static void m2lb_plan_p(Ctx &c) {
     scan_excl_i32(c, gcur, gid, T);
     read_ints(c, {gid + T - 1, gcur + T - 1}, h2);
     int ng = h2[0] + h2[1];
+    if (dbl && n < (int64_t)MIN_FILL_F64 * ng) {
+        m2lb_plan_keyed<P>(c, n, nkeys, m2l_costs<P>(true).pair * (double)n, f);
+        return;
+    }
     // A group costs a full 64-target operator product whether its targets are
     // all present or not; measured on gfx950 a group costs about as much as
     // 6-7 translations of the per-pair kernel, so sparse groups (irregular
@@ -1435,9 +1603,9 @@ static void m2lb_plan_p(Ctx &c) {
             if (m2lb_plan_keyed<P>(c, n, nkeys, 1.1 * t.group * ng + t.key * nkeys, f)) return;
         }
     c.mb_groups.ensure(sizeof(int4) * ng);
-    k_gk_groups<<<cdiv(T, TPB), TPB, 0, s>>>(T, gcnt, gid, x6 ? nullptr : goff, nkeys, c.mb_groups.as<int4>(), gcur);
+    k_gk_groups<<<cdiv(T, TPB), TPB, 0, s>>>(T, gcnt, gid, dense ? nullptr : goff, nkeys, c.mb_groups.as<int4>(), gcur);
     VFMM_LAUNCH_CHECK();
-    if (x6) {  // the split-product kernel reads each group's sources from its slot table
+    if (dense) {  // the kernel reads each group's sources from its slot table
         c.mb_slots.ensure(sizeof(int) * 64 * (size_t)ng);
         k_fill_i32<<<cdiv(64 * (int64_t)ng, TPB), TPB, 0, s>>>(64 * (int64_t)ng, nc, c.mb_slots.as<int>());
         VFMM_LAUNCH_CHECK();
@@ -1445,7 +1613,7 @@ static void m2lb_plan_p(Ctx &c) {
                                                  nkeys, gid, c.mb_slots.as<int>());
         VFMM_LAUNCH_CHECK();
         if constexpr (C::X6)
-            if (c.prm.m2l_mode == 0 && n < FULL_FILL * (int64_t)ng && m2lb_fill_plan<P>(c, n, nkeys, ng, f)) return;
+            if (x6 && c.prm.m2l_mode == 0 && n < FULL_FILL * (int64_t)ng && m2lb_fill_plan<P>(c, n, nkeys, ng, f)) return;
     } else {  // the float32-product kernel reads each group's entry list
         c.mb_ent.ensure(sizeof(int2) * n);
         k_gk_scatter<<<cdiv(n, TPB), TPB, 0, s>>>(n, c.m2l_raw.as<int4>(), c.mb_cellbs.as<int2>(),
@@ -1455,7 +1623,7 @@ static void m2lb_plan_p(Ctx &c) {
     c.mb_blk.ensure(sizeof(int) * 3 * (size_t)nblk);
     int *blk_first = c.mb_blk.as<int>(), *blk_item0 = blk_first + nblk, *blk_nitem = blk_item0 + nblk;
     VFMM_HIP(hipMemsetAsync(c.mb_blk.ptr, 0, sizeof(int) * 3 * (size_t)nblk, s));
-    k_group_counts<<<cdiv(ng, TPB), TPB, 0, s>>>(ng, n, !x6, c.mb_groups.as<int4>(), blk_first);
+    k_group_counts<<<cdiv(ng, TPB), TPB, 0, s>>>(ng, n, !dense, c.mb_groups.as<int4>(), blk_first);
     VFMM_LAUNCH_CHECK();
     k_item_flags<<<cdiv(ng, TPB), TPB, 0, s>>>(ng, c.mb_groups.as<int4>(), blk_first, flag);
     VFMM_LAUNCH_CHECK();
@@ -1479,10 +1647,13 @@ static void m2lb_plan_p(Ctx &c) {
         VFMM_HIP(hipMemcpyAsync(c.mb_order.ptr, c.lval.ptr, sizeof(int) * (size_t)nitems, hipMemcpyDeviceToDevice, s));
     }
     // ---- one operator per key ----
-    const size_t tab_bytes = (x6 ? sizeof(uint32_t) * C::OPX : sizeof(float) * C::OP) * (size_t)nkeys;
+    const size_t tab_bytes =
+        (x6 ? sizeof(uint32_t) * C::OPX : (dbl ? sizeof(double) : sizeof(float)) * C::OP) * (size_t)nkeys;
     if (tab_bytes > MAX_TABLE_BYTES) return;  // too many distinct offsets: generic kernel
     c.mb_tab.ensure(tab_bytes);
-    if (x6)
+    if (dbl)
+        k_m2lb_optab<P, 0, double><<<nkeys, 256, 0, s>>>(nkeys, c.mb_ukey.as<uint64_t>(), f, c.mb_tab.as<double>());
+    else if (x6)
         k_m2lb_optab<P, 1><<<nkeys, 256, 0, s>>>(nkeys, c.mb_ukey.as<uint64_t>(), f, c.mb_tab.as<float>());
     else
         k_m2lb_optab<P, 0><<<nkeys, 256, 0, s>>>(nkeys, c.mb_ukey.as<uint64_t>(), f, c.mb_tab.as<float>());
@@ -1513,10 +1684,11 @@ void m2lb_plan(Ctx &c) {
 template <int P>
 static void m2lb_prealloc_p(Ctx &c) {
     constexpr int R = NR(P), RP = NRP(P);
-    c.mb_mr.ensure(sizeof(float) * (size_t)(c.ncells + 1) * 3 * RP);
-    if (c.mb_keyed) c.mb_cols.ensure(sizeof(float) * 3 * RP * (size_t)c.mb_ncols);
+    const size_t rs = c.prm.precision == VFMM_PRECISION_FP64 ? sizeof(double) : sizeof(float);
+    c.mb_mr.ensure(rs * (size_t)(c.ncells + 1) * 3 * RP);
+    if (c.mb_keyed) c.mb_cols.ensure(rs * 3 * RP * (size_t)c.mb_ncols);
     if (c.mb_nitems > 0)
-        c.mb_partial.ensure(sizeof(float) * (size_t)std::max(c.mb_nitems, 1) * 3 * R * 64);
+        c.mb_partial.ensure(rs * (size_t)std::max(c.mb_nitems, 1) * 3 * R * 64);
 }
 
 void m2lb_prealloc(Ctx &c) {
@@ -1536,11 +1708,39 @@ static void m2lb_run_p(Ctx &c) {
     hipStream_t s = c.stream;
     constexpr int R = NR(P), RP = NRP(P);
     const int64_t mr_total = (int64_t)(c.ncells + 1) * 3 * RP;
-    c.mb_mr.ensure(sizeof(float) * mr_total);
-    k_m2lb_mreal<P><<<cdiv(mr_total, TPB), TPB, 0, s>>>(c.ncells, c.Mexp.as<float2>(), c.mb_mr.as<float>());
+    const bool dbl = c.prm.precision == VFMM_PRECISION_FP64;
+    if (dbl)
+        k_m2lb_mreal<P, double><<<cdiv(mr_total, TPB), TPB, 0, s>>>(c.ncells, c.Mexp.as<double2>(),
+                                                                    c.mb_mr.as<double>());
+    else
+        k_m2lb_mreal<P, float><<<cdiv(mr_total, TPB), TPB, 0, s>>>(c.ncells, c.Mexp.as<float2>(),
+                                                                   c.mb_mr.as<float>());
     VFMM_LAUNCH_CHECK();
     m2lb_prealloc_p<P>(c);
-    if (c.mb_x6) {
+    if (dbl) {
+        if constexpr (Mb64Cfg<P>::OK) {
+            using X = Mb64Cfg<P>;
+            auto launch = [&](auto by_key) {
+                constexpr bool KEYED = decltype(by_key)::value;
+                const unsigned bit = 1u << (16 + P / 2 + (KEYED ? 8 : 0));
+                if (!(c.m2lbk_lds_set & bit)) {  // once per context (a context lives on one device)
+                    VFMM_HIP(hipFuncSetAttribute((const void *)k_m2lb_f64<P, KEYED>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)X::LDS));
+                    c.m2lbk_lds_set |= bit;
+                }
+                const int nitems = KEYED ? c.mb_kitems : c.mb_nitems;
+                k_m2lb_f64<P, KEYED><<<xcd_grid(nitems), X::THREADS, X::LDS, s>>>(
+                    (KEYED ? c.mb_kitem : c.mb_items).template as<int4>(), c.mb_order.as<int>(),
+                    (KEYED ? c.mb_kgroups : c.mb_groups).template as<int4>(),
+                    (KEYED ? c.mb_kslots : c.mb_slots).template as<int>(), c.mb_mr.as<double>(),
+                    c.mb_tab.as<double>(), c.mb_dst.as<int>(), nitems,
+                    (KEYED ? c.mb_cols : c.mb_partial).template as<double>());
+                VFMM_LAUNCH_CHECK();
+            };
+            if (c.mb_nitems > 0) launch(std::false_type{});
+            if (c.mb_keyed) launch(std::true_type{});
+        }
+    } else if (c.mb_x6) {
         using X = MbxCfg<P>;
         auto launch = [&](auto ns, auto by_key) {
             constexpr int NS = decltype(ns)::value;
@@ -1591,7 +1791,10 @@ static void m2lb_run_p(Ctx &c) {
     VFMM_LAUNCH_CHECK();
     if (c.mb_keyed) {
         constexpr int NT = COL_GROUPS * 3 * RP / 2;
-        if (c.prm.precision == VFMM_PRECISION_MIXED)
+        if (dbl)
+            k_m2lb_columns<P, double, double><<<c.ncells, NT, 0, s>>>(c.mb_coff.as<int>(), c.mb_cols.as<double>(),
+                                                                      c.Lexp.as<double2>());
+        else if (c.prm.precision == VFMM_PRECISION_MIXED)
             k_m2lb_columns<P, double><<<c.ncells, NT, 0, s>>>(c.mb_coff.as<int>(), c.mb_cols.as<float>(),
                                                               c.Lexp.as<float2>());
         else
@@ -1603,7 +1806,10 @@ static void m2lb_run_p(Ctx &c) {
     int *blk_item0 = c.mb_blk.as<int>() + nblk, *blk_nitem = blk_item0 + nblk;
     const dim3 rgrid(nblk, 3, cdiv(R, RC));
     if (nblk == 0) return;
-    if (c.prm.precision == VFMM_PRECISION_MIXED)
+    if (dbl)
+        k_m2lb_reduce<P, double, double><<<rgrid, TPB, 0, s>>>(blk_item0, blk_nitem, c.mb_bcells.as<int>(),
+                                                               c.mb_partial.as<double>(), c.Lexp.as<double2>());
+    else if (c.prm.precision == VFMM_PRECISION_MIXED)
         k_m2lb_reduce<P, double><<<rgrid, TPB, 0, s>>>(blk_item0, blk_nitem, c.mb_bcells.as<int>(),
                                                         c.mb_partial.as<float>(), c.Lexp.as<float2>());
     else

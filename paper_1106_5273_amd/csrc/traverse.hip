@@ -673,7 +673,7 @@ void traverse_and_lists(Ctx &c) {
 
     // ---- M2L CSR: only for the per-pair M2L (the batched plan reads the raw list) ----
     c.m2l_csr = false;
-    if (!(c.prm.m2l_mode != 1 && c.prm.precision != VFMM_PRECISION_FP64)) build_m2l_csr(c);
+    if (!m2l_batched(c.prm)) build_m2l_csr(c);
     // ---- P2P CSR ----
     csr_by_target(c, c.p2p_raw.as<int4>(), n_p2p, c.p2p_off);
     c.p2p_ent.ensure(sizeof(int4) * (size_t)std::max<int64_t>(n_p2p, 1));

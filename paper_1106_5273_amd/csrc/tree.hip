@@ -1042,8 +1042,8 @@ static constexpr int GEO_LANES = 16;
 __global__ __launch_bounds__(TPB) void k_leaf_geometry(int ncell, const RootBox *boxes, int KL, const int *start,
                                                        const int *count,
                                                        const int *level, const int *nchild, const uint64_t *keys,
-                                                       const float4 *rec, float4 *geo, float *rad, float4 *blo,
-                                                       float4 *bhi) {
+                                                       const float4 *rec, float4 *geo, double4 *geo64, float *rad,
+                                                       float4 *blo, float4 *bhi) {
     const int cell = blockIdx.x * (TPB / GEO_LANES) + threadIdx.x / GEO_LANES, sub = threadIdx.x % GEO_LANES;
     if (cell >= ncell) return;
     const int lvl = level[cell];
@@ -1064,7 +1064,12 @@ __global__ __launch_bounds__(TPB) void k_leaf_geometry(int ncell, const RootBox 
     g.y = (float)(box.lo[1] + (q[1] + 0.5) * size);
     g.z = (float)(box.lo[2] + (q[2] + 0.5) * size);
     g.w = (float)size;
-    if (sub == 0) geo[cell] = g;
+    if (sub == 0) {
+        geo[cell] = g;
+        if (geo64)
+            geo64[cell] = make_double4(box.lo[0] + (q[0] + 0.5) * size, box.lo[1] + (q[1] + 0.5) * size,
+                                       box.lo[2] + (q[2] + 0.5) * size, size);
+    }
     if (nchild[cell] != 0) return;
     float r2 = 0.f;
     float4 lo = make_float4(3.4e38f, 3.4e38f, 3.4e38f, 0.f), hi = make_float4(-3.4e38f, -3.4e38f, -3.4e38f, 0.f);
@@ -1291,9 +1296,12 @@ void build_tree(Ctx &c, int64_t n, const float *x, const float *y, const float *
     c.c_rad.ensure(sizeof(float) * nc);
     c.c_lo.ensure(sizeof(float4) * nc);
     c.c_hi.ensure(sizeof(float4) * nc);
+    const bool dbl = c.prm.precision == VFMM_PRECISION_FP64;
+    if (dbl) c.c_geo64.ensure(sizeof(double4) * nc);
     k_leaf_geometry<<<cdiv(nc * (int64_t)GEO_LANES, TPB), TPB, 0, s>>>(nc, c.pbox.as<RootBox>(), KL, c.c_start.as<int>(), c.c_count.as<int>(),
                                                    c.c_level.as<int>(), c.c_nchild.as<int>(), keys,
-                                                   c.rec.as<float4>(), c.c_geo.as<float4>(), c.c_rad.as<float>(),
+                                                   c.rec.as<float4>(), c.c_geo.as<float4>(),
+                                                   dbl ? c.c_geo64.as<double4>() : nullptr, c.c_rad.as<float>(),
                                                    c.c_lo.as<float4>(), c.c_hi.as<float4>());
     VFMM_LAUNCH_CHECK();
     if (nc <= TREE_GEO_GROUP) {
