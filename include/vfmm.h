@@ -92,10 +92,11 @@ typedef struct vfmm_params {
     int32_t kahan;       /* 1: compensated per-target sums in P2P (default 0: blocked sums)    */
     int32_t zero_mean;   /* periodic: subtract (1/3V) sum x_j x alpha_j (default 1)           */
     int32_t direct;      /* 1: all-pairs P2P without a tree (test mode; free space only)      */
-    int32_t m2l_mode;    /* 0 (default): operator-batched M2L when the tree's translations group
-                            densely (at least 8 per (64-target block, offset) group), else per
-                            pair; 1: per-pair M2L; 2: operator-batched whenever the offsets can be
-                            keyed (falls back to per pair only when they cannot)                 */
+    int32_t m2l_mode;    /* 0 (default): the form of least estimated cost: operator-batched M2L
+                            with groups by (64-target block, offset) where they fill, by offset
+                            alone where they do not, else per pair; 1: per-pair M2L; 2: groups by
+                            (block, offset) whenever the offsets can be keyed (per pair only when
+                            they cannot; in the float64 form always)                           */
     int32_t use_graph;   /* 1: fmm_evaluate runs as a hipGraph, captured on the first call after
                             a build (or when its pointers change) and replayed afterwards; needs
                             a non-default stream and the tree path (default 0)                */
@@ -104,10 +105,11 @@ typedef struct vfmm_params {
                             kahan = 1), float64 accumulation in M2M, L2L and in the reduction of
                             the batched M2L's partial sums, float64 periodic lattice operator.
                             VFMM_PRECISION_FP64: particle records, expansions, every far-field
-                            operator (M2L per pair) and P2P in float64 (cutoff always in its full
-                            form), outputs rounded to float32 once; with the same tree and lists
-                            as the other forms, its difference from them is their rounding error
-                            (Sec. 4.2 normalises the expansions so that float32 stays in range). */
+                            operator (M2L batched on the float64 matrix instructions up to p = 10,
+                            else per pair) and P2P in float64 (cutoff always in its full form),
+                            outputs rounded to float32 once; with the same tree and lists as the
+                            other forms, its difference from them is their rounding error (Sec.
+                            4.2 normalises the expansions so that float32 stays in range).    */
     int32_t overlap;     /* 0: one stream, the phases run one after the other (P2P last).  1:
                             the near field (P2P) runs on a second stream of the library
                             concurrently with the far field and a final kernel adds them (the
@@ -162,8 +164,8 @@ typedef struct vfmm_stats {
     double sum_alpha[3];    /* float64 sum of alpha (set by fmm_evaluate)         */
     double sigma_min, sigma_max;
     int32_t m2l_keys;       /* batched M2L: distinct translation operators (0 if per pair) */
-    int32_t m2l_groups;     /* batched M2L: (target block, operator) groups        */
-    int32_t m2l_items;      /* batched M2L: work items (<= 24 groups of one block) */
+    int32_t m2l_groups;     /* batched M2L: groups of one operator's translations  */
+    int32_t m2l_items;      /* batched M2L: work items (<= 24 groups)              */
     int32_t m2l_split;      /* batched M2L: 1 when it runs the split bf16 products
                                (six per product), 2 for the three-product form      */
     int32_t stale;          /* 1 when the last fmm_evaluate found positions or cores

@@ -1278,6 +1278,14 @@ __global__ __launch_bounds__(TPB) void k_group_split(int ng, int nc, const int4 
 // per-pair kernel (0.29 ms; by key 0.16, for a plan of 0.17 more).
 static constexpr size_t MAX_COLUMN_BYTES = size_t(8) << 30;
 
+// Whether a buffer of these plans holds the bytes or may grow to them: within half of
+// the free memory, so that a call near the card's capacity keeps the form it had.
+static bool may_hold(const DevBuf &b, size_t bytes) {
+    if (bytes <= b.cap) return true;
+    size_t free_bytes = 0, total = 0;
+    return hipMemGetInfo(&free_bytes, &total) == hipSuccess && bytes <= free_bytes / 2;
+}
+
 struct M2lCosts {
     double group, col, key, pair;
 };
@@ -1377,7 +1385,9 @@ static bool m2lb_plan_keyed(Ctx &c, int64_t n, int nkeys, double other, const Ke
     const int ng = h[0], nused = h[1], nrest = h[2];
     const int64_t ncols = n - nrest;
     const size_t tab_bytes = (dbl ? sizeof(double) * C::OP : sizeof(uint32_t) * C::OPX) * (size_t)nused;
-    if (ng == 0 || tab_bytes > MAX_TABLE_BYTES || rs * 3 * C::RP * (size_t)ncols > MAX_COLUMN_BYTES ||
+    const size_t col_bytes = rs * 3 * C::RP * (size_t)ncols;
+    if (ng == 0 || tab_bytes > MAX_TABLE_BYTES || col_bytes > MAX_COLUMN_BYTES || !may_hold(c.mb_cols, col_bytes) ||
+        (dbl && !may_hold(c.mb_tab, tab_bytes)) ||
         plan + t.group * ng + t.col * (double)ncols + t.key * nused + t.pair * nrest > other)
         return false;
     c.mb_low.ensure(sizeof(uint64_t) * (size_t)nused);
@@ -1420,8 +1430,9 @@ static bool m2lb_fill_plan(Ctx &c, int64_t n, int nkeys, int &ng, const KeyFmt &
     const double block = 1.1 * t.group * ng, tab = t.key * nkeys;
     const double split = 1.1 * t.group * stay + t.group * (nlow / 64.0 + std::min(nkeys, nlow) / 2.0) +
                          (t.col + 0.15) * nlow + 3.5e5;
-    const bool low = stay > 0 && nlow > 0 && split < block &&
-                     sizeof(float) * 3 * C::RP * (size_t)nlow <= MAX_COLUMN_BYTES;
+    const size_t col_bytes = sizeof(float) * 3 * C::RP * (size_t)nlow;
+    const bool low = stay > 0 && nlow > 0 && split < block && col_bytes <= MAX_COLUMN_BYTES &&
+                     may_hold(c.mb_cols, col_bytes);
     if (m2lb_plan_keyed<P>(c, n, nkeys, (low ? split : block) + tab, f)) return true;
     if (!low) return false;
     c.mb_low.ensure(sizeof(int4) * (size_t)nlow);
@@ -1560,6 +1571,8 @@ static void m2lb_plan_p(Ctx &c) {
     // ---- groups (block, key) in (block, key) order ----
     const int64_t T = (int64_t)nblk * nkeys;
     if (T > ((int64_t)1 << 28)) return;  // table too large: per-pair M2L
+    if (dbl && c.mb_gcnt.cap < sizeof(int) * (size_t)(T + 1) && !may_hold(c.mb_gcnt, 4 * sizeof(int) * (size_t)T))
+        return;
     c.mb_gcnt.ensure(sizeof(int) * (size_t)(T + 1));
     c.mb_gid.ensure(sizeof(int) * (size_t)(T + 1));
     c.mb_goff.ensure(sizeof(int) * (size_t)(T + 1));
@@ -1650,6 +1663,7 @@ static void m2lb_plan_p(Ctx &c) {
     const size_t tab_bytes =
         (x6 ? sizeof(uint32_t) * C::OPX : (dbl ? sizeof(double) : sizeof(float)) * C::OP) * (size_t)nkeys;
     if (tab_bytes > MAX_TABLE_BYTES) return;  // too many distinct offsets: generic kernel
+    if (dbl && !may_hold(c.mb_tab, tab_bytes)) return;
     c.mb_tab.ensure(tab_bytes);
     if (dbl)
         k_m2lb_optab<P, 0, double><<<nkeys, 256, 0, s>>>(nkeys, c.mb_ukey.as<uint64_t>(), f, c.mb_tab.as<double>());

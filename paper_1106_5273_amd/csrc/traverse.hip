@@ -390,7 +390,10 @@ __global__ __launch_bounds__(TPB) void k_sum_u64x2(const unsigned long long *par
 // a part is chosen from the whole build's work: total wave steps / 172,032 (24
 // rounds of the 7,168 waves that fill the chip), but at least 48 steps (shorter
 // parts cost more in their prologue and partial sums than they spread) and at
-// most 2,400 (the four parts of 37 leaves at 128^3).  A fixed four parts per
+// most 1,200.  More than two parts are made a multiple of the four waves of a
+// work-group, which then share one block's targets and neighbouring sources: 512
+// rings with leaves of 384 take 60.3 ms an evaluation with 8 parts a block, 68.3
+// with 4, 68.8 with 6 and 71.6 with 3; 128^3 takes four or eight alike.  A fixed four parts per
 // block left one list of 4,849 entries in a clustered tree of 100,003 particles
 // to four waves, which alone set the kernel's time.
 // ---------------------------------------------------------------------------
@@ -402,7 +405,7 @@ struct LeafWork {
 __device__ inline LeafWork leaf_work(const unsigned long long *tot, int64_t nent) {
     const float pairs = (float)tot[0], srcs = (float)tot[1];
     return LeafWork{fmaxf(1.f, srcs / (float)max((int64_t)1, nent)),
-                    fminf(2400.f, fmaxf(48.f, pairs * (1.f / (48.f * 172032.f))))};
+                    fminf(1200.f, fmaxf(48.f, pairs * (1.f / (48.f * 172032.f))))};
 }
 
 // The remainder r = 1 .. 63 of a leaf's targets past its blocks of 64 is cut
@@ -448,7 +451,10 @@ __device__ inline void leaf_blocks(int cnt, int ns, F f) {
 // per entry, lane groups take a share of the list's sources; a part of theirs
 // holds at least 128 sources (the last pass of 64 is partly empty)
 __device__ inline int list_parts(const LeafWork &W, int tc, int lc) {
-    if (tc > 32) return max(1, min(lc, (int)((float)lc * (W.src_per_entry + 6.f) / W.part + 0.5f)));
+    if (tc > 32) {
+        const int np = max(1, min(lc, (int)((float)lc * (W.src_per_entry + 6.f) / W.part + 0.5f)));
+        return np > 2 && lc >= 8 ? (np + 2) / 4 * 4 : np;
+    }
     const float srcs = (float)lc * W.src_per_entry;
     const int most = min(lc, (int)(srcs * (1.f / 128.f)));
     return max(1, min(most, (int)(srcs / ((float)p2p_groups(tc) * W.part) + 0.5f)));
