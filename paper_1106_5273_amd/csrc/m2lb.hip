@@ -19,8 +19,12 @@
 // group stages the source multipoles of the 64 target slots in LDS, and the
 // products [rows x inputs] x [inputs x 64 targets] run on FP32 matrix-core
 // instructions (v_mfma_f32_16x16x4f32).  Partial sums of the work items are
-// added per block in item order, so results are bit-reproducible.  Trees
-// whose groups stay sparse (irregular particle sets) use the per-pair M2L.
+// added per block in item order, so results are bit-reproducible.  The default
+// form splits the float32 operands for the bfloat16 matrix cores (k_m2lb_x6), the
+// float64 form runs on the float64 ones (k_m2lb_f64).  Where the targets of a
+// block share too few keys to fill groups (irregular particle sets), groups take
+// the translations of one key whatever their targets (keyed_lists,
+// k_m2lb_columns); short lists and rare keys use the per-pair M2L.
 #include <algorithm>
 #include <type_traits>
 #include <utility>

@@ -602,7 +602,7 @@ __device__ __forceinline__ void p2p_group(const P2PConst &k, const P2PArgs &A, i
 // One wave per item; neighbouring waves take the parts of one block (they share
 // its target records and much of its source data in the caches).  The two kinds
 // of blocks are two kernels: the group form needs 74 vector registers, which
-// would cost the scalar form (51) one of its seven waves per SIMD.
+// would cost the scalar form (51) two of its eight waves per SIMD.
 __device__ __forceinline__ bool load_item(const P2PArgs &A, int item0, int item1, int &t0, int &tc, int &l0, int &lc,
                                           float *&near) {
     const int j = xcd_logical(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
@@ -1081,11 +1081,11 @@ static P2PArgs tree_args(Ctx &c) {
 // Near field alone, on stream s, into c.near (the partial results of every
 // work item); the far field runs before, after or beside it on the library
 // stream and finalize_near_far adds a block's parts and the far field.  At
-// 128^3 a block's list is four parts: its 32,768 one-block waves would fill
+// 128^3 a block's list is eight parts: its 32,768 one-block waves would fill
 // every SIMD exactly four times over, and the uneven end of the last round
-// costs a few percent; a work-group then also covers one block instead of
-// four, so fewer target neighbourhoods are in flight on each XCD and more
-// source records hit in L2.
+// costs a few percent; a work-group's waves then also share one block, so fewer
+// target neighbourhoods are in flight on each XCD and more source records hit in
+// L2.
 void p2p_near(Ctx &c, hipStream_t s) {
     const P2PConst k = make_const(c.sigma_uniform, c.var_sigma);
     c.near.ensure(sizeof(float) * 6 * (size_t)std::max(c.n_partial, 1));
