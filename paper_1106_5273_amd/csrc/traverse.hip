@@ -393,9 +393,9 @@ __global__ __launch_bounds__(TPB) void k_sum_u64x2(const unsigned long long *par
 // most 1,200.  More than two parts are made a multiple of the four waves of a
 // work-group, which then share one block's targets and neighbouring sources: 512
 // rings with leaves of 384 take 60.3 ms an evaluation with 8 parts a block, 68.3
-// with 4, 68.8 with 6 and 71.6 with 3; 128^3 takes four or eight alike.  A fixed four parts per
-// block left one list of 4,849 entries in a clustered tree of 100,003 particles
-// to four waves, which alone set the kernel's time.
+// with 4, 68.8 with 6 and 71.6 with 3; 128^3 takes four or eight alike.  A fixed
+// four parts per block left one list of 4,849 entries in a clustered tree of
+// 100,003 particles to four waves, which alone set the kernel's time.
 // ---------------------------------------------------------------------------
 struct LeafWork {
     float src_per_entry;  // mean sources of a list entry
@@ -453,7 +453,7 @@ __device__ inline void leaf_blocks(int cnt, int ns, F f) {
 __device__ inline int list_parts(const LeafWork &W, int tc, int lc) {
     if (tc > 32) {
         const int np = max(1, min(lc, (int)((float)lc * (W.src_per_entry + 6.f) / W.part + 0.5f)));
-        return np > 2 && lc >= 8 ? (np + 2) / 4 * 4 : np;
+        return np > 2 ? min(lc, (np + 2) / 4 * 4) : np;  // every part keeps an entry
     }
     const float srcs = (float)lc * W.src_per_entry;
     const int most = min(lc, (int)(srcs * (1.f / 128.f)));
