@@ -3,6 +3,7 @@
 #include <initializer_list>
 
 #include "common.h"
+#include "near_parts.h"
 
 namespace vfmm {
 
@@ -235,10 +236,6 @@ __host__ __device__ inline int parts_left(int w) {
     const int np = w & PBLOCK_PARTS;
     return np > LONG_PARTS ? 1 : np;
 }
-// Lane groups of a near-field block of tc targets: more than 32 targets take the
-// wave alone; fewer are held by several groups of tc lanes each (at most 16),
-// which take different sources.
-__host__ __device__ inline int p2p_groups(int tc) { return tc > 32 ? 1 : tc < 4 ? 16 : 64 / tc; }
 // Scale of the float32 near field: lengths times kappa = log2(e)^(1/2) / (sqrt 2 sigma)
 // turn the Gaussian e^{-rho^2/(2 sigma^2)} into 2^{-rho'^2}; a = (2/sqrt pi) ln(2)^(1/2).
 inline double p2p_kappa(double sigma) { return std::sqrt(1.0 / std::log(2.0)) / (std::sqrt(2.0) * sigma); }

@@ -384,113 +384,63 @@ __global__ __launch_bounds__(TPB) void k_sum_u64x2(const unsigned long long *par
     }
 }
 
-// ---------------------------------------------------------------------------
-// P2P work: every leaf's targets are cut into blocks of at most 64, and every
-// block's list into parts of about equal length, one wave each.  The length of
-// a part is chosen from the whole build's work: total wave steps / 172,032 (24
-// rounds of the 7,168 waves that fill the chip), but at least 48 steps (shorter
-// parts cost more in their prologue and partial sums than they spread) and at
-// most 1,200.  More than two parts are made a multiple of the four waves of a
-// work-group, which then share one block's targets and neighbouring sources: 512
-// rings with leaves of 384 take 60.3 ms an evaluation with 8 parts a block, 68.3
-// with 4, 68.8 with 6 and 71.6 with 3; 128^3 takes four or eight alike.  A fixed
-// four parts per block left one list of 4,849 entries in a clustered tree of
-// 100,003 particles to four waves, which alone set the kernel's time.
-// ---------------------------------------------------------------------------
-struct LeafWork {
-    float src_per_entry;  // mean sources of a list entry
-    float part;           // wave steps per part
-};
-
-__device__ inline LeafWork leaf_work(const unsigned long long *tot, int64_t nent) {
-    const float pairs = (float)tot[0], srcs = (float)tot[1];
-    return LeafWork{fmaxf(1.f, srcs / (float)max((int64_t)1, nent)),
-                    fminf(1200.f, fmaxf(48.f, pairs * (1.f / (48.f * 172032.f))))};
-}
-
-// The remainder r = 1 .. 63 of a leaf's targets past its blocks of 64 is cut
-// into k blocks of nearly equal size.  A block of more than 32 targets leaves
-// the other lanes idle, one of g <= 32 fills the wave with several groups that
-// take different list entries (p2p_groups), so the wave rounds per list entry
-// are k / p2p_groups(ceil(r / k)); k grows where that saves at least a fifth
-// (33 .. 42 targets: two blocks, 2/3; 43 .. 48: three, 3/4).  Leaves of 27, 36
-// and 48 (per-particle cores, 50^3): near field 1.28 -> 1.10 ms.
-__device__ inline int remainder_blocks(int r) {
-    int best = 1;
-    float cost = 1.f / (float)p2p_groups(r);
-    for (int k = 2; k <= 3 && k <= r; ++k) {
-        const float ck = (float)k / (float)p2p_groups((r + k - 1) / k);
-        if (ck <= 0.8f * cost) {
-            best = k;
-            cost = ck;
-        }
-    }
-    return best;
-}
-
-// The near-field blocks of a leaf of cnt targets, of which the first ns are
-// particles and the rest target points without strength (their blocks compute
-// the velocity alone): f(first target, targets, whether target points).
-template <class F>
-__device__ inline void leaf_blocks(int cnt, int ns, F f) {
-    for (int half = 0; half < 2; ++half) {
-        const int lo = half ? ns : 0, c = half ? cnt - ns : ns;
-        const int full = c / 64, r = c % 64;
-        for (int b = 0; b < full; ++b) f(lo + 64 * b, 64, half != 0);
-        if (r == 0) continue;
-        const int k = remainder_blocks(r);
-        for (int q = 0; q < k; ++q) {
-            const int a = q * r / k, e = (q + 1) * r / k;
-            f(lo + 64 * full + a, e - a, half != 0);
-        }
-    }
-}
-
-// parts of the list (lc entries) of a block of tc targets: whole-wave blocks
-// take an entry's sources one per step with a fixed cost of about six steps
-// per entry, lane groups take a share of the list's sources; a part of theirs
-// holds at least 128 sources (the last pass of 64 is partly empty)
-__device__ inline int list_parts(const LeafWork &W, int tc, int lc) {
-    if (tc > 32) {
-        const int np = max(1, min(lc, (int)((float)lc * (W.src_per_entry + 6.f) / W.part + 0.5f)));
-        return np > 2 ? min(lc, (np + 2) / 4 * 4) : np;  // every part keeps an entry
-    }
-    const float srcs = (float)lc * W.src_per_entry;
-    const int most = min(lc, (int)(srcs * (1.f / 128.f)));
-    return max(1, min(most, (int)(srcs / ((float)p2p_groups(tc) * W.part) + 0.5f)));
-}
-
 // per leaf: its blocks of 64 (Gaussian sums), its near-field blocks, the parts
 // by kind (whole waves, lane groups, the same for target points), the float[6]
 // outputs of the parts, and the blocks of many parts
 constexpr int LEAF_SUMS = 8;
 
+// partials: the work-group's targets times parts, in 64 bits.  The 32-bit sums
+// may wrap; they are used only once the total of these is within its limit.
 __global__ __launch_bounds__(TPB) void k_leaf_counts(const int *leaves, int nl, const int *count, const int *nsrc,
                                                      const int *loff, const unsigned long long *tot, int64_t nent,
-                                                     int *out) {
+                                                     float stretch, int *out, unsigned long long *partials) {
     const int i = blockIdx.x * TPB + threadIdx.x;
-    if (i >= nl) return;
-    const LeafWork W = leaf_work(tot, nent);
-    const int cell = leaves[i];
-    const int cnt = count[cell], lc = loff[cell + 1] - loff[cell];
-    int s[LEAF_SUMS] = {(cnt + 63) / 64, 0, 0, 0, 0, 0, 0, 0};
-    leaf_blocks(cnt, nsrc ? nsrc[cell] : cnt, [&](int, int tc, bool pts) {
-        const int np = list_parts(W, tc, lc), kind = (pts ? 2 : 0) + (tc > 32 ? 0 : 1);
-        ++s[1];
+    unsigned long long np64 = 0;
+    if (i < nl) {
+        const LeafWork W = leaf_work(tot[0], tot[1], nent, stretch);
+        const int cell = leaves[i];
+        const int cnt = count[cell], lc = loff[cell + 1] - loff[cell];
+        unsigned s[LEAF_SUMS] = {(cnt + 63u) / 64u, 0, 0, 0, 0, 0, 0, 0};
+        leaf_blocks(cnt, nsrc ? nsrc[cell] : cnt, [&](int, int tc, bool pts) {
+            const int np = list_parts(W, tc, lc), kind = (pts ? 2 : 0) + (tc > 32 ? 0 : 1);
+            ++s[1];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) s[2 + k] += k == kind ? np : 0;
-        s[6] += np * tc;
-        s[7] += np > LONG_PARTS;
-    });
+            for (int k = 0; k < 4; ++k) s[2 + k] += k == kind ? np : 0;
+            np64 += (unsigned long long)np * (unsigned)tc;
+            s[7] += np > LONG_PARTS;
+        });
+        s[6] = (unsigned)np64;
 #pragma unroll
-    for (int k = 0; k < LEAF_SUMS; ++k) out[k * nl + i] = s[k];
+        for (int k = 0; k < LEAF_SUMS; ++k) out[(size_t)k * nl + i] = (int)s[k];
+    }
+    __shared__ unsigned long long red[TPB / 64];
+    for (int o = 32; o > 0; o >>= 1) np64 += __shfl_xor(np64, o, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = np64;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < TPB / 64; ++w) np64 += red[w];
+        partials[blockIdx.x] = np64;
+    }
 }
 
-// the totals and the pair count, straight to pinned host memory
-__global__ void k_leaf_totals(const int *cnt, const int *off, int nl, const int *tot, int *out) {
-    for (int k = 0; k < LEAF_SUMS; ++k) out[k] = off[(k + 1) * nl - 1] + cnt[(k + 1) * nl - 1] - off[k * nl];
-    out[LEAF_SUMS] = tot[0];
-    out[LEAF_SUMS + 1] = tot[1];
+// the totals, the pair count and the targets times parts (np work-groups'), straight to pinned host memory
+__global__ __launch_bounds__(TPB) void k_leaf_totals(const int *cnt, const int *off, int nl, const int *tot,
+                                                     const unsigned long long *partials, int np, int *out) {
+    __shared__ unsigned long long red[TPB / 64];
+    unsigned long long v = 0;
+    for (int i = threadIdx.x; i < np; i += TPB) v += partials[i];
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    const int k = threadIdx.x;
+    if (k < LEAF_SUMS)
+        out[k] = off[(size_t)(k + 1) * nl - 1] + cnt[(size_t)(k + 1) * nl - 1] - off[(size_t)k * nl];
+    if (k < 2) out[LEAF_SUMS + k] = tot[k];
+    if (k == 0) {
+        for (int w = 1; w < TPB / 64; ++w) v += red[w];
+        out[LEAF_SUMS + 2] = (int)(unsigned)v;
+        out[LEAF_SUMS + 3] = (int)(unsigned)(v >> 32);
+    }
 }
 
 struct ItemKinds {
@@ -503,21 +453,26 @@ struct ItemKinds {
 // items of kind k from K.first[k] on
 __global__ __launch_bounds__(TPB) void k_leaf_items(const int *leaves, int nl, const int *start, const int *count,
                                                     const int *nsrc, const int *loff, const unsigned long long *tot,
-                                                    int64_t nent, const int *off, ItemKinds K, int4 *blocks,
+                                                    int64_t nent, float stretch, const int *off, ItemKinds K,
+                                                    int4 *blocks,
                                                     int4 *pblocks, int *pblong, int4 *items, int *item_out) {
     // one wave per leaf: a leaf may have hundreds of parts
     const int i = blockIdx.x * (TPB / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (i >= nl) return;
-    const LeafWork W = leaf_work(tot, nent);
+    const LeafWork W = leaf_work(tot[0], tot[1], nent, stretch);
     const int cell = leaves[i];
     const int s = start[cell], cnt = count[cell];
     const int l0 = loff[cell], lc = loff[cell + 1] - l0;
     for (int k = 64 * lane, b = off[i] + lane; k < cnt; k += 64 * 64, b += 64)
         blocks[b] = make_int4(s + k, min(64, cnt - k), l0, lc);
-    int pb = off[nl + i] - off[nl], u = off[6 * nl + i] - off[6 * nl], ib = off[7 * nl + i] - off[7 * nl];
+    auto before = [&](int k) {  // sum k of the leaves before this one
+        const int *o = off + (size_t)k * nl;
+        return o[i] - o[0];
+    };
+    int pb = before(1), u = before(6), ib = before(7);
     int it[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) it[k] = K.first[k] + off[(2 + k) * nl + i] - off[(2 + k) * nl];
+    for (int k = 0; k < 4; ++k) it[k] = K.first[k] + before(2 + k);
     leaf_blocks(cnt, nsrc ? nsrc[cell] : cnt, [&](int t0, int tc, bool pts) {
         const int np = list_parts(W, tc, lc), kind = (pts ? 2 : 0) + (tc > 32 ? 0 : 1);
         int i0 = it[0];
@@ -718,37 +673,40 @@ void traverse_and_lists(Ctx &c) {
     int *cnt = c.c_tmp.as<int>(), *off = cnt + LEAF_SUMS * (size_t)nl;
     const int *nsrc = c.parted ? c.c_nsrc.as<int>() : nullptr;
     const unsigned long long *tot = c.pairs64.as<unsigned long long>();
-    k_leaf_counts<<<cdiv(nl, TPB), TPB, 0, s>>>(c.leaves.as<int>(), nl, c.c_count.as<int>(), nsrc, c.p2p_off.as<int>(),
-                                                tot, n_p2p, cnt);
-    VFMM_LAUNCH_CHECK();
-    scan_excl_i32(c, cnt, off, LEAF_SUMS * (int64_t)nl);
-    k_leaf_totals<<<1, 1, 0, s>>>(cnt, off, nl, c.pairs64.as<int>(), pinned_ints(c));
-    VFMM_LAUNCH_CHECK();
-    int h[LEAF_SUMS + 2];
-    sync_ints(c, LEAF_SUMS + 2, h);
+    const int ncb = (int)cdiv(nl, TPB);
+    c.gpart.ensure(sizeof(unsigned long long) * (size_t)ncb);
+    int h[LEAF_SUMS + 4];
+    auto count64 = [&](int k) { return (int64_t)((uint64_t)(uint32_t)h[k] | ((uint64_t)(uint32_t)h[k + 1] << 32)); };
+    float stretch = 1.f;
+    c.n_partial = (int)fit_parts(partials_limit(c.n), [&](float by) {
+        k_leaf_counts<<<ncb, TPB, 0, s>>>(c.leaves.as<int>(), nl, c.c_count.as<int>(), nsrc, c.p2p_off.as<int>(), tot,
+                                          n_p2p, by, cnt, c.gpart.as<unsigned long long>());
+        VFMM_LAUNCH_CHECK();
+        scan_excl_i32(c, cnt, off, LEAF_SUMS * (int64_t)nl);
+        k_leaf_totals<<<1, TPB, 0, s>>>(cnt, off, nl, c.pairs64.as<int>(), c.gpart.as<unsigned long long>(), ncb,
+                                        pinned_ints(c));
+        VFMM_LAUNCH_CHECK();
+        sync_ints(c, LEAF_SUMS + 4, h);
+        return count64(LEAF_SUMS + 2);
+    }, stretch);
     c.n_blocks = h[0];
     c.n_pblocks = h[1];
     ItemKinds K{};
-    int64_t items = 0;
+    int items = 0;  // at most n_partial
     for (int k = 0; k < 4; ++k) {
-        c.item0[k] = K.first[k] = (int)items;
+        c.item0[k] = K.first[k] = items;
         items += h[2 + k];
-        if (h[2 + k] < 0) items = INT64_MAX / 2;
     }
-    c.item0[4] = (int)items;
-    c.n_partial = h[6];
+    c.item0[4] = items;
     c.n_long = h[7];
-    c.p2p_pairs = (int64_t)((unsigned long long)(uint32_t)h[LEAF_SUMS] |
-                            ((unsigned long long)(uint32_t)h[LEAF_SUMS + 1] << 32));
-    if (c.n_pblocks < 0 || items > INT32_MAX || c.n_partial < 0)
-        throw Error{VFMM_ENOMEM, "near-field work items exceed 2^31 entries"};
+    c.p2p_pairs = count64(LEAF_SUMS);
     c.blocks.ensure(sizeof(int4) * (size_t)std::max(c.n_blocks, 1));
     c.pblong.ensure(sizeof(int) * (size_t)std::max(c.n_long, 1));
     c.pblocks.ensure(sizeof(int4) * (size_t)std::max(c.n_pblocks, 1));
-    c.items.ensure(sizeof(int4) * (size_t)std::max<int64_t>(items, 1));
-    c.item_out.ensure(sizeof(int) * (size_t)std::max<int64_t>(items, 1));
+    c.items.ensure(sizeof(int4) * (size_t)std::max(items, 1));
+    c.item_out.ensure(sizeof(int) * (size_t)std::max(items, 1));
     k_leaf_items<<<cdiv(nl, TPB / 64), TPB, 0, s>>>(c.leaves.as<int>(), nl, c.c_start.as<int>(), c.c_count.as<int>(),
-                                                    nsrc, c.p2p_off.as<int>(), tot, n_p2p, off, K,
+                                                    nsrc, c.p2p_off.as<int>(), tot, n_p2p, stretch, off, K,
                                                     c.blocks.as<int4>(), c.pblocks.as<int4>(), c.pblong.as<int>(),
                                                     c.items.as<int4>(), c.item_out.as<int>());
     VFMM_LAUNCH_CHECK();
