@@ -483,7 +483,9 @@ __device__ __forceinline__ void p2p_block(const P2PConst &k, const P2PArgs &A, i
 // have equal work whatever the leaves' sizes, and a lane moves its source into
 // the target leaf's frame as it stages it (delta_j - D', and ah x of it), so
 // that there is no work per entry left in the pair loop.  Lanes past the end of
-// the stream stage zero strengths far away, which contribute exactly zero.
+// the stream stage the last source, which is of the same pass, without its
+// strength: the pass's form of the cutoff is finite for its pairs, so it contributes
+// exactly zero (a record at a place of its own could meet a target).
 // Bound by VALU issue like the scalar form (70 of about 85 instructions per
 // trip of two sources are pair arithmetic).  An 80^3 jittered lattice (15.6
 // particles per leaf, 2.88e9 pairs): 7.1 ms with groups of 16 or 32 lanes that
@@ -564,9 +566,9 @@ __device__ __forceinline__ void p2p_group(const P2PConst &k, const P2PArgs &A, i
             sb.x = fmaf(sa.z, h.y, fmaf(-sa.y, h.z, sb.x));
             sb.y = fmaf(sa.x, h.z, fmaf(-sa.z, h.x, sb.y));
             sb.z = fmaf(sa.y, h.x, fmaf(-sa.x, h.y, sb.z));
-            if (!ok) {
-                sp = make_float4(1e4f, 0.f, 0.f, 1.f);
-                sa = sb = make_float4(0.f, 0.f, 0.f, 1.f);
+            if (!ok) {  // the last source again without its strength: its form holds for it
+                sa = make_float4(0.f, 0.f, 0.f, sa.w);
+                sb = make_float4(0.f, 0.f, 0.f, sb.w);
             }
             // the form that every staged source allows
             const int any0 = __any(form == 0), any1 = __any(form == 1);
@@ -1292,9 +1294,9 @@ __global__ __launch_bounds__(64 * DIRECT_SMALL_WAVES) void k_direct_small(P2PCon
         const bool ok = f < n;
         const float4 *src = A.rec + RS * (size_t)min(f, n - 1);
         float4 sp = src[0], sa = src[1], sb = src[2];
-        if (!ok) {  // zero strength far away
-            sp = make_float4(1e4f, 0.f, 0.f, 1.f);
-            sa = sb = make_float4(0.f, 0.f, 0.f, 1.f);
+        if (!ok) {  // the last source again without its strength
+            sa = make_float4(0.f, 0.f, 0.f, sa.w);
+            sb = make_float4(0.f, 0.f, 0.f, sb.w);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // LDS order within the wave
         L[3 * lane] = sp;

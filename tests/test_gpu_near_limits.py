@@ -1,4 +1,5 @@
-"""Large leaves, whose lists would be cut into more partial results than a build may have."""
+"""Places of the near field that ordinary cases do not reach: large leaves, whose lists would be cut into more partial
+results than a build may have; particles at round offsets from their leaf's centre."""
 import numpy as np
 import pytest
 
@@ -32,3 +33,35 @@ def test_leaves_of_512():
     ref = oracle.direct(case, targets=sub)
     check("leaves of 512, u", o[sub, :3], ref["u"], 1e-4, 1e-3)
     check("leaves of 512, dalpha", o[sub, 3:], ref["da_t"], 1e-4, 1e-3)
+
+
+@pytest.mark.parametrize("scheme", [0, 1])
+@pytest.mark.parametrize("step", [1e4, 5e3, 2.5e3])
+def test_round_offsets_in_the_callers_units(step, scheme):
+    """Per-particle cores keep offsets in the caller's units.  Each of 64 leaves of 8 holds a particle at exactly
+    (1e4, 0, 0) from its centre, with list ends whose sources are all of the singular form.  The evaluation's gate of
+    1e-4."""
+    import torch
+    import paper_1106_5273_amd as vf
+    rng = np.random.default_rng(3)
+    g = np.stack(np.meshgrid(*[np.arange(4)] * 3, indexing="ij"), -1).reshape(-1, 1, 3) * 4e4 + 2e4
+    d = np.round(rng.uniform(-1e4, 1e4, (64, 8, 3)) / step) * step
+    d += rng.uniform(-0.1, 0.1, d.shape) * step * (np.arange(8) > 0)[:, None]
+    d[:, 0] = [1e4, 0.0, 0.0]
+    x = np.clip(d, -1.2e4, 1.2e4).reshape(64, 8, 3) + g
+    x = x.reshape(-1, 3)
+    n = len(x)
+    a = rng.standard_normal((n, 3))
+    f = lambda v: np.ascontiguousarray(v, np.float32)  # noqa: E731
+    case = dict(x=f(x[:, 0]), y=f(x[:, 1]), z=f(x[:, 2]), ax=f(a[:, 0]), ay=f(a[:, 1]), az=f(a[:, 2]),
+                sigma=f(1000.0 * rng.uniform(0.6, 1.4, n)), n=n)
+    t = vf.case_to_device(case)
+    with vf.Context(p=8, ncrit=8, box_len=1.6e5, theta=0.3, scheme=scheme) as ctx:
+        ctx.build(t[0], t[1], t[2], t[6])
+        out = ctx.evaluate(*t)
+        torch.cuda.synchronize()
+        assert ctx.stats()["nleaves"] == 64
+    o = np.stack([v.cpu().numpy() for v in out], 1).astype(np.float64)
+    ref = oracle.direct(case)
+    check("step %g, u" % step, o[:, :3], ref["u"], 1e-4, 1e-3)
+    check("step %g, dalpha" % step, o[:, 3:], ref["da_c" if scheme else "da_t"], 1e-4, 1e-3)
