@@ -731,8 +731,10 @@ __device__ __forceinline__ double fma_const(double a, double b, double k) {
     return d;
 }
 
-// e^{-x}, x >= 0: 2^n e^r with |r| <= ln 2 / 2 and e^r by its Taylor sum
+// e^{-x}, x >= 0: 2^n e^r with |r| <= ln 2 / 2 and e^r by its Taylor sum.  Zero
+// from x = 745 on; larger x are cut off, as r would grow with their rounding.
 __device__ __forceinline__ double exp_minus(double x) {
+    x = fmin(x, 800.0);
     const double n = __builtin_rint(-1.4426950408889634 * x);
     double r = fma(n, -6.93147180369123816490e-01, -x);
     r = fma(n, -1.90821492927058770002e-10, r);

@@ -1,5 +1,5 @@
 """Places of the near field that ordinary cases do not reach: large leaves, whose lists would be cut into more partial
-results than a build may have; particles at round offsets from their leaf's centre."""
+results than a build may have; particles at round offsets from their leaf's centre; cores far below the distances."""
 import numpy as np
 import pytest
 
@@ -65,3 +65,26 @@ def test_round_offsets_in_the_callers_units(step, scheme):
     ref = oracle.direct(case)
     check("step %g, u" % step, o[:, :3], ref["u"], 1e-4, 1e-3)
     check("step %g, dalpha" % step, o[:, 3:], ref["da_c" if scheme else "da_t"], 1e-4, 1e-3)
+
+
+@pytest.mark.parametrize("direct", [0, 1])
+@pytest.mark.parametrize("sig", [1e-12, 1e-21, 1e-25, 1e-30])
+def test_float64_cores_far_below_the_distances(sig, direct):
+    """The float64 form takes any core: (rho / sigma)^2 of up to 1e60 beside the self pairs' zero.  The velocity, to
+    the evaluation's 1e-4 with a far field and to 2^-23 of the rms without one (outputs rounded to float32)."""
+    import torch
+    import paper_1106_5273_amd as vf
+    rng = np.random.default_rng(5)
+    n = 300
+    x, a = rng.uniform(0.0, 1.0, (n, 3)), rng.standard_normal((n, 3))
+    f = lambda v: np.ascontiguousarray(v, np.float32)  # noqa: E731
+    case = dict(x=f(x[:, 0]), y=f(x[:, 1]), z=f(x[:, 2]), ax=f(a[:, 0]), ay=f(a[:, 1]), az=f(a[:, 2]),
+                sigma=f(np.full(n, sig)), n=n)
+    t = vf.case_to_device(case)
+    with vf.Context(p=10, ncrit=16, precision=2, theta=0.3, direct=direct) as ctx:
+        ctx.build(t[0], t[1], t[2], t[6])
+        out = ctx.evaluate(*t)
+        torch.cuda.synchronize()
+    u = np.stack([v.cpu().numpy() for v in out[:3]], 1).astype(np.float64)
+    tol = 2.0 ** -23 if direct else 1e-4
+    check("core %g, direct %d, u" % (sig, direct), u, oracle.direct(case)["u"], tol, 1e-3)
