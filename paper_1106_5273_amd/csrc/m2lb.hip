@@ -26,6 +26,7 @@
 // the translations of one key whatever their targets (keyed_lists,
 // k_m2lb_columns); short lists and rare keys use the per-pair M2L.
 #include <algorithm>
+#include <cstring>
 #include <type_traits>
 #include <utility>
 
@@ -43,6 +44,10 @@ static constexpr size_t MAX_TABLE_BYTES = size_t(8) << 30;  // operator table ca
 static constexpr double MIN_PAIR_NS = 2.5e5, MIN_PAIR_NS_F64 = 6e5;
 // the same for the float64 products, whose group costs as much as 17 translations one at a time
 static constexpr int MIN_FILL_F64 = 24;
+// an operator is built for whole quarter cells between two centres.  The float64 form
+// keeps a rest of 2^-34 of one (2e-11 of a cell, and of a translation's result): cells
+// of 2^-17 of their coordinates.  Finer ones run one at a time between their centres.
+static constexpr float MAX_RESIDUAL_F64 = 5.8e-11f;
 static constexpr int MIN_GROUP_FILL = 8;  // translations per (block, key) group below which per-pair M2L runs
 
 void sort_pairs_u64(Ctx &c, DevBuf &kA, DevBuf &vA, DevBuf &kB, DevBuf &vB, int64_t n, int nbits);
@@ -169,47 +174,57 @@ __global__ __launch_bounds__(TPB) void k_bucket_assign(int nc, const uint64_t *k
 }
 
 // ---------------------------------------------------------------------------
-// per entry: level difference and quantised offset; track the ranges
+// per entry: level difference and quantised offset; track the ranges and the
+// largest residual (in quarter cells, as the bits of a non-negative float) that the
+// quantised offsets leave of the centres' differences
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(TPB) void k_m2lb_offsets(int64_t n, const int4 *raw, const float4 *geo, const int *level,
+template <class V4>
+__global__ __launch_bounds__(TPB) void k_m2lb_offsets(int64_t n, const int4 *raw, const V4 *geo, const int *level,
                                                       int B, float len, int4 *eq, int *range) {
-    __shared__ int red[2][TPB / 64];
+    using R = decltype(V4::x);
+    __shared__ int red[3][TPB / 64];
     int aq = 0, adl = 0;
+    R res = R(0);
     const int W = 2 * B + 1;
     for (int64_t e = (int64_t)blockIdx.x * TPB + threadIdx.x; e < n; e += (int64_t)gridDim.x * TPB) {
         const int4 r = raw[e];  // (target, source, image code, -)
         const int t = r.x;
         const int2 s = make_int2(r.y, r.z);
-        const float shx = (float)(s.y % W - B) * len;
-        const float shy = (float)((s.y / W) % W - B) * len;
-        const float shz = (float)(s.y / (W * W) - B) * len;
-        const float4 ga = geo[t], gb = geo[s.x];
+        const R shx = (R)(s.y % W - B) * (R)len;
+        const R shy = (R)((s.y / W) % W - B) * (R)len;
+        const R shz = (R)(s.y / (W * W) - B) * (R)len;
+        const V4 ga = geo[t], gb = geo[s.x];
         const int dl = level[s.x] - level[t];
-        const float unit = ga.w * exp2f(-(float)(max(dl, 0) + 2));
-        const int qx = (int)rintf((gb.x + shx - ga.x) / unit);
-        const int qy = (int)rintf((gb.y + shy - ga.y) / unit);
-        const int qz = (int)rintf((gb.z + shz - ga.z) / unit);
+        const R unit = ldexp(ga.w, -(max(dl, 0) + 2));
+        const R vx = (gb.x + shx - ga.x) / unit, vy = (gb.y + shy - ga.y) / unit, vz = (gb.z + shz - ga.z) / unit;
+        const int qx = (int)rint(vx), qy = (int)rint(vy), qz = (int)rint(vz);
         eq[e] = make_int4(qx, qy, qz, dl);
         aq = max(aq, max(abs(qx), max(abs(qy), abs(qz))));
         adl = max(adl, abs(dl));
+        res = fmax(res, fmax(fabs(vx - (R)qx), fmax(fabs(vy - (R)qy), fabs(vz - (R)qz))));
     }
+    int ares = __float_as_int((float)res);
     // block max, then one atomic per block (the grid is capped, so few atomics)
     for (int o = 32; o > 0; o >>= 1) {
         aq = max(aq, __shfl_xor(aq, o, 64));
         adl = max(adl, __shfl_xor(adl, o, 64));
+        ares = max(ares, __shfl_xor(ares, o, 64));
     }
     if ((threadIdx.x & 63) == 0) {
         red[0][threadIdx.x >> 6] = aq;
         red[1][threadIdx.x >> 6] = adl;
+        red[2][threadIdx.x >> 6] = ares;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < TPB / 64; ++w) {
             aq = max(aq, red[0][w]);
             adl = max(adl, red[1][w]);
+            ares = max(ares, red[2][w]);
         }
         atomicMax(&range[0], aq);
         atomicMax(&range[1], adl);
+        atomicMax(&range[2], ares);
     }
 }
 
@@ -1478,14 +1493,21 @@ static void m2lb_plan_p(Ctx &c) {
     // ---- offsets and ranges ----
     c.mb_eq.ensure(sizeof(int4) * n);
     c.pairs64.ensure(64);
-    VFMM_HIP(hipMemsetAsync(c.pairs64.ptr, 0, 8, s));
-    k_m2lb_offsets<<<std::min<unsigned>(cdiv(n, TPB), 1024), TPB, 0, s>>>(n, c.m2l_raw.as<int4>(), c.c_geo.as<float4>(),
-                                                 c.c_level.as<int>(), c.img_B,
-                                                 c.prm.periodic ? (float)c.prm.box_len : 0.f, c.mb_eq.as<int4>(),
-                                                 c.pairs64.as<int>());
+    VFMM_HIP(hipMemsetAsync(c.pairs64.ptr, 0, 12, s));
+    const unsigned og = std::min<unsigned>(cdiv(n, TPB), 1024);
+    const float len = c.prm.periodic ? (float)c.prm.box_len : 0.f;
+    if (dbl)
+        k_m2lb_offsets<<<og, TPB, 0, s>>>(n, c.m2l_raw.as<int4>(), c.c_geo64.as<double4>(), c.c_level.as<int>(), c.img_B,
+                                          len, c.mb_eq.as<int4>(), c.pairs64.as<int>());
+    else
+        k_m2lb_offsets<<<og, TPB, 0, s>>>(n, c.m2l_raw.as<int4>(), c.c_geo.as<float4>(), c.c_level.as<int>(), c.img_B,
+                                          len, c.mb_eq.as<int4>(), c.pairs64.as<int>());
     VFMM_LAUNCH_CHECK();
-    int rng[2];
-    read_ints(c, {c.pairs64.as<int>(), c.pairs64.as<int>() + 1}, rng);
+    int rng[3];
+    read_ints(c, {c.pairs64.as<int>(), c.pairs64.as<int>() + 1, c.pairs64.as<int>() + 2}, rng);
+    float residual;
+    std::memcpy(&residual, &rng[2], sizeof residual);
+    if (dbl && residual > MAX_RESIDUAL_F64) return;
     KeyFmt f{};
     f.bq = bits_for_range(rng[0]);
     f.bdl = bits_for_range(rng[1]);
