@@ -1059,16 +1059,18 @@ __global__ __launch_bounds__(TPB) void k_leaf_geometry(int ncell, const RootBox 
         q[2] = (q[2] << 1) | (o & 1);
     }
     const double size = (double)box.len / (double)(1u << lvl);
-    float4 g;
-    g.x = (float)(box.lo[0] + (q[0] + 0.5) * size);
-    g.y = (float)(box.lo[1] + (q[1] + 0.5) * size);
-    g.z = (float)(box.lo[2] + (q[2] + 0.5) * size);
-    g.w = (float)size;
+    const double c[3] = {box.lo[0] + (q[0] + 0.5) * size, box.lo[1] + (q[1] + 0.5) * size,
+                         box.lo[2] + (q[2] + 0.5) * size};
+    const float4 g = make_float4((float)c[0], (float)c[1], (float)c[2], (float)size);
     if (sub == 0) {
         geo[cell] = g;
-        if (geo64)
-            geo64[cell] = make_double4(box.lo[0] + (q[0] + 0.5) * size, box.lo[1] + (q[1] + 0.5) * size,
-                                       box.lo[2] + (q[2] + 0.5) * size, size);
+        if (geo64) {
+            // the acceptance test knows the float32 centres: where they are off by more than 1/256
+            // of the cell (cells of about 128 float32 steps), expansions are about them too
+            const double near = size / 256.0;
+            geo64[cell] = make_double4(fabs(g.x - c[0]) <= near ? c[0] : g.x, fabs(g.y - c[1]) <= near ? c[1] : g.y,
+                                       fabs(g.z - c[2]) <= near ? c[2] : g.z, size);
+        }
     }
     if (nchild[cell] != 0) return;
     float r2 = 0.f;

@@ -1,5 +1,5 @@
-"""Trees as deep as float32 coordinates resolve: boxes whose cell centres are not float32 numbers, cells a few float32
-steps wide, boxes far from the origin."""
+"""Trees as deep as float32 coordinates resolve: boxes whose cell centres are not float32 numbers, clusters whose cells
+are a few float32 steps wide, boxes far from the origin."""
 import numpy as np
 import pytest
 
@@ -7,6 +7,19 @@ import oracle
 from parity_util import check
 
 pytestmark = pytest.mark.gpu
+
+
+def _clusters(lo, w, n=60000):
+    """Four clusters of width w / 10 in a cube of side 0.997 with its corner at lo + 0.0013."""
+    rng = np.random.default_rng(8)
+    c = rng.uniform(0.2, 0.8, (4, 3))
+    x = np.concatenate([c[k] + w * 0.1 * rng.standard_normal((n // 4, 3)) for k in range(4)])
+    x = lo + np.clip(x, 0.01, 0.97)
+    a = rng.standard_normal((n, 3)) / n
+    f = lambda v: np.ascontiguousarray(v, np.float32)  # noqa: E731
+    case = dict(x=f(x[:, 0]), y=f(x[:, 1]), z=f(x[:, 2]), ax=f(a[:, 0]), ay=f(a[:, 1]), az=f(a[:, 2]),
+                sigma=f(np.full(n, w * 0.004)), n=n)
+    return case, dict(p=10, ncrit=32, box_len=0.997, box_lo=(lo + 0.0013,) * 3)
 
 
 def _run(case, expansions=False, **kw):
@@ -50,3 +63,15 @@ def test_float64_operators_far_from_the_origin(lo, side):
         assert err <= 1e-11, (m, err)
     sub = np.arange(0, n, 499)
     check("lo %g side %g, u" % (lo, side), u[sub], oracle.direct(case, targets=sub)["u"], 1e-4, 1e-2)
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("lo,w", [(0.0, 0.1), (0.0, 1e-3), (0.0, 1e-5), (20.0, 0.1), (20.0, 1e-3), (20.0, 1e-4)])
+def test_float64_form_in_deep_trees(lo, w, mode):
+    """Against the direct sum of the same float32 coordinates (the evaluation's 1e-4)."""
+    case, kw = _clusters(lo, w)
+    u, d, st, _ = _run(case, precision=2, m2l_mode=mode, **kw)
+    sub = np.arange(0, case["n"], 97)
+    ref = oracle.direct(case, targets=sub)
+    check("lo %g width %g depth %d, u" % (lo, w, st["depth"]), u[sub], ref["u"], 1e-4, 1e-2)
+    check("lo %g width %g dalpha" % (lo, w), d[sub], ref["da_t"], 1e-4, 1e-2)
