@@ -432,8 +432,9 @@ vfmm_status vfmm_copy_lists(vfmm_ctx *ctx, int32_t *p2p_tgt, int32_t *p2p_src, i
  * n and p as in vfmm_get_stats and the parameters.  Per cell i:
  *   level[i], parent[i] (-1 at a root), first_child[i], nchild[i] (its
  *   children are first_child .. first_child + nchild - 1; 0 for a leaf);
- *   geo[5i .. 5i+4] = centre x, y, z, cube side s and the radius used by the
- *   acceptance test (float32 values widened to double).
+ *   geo[5i .. 5i+4] = centre x, y, z of the expansions, cube side s (float64
+ *   values) and the radius used by the acceptance test (a float32 value, about
+ *   the centre rounded to float32).
  * mult and loc: double[ncells][3][NC][2], NC = (p+1)(p+2)/2, the coefficients
  * c_n^m (0 <= m <= n <= p at index n(n+1)/2 + m; real, imaginary part; the
  * other orders are c_n^{-m} = (-1)^m conj(c_n^m)) of the Laplace potentials

@@ -984,25 +984,15 @@ vfmm_status vfmm_copy_expansions(vfmm_ctx *ctx, int32_t *level, int32_t *parent,
         if (first_child) VFMM_HIP(hipMemcpy(first_child, c.c_child.ptr, sizeof(int) * nc, hipMemcpyDeviceToHost));
         if (nchild) VFMM_HIP(hipMemcpy(nchild, c.c_nchild.ptr, sizeof(int) * nc, hipMemcpyDeviceToHost));
         if (geo) {
-            std::vector<float4> g(nc);
+            std::vector<double4> g(nc);
             std::vector<float> r(nc);
-            VFMM_HIP(hipMemcpy(g.data(), c.c_geo.ptr, sizeof(float4) * nc, hipMemcpyDeviceToHost));
-            std::vector<double4> g64;
-            if (c.prm.precision == VFMM_PRECISION_FP64) {
-                g64.resize(nc);
-                VFMM_HIP(hipMemcpy(g64.data(), c.c_geo64.ptr, sizeof(double4) * nc, hipMemcpyDeviceToHost));
-            }
+            VFMM_HIP(hipMemcpy(g.data(), c.c_geo64.ptr, sizeof(double4) * nc, hipMemcpyDeviceToHost));
             VFMM_HIP(hipMemcpy(r.data(), c.c_rad.ptr, sizeof(float) * nc, hipMemcpyDeviceToHost));
             for (int i = 0; i < nc; ++i) {
                 geo[5 * i] = g[i].x;
                 geo[5 * i + 1] = g[i].y;
                 geo[5 * i + 2] = g[i].z;
                 geo[5 * i + 3] = g[i].w;
-                if (!g64.empty()) {
-                    geo[5 * i] = g64[i].x;
-                    geo[5 * i + 1] = g64[i].y;
-                    geo[5 * i + 2] = g64[i].z;
-                }
                 geo[5 * i + 4] = r[i];
             }
         }

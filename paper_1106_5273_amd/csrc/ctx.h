@@ -53,8 +53,8 @@ struct Ctx {
     DevBuf recp;                         // float4[3n]: float32 near-field records (scaled, leaf-local)
     // cells
     DevBuf c_start, c_count, c_parent, c_child, c_nchild, c_level;  // int
-    DevBuf c_geo64;                      // double4 in the float64 form: the same, centres not rounded to float32
-    DevBuf c_geo;                        // float4 (cx, cy, cz, size)
+    DevBuf c_geo;                        // float4 (cx, cy, cz, size): acceptance test, near-field frames
+    DevBuf c_geo64;                      // double4: the same of the expansions, not rounded (but in very fine cells)
     DevBuf c_rad;                        // float tight radius
     DevBuf c_lo, c_hi;                   // float4 particle bounding box
     DevBuf c_tmp;                        // build scratch: child counts

@@ -7,7 +7,9 @@
 // coefficients keep float32 in range): a cell with centre c stores
 //   Mt_n^m = sum_j q_j conj(R_n^m((x_j - c)/s)),        psi = (1/s) sum Mt I_n^m((x-c)/s)
 //   Lt_n^m with psi(x) = (1/s) sum Lt_n^m R_n^m((x - c)/s)
-// and sums run from the highest degree to the lowest (Sec. 4.2).
+// and sums run from the highest degree to the lowest (Sec. 4.2).  Centres are in
+// float64 whatever the expansions' type: the translations by operator take the
+// difference of two centres as whole quarter cells, which rounded centres are not.
 #include "ctx.h"
 
 namespace vfmm {
@@ -46,7 +48,7 @@ __device__ inline void decode_nm(int t, int &n, int &m) {
 // ---------------------------------------------------------------------------
 template <int P, class R>
 __global__ __launch_bounds__(64) void k_p2m(const int *leaves, const int *start, const int *count, const int *nsrc,
-                                            const typename VT<R>::V4 *geo, const typename VT<R>::V4 *rec,
+                                            const double4 *geo, const typename VT<R>::V4 *rec,
                                             typename VT<R>::V2 *Mexp) {
     using V2 = typename VT<R>::V2;
     using V4 = typename VT<R>::V4;
@@ -72,7 +74,7 @@ __global__ __launch_bounds__(64) void k_p2m(const int *leaves, const int *start,
             if (b + lane < cnt) {
                 const V4 p = rec[2 * j];
                 V2 Rl[NCP];
-                regular_harmonics<P, R, V2>((p.x - R(g.x)) * inv, (p.y - R(g.y)) * inv, (p.z - R(g.z)) * inv, Rl);
+                regular_harmonics<P, R, V2>(R(p.x - g.x) * inv, R(p.y - g.y) * inv, R(p.z - g.z) * inv, Rl);
 #pragma unroll
                 for (int t = 0; t < NCP; ++t) Rs[lane][t] = Rl[t];
                 al[lane] = rec[2 * j + 1];
@@ -173,7 +175,7 @@ __device__ inline void harmonics_order(R x, R y, R z, int m, V2 *T) {
 
 template <int P, class R, class S>
 __global__ __launch_bounds__((XferCfg<P, R>::M2M_THREADS)) void k_m2m(int c0, int c1, const int *child,
-                                                                     const int *nchild, const typename VT<S>::V4 *geo,
+                                                                     const int *nchild, const double4 *geo,
                                                                      typename VT<S>::V2 *Mexp) {
     using V2 = typename VT<R>::V2;
     using C = XferCfg<P, R>;
@@ -202,8 +204,8 @@ __global__ __launch_bounds__((XferCfg<P, R>::M2M_THREADS)) void k_m2m(int c0, in
             const int k = tid % CH;
             if (k < nk && tid / CH <= P) {
                 const auto gc = geo[f + k0 + k];
-                harmonics_order<P, R, true>((R(gc.x) - R(gp.x)) * inv, (R(gc.y) - R(gp.y)) * inv,
-                                            (R(gc.z) - R(gp.z)) * inv, tid / CH, Rf[k]);
+                harmonics_order<P, R, true>(R(gc.x - gp.x) * inv, R(gc.y - gp.y) * inv, R(gc.z - gp.z) * inv,
+                                            tid / CH, Rf[k]);
             }
         } else {
             for (int i = tid - C::M2M_HARM; i < nk * 3 * NCP; i += C::M2M_THREADS - C::M2M_HARM) {
@@ -304,7 +306,7 @@ struct M2LCfg {
 
 template <int P, class R>
 __global__ __launch_bounds__((M2LCfg<P, R>::THREADS)) void k_m2l(const int4 *parts, const int2 *src,
-                                                               const typename VT<R>::V4 *geo,
+                                                               const double4 *geo,
                                                                const typename VT<R>::V2 *__restrict__ Mexp,
                                                                typename VT<R>::V2 *__restrict__ partial, int B,
                                                                float len) {
@@ -343,11 +345,11 @@ __global__ __launch_bounds__((M2LCfg<P, R>::THREADS)) void k_m2l(const int4 *par
             const int s = i / (C::Q + 1), M = i % (C::Q + 1);
             const int2 ent = src[e0 + s];
             const auto gb = geo[ent.x];
-            const R ix = (R)(ent.y % W - B), iy = (R)((ent.y / W) % W - B), iz = (R)(ent.y / (W * W) - B);
+            const double L = len;
             const R inv = R(1) / R(gb.w);
-            const R dx = (R(ga.x) - R(gb.x) - ix * R(len)) * inv;
-            const R dy = (R(ga.y) - R(gb.y) - iy * R(len)) * inv;
-            const R dz = (R(ga.z) - R(gb.z) - iz * R(len)) * inv;
+            const R dx = R(ga.x - gb.x - (ent.y % W - B) * L) * inv;
+            const R dy = R(ga.y - gb.y - ((ent.y / W) % W - B) * L) * inv;
+            const R dz = R(ga.z - gb.z - (ent.y / (W * W) - B) * L) * inv;
             const R r2 = dx * dx + dy * dy + dz * dz;
             const R ir2 = R(1) / r2;
             // I_M^M by the diagonal recurrence, then upward in N
@@ -560,7 +562,7 @@ void m2l_pair_plan(Ctx &c, const int *off, int64_t n) {
 // ---------------------------------------------------------------------------
 template <int P, class R, class S>
 __global__ __launch_bounds__((XferCfg<P, R>::L2L_THREADS)) void k_l2l(int c0, int c1, const int *child,
-                                                                     const int *nchild, const typename VT<S>::V4 *geo,
+                                                                     const int *nchild, const double4 *geo,
                                                                      typename VT<S>::V2 *Lexp) {
     using V2 = typename VT<R>::V2;
     using C = XferCfg<P, R>;
@@ -579,8 +581,8 @@ __global__ __launch_bounds__((XferCfg<P, R>::L2L_THREADS)) void k_l2l(int c0, in
         const int j = tid % 8;
         if (j < nc && tid / 8 <= P) {
             const auto gc = geo[f + j];
-            harmonics_order<P, R, false>((R(gc.x) - R(gp.x)) * inv, (R(gc.y) - R(gp.y)) * inv,
-                                         (R(gc.z) - R(gp.z)) * inv, tid / 8, Rf[j]);
+            harmonics_order<P, R, false>(R(gc.x - gp.x) * inv, R(gc.y - gp.y) * inv, R(gc.z - gp.z) * inv, tid / 8,
+                                         Rf[j]);
         }
     } else {
         for (int i = tid - C::L2L_HARM; i < 3 * NCP; i += C::L2L_THREADS - C::L2L_HARM) {
@@ -633,7 +635,8 @@ __global__ __launch_bounds__((XferCfg<P, R>::L2L_THREADS)) void k_l2l(int c0, in
 // ---------------------------------------------------------------------------
 template <int P, class R>
 __global__ __launch_bounds__(64) void k_l2p(const int *leaves, const int *start, const int *count,
-                                            const typename VT<R>::V4 *geo, const typename VT<R>::V4 *rec, const typename VT<R>::V2 *Lexp,
+                                            const double4 *geo, const typename VT<R>::V4 *rec,
+                                            const typename VT<R>::V2 *Lexp,
                                             int64_t n_all, R *far_u, R *far_da, int scheme) {
     using V2 = typename VT<R>::V2;
     using V4 = typename VT<R>::V4;
@@ -652,7 +655,7 @@ __global__ __launch_bounds__(64) void k_l2p(const int *leaves, const int *start,
         const int j = s0 + b + lane;
         const V4 p = rec[2 * j];
         V2 Rl[NR];
-        regular_harmonics<P - 1, R, V2>((p.x - R(g.x)) * inv, (p.y - R(g.y)) * inv, (p.z - R(g.z)) * inv, Rl);
+        regular_harmonics<P - 1, R, V2>(R(p.x - g.x) * inv, R(p.y - g.y) * inv, R(p.z - g.z) * inv, Rl);
         R G[3][3], H[3][3][3];
         for (int c = 0; c < 3; ++c) {
             R pz = R(0), pzz = R(0);
@@ -800,7 +803,7 @@ static void far_field_t(Ctx &c) {
     c.far_u.ensure(sizeof(S) * 3 * (size_t)c.n);
     c.far_da.ensure(sizeof(S) * 3 * (size_t)c.n);
     const V4 *rec = (sizeof(S) == 8) ? reinterpret_cast<const V4 *>(c.rec64.ptr) : reinterpret_cast<const V4 *>(c.rec.ptr);
-    const V4 *geo = reinterpret_cast<const V4 *>(sizeof(S) == 8 ? c.c_geo64.ptr : c.c_geo.ptr);
+    const double4 *geo = c.c_geo64.as<double4>();
     c.record(2 * PH_P2M_M2M);
     // a fill kernel rather than a memset, so that the evaluation can be captured in a graph
     k_zero<<<cdiv(cdiv(bytes, 16), 256), 256, 0, s>>>(c.Lexp.as<float>(), (int64_t)(bytes / 4));

@@ -47,7 +47,9 @@ static constexpr int MIN_FILL_F64 = 24;
 // an operator is built for whole quarter cells between two centres.  The float64 form
 // keeps a rest of 2^-34 of one (2e-11 of a cell, and of a translation's result): cells
 // of 2^-17 of their coordinates.  Finer ones run one at a time between their centres.
-static constexpr float MAX_RESIDUAL_F64 = 5.8e-11f;
+// The float32 forms' groups by operator alone, which take irregular and so the
+// deepest trees, keep 2^-20 (4e-7): all but cells whose centres are rounded.
+static constexpr float MAX_RESIDUAL_F64 = 5.8e-11f, MAX_RESIDUAL = 9.5e-7f;
 static constexpr int MIN_GROUP_FILL = 8;  // translations per (block, key) group below which per-pair M2L runs
 
 void sort_pairs_u64(Ctx &c, DevBuf &kA, DevBuf &vA, DevBuf &kB, DevBuf &vB, int64_t n, int nbits);
@@ -178,32 +180,28 @@ __global__ __launch_bounds__(TPB) void k_bucket_assign(int nc, const uint64_t *k
 // largest residual (in quarter cells, as the bits of a non-negative float) that the
 // quantised offsets leave of the centres' differences
 // ---------------------------------------------------------------------------
-template <class V4>
-__global__ __launch_bounds__(TPB) void k_m2lb_offsets(int64_t n, const int4 *raw, const V4 *geo, const int *level,
+__global__ __launch_bounds__(TPB) void k_m2lb_offsets(int64_t n, const int4 *raw, const double4 *geo, const int *level,
                                                       int B, float len, int4 *eq, int *range) {
-    using R = decltype(V4::x);
     __shared__ int red[3][TPB / 64];
     int aq = 0, adl = 0;
-    R res = R(0);
+    float res = 0.f;
     const int W = 2 * B + 1;
+    const double L = len;
     for (int64_t e = (int64_t)blockIdx.x * TPB + threadIdx.x; e < n; e += (int64_t)gridDim.x * TPB) {
         const int4 r = raw[e];  // (target, source, image code, -)
-        const int t = r.x;
-        const int2 s = make_int2(r.y, r.z);
-        const R shx = (R)(s.y % W - B) * (R)len;
-        const R shy = (R)((s.y / W) % W - B) * (R)len;
-        const R shz = (R)(s.y / (W * W) - B) * (R)len;
-        const V4 ga = geo[t], gb = geo[s.x];
-        const int dl = level[s.x] - level[t];
-        const R unit = ldexp(ga.w, -(max(dl, 0) + 2));
-        const R vx = (gb.x + shx - ga.x) / unit, vy = (gb.y + shy - ga.y) / unit, vz = (gb.z + shz - ga.z) / unit;
+        const double4 ga = geo[r.x], gb = geo[r.y];
+        const int dl = level[r.y] - level[r.x];
+        const double unit = ldexp(ga.w, -(max(dl, 0) + 2));
+        const double vx = (gb.x + (r.z % W - B) * L - ga.x) / unit;
+        const double vy = (gb.y + ((r.z / W) % W - B) * L - ga.y) / unit;
+        const double vz = (gb.z + (r.z / (W * W) - B) * L - ga.z) / unit;
         const int qx = (int)rint(vx), qy = (int)rint(vy), qz = (int)rint(vz);
         eq[e] = make_int4(qx, qy, qz, dl);
         aq = max(aq, max(abs(qx), max(abs(qy), abs(qz))));
         adl = max(adl, abs(dl));
-        res = fmax(res, fmax(fabs(vx - (R)qx), fmax(fabs(vy - (R)qy), fabs(vz - (R)qz))));
+        res = fmaxf(res, (float)fmax(fabs(vx - qx), fmax(fabs(vy - qy), fabs(vz - qz))));
     }
-    int ares = __float_as_int((float)res);
+    int ares = __float_as_int(res);
     // block max, then one atomic per block (the grid is capped, so few atomics)
     for (int o = 32; o > 0; o >>= 1) {
         aq = max(aq, __shfl_xor(aq, o, 64));
@@ -1496,18 +1494,16 @@ static void m2lb_plan_p(Ctx &c) {
     VFMM_HIP(hipMemsetAsync(c.pairs64.ptr, 0, 12, s));
     const unsigned og = std::min<unsigned>(cdiv(n, TPB), 1024);
     const float len = c.prm.periodic ? (float)c.prm.box_len : 0.f;
-    if (dbl)
-        k_m2lb_offsets<<<og, TPB, 0, s>>>(n, c.m2l_raw.as<int4>(), c.c_geo64.as<double4>(), c.c_level.as<int>(), c.img_B,
-                                          len, c.mb_eq.as<int4>(), c.pairs64.as<int>());
-    else
-        k_m2lb_offsets<<<og, TPB, 0, s>>>(n, c.m2l_raw.as<int4>(), c.c_geo.as<float4>(), c.c_level.as<int>(), c.img_B,
-                                          len, c.mb_eq.as<int4>(), c.pairs64.as<int>());
+    k_m2lb_offsets<<<og, TPB, 0, s>>>(n, c.m2l_raw.as<int4>(), c.c_geo64.as<double4>(), c.c_level.as<int>(), c.img_B,
+                                      len, c.mb_eq.as<int4>(), c.pairs64.as<int>());
     VFMM_LAUNCH_CHECK();
     int rng[3];
     read_ints(c, {c.pairs64.as<int>(), c.pairs64.as<int>() + 1, c.pairs64.as<int>() + 2}, rng);
     float residual;
     std::memcpy(&residual, &rng[2], sizeof residual);
     if (dbl && residual > MAX_RESIDUAL_F64) return;
+    // groups by block of the float32 forms have always rounded; by operator irregular trees must not
+    const bool by_operator = dbl || residual <= MAX_RESIDUAL;
     KeyFmt f{};
     f.bq = bits_for_range(rng[0]);
     f.bdl = bits_for_range(rng[1]);
@@ -1633,11 +1629,11 @@ static void m2lb_plan_p(Ctx &c) {
     // trees: many offsets, few targets sharing each) go to the per-pair M2L.
     if (c.prm.m2l_mode == 0 && n < (int64_t)MIN_GROUP_FILL * ng) {
         if constexpr (C::X6)
-            if (x6) m2lb_plan_keyed<P>(c, n, nkeys, m2l_costs<P>().pair * (double)n, f);
+            if (x6 && by_operator) m2lb_plan_keyed<P>(c, n, nkeys, m2l_costs<P>().pair * (double)n, f);
         return;
     }
     if constexpr (C::X6)  // so thin that the groups by block need not be laid out to tell
-        if (c.prm.m2l_mode == 0 && x6 && n < LOW_FILL * (int64_t)ng) {
+        if (c.prm.m2l_mode == 0 && x6 && by_operator && n < LOW_FILL * (int64_t)ng) {
             const M2lCosts t = m2l_costs<P>();
             if (m2lb_plan_keyed<P>(c, n, nkeys, 1.1 * t.group * ng + t.key * nkeys, f)) return;
         }

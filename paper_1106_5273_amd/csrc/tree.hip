@@ -1064,13 +1064,11 @@ __global__ __launch_bounds__(TPB) void k_leaf_geometry(int ncell, const RootBox 
     const float4 g = make_float4((float)c[0], (float)c[1], (float)c[2], (float)size);
     if (sub == 0) {
         geo[cell] = g;
-        if (geo64) {
-            // the acceptance test knows the float32 centres: where they are off by more than 1/256
-            // of the cell (cells of about 128 float32 steps), expansions are about them too
-            const double near = size / 256.0;
-            geo64[cell] = make_double4(fabs(g.x - c[0]) <= near ? c[0] : g.x, fabs(g.y - c[1]) <= near ? c[1] : g.y,
-                                       fabs(g.z - c[2]) <= near ? c[2] : g.z, size);
-        }
+        // the acceptance test knows the float32 centres: where they are off by more than 1/256
+        // of the cell (cells of about 128 float32 steps), expansions are about them too
+        const double near = size / 256.0;
+        geo64[cell] = make_double4(fabs(g.x - c[0]) <= near ? c[0] : g.x, fabs(g.y - c[1]) <= near ? c[1] : g.y,
+                                   fabs(g.z - c[2]) <= near ? c[2] : g.z, size);
     }
     if (nchild[cell] != 0) return;
     float r2 = 0.f;
@@ -1298,12 +1296,11 @@ void build_tree(Ctx &c, int64_t n, const float *x, const float *y, const float *
     c.c_rad.ensure(sizeof(float) * nc);
     c.c_lo.ensure(sizeof(float4) * nc);
     c.c_hi.ensure(sizeof(float4) * nc);
-    const bool dbl = c.prm.precision == VFMM_PRECISION_FP64;
-    if (dbl) c.c_geo64.ensure(sizeof(double4) * nc);
+    c.c_geo64.ensure(sizeof(double4) * nc);
     k_leaf_geometry<<<cdiv(nc * (int64_t)GEO_LANES, TPB), TPB, 0, s>>>(nc, c.pbox.as<RootBox>(), KL, c.c_start.as<int>(), c.c_count.as<int>(),
                                                    c.c_level.as<int>(), c.c_nchild.as<int>(), keys,
                                                    c.rec.as<float4>(), c.c_geo.as<float4>(),
-                                                   dbl ? c.c_geo64.as<double4>() : nullptr, c.c_rad.as<float>(),
+                                                   c.c_geo64.as<double4>(), c.c_rad.as<float>(),
                                                    c.c_lo.as<float4>(), c.c_hi.as<float4>());
     VFMM_LAUNCH_CHECK();
     if (nc <= TREE_GEO_GROUP) {
