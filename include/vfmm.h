@@ -96,7 +96,9 @@ typedef struct vfmm_params {
                             with groups by (64-target block, offset) where they fill, by offset
                             alone where they do not, else per pair; 1: per-pair M2L; 2: groups by
                             (block, offset) whenever the offsets can be keyed (per pair only when
-                            they cannot; in the float64 form always)                           */
+                            they cannot; in the float64 form always).  The form follows from the
+                            input alone (in float64 at most 32 GiB of buffers, else per pair);
+                            only where its buffers cannot be allocated does a smaller one run  */
     int32_t use_graph;   /* 1: fmm_evaluate runs as a hipGraph, captured on the first call after
                             a build (or when its pointers change) and replayed afterwards; needs
                             a non-default stream and the tree path (default 0)                */

@@ -210,14 +210,13 @@ static void do_build(Ctx &c, int64_t n, const float *x, const float *y, const fl
     }
     c.record(2 * PH_TRAVERSE);
     traverse_and_lists(c);
+    far_prealloc(c);  // before the plan, whose forms differ in what they need beside it
     c.m2lb_ok = false;
     if (m2l_batched(c.prm)) m2lb_plan(c);
     if (!c.m2lb_ok) {  // the per-pair M2L runs instead
         if (!c.m2l_csr) build_m2l_csr(c);
         m2l_pair_plan(c, c.m2l_off.as<int>(), c.n_m2l);
     }
-    far_prealloc(c);
-    m2lb_prealloc(c);
     if (c.prm.precision != VFMM_PRECISION_FP64 && c.prm.overlap == 1) ensure_side(c);
     ++c.build_id;
     c.record(2 * PH_TRAVERSE + 1);

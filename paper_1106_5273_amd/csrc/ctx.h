@@ -212,7 +212,6 @@ void m2l_pair_plan(Ctx &c, const int *off, int64_t n);
 // m2lb.hip
 void m2lb_plan(Ctx &c);
 void m2lb_run(Ctx &c);
-void m2lb_prealloc(Ctx &c);
 // p2p.hip
 void p2p_and_finalize(Ctx &c, float *ux, float *uy, float *uz, float *dax, float *day, float *daz);
 void direct_all_pairs(Ctx &c, const float *x, const float *y, const float *z, const float *ax,

@@ -31,13 +31,13 @@
 #include <utility>
 
 #include "ctx.h"
+#include "m2l_forms.h"
 
 namespace vfmm {
 
 static constexpr int TPB = 256;
 static constexpr int ITEM_GROUPS = 24;
 static constexpr int TABLE_KEY_BITS = 24;  // offset keys up to this width are numbered through a direct table
-static constexpr size_t MAX_TABLE_BYTES = size_t(8) << 30;  // operator table cap (else the per-pair kernel)
 // time (ns) of all translations one at a time below which they run so at once: the
 // batched plan's 25 launches and 6 waits take 0.2 ms, in float64, where groups cost
 // four times as much, with lists by operator 0.4
@@ -1293,16 +1293,6 @@ __global__ __launch_bounds__(TPB) void k_group_split(int ng, int nc, const int4 
 // of 64 filled on average, gives up a fifth of its groups and 4 % of its
 // translations: 11.4 -> 10.4 ms, for a plan of 0.3 more.  64 rings' 70,516 translations stay with the
 // per-pair kernel (0.29 ms; by key 0.16, for a plan of 0.17 more).
-static constexpr size_t MAX_COLUMN_BYTES = size_t(8) << 30;
-
-// Whether a buffer of these plans holds the bytes or may grow to them: within half of
-// the free memory, so that a call near the card's capacity keeps the form it had.
-static bool may_hold(const DevBuf &b, size_t bytes) {
-    if (bytes <= b.cap) return true;
-    size_t free_bytes = 0, total = 0;
-    return hipMemGetInfo(&free_bytes, &total) == hipSuccess && bytes <= free_bytes / 2;
-}
-
 struct M2lCosts {
     double group, col, key, pair;
 };
@@ -1403,8 +1393,7 @@ static bool m2lb_plan_keyed(Ctx &c, int64_t n, int nkeys, double other, const Ke
     const int64_t ncols = n - nrest;
     const size_t tab_bytes = (dbl ? sizeof(double) * C::OP : sizeof(uint32_t) * C::OPX) * (size_t)nused;
     const size_t col_bytes = rs * 3 * C::RP * (size_t)ncols;
-    if (ng == 0 || tab_bytes > MAX_TABLE_BYTES || col_bytes > MAX_COLUMN_BYTES || !may_hold(c.mb_cols, col_bytes) ||
-        (dbl && !may_hold(c.mb_tab, tab_bytes)) ||
+    if (ng == 0 || tab_bytes > MAX_TABLE_BYTES || col_bytes > MAX_COLUMN_BYTES ||
         plan + t.group * ng + t.col * (double)ncols + t.key * nused + t.pair * nrest > other)
         return false;
     c.mb_low.ensure(sizeof(uint64_t) * (size_t)nused);
@@ -1448,8 +1437,7 @@ static bool m2lb_fill_plan(Ctx &c, int64_t n, int nkeys, int &ng, const KeyFmt &
     const double split = 1.1 * t.group * stay + t.group * (nlow / 64.0 + std::min(nkeys, nlow) / 2.0) +
                          (t.col + 0.15) * nlow + 3.5e5;
     const size_t col_bytes = sizeof(float) * 3 * C::RP * (size_t)nlow;
-    const bool low = stay > 0 && nlow > 0 && split < block && col_bytes <= MAX_COLUMN_BYTES &&
-                     may_hold(c.mb_cols, col_bytes);
+    const bool low = stay > 0 && nlow > 0 && split < block && col_bytes <= MAX_COLUMN_BYTES;
     if (m2lb_plan_keyed<P>(c, n, nkeys, (low ? split : block) + tab, f)) return true;
     if (!low) return false;
     c.mb_low.ensure(sizeof(int4) * (size_t)nlow);
@@ -1478,8 +1466,10 @@ static int bits_for_range(int64_t maxabs) {
     return b;
 }
 
+// operators: whether groups by operator may be taken (the float32 forms; the
+// float64 form has no other fallback than the translations one at a time)
 template <int P>
-static void m2lb_plan_p(Ctx &c) {
+static void m2lb_plan_p(Ctx &c, bool operators) {
     hipStream_t s = c.stream;
     const int64_t n = c.n_m2l;
     c.m2lb_ok = false;
@@ -1487,6 +1477,8 @@ static void m2lb_plan_p(Ctx &c) {
     if (n == 0) return;
     if (c.prm.precision == VFMM_PRECISION_FP64 && !Mb64Cfg<P>::OK) return;  // p = 12: two tiles exceed the LDS
     const bool dbl = c.prm.precision == VFMM_PRECISION_FP64;
+    // full groups would need more already (and columns, 3 NRP(P) doubles a translation, more still)
+    if (dbl && f64_block_bytes(NR(P), NRP(P), ITEM_GROUPS, c.ncells, 0, 0, n / 64) > MAX_F64_BYTES) return;
     if (c.prm.m2l_mode == 0 && m2l_costs<P>(dbl).pair * (double)n < (dbl ? MIN_PAIR_NS_F64 : MIN_PAIR_NS)) return;
     // ---- offsets and ranges ----
     c.mb_eq.ensure(sizeof(int4) * n);
@@ -1503,7 +1495,7 @@ static void m2lb_plan_p(Ctx &c) {
     std::memcpy(&residual, &rng[2], sizeof residual);
     if (dbl && residual > MAX_RESIDUAL_F64) return;
     // groups by block of the float32 forms have always rounded; by operator irregular trees must not
-    const bool by_operator = dbl || residual <= MAX_RESIDUAL;
+    const bool by_operator = operators && (dbl || residual <= MAX_RESIDUAL);
     KeyFmt f{};
     f.bq = bits_for_range(rng[0]);
     f.bdl = bits_for_range(rng[1]);
@@ -1593,8 +1585,6 @@ static void m2lb_plan_p(Ctx &c) {
     // ---- groups (block, key) in (block, key) order ----
     const int64_t T = (int64_t)nblk * nkeys;
     if (T > ((int64_t)1 << 28)) return;  // table too large: per-pair M2L
-    if (dbl && c.mb_gcnt.cap < sizeof(int) * (size_t)(T + 1) && !may_hold(c.mb_gcnt, 4 * sizeof(int) * (size_t)T))
-        return;
     c.mb_gcnt.ensure(sizeof(int) * (size_t)(T + 1));
     c.mb_gid.ensure(sizeof(int) * (size_t)(T + 1));
     c.mb_goff.ensure(sizeof(int) * (size_t)(T + 1));
@@ -1623,6 +1613,7 @@ static void m2lb_plan_p(Ctx &c) {
         m2lb_plan_keyed<P>(c, n, nkeys, m2l_costs<P>(true).pair * (double)n, f);
         return;
     }
+    if (dbl && f64_block_bytes(C::R, C::RP, ITEM_GROUPS, c.ncells, nblk, nkeys, ng) > MAX_F64_BYTES) return;
     // A group costs a full 64-target operator product whether its targets are
     // all present or not; measured on gfx950 a group costs about as much as
     // 6-7 translations of the per-pair kernel, so sparse groups (irregular
@@ -1648,7 +1639,7 @@ static void m2lb_plan_p(Ctx &c) {
                                                  nkeys, gid, c.mb_slots.as<int>());
         VFMM_LAUNCH_CHECK();
         if constexpr (C::X6)
-            if (x6 && c.prm.m2l_mode == 0 && n < FULL_FILL * (int64_t)ng && m2lb_fill_plan<P>(c, n, nkeys, ng, f)) return;
+            if (x6 && operators && c.prm.m2l_mode == 0 && n < FULL_FILL * (int64_t)ng && m2lb_fill_plan<P>(c, n, nkeys, ng, f)) return;
     } else {  // the float32-product kernel reads each group's entry list
         c.mb_ent.ensure(sizeof(int2) * n);
         k_gk_scatter<<<cdiv(n, TPB), TPB, 0, s>>>(n, c.m2l_raw.as<int4>(), c.mb_cellbs.as<int2>(),
@@ -1685,7 +1676,6 @@ static void m2lb_plan_p(Ctx &c) {
     const size_t tab_bytes =
         (x6 ? sizeof(uint32_t) * C::OPX : (dbl ? sizeof(double) : sizeof(float)) * C::OP) * (size_t)nkeys;
     if (tab_bytes > MAX_TABLE_BYTES) return;  // too many distinct offsets: generic kernel
-    if (dbl && !may_hold(c.mb_tab, tab_bytes)) return;
     c.mb_tab.ensure(tab_bytes);
     if (dbl)
         k_m2lb_optab<P, 0, double><<<nkeys, 256, 0, s>>>(nkeys, c.mb_ukey.as<uint64_t>(), f, c.mb_tab.as<double>());
@@ -1706,17 +1696,6 @@ static void m2lb_plan_p(Ctx &c) {
     c.m2lb_ok = true;
 }
 
-void m2lb_plan(Ctx &c) {
-    switch (c.prm.p) {
-        case 4: m2lb_plan_p<4>(c); break;
-        case 6: m2lb_plan_p<6>(c); break;
-        case 8: m2lb_plan_p<8>(c); break;
-        case 10: m2lb_plan_p<10>(c); break;
-        case 12: m2lb_plan_p<12>(c); break;
-        default: throw Error{VFMM_EINVAL, "unsupported expansion degree p"};
-    }
-}
-
 template <int P>
 static void m2lb_prealloc_p(Ctx &c) {
     constexpr int R = NR(P), RP = NRP(P);
@@ -1727,16 +1706,38 @@ static void m2lb_prealloc_p(Ctx &c) {
         c.mb_partial.ensure(rs * (size_t)std::max(c.mb_nitems, 1) * 3 * R * 64);
 }
 
-void m2lb_prealloc(Ctx &c) {
-    if (!c.m2lb_ok) return;
-    switch (c.prm.p) {
-        case 4: m2lb_prealloc_p<4>(c); break;
-        case 6: m2lb_prealloc_p<6>(c); break;
-        case 8: m2lb_prealloc_p<8>(c); break;
-        case 10: m2lb_prealloc_p<10>(c); break;
-        case 12: m2lb_prealloc_p<12>(c); break;
-        default: throw Error{VFMM_EINVAL, "unsupported expansion degree p"};
-    }
+template <int P>
+static void m2lb_form(Ctx &c, bool operators) {
+    m2lb_plan_p<P>(c, operators);
+    if (c.m2lb_ok) m2lb_prealloc_p<P>(c);
+}
+
+// gives back every buffer that only the batched translations use
+static void m2lb_drop(Ctx &c) {
+    c.m2lb_ok = c.mb_keyed = false;
+    DevBuf *bufs[] = {&c.mb_kord, &c.mb_inv, &c.mb_koff, &c.mb_ksec, &c.mb_toff, &c.mb_dst, &c.mb_coff, &c.mb_roff,
+                      &c.mb_rsrc, &c.mb_cols, &c.mb_kgroups, &c.mb_kslots, &c.mb_kitem, &c.mb_fill, &c.mb_low,
+                      &c.mb_lowkid, &c.mb_eq, &c.mb_flag, &c.mb_pos, &c.mb_kid, &c.mb_ukey, &c.mb_tab, &c.mb_bcells,
+                      &c.mb_ent, &c.mb_groups, &c.mb_blk, &c.mb_items, &c.mb_mr, &c.mb_partial, &c.mb_cls,
+                      &c.mb_cellbs, &c.mb_gcnt, &c.mb_gid, &c.mb_goff, &c.mb_gcur, &c.mb_bkt, &c.mb_order, &c.mb_slots};
+    for (DevBuf *b : bufs) b->release();  // waits for the device
+}
+
+// The form is chosen by sizes alone.  Where its buffers cannot be had, the one that
+// needs less runs: in the float32 forms groups by block without groups by
+// operator (whose failure is the build's), in the float64 form one at a time.
+void m2lb_plan(Ctx &c) {
+    const bool dbl = c.prm.precision == VFMM_PRECISION_FP64;
+    first_form_that_fits<Error>(dbl ? 1 : 2, !dbl, [&](int k) {
+        switch (c.prm.p) {
+            case 4: m2lb_form<4>(c, k == 0); break;
+            case 6: m2lb_form<6>(c, k == 0); break;
+            case 8: m2lb_form<8>(c, k == 0); break;
+            case 10: m2lb_form<10>(c, k == 0); break;
+            case 12: m2lb_form<12>(c, k == 0); break;
+            default: throw Error{VFMM_EINVAL, "unsupported expansion degree p"};
+        }
+    }, [&] { m2lb_drop(c); }, [](const Error &e) { return e.st == VFMM_ENOMEM; });
 }
 
 template <int P>
