@@ -44,6 +44,8 @@
 // kappa_j r with each source's kappa_j (see pair()); a list entry's source
 // count covers only the sources of a leaf whose target points were moved
 // behind them.
+#include <type_traits>
+
 #include "ctx.h"
 #include "cutoff_fits.h"
 
@@ -326,6 +328,15 @@ __device__ __forceinline__ void kahan_add(float &s, float &c, float v) {
     s = t;
 }
 
+// Sums that are compensated within a wave are put together from several in float64.
+template <bool KAHAN>
+using Acc = std::conditional_t<KAHAN, double, float>;
+
+template <bool KAHAN>
+__device__ __forceinline__ Acc<KAHAN> kahan_value(float s, float c) {
+    return KAHAN ? (Acc<KAHAN>)s - (Acc<KAHAN>)c : (Acc<KAHAN>)s;
+}
+
 // Target of a lane: its offset in its leaf and its strength.
 template <bool VAR>
 __device__ __forceinline__ float4 load_target(const P2PArgs &A, int i, Tgt &t) {
@@ -592,10 +603,10 @@ __device__ __forceinline__ void p2p_group(const P2PConst &k, const P2PArgs &A, i
     // the groups' sums, added in group order
 #pragma unroll
     for (int q = 0; q < 9; ++q) {
-        if (KAHAN) S[q] -= Cc[q];
-        float v = S[q];
-        for (int g = 1; g < ng; ++g) v += __shfl(S[q], (lane + g * tc) & 63, 64);
-        S[q] = v;
+        const Acc<KAHAN> own = kahan_value<KAHAN>(S[q], Cc[q]);
+        Acc<KAHAN> v = own;
+        for (int g = 1; g < ng; ++g) v += __shfl(own, (lane + g * tc) & 63, 64);
+        S[q] = (float)v;
     }
     cross_sums<SCHEME>(t, S);
     if (lane < tc) finish<SCHEME>(k, A, i, tl, tc, t, S, near);
@@ -907,19 +918,19 @@ __global__ __launch_bounds__(256) void k_p2p64(P2P64Args A) {
 // Blocks of many parts: the parts of block pblong[blockIdx.x] are summed into the
 // first, one result component (blockIdx.y) per work-group, by up to 64 groups of
 // as many threads as the block has targets (parts g, g + groups, ...; then the
-// groups in order).  A wave per block in k_finalize adds them one after another:
+// groups in order; A: the sums' type).  A wave per block in k_finalize adds them one after another:
 // with 1,600 parts for a lone particle beside a cluster that chain took 570 us of
 // the 100,003-particle clustered evaluation, with the parts summed here 30.
-template <class T>
+template <class T, class A>
 __global__ __launch_bounds__(1024) void k_sum_parts(const int4 *__restrict__ blocks, const int *__restrict__ pblong,
                                                     T *__restrict__ near) {
-    __shared__ T red[1024];
+    __shared__ A red[1024];
     const int4 blk = blocks[pblong[blockIdx.x]];
     const int tc = blk.y, np = blk.w & PBLOCK_PARTS, t = threadIdx.x;
     const int G = min(64, 1024 / tc), g = t / tc, e = t - g * tc;
     T *q = near + 6 * (size_t)blk.z + (size_t)blockIdx.y * tc;
     const size_t stride = 6 * (size_t)tc;
-    T v = 0;
+    A v = 0;
     if (g < G)
         for (int p0 = g; p0 < np; p0 += 8 * G) {
             T w[8];
@@ -932,14 +943,15 @@ __global__ __launch_bounds__(1024) void k_sum_parts(const int4 *__restrict__ blo
     __syncthreads();
     if (t < tc) {
         for (int k = 1; k < G; ++k) v += red[k * tc + t];
-        q[t] = v;
+        q[t] = (T)v;
     }
 }
 
-template <class T>
+template <class T, class A>
 static void sum_parts(Ctx &c) {
     if (c.n_long == 0) return;
-    k_sum_parts<T><<<dim3(c.n_long, 6), 1024, 0, c.stream>>>(c.pblocks.as<int4>(), c.pblong.as<int>(), c.near.as<T>());
+    k_sum_parts<T, A>
+        <<<dim3(c.n_long, 6), 1024, 0, c.stream>>>(c.pblocks.as<int4>(), c.pblong.as<int>(), c.near.as<T>());
     VFMM_LAUNCH_CHECK();
 }
 
@@ -984,7 +996,7 @@ static void launch_p2p64(Ctx &c, const P2P64Args &A) {
         else
             k_p2p64<VFMM_SCHEME_CLASSICAL><<<g, 256, 0, c.stream>>>(A);
         VFMM_LAUNCH_CHECK();
-        if (A.n_long > 0) sum_parts<double>(c);
+        if (A.n_long > 0) sum_parts<double, double>(c);
         k_finalize64<<<cdiv(A.nblocks, 4), 256, 0, c.stream>>>(A);
         VFMM_LAUNCH_CHECK();
     }
@@ -1056,8 +1068,11 @@ static void launch_kinds(int scheme, bool var, const P2PConst &k, const P2PArgs 
     }
 }
 
+// whether the per-target sums are compensated
+static bool compensated(const vfmm_params &prm) { return prm.kahan != 0 || prm.precision == VFMM_PRECISION_MIXED; }
+
 static void dispatch_p2p(const vfmm_params &prm, bool var, const P2PConst &k, const P2PArgs &A, hipStream_t s) {
-    if (prm.kahan != 0 || prm.precision == VFMM_PRECISION_MIXED)
+    if (compensated(prm))
         launch_kinds<true>(prm.scheme, var, k, A, s);
     else
         launch_kinds<false>(prm.scheme, var, k, A, s);
@@ -1102,7 +1117,10 @@ void p2p_near(Ctx &c, hipStream_t s) {
 
 // out[perm[i]] = (sum of the near-field parts)[i] + far[i] (- the zero-mean
 // surface term for u); one wave per block, a lane per target, parts added in
-// list order with four parts' loads in flight
+// list order with four parts' loads in flight.  R: the sums' type, double where the
+// parts' own are compensated (an evaluation of 128^3 with four parts a block takes 15.3
+// ms either way, the 100,003 clustered particles with up to 32 5.00 instead of 4.86)
+template <class R>
 __global__ __launch_bounds__(256) void k_finalize(P2PArgs A, const float *__restrict__ near) {
     const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (b >= A.nblocks) return;
@@ -1113,7 +1131,7 @@ __global__ __launch_bounds__(256) void k_finalize(P2PArgs A, const float *__rest
     const int tc = blk.y, np = parts_left(blk.w);
     const float *q = near + 6 * (size_t)blk.z + lane;
     if (A.velocity && (blk.w & PBLOCK_VELOCITY)) {  // target points: no stretching was computed, none is read
-        float v[3] = {A.far_u[i], A.far_u[n + i], A.far_u[2 * n + i]};
+        R v[3] = {A.far_u[i], A.far_u[n + i], A.far_u[2 * n + i]};
         for (int p = 0; p < np; ++p)
 #pragma unroll
             for (int c = 0; c < 3; ++c) v[c] += q[(size_t)(6 * p + c) * tc];
@@ -1121,12 +1139,12 @@ __global__ __launch_bounds__(256) void k_finalize(P2PArgs A, const float *__rest
             for (int c = 0; c < 3; ++c) v[c] -= (float)(A.bounds->sum_xa[c]) * A.inv3V;
         if (A.bounds->stale) v[0] = v[1] = v[2] = __builtin_nanf("");
         const int o = A.perm[i];
-        A.ux[o] = v[0];
-        A.uy[o] = v[1];
-        A.uz[o] = v[2];
+        A.ux[o] = (float)v[0];
+        A.uy[o] = (float)v[1];
+        A.uz[o] = (float)v[2];
         return;
     }
-    float v[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    R v[6] = {0, 0, 0, 0, 0, 0};
     for (int p0 = 0; p0 < np; p0 += 4) {
         float w[4][6];
 #pragma unroll
@@ -1138,8 +1156,8 @@ __global__ __launch_bounds__(256) void k_finalize(P2PArgs A, const float *__rest
 #pragma unroll
             for (int c = 0; c < 6; ++c) v[c] += w[p][c];
     }
-    float u0 = v[0] + A.far_u[i], u1 = v[1] + A.far_u[n + i], u2 = v[2] + A.far_u[2 * n + i];
-    float d0 = v[3] + A.far_da[i], d1 = v[4] + A.far_da[n + i], d2 = v[5] + A.far_da[2 * n + i];
+    R u0 = v[0] + A.far_u[i], u1 = v[1] + A.far_u[n + i], u2 = v[2] + A.far_u[2 * n + i];
+    R d0 = v[3] + A.far_da[i], d1 = v[4] + A.far_da[n + i], d2 = v[5] + A.far_da[2 * n + i];
     if (A.surface) {
         u0 -= (float)(A.bounds->sum_xa[0]) * A.inv3V;
         u1 -= (float)(A.bounds->sum_xa[1]) * A.inv3V;
@@ -1147,12 +1165,19 @@ __global__ __launch_bounds__(256) void k_finalize(P2PArgs A, const float *__rest
     }
     if (A.bounds->stale) u0 = u1 = u2 = d0 = d1 = d2 = __builtin_nanf("");  // positions differ from the build's
     const int o = A.perm[i];
-    A.ux[o] = u0;
-    A.uy[o] = u1;
-    A.uz[o] = u2;
-    A.dax[o] = d0;
-    A.day[o] = d1;
-    A.daz[o] = d2;
+    A.ux[o] = (float)u0;
+    A.uy[o] = (float)u1;
+    A.uz[o] = (float)u2;
+    A.dax[o] = (float)d0;
+    A.day[o] = (float)d1;
+    A.daz[o] = (float)d2;
+}
+
+template <class R>
+static void finalize(Ctx &c, const P2PArgs &A) {
+    sum_parts<float, R>(c);
+    k_finalize<R><<<cdiv(c.n_pblocks, 4), 256, 0, c.stream>>>(A, c.near.as<float>());
+    VFMM_LAUNCH_CHECK();
 }
 
 void finalize_near_far(Ctx &c, float *ux, float *uy, float *uz, float *dax, float *day, float *daz) {
@@ -1161,9 +1186,10 @@ void finalize_near_far(Ctx &c, float *ux, float *uy, float *uz, float *dax, floa
     A.far_da = c.far_da.as<float>();
     A.ux = ux; A.uy = uy; A.uz = uz; A.dax = dax; A.day = day; A.daz = daz;
     if (c.n == 0) return;
-    sum_parts<float>(c);
-    k_finalize<<<cdiv(c.n_pblocks, 4), 256, 0, c.stream>>>(A, c.near.as<float>());
-    VFMM_LAUNCH_CHECK();
+    if (compensated(c.prm))
+        finalize<double>(c, A);
+    else
+        finalize<float>(c, A);
 }
 
 void p2p_and_finalize(Ctx &c, float *ux, float *uy, float *uz, float *dax, float *day, float *daz) {
@@ -1229,11 +1255,11 @@ __global__ __launch_bounds__(256) void k_direct_records(int64_t n, const float *
 }
 
 // red[0][k] = the sum over the work-group's W waves of red[w][k], in wave order
-template <int W, int K>
-__device__ __forceinline__ void sum_waves(float *red) {
+template <int W, int K, class T>
+__device__ __forceinline__ void sum_waves(T *red) {
     __syncthreads();
     for (int k = threadIdx.x; k < K; k += 64 * W) {
-        float v = red[k];
+        T v = red[k];
         for (int w = 1; w < W; ++w) v += red[w * K + k];
         red[k] = v;
     }
@@ -1248,7 +1274,7 @@ __device__ __forceinline__ void sum_waves(float *red) {
 constexpr int DIRECT_WAVES = 8;
 template <int SCHEME, bool KAHAN, bool VAR>
 __global__ __launch_bounds__(64 * DIRECT_WAVES) void k_direct(P2PConst k, P2PArgs A) {
-    __shared__ float red[DIRECT_WAVES][9][64];
+    __shared__ Acc<KAHAN> red[DIRECT_WAVES][9][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = (int)A.n, i = blockIdx.x * 64 + lane;
     Tgt t;
@@ -1263,11 +1289,11 @@ __global__ __launch_bounds__(64 * DIRECT_WAVES) void k_direct(P2PConst k, P2PArg
         add_leaf<SCHEME, KAHAN>(t, p, S, Cc);  // per 64 sources: |y| spans the domain here
     }
 #pragma unroll
-    for (int q = 0; q < 9; ++q) red[wave][q][lane] = KAHAN ? S[q] - Cc[q] : S[q];
+    for (int q = 0; q < 9; ++q) red[wave][q][lane] = kahan_value<KAHAN>(S[q], Cc[q]);
     sum_waves<DIRECT_WAVES, 9 * 64>(&red[0][0][0]);
     if (wave != 0 || i >= n) return;
 #pragma unroll
-    for (int q = 0; q < 9; ++q) S[q] = red[0][q][lane];
+    for (int q = 0; q < 9; ++q) S[q] = (float)red[0][q][lane];
     finish<SCHEME>(k, A, i, lane, 64, t, S, nullptr);
 }
 
@@ -1281,7 +1307,7 @@ template <int SCHEME, bool KAHAN, bool VAR>
 __global__ __launch_bounds__(64 * DIRECT_SMALL_WAVES) void k_direct_small(P2PConst k, P2PArgs A) {
     constexpr int RS = VAR ? 4 : 3, T = DIRECT_SMALL_T, NG = 64 / T;
     __shared__ float4 stage[DIRECT_SMALL_WAVES][3 * 64];
-    __shared__ float red[DIRECT_SMALL_WAVES][9][T];
+    __shared__ Acc<KAHAN> red[DIRECT_SMALL_WAVES][9][T];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int grp = lane / T, tl = lane % T;
     const int n = (int)A.n, i = blockIdx.x * T + tl;
@@ -1311,15 +1337,15 @@ __global__ __launch_bounds__(64 * DIRECT_SMALL_WAVES) void k_direct_small(P2PCon
     }
 #pragma unroll
     for (int q = 0; q < 9; ++q) {
-        float v = KAHAN ? S[q] - Cc[q] : S[q];
-        const float v0 = v;
-        for (int g = 1; g < NG; ++g) v += __shfl(v0, (lane + g * T) & 63, 64);
+        const Acc<KAHAN> own = kahan_value<KAHAN>(S[q], Cc[q]);
+        Acc<KAHAN> v = own;
+        for (int g = 1; g < NG; ++g) v += __shfl(own, (lane + g * T) & 63, 64);
         if (lane < T) red[wave][q][lane] = v;
     }
     sum_waves<DIRECT_SMALL_WAVES, 9 * T>(&red[0][0][0]);
     if (wave != 0 || lane >= T || i >= n) return;
 #pragma unroll
-    for (int q = 0; q < 9; ++q) S[q] = red[0][q][lane];
+    for (int q = 0; q < 9; ++q) S[q] = (float)red[0][q][lane];
     finish<SCHEME>(k, A, i, lane, T, t, S, nullptr);
 }
 
@@ -1389,7 +1415,7 @@ static void direct_f32_impl(const Ctx &c, Ctx *tc, hipStream_t s, int64_t n, con
     A.bounds = bounds;
     A.ux = ux; A.uy = uy; A.uz = uz; A.dax = dax; A.day = day; A.daz = daz;
     if (tc) tc->record(2 * PH_P2P, s);
-    const bool kah = c.prm.kahan != 0 || c.prm.precision == VFMM_PRECISION_MIXED;
+    const bool kah = compensated(c.prm);
     if (c.prm.scheme == VFMM_SCHEME_TRANSPOSE) {
         if (kah) launch_direct<VFMM_SCHEME_TRANSPOSE, true>(k, A, var, s);
         else launch_direct<VFMM_SCHEME_TRANSPOSE, false>(k, A, var, s);
