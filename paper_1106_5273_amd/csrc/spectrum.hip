@@ -32,7 +32,8 @@ namespace vfmm {
 static constexpr int SP_TPB = 256;
 static constexpr int SP_PARTS = 1024;  // work-groups of the last pass (bins are kept over its tiles)
 
-// lines per tile: eight rows of 16 bytes fill a 128-byte segment; four at n >= 512 keep the tile within 64 KB of LDS
+// lines per tile: eight rows of 16 bytes fill a 128-byte segment; at n >= 512 four, so that several work-groups share
+// a CU's 160 KB of LDS (44 KB each at 512; at 1,024 one, of up to 88 KB)
 __host__ __device__ constexpr int sp_t(int n) { return n >= 512 ? 4 : 8; }
 
 struct SpArgs {
