@@ -703,11 +703,12 @@ __global__ __launch_bounds__(256) void k_p2p_records(const int *__restrict__ lea
 // For x < 3 the power series of the lower incomplete gamma function,
 //   P(a, x) = x^a e^{-x} sum_k x^k / Gamma(a + k + 1),
 // divided by rho^{2a}, gives F and H without cancellation (finite at rho = 0);
-// the sum for a = 5/2 is a fitted polynomial (relative error 5e-18), the one for
-// 3/2 follows from it.  For x >= 3, with u = x^{-1/2},
+// the sum for a = 5/2 is a fitted polynomial (relative error 5e-17 with its
+// coefficients as doubles), the one for 3/2 follows from it.  For x >= 3, with
+// u = x^{-1/2},
 //   1 - P(3/2, x) = e^{-x} (u Pe(u) + (2/sqrt pi) / u),  Pe(1/s) = s erfcx(s),
-// Pe fitted for 3 <= x <= 41 (it changes P by less than 2e-17), and
-// P(5/2, x) = P(3/2, x) - (4/(3 sqrt pi)) x^{3/2} e^{-x}; beyond x = 41 both are 1
+// Pe fitted for 3 <= x <= 43 (it changes P by less than 2e-17), and
+// P(5/2, x) = P(3/2, x) - (4/(3 sqrt pi)) x^{3/2} e^{-x}; beyond x = 43 both are 1
 // to double precision.  Bound by float64 VALU issue (4 clocks an instruction):
 // about 75 instructions per pair in place of the library's exp, erfc and sqrt
 // and a series of up to 60 divisions (64^3 lattice, 2.47e9 pairs: 21.4 -> 7.3 ms).
@@ -747,8 +748,8 @@ __device__ __forceinline__ double fma_const(double a, double b, double k) {
 __device__ __forceinline__ double exp_minus(double x) {
     x = fmin(x, 800.0);
     const double n = __builtin_rint(-1.4426950408889634 * x);
-    double r = fma(n, -6.93147180369123816490e-01, -x);
-    r = fma(n, -1.90821492927058770002e-10, r);
+    double r = fma(n, -VFMM64_LN2_HI, -x);
+    r = fma(n, -VFMM64_LN2_LO, r);
     double p = 1.0 / 6227020800.0;
     p = fma_const(p, r, 1.0 / 479001600.0);
     p = fma_const(p, r, 1.0 / 39916800.0);
@@ -775,44 +776,24 @@ __device__ __forceinline__ void cutoff64(double x, double &F, double &H) {
     const double u2 = u * u;
     F = u2 * u;
     H = F * u2;
-    const bool near = x < 3.0;
-    if (!__any(x < 41.0)) return;
+    const bool near = x < VFMM64_XSPLIT;
+    if (!__any(x < VFMM64_XMAX)) return;
     const double e = exp_minus(x);
     if (__any(!near)) {
-        const double t = fma(u, 4.7486029380327639523, -1.7416071845478640612);
-        double pe = 1.0154139291334610343e-8;
-        pe = fma_const(pe, t, -6.78240140967600289e-8);
-        pe = fma_const(pe, t, 1.3629171185641934622e-7);
-        pe = fma_const(pe, t, 4.9343870167675321161e-7);
-        pe = fma_const(pe, t, -4.8554535549403367007e-6);
-        pe = fma_const(pe, t, 0.000018420223593917519055);
-        pe = fma_const(pe, t, -0.000019826846639273996918);
-        pe = fma_const(pe, t, -0.00022522551963893404409);
-        pe = fma_const(pe, t, 0.0016910379992956190884);
-        pe = fma_const(pe, t, -0.0042781108341645073393);
-        pe = fma_const(pe, t, -0.03159513100524058218);
-        pe = fma_const(pe, t, 0.53210276267808352717);
+        const double t = fma(u, VFMM64_PE_SCALE, VFMM64_PE_SHIFT);
+        constexpr int DEG = sizeof(VFMM64_PE_C) / sizeof(double) - 1;
+        double pe = VFMM64_PE_C[DEG];
+#pragma unroll
+        for (int k = DEG - 1; k >= 0; --k) pe = fma_const(pe, t, VFMM64_PE_C[k]);
         const double q = fma(u, pe, 1.1283791670955125739 * (x * u));  // (1 - P(3/2, x)) e^x
         F *= fma(-e, q, 1.0);
         H = u2 * fma(-0.75225277806367504925, e, F);  // 4 / (3 sqrt pi)
     }
     if (__any(near)) {
-        double s = 2.473165037961738643e-15;
-        s = fma_const(s, x, -1.1889376396170663998e-14);
-        s = fma_const(s, x, 3.5903357402350888376e-13);
-        s = fma_const(s, x, 2.2329913611558775379e-12);
-        s = fma_const(s, x, 4.5659993236357083032e-11);
-        s = fma_const(s, x, 5.7934352867643122933e-10);
-        s = fma_const(s, x, 7.3161834843850830295e-9);
-        s = fma_const(s, x, 8.4027546810691893533e-8);
-        s = fma_const(s, x, 8.8240441348206060814e-7);
-        s = fma_const(s, x, 8.382754048318247031e-6);
-        s = fma_const(s, x, 0.000071253456606512365563);
-        s = fma_const(s, x, 0.00053440090733175414279);
-        s = fma_const(s, x, 0.0034736059016923648073);
-        s = fma_const(s, x, 0.019104832458751436672);
-        s = fma_const(s, x, 0.085971746064420295029);
-        s = fma_const(s, x, 0.30090111122547001809);
+        constexpr int DEG = sizeof(VFMM64_M2_C) / sizeof(double) - 1;
+        double s = VFMM64_M2_C[DEG];
+#pragma unroll
+        for (int k = DEG - 1; k >= 0; --k) s = fma_const(s, x, VFMM64_M2_C[k]);
         const double Fs = e * fma(x, s, 0.75225277806367504925);  // 1/Gamma(5/2)
         F = near ? Fs : F;
         H = near ? e * s : H;
