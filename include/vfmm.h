@@ -30,9 +30,10 @@
  *   boundary.  vfmm_last_error() returns a text description of the last
  *   failure on that context.
  * - The context owns the tree, expansions, interaction lists and scratch space
- *   in device memory, and 256 bytes of pinned host memory (hipHostMalloc) that
- *   the build reads its sizes through (7 KB more once vfmm_energy_spectrum has
- *   been called).  These only grow; vfmm_destroy frees them.
+ *   in device memory, and 256 bytes of pinned host memory (allocated by
+ *   vfmm_create) that the build reads its sizes through (7 KB more once
+ *   vfmm_energy_spectrum has been called).  These only grow; vfmm_destroy
+ *   frees them.
  * - A context is not thread safe; calls on one context must not overlap.
  * - Depth.  Morton keys hold 21 bits per axis (Sec. 3.2), so a cell is split
  *   at most 21 times (fewer in a batch, whose keys also carry the problem id).
@@ -131,8 +132,10 @@ typedef struct vfmm_params {
                             operand (16 significant bits) and only the three leading partial
                             products, half the matrix-core work of form 2; each translation
                             carries relative errors of order 1e-5, meant for error bounds near
-                            1e-4 (the autotuner chooses it only where the bound holds).  p = 12
-                            uses form 1 for 2 and 3.                                           */
+                            1e-4 (the autotuner chooses it only where the bound holds).  Forms
+                            2 and 3 are those of every batched translation, irregular trees'
+                            groups by offset alone included; translations one at a time are
+                            float32 products.  p = 12 uses form 1 for 2 and 3.                */
 } vfmm_params;
 
 /* Per-phase device times of the last fmm_build / fmm_evaluate, in milliseconds,

@@ -160,13 +160,13 @@ struct Ctx {
     void record(int i) { record(i, stream); }
 };
 
-// Sources per leaf when the evaluation needs no stretching at the target points
-// (fmm_evaluate_targets), else null.
 // Whether the operator-batched M2L may run: not in mode 1, and in the float64 form by its own rule alone.
 inline bool m2l_batched(const vfmm_params &p) {
     return p.m2l_mode != 1 && !(p.precision == VFMM_PRECISION_FP64 && p.m2l_mode != 0);
 }
 
+// Sources per leaf when the evaluation needs no stretching at the target points
+// (fmm_evaluate_targets), else null.
 inline const int *eval_sources(const Ctx &c) { return c.tg_eval && c.parted ? c.c_nsrc.as<int>() : nullptr; }
 
 // tree.hip

@@ -254,8 +254,8 @@ __global__ __launch_bounds__((XferCfg<P, R>::M2M_THREADS)) void k_m2m(int c0, in
 }
 
 // ---------------------------------------------------------------------------
-// M2L, one translation at a time (Sec. 3.6), for trees whose translations do
-// not group densely and for the float64 form.
+// M2L, one translation at a time (Sec. 3.6): short lists, rare operators, trees
+// whose translations do not group, and the float64 form at p = 12.
 //   Lt_k^l(A) = (-1)^{k+l} lambda^{-(k+1)} sum_{n,m} Mt_n^m(B) I_{n+k}^{m-l}((c_A - c_B)/s_B),
 //   lambda = s_B/s_A.
 // With I^{-mu} = (-1)^mu conj(I^mu), Mt^{-m} = (-1)^m conj(Mt^m), z1 = I_{n+k}^{m-l},

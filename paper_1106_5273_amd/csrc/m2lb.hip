@@ -38,19 +38,27 @@ namespace vfmm {
 static constexpr int TPB = 256;
 static constexpr int ITEM_GROUPS = 24;
 static constexpr int TABLE_KEY_BITS = 24;  // offset keys up to this width are numbered through a direct table
-// time (ns) of all translations one at a time below which they run so at once: the
-// batched plan's 25 launches and 6 waits take 0.2 ms, in float64, where groups cost
-// four times as much, with lists by operator 0.4
+// Time (ns) of all translations one at a time below which they run so at once: the
+// batched plan's 25 launches and 6 waits take 0.2 to 0.35 ms.  Build and evaluation in
+// ms (planned / one at a time) of clouds and rings in float32, p = 10: 28,000
+// translations 1.35 / 1.16, 55,000 1.65 / 1.68, 85,000 1.11 / 1.15 (1.38 / 1.11 where few
+// share an operator), 174,000 1.42 / 1.90; at p = 8, whose translations cost half, the
+// two meet at twice the line: 85,000 0.98 / 0.82, 174,000 1.29 / 1.27.  Float64, where groups cost four
+// times as much, p = 10: 55,000 2.82 / 2.34, 174,000 2.15 / 1.87, 1.1 million 5.19 / 6.94.
 static constexpr double MIN_PAIR_NS = 2.5e5, MIN_PAIR_NS_F64 = 6e5;
-// the same for the float64 products, whose group costs as much as 17 translations one at a time
-static constexpr int MIN_FILL_F64 = 24;
+// ns at p = 10 of the float64 products, as measured: a group of 64, an operator's bytes, a translation
+// one at a time, a column's bytes
+static constexpr double GROUP_NS_F64 = 125.0, KEY_NS_F64 = 31.2, PAIR_NS_F64 = 5.1, COL_NS_F64 = 1.23;
+// translations per group below which the float64 groups by block cost more than these one at a time
+static constexpr int MIN_FILL_F64 = (int)(GROUP_NS_F64 / PAIR_NS_F64);
 // an operator is built for whole quarter cells between two centres.  The float64 form
 // keeps a rest of 2^-34 of one (2e-11 of a cell, and of a translation's result): cells
 // of 2^-17 of their coordinates.  Finer ones run one at a time between their centres.
 // The float32 forms' groups by operator alone, which take irregular and so the
 // deepest trees, keep 2^-20 (4e-7): all but cells whose centres are rounded.
 static constexpr float MAX_RESIDUAL_F64 = 5.8e-11f, MAX_RESIDUAL = 9.5e-7f;
-static constexpr int MIN_GROUP_FILL = 8;  // translations per (block, key) group below which per-pair M2L runs
+// translations per (block, key) group below which the float32 forms take groups by operator or run one at a time
+static constexpr int MIN_GROUP_FILL = 8;
 
 void sort_pairs_u64(Ctx &c, DevBuf &kA, DevBuf &vA, DevBuf &kB, DevBuf &vB, int64_t n, int nbits);
 
@@ -1160,7 +1168,7 @@ __global__ __launch_bounds__(COL_GROUPS * 3 * NRP(P) / 2) void k_m2lb_columns(co
 // keys of fewer translations than this go to the per-pair kernel: their operator
 // and their group cost what about ten translations one at a time cost
 static constexpr int KEYED_MIN = 10;
-static constexpr int KEYED_MIN_F64 = 40;  // float64: 160 ns against 5.1 each, less 1.2 of column bytes
+static constexpr int KEYED_MIN_F64 = (int)((GROUP_NS_F64 + KEY_NS_F64) / (PAIR_NS_F64 - COL_NS_F64));
 
 __global__ __launch_bounds__(TPB) void k_kid_keys(int64_t n, const int *kid, uint64_t *key, uint32_t *val) {
     const int64_t e = (int64_t)blockIdx.x * TPB + threadIdx.x;
@@ -1300,9 +1308,9 @@ struct M2lCosts {
 template <int P>
 static M2lCosts m2l_costs(bool dbl = false) {
     using C = MbCfg<P>;
-    if (dbl)  // a group 125 at p = 10 (eight waves), a pair 5.1
-        return {125.0 * ((C::RTI + 3) / 4) / 2.0 * C::KC / 8.0, 48.0 * C::RP / 5000.0, 8.0 * (double)C::OP / 4200.0,
-                5.1 * C::R / 121.0};
+    if (dbl)  // scaled from p = 10 (two row tiles per SIMD, eight chunks, 128 padded rows)
+        return {GROUP_NS_F64 * ((C::RTI + 3) / 4) / 2.0 * C::KC / 8.0, COL_NS_F64 * C::RP / 128.0,
+                KEY_NS_F64 * (double)C::OP / (128.0 * 128.0), PAIR_NS_F64 * C::R / 121.0};
     return {(double)C::RTI * (C::RP / 32), 24.0 * C::RP / 5000.0, 4.0 * (double)C::OPX / 4200.0,
             6.0 * std::pow(C::R / 121.0, 1.5)};
 }
@@ -1543,7 +1551,9 @@ static void m2lb_plan_p(Ctx &c, bool operators) {
                                                 c.mb_kid.as<int>(), c.mb_ukey.as<uint64_t>());
         VFMM_LAUNCH_CHECK();
     }
-    // every key has a group: the rule on the groups' fill below fails already
+    // every key has a group, so the groups by block fail their rule below.  Groups by operator could
+    // still pay for a few frequent operators among many rare ones; they are not looked for here, as
+    // their sort would then cost every tree of rare operators 0.1 ms.
     if (c.prm.m2l_mode == 0 && n < (int64_t)MIN_GROUP_FILL * nkeys) return;
     c.lkey.ensure(sizeof(uint64_t) * n);
     c.lval.ensure(sizeof(uint32_t) * n);
@@ -1826,18 +1836,20 @@ static void m2lb_run_p(Ctx &c) {
                                                            c.mb_partial.as<float>());
     }
     VFMM_LAUNCH_CHECK();
-    if (c.mb_keyed) {
-        constexpr int NT = COL_GROUPS * 3 * RP / 2;
-        if (dbl)
-            k_m2lb_columns<P, double, double><<<c.ncells, NT, 0, s>>>(c.mb_coff.as<int>(), c.mb_cols.as<double>(),
-                                                                      c.Lexp.as<double2>());
-        else if (c.prm.precision == VFMM_PRECISION_MIXED)
-            k_m2lb_columns<P, double><<<c.ncells, NT, 0, s>>>(c.mb_coff.as<int>(), c.mb_cols.as<float>(),
-                                                              c.Lexp.as<float2>());
-        else
-            k_m2lb_columns<P, float><<<c.ncells, NT, 0, s>>>(c.mb_coff.as<int>(), c.mb_cols.as<float>(),
-                                                             c.Lexp.as<float2>());
-        VFMM_LAUNCH_CHECK();
+    if constexpr (MbCfg<P>::X6 || Mb64Cfg<P>::OK) {  // the degrees that are grouped by operator
+        if (c.mb_keyed) {
+            constexpr int NT = COL_GROUPS * 3 * RP / 2;
+            if (dbl)
+                k_m2lb_columns<P, double, double><<<c.ncells, NT, 0, s>>>(c.mb_coff.as<int>(), c.mb_cols.as<double>(),
+                                                                          c.Lexp.as<double2>());
+            else if (c.prm.precision == VFMM_PRECISION_MIXED)
+                k_m2lb_columns<P, double><<<c.ncells, NT, 0, s>>>(c.mb_coff.as<int>(), c.mb_cols.as<float>(),
+                                                                  c.Lexp.as<float2>());
+            else
+                k_m2lb_columns<P, float><<<c.ncells, NT, 0, s>>>(c.mb_coff.as<int>(), c.mb_cols.as<float>(),
+                                                                 c.Lexp.as<float2>());
+            VFMM_LAUNCH_CHECK();
+        }
     }
     const int nblk = c.mb_nblk;
     int *blk_item0 = c.mb_blk.as<int>() + nblk, *blk_nitem = blk_item0 + nblk;

@@ -24,8 +24,8 @@ VFMM_HD inline int p2p_groups(int tc) { return tc > 32 ? 1 : tc < 4 ? 16 : 64 / 
 // ---------------------------------------------------------------------------
 // P2P work: every leaf's targets are cut into blocks of at most 64, and every
 // block's list into parts of about equal length, one wave each.  The length of
-// a part is chosen from the whole build's work: total wave steps / 172,032 (24
-// rounds of 7,168 waves), but at least 48 steps (shorter
+// a part is chosen from the whole build's work: total wave steps / 172,032 (21
+// rounds of the 8,192 waves that fill the chip), but at least 48 steps (shorter
 // parts cost more in their prologue and partial sums than they spread) and at
 // most 1,200.  More than two parts are made a multiple of the four waves of a
 // work-group, which then share one block's targets and neighbouring sources: 512

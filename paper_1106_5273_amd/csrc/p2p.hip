@@ -1334,6 +1334,8 @@ __global__ __launch_bounds__(64 * DIRECT_SMALL_WAVES) void k_direct_small(P2PCon
 // scalar form's cheaper pair step outweighs it; measured (scalar / groups):
 // 17,000 particles 516 / 280 us, 24,000 724 / 532, 32,768 973 / 926, 40,000
 // 1,611 / 1,379, 49,152 1,998 / 2,053, 57,344 2,997 / 2,800, 65,536 3,422 / 3,645.
+// The rounds make the two cross more than once; the line lies above the last size at
+// which the groups win, for 3 % lost around 49,152, where the scalar form's rounds end evenly.
 constexpr int64_t DIRECT_SMALL_N = 61440;
 
 template <int SCHEME, bool KAHAN>
