@@ -387,28 +387,6 @@ __device__ __forceinline__ void add_leaf(const Tgt &t, const Acc9 &p, float *S, 
     }
 }
 
-// u's Ah x y_i - Bh once the sums are complete (every source in the target leaf's frame)
-template <int SCHEME>
-__device__ __forceinline__ void cross_sums(const Tgt &t, float *S) {
-    if (SCHEME == VFMM_SCHEME_CLASSICAL) return;
-    const float b0 = S[0], b1 = S[1], b2 = S[2];
-    S[0] = fmaf(S[4], t.y2, fmaf(-S[5], t.y1, -b0));
-    S[1] = fmaf(S[5], t.y0, fmaf(-S[3], t.y2, -b1));
-    S[2] = fmaf(S[3], t.y1, fmaf(-S[4], t.y0, -b2));
-}
-
-template <bool KAHAN>
-__device__ __forceinline__ void add_sums(const Acc9 &p, float *S, float *Cc) {
-    const float pv[9] = {p.u0, p.u1, p.u2, p.a0, p.a1, p.a2, p.t0, p.t1, p.t2};
-#pragma unroll
-    for (int q = 0; q < 9; ++q) {
-        if (KAHAN)
-            kahan_add(S[q], Cc[q], pv[q]);
-        else
-            S[q] += pv[q];
-    }
-}
-
 // u and dalpha of target i (number tl of its block of tc) from the sums S: a
 // partial result when near is given, else (direct mode) the outputs
 template <int SCHEME>
@@ -583,6 +561,7 @@ __device__ __forceinline__ void p2p_group(const P2PConst &k, const P2PArgs &A, i
             }
             // the form that every staged source allows
             const int any0 = __any(form == 0), any1 = __any(form == 1);
+            const int own = __any(ok && h.x == 0.f && h.y == 0.f && h.z == 0.f);  // of the target leaf
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the last pass has read its records
             L.rec[3 * lane] = sp;
             L.rec[3 * lane + 1] = sa;
@@ -590,6 +569,17 @@ __device__ __forceinline__ void p2p_group(const P2PConst &k, const P2PArgs &A, i
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             const int trips = (min(chunk, total - f0) + 2 * ng - 1) / (2 * ng);
             const float4 *stage = L.rec + 3 * grp;
+            // A particle's own term is zero in u, but as the difference of two sums it cancels only
+            // to their rounding, and with a small core it is many times a neighbour's: the passes of
+            // the target leaf take it source by source, before anything is added to it.
+            if (own && SCHEME == VFMM_SCHEME_TRANSPOSE) {
+                for (int j = 0; j < 2 * trips; ++j, stage += 3 * ng) {
+                    Acc9 p = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+                    pair<0, SCHEME, VAR>(k, t, stage[0], stage[1], stage[2], p);
+                    add_leaf<SCHEME, KAHAN>(t, p, S, Cc);
+                }
+                continue;
+            }
             Acc9 p = {0, 0, 0, 0, 0, 0, 0, 0, 0};
             if (any0)
                 group_loop<0, SCHEME, VAR>(k, stage, ng, trips, t, p);
@@ -597,18 +587,19 @@ __device__ __forceinline__ void p2p_group(const P2PConst &k, const P2PArgs &A, i
                 group_loop<1, SCHEME, VAR>(k, stage, ng, trips, t, p);
             else
                 group_loop<2, SCHEME, VAR>(k, stage, ng, trips, t, p);
-            add_sums<KAHAN>(p, S, Cc);
+            add_leaf<SCHEME, KAHAN>(t, p, S, Cc);
         }
     }
-    // the groups' sums, added in group order
+    // the groups' sums, added pairwise
 #pragma unroll
     for (int q = 0; q < 9; ++q) {
-        const Acc<KAHAN> own = kahan_value<KAHAN>(S[q], Cc[q]);
-        Acc<KAHAN> v = own;
-        for (int g = 1; g < ng; ++g) v += __shfl(own, (lane + g * tc) & 63, 64);
+        Acc<KAHAN> v = kahan_value<KAHAN>(S[q], Cc[q]);
+        for (int w = 1; w < ng; w <<= 1) {
+            const Acc<KAHAN> x = __shfl(v, (lane + w * tc) & 63, 64);
+            if (g0 % (2 * w) == 0 && g0 + w < ng) v += x;
+        }
         S[q] = (float)v;
     }
-    cross_sums<SCHEME>(t, S);
     if (lane < tc) finish<SCHEME>(k, A, i, tl, tc, t, S, near);
 }
 

@@ -1,5 +1,6 @@
 """Places of the near field that ordinary cases do not reach: large leaves, whose lists would be cut into more partial
-results than a build may have; particles at round offsets from their leaf's centre; cores far below the distances."""
+results than a build may have; particles at round offsets from their leaf's centre; cores far below the distances,
+in the float32 form too."""
 import numpy as np
 import pytest
 
@@ -88,3 +89,38 @@ def test_float64_cores_far_below_the_distances(sig, direct):
     u = np.stack([v.cpu().numpy() for v in out[:3]], 1).astype(np.float64)
     tol = 2.0 ** -23 if direct else 1e-4
     check("core %g, direct %d, u" % (sig, direct), u, oracle.direct(case)["u"], tol, 1e-3)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("k,theta,core,var", [(1, 0.1, 0.01, False), (3, 0.1, 0.01, False), (8, 0.5, 0.004, False),
+                                              (8, 0.2, 0.004, False), (20, 0.2, 0.003, False), (30, 0.1, 0.002, True)])
+def test_own_terms_of_small_cores(k, theta, core, var, precision):
+    """Cores far below the spacing: a particle's own term F(0) alpha_i x (y_i - y_i), with F(0) = 1 / (6 sqrt 2 pi^1.5
+    sigma^3) up to 1e4 times a neighbour's F, is zero, and formed as a difference of two sums of magnitude F(0) |alpha|
+    |y|.  The roundings of its factors leave some 0.8 2^-24 of that (four of 0.43 2^-24 each, of components of 0.8 of
+    it); a gate of 1.4 on the rms against the float64 form of the same lists."""
+    import torch
+    import paper_1106_5273_amd as vf
+    rng = np.random.default_rng(k)
+    m = 8 if k < 20 else 4
+    g = (np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 1, 3)
+         + rng.uniform(0.02, 0.98, (m ** 3, k, 3))).reshape(-1, 3) / m
+    n = len(g)
+    a = rng.standard_normal((n, 3)) / n
+    sig = np.full(n, core) * (rng.uniform(0.7, 1.3, n) if var else 1.0)
+    f = lambda v: np.ascontiguousarray(v, np.float32)  # noqa: E731
+    case = dict(x=f(g[:, 0]), y=f(g[:, 1]), z=f(g[:, 2]), ax=f(a[:, 0]), ay=f(a[:, 1]), az=f(a[:, 2]), sigma=f(sig))
+    u = []
+    for prec in (precision, 2):
+        t = vf.case_to_device(case)
+        with vf.Context(p=10, ncrit=k, box_len=1.0, theta=theta, precision=prec, m2l_mode=1) as ctx:
+            ctx.build(t[0], t[1], t[2], t[6])
+            out = ctx.evaluate(*t)
+            torch.cuda.synchronize()
+        u.append(np.stack([v.cpu().numpy() for v in out[:3]], 1).astype(np.float64))
+    F0 = 1.0 / (6.0 * np.sqrt(2.0) * np.pi ** 1.5 * sig ** 3)
+    y = np.abs((g * m) % 1.0 - 0.5) / m  # from the leaf's centre
+    scale = 2.0 ** -24 * np.sqrt(np.mean(F0 ** 2 * (a * a).sum(1) * (y * y).sum(1)))
+    err = np.sqrt(np.mean(((u[0] - u[1]) ** 2).sum(1)))
+    print("rms error %.2f 2^-24 F(0) |alpha| |y|" % (err / scale))
+    assert err <= 1.4 * scale
