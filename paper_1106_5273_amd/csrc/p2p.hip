@@ -571,8 +571,9 @@ __device__ __forceinline__ void p2p_group(const P2PConst &k, const P2PArgs &A, i
             const float4 *stage = L.rec + 3 * grp;
             // A particle's own term is zero in u, but as the difference of two sums it cancels only
             // to their rounding, and with a small core it is many times a neighbour's: the passes of
-            // the target leaf take it source by source, before anything is added to it.
-            if (own && SCHEME == VFMM_SCHEME_TRANSPOSE) {
+            // the target leaf take it source by source, before anything is added to it (in the
+            // classical reading u has no such difference, but compensated sums would lose theirs).
+            if (own && (KAHAN || SCHEME != VFMM_SCHEME_CLASSICAL)) {
                 for (int j = 0; j < 2 * trips; ++j, stage += 3 * ng) {
                     Acc9 p = {0, 0, 0, 0, 0, 0, 0, 0, 0};
                     pair<0, SCHEME, VAR>(k, t, stage[0], stage[1], stage[2], p);

@@ -124,3 +124,31 @@ def test_own_terms_of_small_cores(k, theta, core, var, precision):
     err = np.sqrt(np.mean(((u[0] - u[1]) ** 2).sum(1)))
     print("rms error %.2f 2^-24 F(0) |alpha| |y|" % (err / scale))
     assert err <= 1.4 * scale
+
+
+@pytest.mark.parametrize("k,theta,core", [(3, 0.1, 0.01), (8, 0.3, 0.004), (16, 0.2, 0.003)])
+def test_points_at_particles_of_small_cores(k, theta, core):
+    """The same at target points that coincide with particles: the particle's term in the velocity there is zero."""
+    import torch
+    import paper_1106_5273_amd as vf
+    rng = np.random.default_rng(k)
+    m = 8 if k < 16 else 4
+    g = (np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 1, 3)
+         + rng.uniform(0.02, 0.98, (m ** 3, k, 3))).reshape(-1, 3) / m
+    n = len(g)
+    a = rng.standard_normal((n, 3)) / n
+    t = [torch.from_numpy(np.ascontiguousarray(v, np.float32)).cuda()
+         for v in (g[:, 0], g[:, 1], g[:, 2], a[:, 0], a[:, 1], a[:, 2], np.full(n, core))]
+    u = []
+    for prec in (0, 2):
+        with vf.Context(p=10, ncrit=2 * k, box_len=1.0, theta=theta, precision=prec, m2l_mode=1) as ctx:
+            ctx.build_targets(t[0], t[1], t[2], t[6], t[0], t[1], t[2])
+            out = ctx.evaluate_targets(t[3], t[4], t[5])
+            torch.cuda.synchronize()
+        u.append(np.stack([v.cpu().numpy() for v in out[6:]], 1).astype(np.float64))
+    F0 = 1.0 / (6.0 * np.sqrt(2.0) * np.pi ** 1.5 * core ** 3)
+    y = np.abs((g * m) % 1.0 - 0.5) / m
+    scale = 2.0 ** -24 * F0 * np.sqrt(np.mean((a * a).sum(1) * (y * y).sum(1)))
+    err = np.sqrt(np.mean(((u[0] - u[1]) ** 2).sum(1)))
+    print("rms error %.2f 2^-24 F(0) |alpha| |y|" % (err / scale))
+    assert err <= 1.4 * scale
