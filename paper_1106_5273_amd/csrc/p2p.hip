@@ -479,8 +479,8 @@ __device__ __forceinline__ void p2p_block(const P2PConst &k, const P2PArgs &A, i
 // trip of two sources are pair arithmetic).  An 80^3 jittered lattice (15.6
 // particles per leaf, 2.88e9 pairs): 7.1 ms with groups of 16 or 32 lanes that
 // read every source from memory, 4.6 ms with groups that take whole entries
-// from LDS, 3.05 ms so; per-particle cores at 50^3 (27 to 64 per leaf): 1.8,
-// 1.6 and 1.1 ms.
+// from LDS, 2.7 ms so; per-particle cores at 50^3 (27 to 64 per leaf): 1.8,
+// 1.6 and 1.2 ms.
 struct GroupLds {
     float4 rec[3 * 64];  // staged records
     float4 hd[64];       // D' of an entry; its first source less the sources before it
